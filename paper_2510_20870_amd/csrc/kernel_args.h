@@ -36,6 +36,21 @@ struct LineRec {
   double cut, ib, sc, y;
 };
 
+// Tree of line groups over the record range [rec_lo, rec_lo + rec_n) (far_tree.h): level l
+// has cnt[l] nodes from index off[l], n_nodes in all, one array of them per (P, T) point.
+constexpr int kTreeLevels = 5;
+struct TreeDims {
+  int64_t off[kTreeLevels];
+  int64_t cnt[kTreeLevels];
+  int64_t n_nodes;
+  int levels;             // levels in use
+};
+// Lines [n0, n1) of the record range that a tile's own kernel walks; the far kernel takes
+// the others.
+struct NearRange {
+  int64_t n0, n1;
+};
+
 struct ParamArgs {
   LinesDev L;
   SpeciesDev sp;
@@ -44,6 +59,31 @@ struct ParamArgs {
   int pt0, n_pt;          // this batch: points pt0 .. pt0 + n_pt - 1
   int64_t lo, n;          // line range [lo, lo + n)
   LineRec* out;           // [n_pt][n]
+  void* nodes;            // tree nodes [n_pt][dims.n_nodes] (nullptr: no tree)
+  TreeDims dims;
+  int moments;            // kMomFp32 or kMomFp64
+};
+
+// The far kernel: per (tile, P-T point) the sum over the lines outside the tile's near
+// range, and that range.
+struct FarArgs {
+  LinesDev L;
+  SpeciesDev sp;
+  double cut;             // the fixed cut
+  const double* grid;
+  int64_t n_grid;
+  const double* pts;      // [n_pts][2], whole table
+  int pt0, n_pt;          // this batch
+  int P;                  // points per lane of the tile kernel (a tile is 64 P points)
+  int64_t n_items;        // tiles issued * n_pt
+  const int* tile_order;  // issue order of the tiles (nullptr: ascending)
+  int64_t n_tiles;        // tiles of the whole grid
+  const LineRec* recs;
+  int64_t rec_lo, rec_n;
+  const void* nodes;
+  TreeDims dims;
+  double* out;            // [n_pt][n_grid]
+  NearRange* near;        // [n_pt][n_tiles]
 };
 
 struct TileArgs {
@@ -73,6 +113,12 @@ struct TileArgs {
   double* tau;
   int64_t tau_stride;     // groups of the whole grid
   double select_eps;      // select kernel: the allowed relative error
+  // far field by moments (nullptr: every line of the window is walked here): the lines each
+  // tile walks, [n_pt][near_stride], and the others' sums, [n_pt][n_grid], added here when
+  // split == 1 (else by the reduction)
+  const NearRange* near;
+  int64_t near_stride;
+  const double* far;
   // error budget of the shifted forms (shifted_lorentz_ok, dshift_ok) and the far-line
   // threshold kappa (far_ok) for that budget
   float l1_eps, far_kappa;
@@ -92,9 +138,12 @@ hipError_t launch_tile_p1(const TileArgs& A, bool f64, int W, hipStream_t st, di
 hipError_t launch_tile_p2(const TileArgs& A, bool f64, int W, hipStream_t st, dim3 grid);
 hipError_t launch_tile_p4(const TileArgs& A, bool f64, int W, hipStream_t st, dim3 grid);
 hipError_t launch_tile_p8(const TileArgs& A, bool f64, int W, hipStream_t st, dim3 grid);
-// out: float rows when out_f32, else double rows
-hipError_t launch_reduce(const double* part, void* out, int out_f32, int64_t n_grid, int n_pts,
-                         int split, hipStream_t st);
+// the moments of every level above the leaves (launch_params writes those)
+hipError_t launch_tree_up(const ParamArgs& A, hipStream_t st);
+hipError_t launch_far(const FarArgs& A, int moments, hipStream_t st);
+// out: float rows when out_f32, else double rows; far (may be nullptr): one more partial
+hipError_t launch_reduce(const double* part, const double* far, void* out, int out_f32,
+                         int64_t n_grid, int n_pts, int split, hipStream_t st);
 // collision-induced absorption: block k (nodes [off[k], off[k+1]) of nu, alpha) linearly
 // interpolated onto the grid, zero outside the block, out[k][j]
 hipError_t launch_cia(const double* grid, int64_t n_grid, const int64_t* off, int n_blocks,

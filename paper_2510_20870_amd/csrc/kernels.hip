@@ -49,18 +49,26 @@
 
 #include <algorithm>
 
+#include "far_tree.h"
 #include "tile_kernel.h"
 
 namespace xs {
 
 // ------------------------------------------------------------------ parameter kernel
+// One thread per line; a wavefront's 64 lines are one leaf of the tree (NM > 0: with NM
+// moments), whose moments it sums while the parameters are in registers, so the tree costs
+// no pass of its own over the lines.
+template <int NM>
 __global__ __launch_bounds__(256) void xs_params_kernel(ParamArgs A) {
   const int k = blockIdx.y;
   const PtConst pc = make_pt(A.sp, A.pts[2 * (A.pt0 + k)], A.pts[2 * (A.pt0 + k) + 1]);
   LineRec* out = A.out + (int64_t)k * A.n;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < A.n;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = A.lo + t;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane);
+  for (int64_t base = t0; base < A.n; base += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t t = base + lane;
+    const bool ok = t < A.n;
+    const int64_t i = A.lo + (ok ? t : A.n - 1);
     const double nu0 = A.L.nu0[i];
     const LineParams lp = line_params(A.sp, pc, A.cut, nu0, A.L.A[i], A.L.E[i], A.L.gam[i],
                                       A.L.nT[i], A.L.g[i], A.L.J ? A.L.J[i] : (uint16_t)0);
@@ -69,14 +77,19 @@ __global__ __launch_bounds__(256) void xs_params_kernel(ParamArgs A) {
     r.ib = 1.0 / lp.bD;
     r.sc = lp.S * r.ib * (1.0 / kSqrtPiD);
     r.y = lp.gL * r.ib;
-    out[t] = r;
+    if (ok) out[t] = r;
+    if constexpr (NM > 0)
+      leaf_moments<NM>((FarNode<NM>*)A.nodes + (int64_t)k * A.dims.n_nodes + base / kLeafLines,
+                       nu0, ok ? lp.S * (1.0 / kPiD) : 0.0, lp.bD, lp.gL, lane);
   }
 }
 
 // Fixed-order reduction of split partials: out[k][j] = sum_s part[k][s][j], s ascending,
+// then the far field far[k][j] when there is one,
 // stored as OUT (double, or float rounded once from the FP64 sum).
 template <typename OUT>
 __global__ __launch_bounds__(256) void xs_reduce_kernel(const double* __restrict__ part,
+                                                        const double* __restrict__ far,
                                                         OUT* __restrict__ out,
                                                         int64_t n_grid, int n_pts, int split) {
   const int64_t total = (int64_t)n_pts * n_grid;
@@ -86,6 +99,7 @@ __global__ __launch_bounds__(256) void xs_reduce_kernel(const double* __restrict
     const double* p = part + k * split * n_grid + j;
     double acc = 0.0;
     for (int s = 0; s < split; ++s) acc += p[(int64_t)s * n_grid];
+    if (far) acc += far[t];
     out[t] = (OUT)acc;
   }
 }
@@ -307,8 +321,12 @@ hipError_t launch_params(const ParamArgs& A, hipStream_t st) {
   if (A.n <= 0 || A.n_pt <= 0) return hipSuccess;
   int64_t blocks = (A.n + 255) / 256;
   if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(xs_params_kernel, dim3((unsigned)blocks, (unsigned)A.n_pt), dim3(256), 0,
-                     st, A);
+  const dim3 grid((unsigned)blocks, (unsigned)A.n_pt), block(256);
+  if (!A.nodes) hipLaunchKernelGGL(xs_params_kernel<0>, grid, block, 0, st, A);
+  else if (A.moments == kMomFp32)
+    hipLaunchKernelGGL(xs_params_kernel<kMomFp32>, grid, block, 0, st, A);
+  else
+    hipLaunchKernelGGL(xs_params_kernel<kMomFp64>, grid, block, 0, st, A);
   return hipGetLastError();
 }
 
@@ -350,18 +368,18 @@ hipError_t launch_select(const TileArgs& A, int P, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(const double* part, void* out, int out_f32, int64_t n_grid, int n_pts,
-                         int split, hipStream_t st) {
+hipError_t launch_reduce(const double* part, const double* far, void* out, int out_f32,
+                         int64_t n_grid, int n_pts, int split, hipStream_t st) {
   const int64_t total = (int64_t)n_pts * n_grid;
   int64_t blocks = (total + 255) / 256;
   if (blocks > 65536) blocks = 65536;
   if (blocks < 1) blocks = 1;
   if (out_f32)
-    hipLaunchKernelGGL(xs_reduce_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, st, part,
+    hipLaunchKernelGGL(xs_reduce_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, st, part, far,
                        (float*)out, n_grid, n_pts, split);
   else
     hipLaunchKernelGGL(xs_reduce_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, st,
-                       part, (double*)out, n_grid, n_pts, split);
+                       part, far, (double*)out, n_grid, n_pts, split);
   return hipGetLastError();
 }
 

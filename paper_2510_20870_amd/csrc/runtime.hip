@@ -183,10 +183,41 @@ static void line_range(const LinesRes& L, const GridRes& G, const xs_opts& o, in
   line_range_nu(L, G.first, G.last, o.cut_cm1, lo, hi);
 }
 
+// Far field by moments, chosen where a tile's window holds enough lines beyond its near
+// range: with a fixed cut (every line of a group then ends at the same distance), no
+// selection (which drops lines one by one) and the automatic tile_group.
+static bool use_moments(const LinesRes& L, const GridRes& G, const xs_opts& o) {
+  if (o.tile_group != 0 || o.cutoff_kind != XS_CUT_FIXED || o.select_eps > 0.0 || L.n == 0)
+    return false;
+  // lines within the cut of the grid's middle
+  const double mid = G.host[G.n / 2];
+  const std::vector<double>& sm = L.sample;
+  const int64_t w = (int64_t)(std::upper_bound(sm.begin(), sm.end(), mid + o.cut_cm1) -
+                              std::lower_bound(sm.begin(), sm.end(), mid - o.cut_cm1)) *
+                    kSampleStride;
+  return w >= kMomentLines;
+}
+
+void Plan::set_tree() {
+  int64_t n = rec_n, span = kLeafLines;
+  dims = TreeDims{};
+  for (int l = 0; l < kTreeLevels; ++l) {
+    dims.off[l] = dims.n_nodes;
+    dims.cnt[l] = std::max<int64_t>(1, (n + span - 1) / span);
+    dims.n_nodes += dims.cnt[l];
+    dims.levels = l + 1;
+    if (dims.cnt[l] < kArity) break;   // no full node above
+    span *= kArity;
+  }
+}
+
 Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const xs_opts& o,
-               size_t cap_bytes, int64_t max_item_lines, int items_per_slot) {
+               size_t cap_bytes, int64_t max_item_lines, int items_per_slot, bool far_moments) {
   Plan p;
-  p.P = o.pts_per_lane ? o.pts_per_lane : 2;
+  p.n_grid = (int64_t)G.n;
+  if (far_moments && use_moments(L, G, o))
+    p.moments = o.precision == XS_FP64 ? kMomFp64 : kMomFp32;
+  p.P = o.pts_per_lane ? o.pts_per_lane : p.moments ? 1 : 2;
   p.select_eps = o.select_eps;
   const bool f64 = o.precision == XS_FP64;
   p.W = waves_target(o.waves_per_simd, p.P, f64);
@@ -211,6 +242,8 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const x
                          p.P <= 2;
   if (o.tile_group == kGroup) {
     p.group = kGroup;
+  } else if (p.moments) {
+    p.group = 1;
   } else if (o.tile_group == 0 && can_group && G.n >= 2) {
     const size_t m = std::min<size_t>(G.n / 2, G.n - 2);
     const double hv = 0.5 * (double)(kGroup * tile) * (G.host[m + 1] - G.host[m]);
@@ -221,6 +254,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const x
   int64_t hi = 0;
   line_range(L, G, o, &p.rec_lo, &hi);
   p.rec_n = hi - p.rec_lo;
+  if (p.moments) p.set_tree();
   // line windows of the units (from the sampled index, within the largest cut)
   const std::vector<double>& sm = L.sample;
   std::vector<int64_t>& cost = p.tile_cost;
@@ -233,7 +267,13 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const x
                         std::lower_bound(sm.begin(), sm.end(), lo));
     max_cost = std::max(max_cost, cost[t]);
   }
-  const int64_t max_window = (max_cost + 1) * kSampleStride;   // lines, upper estimate
+  int64_t max_window = (max_cost + 1) * kSampleStride;   // lines, upper estimate
+  if (p.moments && p.n_units > 0) {
+    // of which a tile walks its near range: its own span and about half of that around it
+    const double span = (G.last - G.first) / (double)p.n_units;
+    max_window = (int64_t)((double)max_window *
+                           std::min(1.0, 1.5 * span / (span + 2.0 * o.cut_cm1))) + kLeafLines;
+  }
   if (o.split) {
     p.split = o.split;
   } else {
@@ -264,7 +304,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const x
   }
   const size_t per_pt = std::max<size_t>(
       1, (size_t)p.rec_n * 32 + (p.split > 1 ? (size_t)p.split * G.n * 8 : 0) +
-             (p.select_eps > 0.0 ? (size_t)p.n_groups() * 8 : 0));
+             p.extra_bytes());
   p.pt_batch = (int)std::max<size_t>(1, std::min<size_t>(npts, cap / per_pt));
   // issue order: tiles by decreasing number of lines within the largest cut, so the most
   // expensive work items start first
@@ -319,6 +359,8 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
   cut.kind = o.cutoff_kind == XS_CUT_FIXED ? kCutFixed : kCutMinFwhm;
   cut.cut = o.cut_cm1;
   cut.mult = o.fwhm_mult;
+  double* far = p.moments ? (double*)((char*)rec_dev + p.far_offset()) : nullptr;
+  NearRange* near = p.moments ? (NearRange*)((char*)rec_dev + p.near_offset()) : nullptr;
   hipError_t e;
   if (with_params) {
     ParamArgs PA;
@@ -332,8 +374,17 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
     PA.lo = p.rec_lo;
     PA.n = p.rec_n;
     PA.out = (LineRec*)rec_dev;
+    if (p.moments) {
+      PA.nodes = (char*)rec_dev + p.node_offset();
+      PA.dims = p.dims;
+      PA.moments = p.moments;
+    }
     e = launch_params(PA, st);
     if (e != hipSuccess) return hip_fail(e, "parameter kernel launch");
+    if (p.moments) {
+      e = launch_tree_up(PA, st);
+      if (e != hipSuccess) return hip_fail(e, "moment kernel launch");
+    }
     if (p.select_eps > 0.0) {
       // main-contributor selection: the thresholds of every tile group of the grid
       // (the tile launches of the batch, whatever their tile range, read them)
@@ -389,6 +440,34 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
     const int64_t phys = phys_workgroups(A.n_wg);
     int rc = tm ? tm->record(st) : XS_OK;
     if (rc) return rc;
+    if (p.moments && !counts) {
+      FarArgs F;
+      memset(&F, 0, sizeof F);
+      F.L = L.dev;
+      F.sp = L.sp;
+      F.cut = o.cut_cm1;
+      F.grid = G.d;
+      F.n_grid = (int64_t)G.n;
+      F.pts = pts_dev;
+      F.pt0 = pt0;
+      F.n_pt = nb;
+      F.P = p.P;
+      F.n_items = (c1 - c0) * nb;
+      F.tile_order = A.tile_order;
+      F.n_tiles = p.n_tiles;
+      F.recs = (const LineRec*)rec_dev;
+      F.rec_lo = p.rec_lo;
+      F.rec_n = p.rec_n;
+      F.nodes = (char*)rec_dev + p.node_offset();
+      F.dims = p.dims;
+      F.out = far;
+      F.near = near;
+      e = launch_far(F, p.moments, st);
+      if (e != hipSuccess) return hip_fail(e, "far kernel launch");
+      A.near = near;
+      A.near_stride = p.n_tiles;
+      A.far = far;
+    }
     if (counts) {
       A.counts = counts;
       e = launch_count(A, p.P, st, phys);
@@ -403,7 +482,7 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
     if (rc) return rc;
   }
   if (with_reduce && !counts && p.split > 1) {
-    e = launch_reduce((const double*)part_dev,
+    e = launch_reduce((const double*)part_dev, far,
                       (char*)out_dev + (size_t)pt0 * G.n * out_elem_bytes(o),
                       o.out_dtype == XS_F32, (int64_t)G.n, nb, p.split, st);
     if (e != hipSuccess) return hip_fail(e, "reduce kernel launch");
@@ -916,24 +995,26 @@ int xs_compute(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, size_t 
     e = hipEventSynchronize(c->pts_event);
     if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
   }
-  const Plan p = make_plan(*c, *L, *G, npts, *opts);
+  Plan p = make_plan(*c, *L, *G, npts, *opts);
   rc = upload_pts(*c, pts, npts, st);
   if (rc) return rc;
   const size_t out_bytes = npts * G->n * out_elem_bytes(*opts);
-  rc = c->scratch(c->rec_buf, p.rec_bytes(), "line records");
+  // records and partials; a call whose moments do not fit the budget goes line by line
+  auto buffers = [&]() {
+    int r = c->scratch(c->rec_buf, p.rec_bytes(), "line records");
+    if (r == XS_OK && p.split > 1)
+      r = c->scratch(c->part_buf, p.part_bytes(G->n), "split partials");
+    if (r == XS_OK && !out_on_device) r = c->scratch(c->out_buf, out_bytes, "output staging");
+    return r;
+  };
+  rc = buffers();
+  if (rc == XS_ENOMEM && p.moments) {
+    p = make_plan(*c, *L, *G, npts, *opts, 0, 0, 0, false);
+    rc = buffers();
+  }
   if (rc) return rc;
-  void* part = nullptr;
-  if (p.split > 1) {
-    rc = c->scratch(c->part_buf, p.part_bytes(G->n), "split partials");
-    if (rc) return rc;
-    part = c->part_buf.ptr;
-  }
-  void* out_dev = sigma_out;
-  if (!out_on_device) {
-    rc = c->scratch(c->out_buf, out_bytes, "output staging");
-    if (rc) return rc;
-    out_dev = c->out_buf.ptr;
-  }
+  void* part = p.split > 1 ? c->part_buf.ptr : nullptr;
+  void* out_dev = out_on_device ? sigma_out : c->out_buf.ptr;
   rc = upload_order(*c, p, st);
   if (rc) return rc;
   rc = enqueue_path(*L, *G, *opts, p, (const double*)c->pts_buf.ptr,
@@ -979,9 +1060,15 @@ int xs_compute_noalloc(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts,
   if (pts_area >= kNoAllocScratchBytes)
     return fail(XS_ENOMEM, "%zu P-T points exceed the scratch of %zu bytes", npts,
                 kNoAllocScratchBytes);
-  const Plan p = make_plan(*c, *L, *G, npts, *opts, kNoAllocScratchBytes - pts_area);
-  const size_t rec_area = al(p.rec_bytes());
-  const size_t need = pts_area + rec_area + p.part_bytes(G->n);
+  Plan p = make_plan(*c, *L, *G, npts, *opts, kNoAllocScratchBytes - pts_area);
+  size_t rec_area = al(p.rec_bytes());
+  size_t need = pts_area + rec_area + p.part_bytes(G->n);
+  if (need > kNoAllocScratchBytes && p.moments) {
+    // one point fits only without the moments: line by line
+    p = make_plan(*c, *L, *G, npts, *opts, kNoAllocScratchBytes - pts_area, 0, 0, false);
+    rec_area = al(p.rec_bytes());
+    need = pts_area + rec_area + p.part_bytes(G->n);
+  }
   if (need > kNoAllocScratchBytes)
     return fail(XS_ENOMEM,
                 "one P-T point needs %zu bytes of scratch (records of %lld lines, %d split "
@@ -1155,7 +1242,7 @@ int xs_graph_create(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, si
   };
   hipError_t e = hipSetDevice(c->device);
   if (e != hipSuccess) return give_up(hip_fail(e, "hipSetDevice"));
-  const Plan p = make_plan(*c, *L, *G, npts, *opts);
+  Plan p = make_plan(*c, *L, *G, npts, *opts);
   g->pts_bytes = npts * 2 * sizeof(double);
   rc = c->dev_alloc(&g->pts, g->pts_bytes, "graph point table");
   if (rc) return give_up(rc);
@@ -1166,13 +1253,25 @@ int xs_graph_create(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, si
   }
   e = hipMemcpy(g->pts, h.data(), g->pts_bytes, hipMemcpyHostToDevice);
   if (e != hipSuccess) return give_up(hip_fail(e, "graph point table upload"));
-  if (p.split > 1) {
-    g->part_bytes = p.part_bytes(G->n);
-    rc = c->dev_alloc(&g->part, g->part_bytes, "graph partials");
-    if (rc) return give_up(rc);
+  // records and partials; a graph whose moments do not fit the budget goes line by line
+  auto buffers = [&]() {
+    g->rec_bytes = p.rec_bytes();
+    int r = c->dev_alloc(&g->rec, g->rec_bytes, "graph line records");
+    if (r != XS_OK) g->rec = nullptr;
+    if (r == XS_OK && p.split > 1) {
+      g->part_bytes = p.part_bytes(G->n);
+      r = c->dev_alloc(&g->part, g->part_bytes, "graph partials");
+      if (r != XS_OK) g->part = nullptr;
+    }
+    return r;
+  };
+  rc = buffers();
+  if (rc == XS_ENOMEM && p.moments) {
+    if (g->rec) c->dev_free(g->rec, g->rec_bytes);
+    g->rec = nullptr;
+    p = make_plan(*c, *L, *G, npts, *opts, 0, 0, 0, false);
+    rc = buffers();
   }
-  g->rec_bytes = p.rec_bytes();
-  rc = c->dev_alloc(&g->rec, g->rec_bytes, "graph line records");
   if (rc) return give_up(rc);
   g->order_bytes = p.tile_order.size() * sizeof(int);
   rc = c->dev_alloc(&g->order, g->order_bytes, "graph tile order");

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/xsec.h"
+#include "far_tree.h"
 #include "kernel_args.h"
 
 namespace xs {
@@ -36,6 +37,9 @@ constexpr int64_t kSampleStride = 1024;
 // at or under it, so that a new request's kernels find free wavefront slots quickly).
 constexpr int64_t kServeItemLines = 4096;
 
+// Lines within the cut of the grid's middle from which the far field goes by moments.
+constexpr int64_t kMomentLines = 16384;
+
 struct GridRes {
   double* d = nullptr;
   size_t n = 0;
@@ -60,11 +64,33 @@ struct Plan {
   std::vector<int64_t> tile_cost;  // sampled line count in each unit's window (x 1024)
   bool tuned = false;              // launch shape from the tuning cache
   double select_eps = 0.0;         // main-contributor selection (0: off)
+  // Far field by moments (far_tree.h): the tree over the records, 0 moments: off.
+  int moments = 0;
+  TreeDims dims{};
+  int64_t n_grid = 0;
+  size_t node_bytes() const {
+    return moments == kMomFp32 ? sizeof(FarNode<kMomFp32>) : sizeof(FarNode<kMomFp64>);
+  }
+  void set_tree();   // dims from rec_n
   // line records [pt_batch][rec_n] (32 B), then with selection the thresholds of the
-  // groups of kSelGroup tiles [pt_batch][n_groups()] (8 B)
+  // groups of kSelGroup tiles [pt_batch][n_groups()] (8 B), or with the far field by moments
+  // the tree [pt_batch][n_nodes], the far sums [pt_batch][n_grid] (8 B) and the near ranges
+  // [pt_batch][n_tiles] (16 B)
   int64_t n_groups() const { return (n_tiles + kSelGroup - 1) / kSelGroup; }
   size_t tau_offset() const { return (size_t)rec_n * pt_batch * 32; }
+  size_t node_offset() const { return tau_offset(); }
+  size_t far_offset() const {
+    return node_offset() + (size_t)pt_batch * dims.n_nodes * node_bytes();
+  }
+  size_t near_offset() const { return far_offset() + ((size_t)pt_batch * n_grid * 8 + 15) / 16 * 16; }
+  // bytes per P-T point beside the records
+  size_t extra_bytes() const {
+    return moments ? (size_t)dims.n_nodes * node_bytes() + (size_t)n_grid * 8 +
+                         (size_t)n_tiles * sizeof(NearRange)
+           : select_eps > 0.0 ? (size_t)n_groups() * 8 : 0;
+  }
   size_t rec_bytes() const {
+    if (moments) return near_offset() + (size_t)pt_batch * n_tiles * sizeof(NearRange);
     return tau_offset() + (select_eps > 0.0 ? (size_t)pt_batch * n_groups() * 8 : 0);
   }
   size_t part_bytes(size_t n_grid) const {
@@ -133,9 +159,11 @@ int validate_pts(const xs_pt* pts, size_t npts);
 // the inputs, the options and max_item_lines, never on the memory left.
 // items_per_slot > 0 sets the work items per resident wavefront slot of the automatic
 // split (default 4). With pts_per_lane, split and waves_per_simd all 0 the shape comes
-// from the tuning cache when it holds the workload's class.
+// from the tuning cache when it holds the workload's class. far_moments false: every line by
+// the tile kernel (the callers' second choice where memory for the moments is missing).
 Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const xs_opts& o,
-               size_t cap_bytes = 0, int64_t max_item_lines = 0, int items_per_slot = 0);
+               size_t cap_bytes = 0, int64_t max_item_lines = 0, int items_per_slot = 0,
+               bool far_moments = true);
 
 // Lines [lo, hi) that can reach [first, last] within cut (from the sampled index; the
 // range errs on the inclusive side).

@@ -566,24 +566,33 @@ static int submit(Ctx* c, xs_lines_t lh, xs_grid_t gh, bool window, double nu_st
   }
   r->out = sigma_out;
   r->out_dev = out_on_device != 0;
-  r->plan = make_plan(*c, *r->L, *r->G, npts, *opts, s->mem / 4, kServeItemLines);
   const size_t n = r->G->n;
-  size_t at = 0;
-  auto part = [&](size_t bytes) {
-    const size_t o = at;
-    at += round256(bytes);
-    return o;
+  // the launch plan and the parts of the request's arena block
+  auto lay_out = [&](bool far_moments) {
+    r->plan = make_plan(*c, *r->L, *r->G, npts, *opts, s->mem / 4, kServeItemLines, 0, far_moments);
+    size_t at = 0;
+    auto part = [&](size_t bytes) {
+      const size_t o = at;
+      at += round256(bytes);
+      return o;
+    };
+    r->o_rec = part(r->plan.rec_bytes());
+    r->o_part = part(r->plan.part_bytes(n));
+    r->o_out = part(r->out_dev ? 0 : npts * n * out_elem_bytes(*opts));
+    r->o_grid = part(window ? n * sizeof(double) : 0);
+    r->o_pts = part(npts * 2 * sizeof(double));
+    r->o_order = part(r->plan.tile_order.size() * sizeof(int));
+    r->bytes = at;
+    r->pin_bytes = round256(npts * 2 * sizeof(double)) + r->plan.tile_order.size() * sizeof(int);
   };
-  r->o_rec = part(r->plan.rec_bytes());
-  r->o_part = part(r->plan.part_bytes(n));
-  r->o_out = part(r->out_dev ? 0 : npts * n * out_elem_bytes(*opts));
-  r->o_grid = part(window ? n * sizeof(double) : 0);
-  r->o_pts = part(npts * 2 * sizeof(double));
-  r->o_order = part(r->plan.tile_order.size() * sizeof(int));
-  r->bytes = at;
-  r->pin_bytes = round256(npts * 2 * sizeof(double)) + r->plan.tile_order.size() * sizeof(int);
+  auto fits = [&]() {
+    return r->bytes <= s->arena.size() && round256(r->pin_bytes) <= s->pin_arena.size();
+  };
+  lay_out(true);
+  // a request that the arena holds only without the moments goes line by line
+  if (!fits() && r->plan.moments) lay_out(false);
   s->build_steps(*r);
-  if (r->bytes > s->arena.size() || round256(r->pin_bytes) > s->pin_arena.size()) {
+  if (!fits()) {
     const size_t b = r->bytes;
     r->L->refs.fetch_sub(1);
     if (!window) r->G->refs.fetch_sub(1);

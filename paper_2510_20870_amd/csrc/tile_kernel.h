@@ -286,7 +286,14 @@ __device__ __forceinline__ bool decode_item(const TileArgs& A, int lane, ItemInf
   it.tile = tile;
   it.nu_last = A.grid[jl];
   int64_t lo, hi;
-  line_window(A, it.k, A.grid[it.j0], it.nu_last, lane, &lo, &hi);
+  if (A.near) {
+    // far field by moments: only the lines of the tile's near range are walked
+    const NearRange nr = A.near[(int64_t)it.k * A.near_stride + tile];
+    lo = A.rec_lo + nr.n0;
+    hi = A.rec_lo + nr.n1;
+  } else {
+    line_window(A, it.k, A.grid[it.j0], it.nu_last, lane, &lo, &hi);
+  }
   const int64_t cnt = hi > lo ? hi - lo : 0;
   it.b = lo + cnt * it.s / A.split;
   it.e = lo + cnt * (it.s + 1) / A.split;
@@ -1307,6 +1314,9 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
       if constexpr (F64) v = s[p];
       else v = ldexp((double)s[p] - (double)c[p], e_ref - kScaleTarget);
       if constexpr (GRP) v += gv[p];
+      if constexpr (!GRP && !SEL) {
+        if (A.far && A.split == 1) v += A.far[(int64_t)it.k * A.n_grid + j];
+      }
       if (A.out_f32) ((float*)A.out)[row * A.n_grid + j] = (float)v;
       else A.out[row * A.n_grid + j] = v;
     }

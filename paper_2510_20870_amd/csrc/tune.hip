@@ -215,6 +215,7 @@ int time_candidate(Ctx& c, const LinesRes& L, const GridRes& G, const xs_opts& o
     p.rec_n = b.rec_n;
     p.npts = nprobe;
     p.pt_batch = nprobe;
+    if (p.moments) p.set_tree();
     const int64_t t0 = b.j0 / tile, t1 = (b.j1 + tile - 1) / tile;
     const int64_t nt = t1 - t0;
     int64_t sp = std::max<int64_t>(p.split, (round_items + nt * nprobe - 1) / (nt * nprobe));
