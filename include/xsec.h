@@ -185,11 +185,11 @@ typedef struct { double P_bar, T_K; } xs_pt;
  * cut, are expanded once about the span's centre, the expansion split among the four
  * wavefronts and added in a fixed order (FP32 path, fixed cut, no selection, 1 or 2
  * points per lane; XS_EINVAL otherwise). 0: automatic. With a fixed cut, no selection and
- * enough lines inside the cut, the lines far from a tile enter by moments of line groups
- * (FP64, within 5e-8 of each line's contribution on the FP32 path and 1e-13 on the FP64
- * path), and each wavefront walks only the lines near its tile; where the memory for the
- * moments (about 3 bytes per line, FP64 path 5) is missing, and everywhere else, 4 where it
- * applies and the cut spans at least 3 kappa half-widths of a four-tile span at the grid's
+ * enough lines inside the cut, the lines far from a grid point enter by moments of line
+ * groups (FP64, within 5e-8 of each line's contribution on the FP32 path and 1e-13 on the
+ * FP64 path) and only those near it one by one (pts_per_lane and waves_per_simd then shape
+ * only the (P, T) points whose lines are so broad that tiles take them); where the memory for the moments (about 13 bytes per line and (P, T) point, FP64 path
+ * 21) is missing, and everywhere else, 4 where it applies and the cut spans at least 3 kappa half-widths of a four-tile span at the grid's
  * middle, kappa the far threshold below, else 1.
  * tol: the error budget of the FP32 path's cheaper far forms, relative to each line's
  * contribution at each point (section "Functionality of pyROX" leaves the accuracy of the

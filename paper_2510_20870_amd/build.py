@@ -20,7 +20,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libxsec.so")
 ARCH = os.environ.get("XSEC_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["kernels.hip", "far.hip", "tile_p1.hip", "tile_p2.hip", "tile_p4.hip", "tile_p8.hip",
+SOURCES = ["kernels.hip", "far.hip", "point.hip", "tile_p1.hip", "tile_p2.hip", "tile_p4.hip", "tile_p8.hip",
            "runtime.hip", "serve.hip", "tune.hip", "regrid.hip"]
 
 # -ffp-contract=off: no implicit FMA anywhere (the cutoff test must match a plain FP64

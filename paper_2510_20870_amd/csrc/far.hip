@@ -1,5 +1,8 @@
 // Far field by moments of line groups (far_tree.h): the levels of the tree above its leaves,
-// and the far kernel, which sums for every grid tile the lines outside its near range.
+// and the far kernel, which sums for every grid tile the lines outside its near range. The
+// tile kernel walks the near range; this pair serves the (P, T) points whose lines are so
+// broad that a near range spans many tiles (there the tile polynomial takes most of it). The
+// others go by the point kernel (point.hip).
 //
 // Section "Functionality of pyROX" (bullets "Compute line profiles", "Combine and save"): the
 // sum over every line inside the cutoff; here the lines far from a grid point enter group by
@@ -9,97 +12,113 @@
 
 namespace xs {
 
-static __device__ const BinomTable kBinom = make_binom();
-
-// Scale of a node from its extent and its largest Lorentz width (b = kb nu0).
-template <int NM>
-__device__ __forceinline__ double node_scale(double lo, double hi, double g, double kb) {
-  const double h = 0.5 * (hi - lo);
-  return sqrt(fma(h, h, g * g)) + far_beta<NM>() * (kb * hi);
-}
-
-// Moment m of a parent (centre c, 1/scale is) from n children.
-template <int NM>
-__device__ __forceinline__ double shift_moment(const FarNode<NM>* ch, int n, int m, double c,
-                                               double is) {
-  double sum = 0.0;
-  for (int q = 0; q < n; ++q) {
-    const FarNode<NM>& f = ch[q];
-    const double D = (0.5 * (f.lo + f.hi) - c) * is, R = f.s * is;
-    // sum_j C(m, j) D^j R^(m-j) A_(m-j), Horner in D
-    double pw = R;
-    double acc = kBinom.c[m][m - 1] * pw * f.A[0];
-    for (int j = m - 2; j >= 0; --j) {
-      pw *= R;
-      acc = fma(acc, D, kBinom.c[m][j] * pw * f.A[m - j - 1]);
-    }
-    sum += acc;
+// 1/n! and n! for n <= kMomFp64
+struct Factorials {
+  double inv[kMomFp64 + 1], val[kMomFp64 + 1];
+};
+constexpr Factorials make_factorials() {
+  Factorials f{};
+  f.inv[0] = f.val[0] = 1.0;
+  for (int n = 1; n <= kMomFp64; ++n) {
+    f.val[n] = f.val[n - 1] * n;
+    f.inv[n] = 1.0 / f.val[n];
   }
-  return sum;
+  return f;
 }
+static __device__ const Factorials kFact = make_factorials();
 
-// Two levels at once: a workgroup takes kArity^2 nodes of level l (staged in LDS), writes
-// their kArity parents and, where the level exists, the one parent of those. One thread per
-// (parent, moment).
+// Three levels at once: a workgroup takes 64 nodes of level l, writes their 16 parents and,
+// where those levels exist, the 4 parents of those and the one above. A child's moments move
+// to the parent's centre and scale by the binomial theorem, which for moments divided by m!
+// is a plain product of series: T'_m / m! = sum_k (R^k A_k / k!) (D^(m-k) / (m-k)!), D the
+// distance of the centres and R the child's scale, in parent scales. Both series are
+// written to LDS first, one thread per term, so that the products run without a chain.
+// Latency sets its time (one workgroup per 1024 lines, three short dependent phases per
+// level).
 template <int NM>
 __global__ __launch_bounds__(256) void xs_tree_up_kernel(ParamArgs A, int l) {
-  constexpr int kChild = kArity * kArity;
-  __shared__ FarNode<NM> ch[kChild], up[kArity];
+  constexpr int kChild = 64, NF = node_fields<NM>(), kPad = NF + 1;
+  __shared__ double ch[kChild][kPad];        // the children's fields
+  __shared__ double ra[kChild][NM + 1], ed[kChild][NM];   // R^k A_k / k!, D^j / j!
   const int k = blockIdx.y;
-  FarNode<NM>* nodes = (FarNode<NM>*)A.nodes + (int64_t)k * A.dims.n_nodes;
+  double* nodes = A.nodes + (int64_t)k * A.dims.n_nodes * NF;
   const double kb =
       make_pt(A.sp, A.pts[2 * (A.pt0 + k)], A.pts[2 * (A.pt0 + k) + 1]).dopp / kCLight;
   const int64_t c0 = (int64_t)blockIdx.x * kChild;
-  const int nc = (int)min((int64_t)kChild, A.dims.cnt[l] - c0);
-  constexpr int kWords = sizeof(FarNode<NM>) / sizeof(double);
-  typedef double __attribute__((may_alias)) word;
+  int nc = (int)min((int64_t)kChild, A.dims.cnt[l] - c0);
   {
-    const word* src = (const word*)(nodes + A.dims.off[l] + c0);
-    word* dst = (word*)ch;
-    for (int t = threadIdx.x; t < nc * kWords; t += blockDim.x) dst[t] = src[t];
+    const double* src = nodes + node_pos<NM>(A.dims.off[l] + c0);
+    for (int t = threadIdx.x; t < kChild * NF; t += blockDim.x) {
+      const int blk = t / (kNodeBlock * NF), r = t - blk * (kNodeBlock * NF);
+      const int f = r / kNodeBlock, n = blk * kNodeBlock + r % kNodeBlock;
+      if (n < nc) ch[n][f] = src[t];
+    }
   }
   __syncthreads();
-  auto level = [&](const FarNode<NM>* from, int nfrom, FarNode<NM>* lds, FarNode<NM>* to) {
-    const int np = (nfrom + kArity - 1) / kArity;
+  int per = kChild / kArity;   // parents of a whole workgroup at the next level
+  for (int up = l + 1; up <= l + 3 && up < A.dims.levels; ++up, per /= kArity) {
+    const int np = (nc + kArity - 1) / kArity;
+    // a parent's extent, largest width and scale, from its children in LDS
+    auto parent = [&](int q, double* lo, double* hi, double* g, double* sc) {
+      const int c1 = min(kArity * q + kArity, nc) - 1;
+      *lo = ch[kArity * q][kNodeLo];
+      *hi = ch[c1][kNodeHi];
+      double gm = 0.0;
+      for (int i = kArity * q; i <= c1; ++i) gm = fmax(gm, ch[i][kNodeG]);
+      *g = gm;
+      const double h = 0.5 * (*hi - *lo);
+      *sc = sqrt(fma(h, h, gm * gm)) + far_beta<NM>() * (kb * *hi);
+    };
+    for (int t = threadIdx.x; t < nc * NM; t += blockDim.x) {
+      const int i = t / NM, j = t - i * NM;
+      double lo, hi, g, sc;
+      parent(i / kArity, &lo, &hi, &g, &sc);
+      const double is = 1.0 / sc;
+      const double D = (0.5 * (ch[i][kNodeLo] + ch[i][kNodeHi]) - 0.5 * (lo + hi)) * is;
+      const double R = ch[i][kNodeS] * is;
+      double pd = 1.0, pr = R;
+      for (int q = 0; q < j; ++q) {
+        pd *= D;
+        pr *= R;
+      }
+      ed[i][j] = pd * kFact.inv[j];
+      ra[i][j + 1] = pr * kFact.inv[j + 1] * ch[i][kNodeA + j];
+    }
+    // (the parents' headers stay in registers over the barrier: ch is overwritten)
+    double hlo = 0.0, hhi = 0.0, hg = 0.0, hs = 0.0;
+    if ((int)threadIdx.x < np) parent((int)threadIdx.x, &hlo, &hhi, &hg, &hs);
+    __syncthreads();
+    const int64_t q0 = (int64_t)blockIdx.x * per;
     for (int t = threadIdx.x; t < np * NM; t += blockDim.x) {
       const int q = t / NM, m = t - q * NM + 1;
-      const FarNode<NM>* f = from + q * kArity;
-      const int n = min(kArity, nfrom - q * kArity);
-      const double lo = f[0].lo, hi = f[n - 1].hi;
-      double g = 0.0;
-      for (int i = 0; i < n; ++i) g = fmax(g, f[i].g);
-      const double s = node_scale<NM>(lo, hi, g, kb);
-      const double a = shift_moment<NM>(f, n, m, 0.5 * (lo + hi), 1.0 / s);
-      to[q].A[m - 1] = a;
-      if (lds) lds[q].A[m - 1] = a;
-      if (m == 1) {
-        to[q].lo = lo;
-        to[q].hi = hi;
-        to[q].s = s;
-        to[q].g = g;
-        if (lds) {
-          lds[q].lo = lo;
-          lds[q].hi = hi;
-          lds[q].s = s;
-          lds[q].g = g;
-        }
+      const int c1 = min(kArity * q + kArity, nc);
+      double sum = 0.0;
+      for (int i = kArity * q; i < c1; ++i) {
+        double a = 0.0;
+        for (int j = 1; j <= m; ++j) a = fma(ra[i][j], ed[i][m - j], a);
+        sum += a;
       }
+      sum *= kFact.val[m];
+      ch[q][kNodeA + m - 1] = sum;
+      nodes[node_pos<NM>(A.dims.off[up] + q0 + q) + (kNodeA + m - 1) * kNodeBlock] = sum;
     }
-    return np;
-  };
-  const bool two = l + 2 < A.dims.levels;
-  const int np = level(ch, nc, two ? up : nullptr,
-                       nodes + A.dims.off[l + 1] + (int64_t)blockIdx.x * kArity);
-  if (!two) return;
-  __syncthreads();
-  level(up, np, nullptr, nodes + A.dims.off[l + 2] + blockIdx.x);
+    if ((int)threadIdx.x < np) {
+      const int q = threadIdx.x;
+      const NodeRef<NM, double> nd{nodes + node_pos<NM>(A.dims.off[up] + q0 + q)};
+      ch[q][kNodeLo] = nd.at(kNodeLo) = hlo;
+      ch[q][kNodeHi] = nd.at(kNodeHi) = hhi;
+      ch[q][kNodeS] = nd.at(kNodeS) = hs;
+      ch[q][kNodeG] = nd.at(kNodeG) = hg;
+    }
+    nc = np;
+    __syncthreads();
+  }
 }
 
 hipError_t launch_tree_up(const ParamArgs& A, hipStream_t st) {
   if (A.n <= 0 || A.n_pt <= 0) return hipSuccess;
-  for (int l = 0; l + 1 < A.dims.levels; l += 2) {
-    const int64_t blocks = (A.dims.cnt[l] + kArity * kArity - 1) / (kArity * kArity);
-    const dim3 grid((unsigned)blocks, (unsigned)A.n_pt), block(256);
+  for (int l = 0; l + 1 < A.dims.levels; l += 3) {
+    const dim3 grid((unsigned)((A.dims.cnt[l] + 63) / 64), (unsigned)A.n_pt), block(256);
     if (A.moments == kMomFp32)
       hipLaunchKernelGGL(xs_tree_up_kernel<kMomFp32>, grid, block, 0, st, A, l);
     else
@@ -110,35 +129,17 @@ hipError_t launch_tree_up(const ParamArgs& A, hipStream_t st) {
   return hipSuccess;
 }
 
-// One line at one point, with the cut test: the sums of the ragged ends of the far ranges
-// (lines of a leaf that the cut of a point splits) and of the few leaves that are neither far
-// nor inside the near range. FP32 path (NM = 16): the doubly shifted Lorentzian in FP64 where
-// it holds to 5e-8 (r >= 74), else the tile kernel's forms; FP64 path: voigt_k64.
-template <int NM>
-__device__ __forceinline__ double one_line(double nu, double nu0, const LineRec& r) {
-  const double d = nu - nu0;
-  if (!(fabs(d) <= r.cut)) return 0.0;
-  const double x = d * r.ib;
-  if constexpr (NM == kMomFp32) {
-    const double y2 = r.y * r.y;
-    const double r2 = fma(x, x, y2);
-    if (r2 >= 74.0 * 74.0)
-      return kInvSqrtPi * r.sc * r.y * r2 * rcp64(fma(r2, r2 - 1.5, 2.0 * y2));
-    return r.sc * (double)voigt_k32(x, (float)r.y);
-  } else {
-    return r.sc * voigt_k64(x, r.y);
-  }
-}
-
 // Far kernel. One workgroup per (tile, P-T point): wavefronts 0 and 1 take the groups left
 // and right of the near range that are inside the cut of every point of the tile (the same
 // nodes for all lanes), wavefronts 2 and 3 the lines beyond, up to each point's own cut
 // (a walk over nodes per lane). What bounds it is the latency of a node's loads and of its
 // Horner chain: the node counts grow with the logarithm of the window, not with its lines.
 //
-// Near range: from the tile outwards, the leaves up to the last of the leaves nearby that are
-// not far from the whole tile (|nu - c| < theta s for some point); each 64-leaf group is
-// tested at once, and the range ends at the first group of far leaves.
+// Near range: from the tile outwards by theta times the list's largest widths there, then
+// over the leaves up to the last of the leaves nearby that are not far from the whole tile
+// (|nu - c| < theta s for some point); each 64-leaf group is tested at once, and the range
+// ends at the first group of far leaves. (Taking the widths from the leaves alone costs a
+// dependent step per 64 leaves: 1.6 ms instead of 0.1 at 100 bar on the 1e9-line list.)
 template <int NM>
 __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -151,27 +152,27 @@ __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
   const int64_t jl = min(j0 + (int64_t)kWave * A.P, A.n_grid) - 1;
   const double g0 = A.grid[j0], g1 = A.grid[jl];
   const int pt = A.pt0 + k;
-  const double kb = make_pt(A.sp, A.pts[2 * pt], A.pts[2 * pt + 1]).dopp / kCLight;
+  const PtConst pc = make_pt(A.sp, A.pts[2 * pt], A.pts[2 * pt + 1]);
+  const double kb = pc.dopp / kCLight;
+  // the list's largest Lorentz width here
+  const double gmax = A.sp.gam_max * pc.pfac * fmax(pow(pc.tratio, A.sp.n_min),
+                                                    pow(pc.tratio, A.sp.n_max));
   const double cut = A.cut;
   const double* nu = A.L.nu0 + A.rec_lo;
   const LineRec* recs = A.recs + (int64_t)k * A.rec_n;
-  const FarNode<NM>* nodes = (const FarNode<NM>*)A.nodes + (int64_t)k * A.dims.n_nodes;
+  const double* nodes = A.nodes + (int64_t)k * A.dims.n_nodes * node_fields<NM>();
+  using Node = NodeRef<NM, const double>;
   const int levels = A.dims.levels;
   const bool left = (wv & 1) == 0, edge = wv >= 2;
-  auto node_at = [&](int l, int64_t q) -> const FarNode<NM>& {
-    return nodes[A.dims.off[l] + q];
-  };
+  auto node = [&](int l, int64_t q) -> Node { return node_at<NM>(nodes, A.dims, l, q); };
   // signed distance from v outwards to the node's centre
-  auto dist = [&](const FarNode<NM>& f, double v) {
-    const double c = 0.5 * (f.lo + f.hi);
-    return left ? v - c : c - v;
-  };
+  auto dist = [&](const Node& f, double v) { return left ? v - f.c() : f.c() - v; };
   const double g_near = left ? g0 : g1;   // the tile's point nearest to this side's lines
 
   // this side's ranges, in lines of the record range: near boundary (a leaf boundary),
   // lines inside the cut of every point up to `cov` (leaf boundary), reachable up to `end`
   int64_t near_b, cov, end;   // near_b, cov: leaf indices
-  const double reach = (kFarTheta * far_beta<NM>()) * kb * g_near;
+  const double reach = kFarTheta * (gmax + far_beta<NM>() * kb * g_near);
   if (left) {
     near_b = wave_search<false>(nu, A.rec_n, g0 - reach, lane) / kLeafLines;
     end = wave_search<false>(nu, A.rec_n, g0 - cut - fabs(g0) * 0x1p-48, lane);
@@ -189,8 +190,8 @@ __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
     const bool in = left ? q >= cov : q < cov;
     bool bad = false;
     if (in) {
-      const FarNode<NM>& f = node_at(0, q);
-      bad = dist(f, g_near) < kFarTheta * f.s;
+      const Node f = node(0, q);
+      bad = dist(f, g_near) < kFarTheta * f.s();
     }
     const uint64_t m = __ballot(bad);
     if (m == 0ull) break;
@@ -213,9 +214,12 @@ __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
     const int64_t j = j0 + (int64_t)kWave * p + lane;
     const double v = A.grid[min(j, jl)];
     double sum = 0.0;
-    auto add_node = [&](const FarNode<NM>& f) {
-      const double rX = rcp64(v - 0.5 * (f.lo + f.hi));
-      sum += moment_sum<NM>(f.A, f.s * rX, rX);
+    auto add_node = [&](const Node& f) {
+      const double rX = rcp64(v - f.c()), t = f.s() * rX;
+      double a = f.at(kNodeA + NM - 1);
+#pragma unroll
+      for (int m = NM - 2; m >= 0; --m) a = fma(a, t, f.at(kNodeA + m));
+      sum = fma(a * t, rX, sum);
     };
     auto add_lines = [&](int64_t i0, int64_t i1) {
       for (int64_t i = i0; i < i1; ++i) sum += one_line<NM>(v, nu[i], recs[i]);
@@ -225,11 +229,11 @@ __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
     auto pick = [&](int64_t pos, int64_t last, double w) {
       int l = -1;
       while (l + 1 < levels) {
-        const int sh = 3 * (l + 1);
+        const int sh = kArityBits * (l + 1);
         const int64_t size = (int64_t)1 << sh;
         if ((pos & (size - 1)) != 0 || (left ? pos - size < last : pos + size > last)) break;
-        const FarNode<NM>& f = node_at(l + 1, left ? (pos >> sh) - 1 : pos >> sh);
-        if (dist(f, w) < kFarTheta * f.s) break;
+        const Node f = node(l + 1, left ? (pos >> sh) - 1 : pos >> sh);
+        if (dist(f, w) < kFarTheta * f.s()) break;
         ++l;
       }
       return l;
@@ -244,8 +248,8 @@ __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
           pos = left ? pos - 1 : pos + 1;
           continue;
         }
-        const int sh = 3 * l;
-        add_node(node_at(l, left ? (pos >> sh) - 1 : pos >> sh));
+        const int sh = kArityBits * l;
+        add_node(node(l, left ? (pos >> sh) - 1 : pos >> sh));
         pos = left ? pos - ((int64_t)1 << sh) : pos + ((int64_t)1 << sh);
       }
     } else {
@@ -272,8 +276,8 @@ __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
             pos = left ? pos - 1 : pos + 1;
             continue;
           }
-          const int sh = 3 * l;
-          add_node(node_at(l, left ? (pos >> sh) - 1 : pos >> sh));
+          const int sh = kArityBits * l;
+          add_node(node(l, left ? (pos >> sh) - 1 : pos >> sh));
           pos = left ? pos - ((int64_t)1 << sh) : pos + ((int64_t)1 << sh);
         }
       }

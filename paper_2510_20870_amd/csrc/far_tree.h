@@ -12,46 +12,58 @@
 // The sums over a group's lines of (S/pi) V_m / s^m, s = sqrt(h^2 + g_max^2) + beta b_max
 // (h half the group's extent, c its middle), are its moments A_1 .. A_NM. They move to a
 // parent's centre by the binomial theorem. At |X| >= theta s the series is within
-// 5e-8 of every line's own contribution with 16 moments (theta 3.5, beta 2.3), and within
-// 3e-14 with 28 (beta 2.6), measured against a reference Faddeeva routine over the whole
+// 5e-8 of every line's own contribution with 16 moments (theta 3.5, beta 2.05), and within
+// 3e-14 with 28 (beta 2.35), measured against a reference Faddeeva routine over the whole
 // range of h, g and b. All of it is FP64.
+//
+// Leaves of 16 lines, because the lines of the leaves around a point are summed one by one:
+// a leaf's half extent enters the distance from which it counts as far 3.5-fold. Four
+// children, because a level's nodes then serve distances up to four times its own.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "kernel_args.h"
+#include "voigt.h"
 
 namespace xs {
 
-constexpr int kLeafLines = 64;       // one wavefront of lines
-constexpr int kArity = 8;
+constexpr int kLeafLines = 16;       // one DPP row of lines
+constexpr int kArityBits = 2;
+constexpr int kArity = 1 << kArityBits;
 constexpr double kFarTheta = 3.5;    // a group is far where |nu - c| >= kFarTheta * s
 // moments of the FP32 and the FP64 path, and the weight of the Doppler width in s
 constexpr int kMomFp32 = 16, kMomFp64 = 28;
-constexpr double kBetaFp32 = 2.3, kBetaFp64 = 2.6;
+constexpr double kBetaFp32 = 2.05, kBetaFp64 = 2.35;
 template <int NM> constexpr double far_beta() { return NM == kMomFp32 ? kBetaFp32 : kBetaFp64; }
 
+// A node's fields: centres of the group's first and last line, scale s, largest Lorentz
+// width, moments. Nodes are stored eight by eight, field by field (kNodeBlock nodes of a
+// field side by side), so that wavefronts reading one field of neighbouring nodes read
+// whole lines of the cache; every level starts at a multiple of kNodeBlock.
+constexpr int kNodeBlock = 8;
+enum { kNodeLo = 0, kNodeHi = 1, kNodeS = 2, kNodeG = 3, kNodeA = 4 };
+template <int NM> constexpr int node_fields() { return kNodeA + NM; }
+constexpr size_t node_bytes(int moments) { return (size_t)(kNodeA + moments) * sizeof(double); }
 template <int NM>
-struct alignas(16) FarNode {
-  double lo, hi;   // centres of the group's first and last line
-  double s;        // scale
-  double g;        // largest Lorentz width
-  double A[NM];    // A[m - 1]: moment m
+__host__ __device__ __forceinline__ int64_t node_pos(int64_t node) {
+  return (node / kNodeBlock) * (kNodeBlock * node_fields<NM>()) + node % kNodeBlock;
+}
+template <int NM, class T>   // T: double or const double
+struct NodeRef {
+  T* p;
+  __host__ __device__ __forceinline__ T& at(int f) const { return p[f * kNodeBlock]; }
+  __host__ __device__ __forceinline__ double lo() const { return at(kNodeLo); }
+  __host__ __device__ __forceinline__ double hi() const { return at(kNodeHi); }
+  __host__ __device__ __forceinline__ double s() const { return at(kNodeS); }
+  __host__ __device__ __forceinline__ double c() const { return 0.5 * (lo() + hi()); }
 };
-
-// C(n, k) for n <= kMomFp64
-struct BinomTable {
-  double c[kMomFp64 + 1][kMomFp64 + 1];
-};
-constexpr BinomTable make_binom() {
-  BinomTable t{};
-  for (int n = 0; n <= kMomFp64; ++n) {
-    t.c[n][0] = 1.0;
-    for (int k = 1; k <= n; ++k)
-      t.c[n][k] = t.c[n - 1][k - 1] + (k <= n - 1 ? t.c[n - 1][k] : 0.0);
-  }
-  return t;
+template <int NM>
+__host__ __device__ __forceinline__ NodeRef<NM, const double> node_at(const double* nodes,
+                                                                      const TreeDims& d, int l,
+                                                                      int64_t q) {
+  return {nodes + node_pos<NM>(d.off[l] + q)};
 }
 
 // Moments V_m (m = 1 .. NM, times w) of one line in units of the scale: d = (nu0 - c)/s,
@@ -74,30 +86,49 @@ __host__ __device__ __forceinline__ void line_moments(double w, double d, double
   }
 }
 
-// The series at X = nu - c: sum_m A_m s^m / X^(m+1).
-template <int NM>
-__host__ __device__ __forceinline__ double moment_sum(const double* A, double t, double rX) {
-  double f = A[NM - 1];
+#if defined(__HIPCC__)
+// Exchange with the lane whose index differs by the mask 8, 7, 2 or 1 inside a row of 16
+// lanes (row_ror:8, row_half_mirror, two quad permutations).
+template <int kCtrl>
+__device__ __forceinline__ double row_swap(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kCtrl, 0xf, 0xf,
+                                                            false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl,
+                                                            0xf, 0xf, false);
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+constexpr int kRowX8 = 0x128, kRowX7 = 0x141, kRowX2 = 0x4e, kRowX1 = 0xb1;
+
+// One step of a halving sum: lanes with `up` keep the upper half of v[0 .. 2n), the others
+// the lower, and add their partner's values of it.
+template <int kCtrl, int n, int kV>
+__device__ __forceinline__ void row_halve(double (&v)[kV], bool up) {
 #pragma unroll
-  for (int m = NM - 2; m >= 0; --m) f = fma(f, t, A[m]);
-  return f * t * rX;   // t = s / X, rX = 1 / X
+  for (int i = 0; i < n; ++i) {
+    const double x = v[i], y = v[i + n];
+    const double give = up ? x : y, keep = up ? y : x;
+    v[i] = keep + row_swap<kCtrl>(give);
+  }
 }
 
-#if defined(__HIPCC__)
-// One leaf from its wavefront's lines (lanes past the list's end repeat its last line with
-// w = 0; the lines are in order, so lane 63 holds the largest centre and Doppler width).
-// Each lane forms the moments of its line; the sums over the wavefront go by halving: at
-// every step a lane keeps half of the values and adds its partner's (NM + 1 exchanges
-// instead of 6 NM), after which lane i holds the sum of one moment.
+// One leaf from its 16 lanes' lines (lanes past the list's end repeat its last line with
+// w = 0; the lines are in order, so the row's last lane holds the largest centre and Doppler
+// width). Each lane forms the moments of its line; the sums over the row go by halving: at
+// every step a lane keeps half of the values and adds its partner's, so 16 sums over 16 lanes
+// take 15 exchanges, and lane i ends with moment i + 1 (28 moments: 2 i + 1 and 2 i + 2).
 template <int NM>
-__device__ __forceinline__ void leaf_moments(FarNode<NM>* node, double nu0, double w, double b,
-                                             double g, int lane) {
+__device__ __forceinline__ void leaf_moments(double* nodes, int64_t leaf, double nu0, double w,
+                                             double b, double g, int lane) {
   constexpr int kV = NM <= 16 ? 16 : 32;
-  static_assert(NM <= 32, "moments of a wavefront reduction");
-  const double lo = __shfl(nu0, 0), hi = __shfl(nu0, 63), bm = __shfl(b, 63);
+  static_assert(NM <= 32 && kLeafLines == 16, "a leaf is a DPP row");
+  const int row = lane & ~15, i = lane & 15;
+  const double lo = __shfl(nu0, row), hi = __shfl(nu0, row + 15), bm = __shfl(b, row + 15);
   double gm = g;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) gm = fmax(gm, __shfl_xor(gm, o));
+  gm = fmax(gm, row_swap<kRowX8>(gm));
+  gm = fmax(gm, row_swap<kRowX7>(gm));
+  gm = fmax(gm, row_swap<kRowX2>(gm));
+  gm = fmax(gm, row_swap<kRowX1>(gm));
   const double h = 0.5 * (hi - lo);
   const double s = sqrt(fma(h, h, gm * gm)) + far_beta<NM>() * bm;
   const double is = 1.0 / s;
@@ -109,27 +140,34 @@ __device__ __forceinline__ void leaf_moments(FarNode<NM>* node, double nu0, doub
 #pragma unroll
     for (int m = 0; m < kV; ++m) v[m] = m < NM ? A[m < NM ? m : 0] : 0.0;
   }
-  int o = 32, m = 0;
+  row_halve<kRowX8, kV / 2>(v, (i & 8) != 0);
+  row_halve<kRowX7, kV / 4>(v, (i & 4) != 0);
+  row_halve<kRowX2, kV / 8>(v, (i & 2) != 0);
+  row_halve<kRowX1, kV / 16>(v, (i & 1) != 0);
+  constexpr int kPer = kV / 16;   // moments per lane
+  const NodeRef<NM, double> nd{nodes + node_pos<NM>(leaf)};
 #pragma unroll
-  for (int n = kV / 2; n > 0; n >>= 1, o >>= 1) {
-    const bool up = (lane & o) != 0;
-#pragma unroll
-    for (int i = 0; i < n; ++i) {
-      const double give = up ? v[i] : v[i + n], keep = up ? v[i + n] : v[i];
-      v[i] = keep + __shfl_xor(give, o);
-    }
-    m = 2 * m + (up ? 1 : 0);
-  }
-  double t = v[0];
-#pragma unroll
-  for (; o > 0; o >>= 1) t += __shfl_xor(t, o);
-  constexpr int kRep = kWave / kV;   // lanes holding the same moment
-  if ((lane & (kRep - 1)) == 0 && m < NM) node->A[m] = t;
-  if (lane == 0) {
-    node->lo = lo;
-    node->hi = hi;
-    node->s = s;
-    node->g = gm;
+  for (int m = 0; m < kPer; ++m)
+    if (kPer * i + m < NM) nd.at(kNodeA + kPer * i + m) = v[m];
+  if (i < kNodeA) nd.at(i) = i == 0 ? lo : i == 1 ? hi : i == 2 ? s : gm;
+}
+// One line at one point, with the cut test: the sums of the ragged ends of the far ranges
+// (lines of a leaf that the cut of a point splits) and of the few leaves that are neither far
+// nor inside the near range. FP32 path (NM = 16): the doubly shifted Lorentzian in FP64 where
+// it holds to 5e-8 (r >= 74), else the tile kernel's forms; FP64 path: voigt_k64.
+template <int NM>
+__device__ __forceinline__ double one_line(double nu, double nu0, const LineRec& r) {
+  const double d = nu - nu0;
+  if (!(fabs(d) <= r.cut)) return 0.0;
+  const double x = d * r.ib;
+  if constexpr (NM == kMomFp32) {
+    const double y2 = r.y * r.y;
+    const double r2 = fma(x, x, y2);
+    if (r2 >= 74.0 * 74.0)
+      return kInvSqrtPi * r.sc * r.y * r2 * rcp64(fma(r2, r2 - 1.5, 2.0 * y2));
+    return r.sc * (double)voigt_k32(x, (float)r.y);
+  } else {
+    return r.sc * voigt_k64(x, r.y);
   }
 }
 #endif

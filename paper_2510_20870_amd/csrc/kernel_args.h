@@ -38,7 +38,8 @@ struct LineRec {
 
 // Tree of line groups over the record range [rec_lo, rec_lo + rec_n) (far_tree.h): level l
 // has cnt[l] nodes from index off[l], n_nodes in all, one array of them per (P, T) point.
-constexpr int kTreeLevels = 5;
+constexpr int kPointGroup = 8;   // grid points per wavefront of the point kernel
+constexpr int kTreeLevels = 7;
 struct TreeDims {
   int64_t off[kTreeLevels];
   int64_t cnt[kTreeLevels];
@@ -59,7 +60,7 @@ struct ParamArgs {
   int pt0, n_pt;          // this batch: points pt0 .. pt0 + n_pt - 1
   int64_t lo, n;          // line range [lo, lo + n)
   LineRec* out;           // [n_pt][n]
-  void* nodes;            // tree nodes [n_pt][dims.n_nodes] (nullptr: no tree)
+  double* nodes;          // tree nodes [n_pt][dims.n_nodes] (nullptr: no tree)
   TreeDims dims;
   int moments;            // kMomFp32 or kMomFp64
 };
@@ -80,10 +81,32 @@ struct FarArgs {
   int64_t n_tiles;        // tiles of the whole grid
   const LineRec* recs;
   int64_t rec_lo, rec_n;
-  const void* nodes;
+  const double* nodes;
   TreeDims dims;
   double* out;            // [n_pt][n_grid]
   NearRange* near;        // [n_pt][n_tiles]
+};
+
+// The point kernel: whole sums at kPointGroup neighbouring grid points per wavefront.
+struct PointArgs {
+  LinesDev L;
+  SpeciesDev sp;
+  double cut;             // the fixed cut
+  const double* grid;
+  int64_t n_grid;
+  const double* pts;      // [n_pts][2], whole table
+  int pt0, n_pt;          // points of this launch
+  int split;              // parts of a group's work, each a wavefront of its own
+  int64_t g0, n_groups;   // groups of kPointGroup grid points
+  const LineRec* recs;    // [n_pt][rec_n]
+  int64_t rec_lo;
+  int rec_n;
+  const double* nodes;
+  TreeDims dims;
+  void* out;              // split == 1: sigma rows [n_pts][n_grid] (row pt0 + k); else
+                          // partials [n_pt][split][n_grid] (double)
+  int out_f32;
+  float l1_eps;           // error budget of the shifted Lorentzian
 };
 
 struct TileArgs {
@@ -141,6 +164,7 @@ hipError_t launch_tile_p8(const TileArgs& A, bool f64, int W, hipStream_t st, di
 // the moments of every level above the leaves (launch_params writes those)
 hipError_t launch_tree_up(const ParamArgs& A, hipStream_t st);
 hipError_t launch_far(const FarArgs& A, int moments, hipStream_t st);
+hipError_t launch_point(const PointArgs& A, int moments, hipStream_t st);
 // out: float rows when out_f32, else double rows; far (may be nullptr): one more partial
 hipError_t launch_reduce(const double* part, const double* far, void* out, int out_f32,
                          int64_t n_grid, int n_pts, int split, hipStream_t st);

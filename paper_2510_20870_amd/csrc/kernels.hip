@@ -55,7 +55,7 @@
 namespace xs {
 
 // ------------------------------------------------------------------ parameter kernel
-// One thread per line; a wavefront's 64 lines are one leaf of the tree (NM > 0: with NM
+// One thread per line; each row of 16 lanes is one leaf of the tree (NM > 0: with NM
 // moments), whose moments it sums while the parameters are in registers, so the tree costs
 // no pass of its own over the lines.
 template <int NM>
@@ -79,8 +79,8 @@ __global__ __launch_bounds__(256) void xs_params_kernel(ParamArgs A) {
     r.y = lp.gL * r.ib;
     if (ok) out[t] = r;
     if constexpr (NM > 0)
-      leaf_moments<NM>((FarNode<NM>*)A.nodes + (int64_t)k * A.dims.n_nodes + base / kLeafLines,
-                       nu0, ok ? lp.S * (1.0 / kPiD) : 0.0, lp.bD, lp.gL, lane);
+      leaf_moments<NM>(A.nodes + (int64_t)k * A.dims.n_nodes * node_fields<NM>(),
+                       (base + lane) / kLeafLines, nu0, ok ? lp.S * (1.0 / kPiD) : 0.0, lp.bD, lp.gL, lane);
   }
 }
 

@@ -1,0 +1,493 @@
+// Point kernel: the whole sum at a few neighbouring grid points by one wavefront, its lanes
+// being lines (or line groups) instead of grid points.
+//
+// Section "Functionality of pyROX" (bullets "Compute line profiles", "Combine and save"). A
+// wavefront takes kPointGroup neighbouring points of one (P, T) point. Around them it finds
+// the lines that have to be summed one by one (the near range: leaves of the tree that are
+// not far from every point), 64 lines at a time, one per lane, read once and evaluated at
+// every point of the group; outside, up to the cut, the tree's nodes (far_tree.h), 64 at a
+// time, one per lane; at the cut, the leaves that some points' cuts leave out, and the lines
+// of the leaf that a cut splits. Each lane keeps one FP64 sum per point; they are added over
+// the wavefront once, at the end.
+//
+// Why lanes are lines: with lanes as points of a tile, every line near the tile costs all 64
+// lanes although its core covers a few points (3 to 60 of them on a 0.01 cm^-1 grid), its
+// record passes through LDS, and its row classes and lane ranges have to be found first.
+// Here a record is one coalesced load, no lane is idle for a point's sake, and whether a
+// chunk of 64 neighbouring lines lies in the core or outside is nearly uniform. The group's
+// width trades the loads and the tree walk, paid once per group, against the lines that only
+// some of its points need. VALU-bound: about 55 instructions per 64 core pairs with y < 0.1,
+// 30 outside the core.
+#include "far_tree.h"
+#include "tile_kernel.h"
+
+namespace xs {
+
+constexpr int kPointRanges = 32;    // line ranges summed one by one, per wavefront
+constexpr int kNodeList = 128;      // pending tree nodes, per wavefront
+
+// Two searches at once, lanes 0-31 for one key and lanes 32-63 for the other: the first i in
+// [lo, hi) with pred(a[i]), pred false and then true along the array (hi if none). The
+// bounds are per half-wavefront.
+template <class F>
+__device__ __forceinline__ int pair_search(const double* __restrict__ a, int lo, int hi, F pred,
+                                           int lane) {
+  const int l5 = lane & 31, sh = lane & 32;
+  while (__ballot(hi - lo > 32) != 0ull) {
+    const int step = (hi - lo + 32) / 33;
+    const int i = lo + (l5 + 1) * step;   // at most hi + 32 (step is rounded up)
+    const bool before = i < hi && !pred(a[i]);
+    const int c = __popc((uint32_t)(__ballot(before) >> sh));
+    // the probes before the answer are the first c ones
+    const int nlo = c > 0 ? lo + c * step + 1 : lo;
+    hi = min(hi, lo + (c + 1) * step);
+    lo = min(nlo, hi);
+  }
+  const int i = lo + l5;
+  const bool before = i < hi && !pred(a[i]);
+  return lo + __popc((uint32_t)(__ballot(before) >> sh));
+}
+
+// Sum of v over the wavefront for each of the R values, by halving (lane l holds value
+// l / (64 / R) afterwards).
+template <int R>
+__device__ __forceinline__ double wave_sums(double (&v)[R], int lane) {
+  int o = 32;
+#pragma unroll
+  for (int n = R / 2; n > 0; n >>= 1, o >>= 1) {
+    const bool up = (lane & o) != 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const double x = v[i], y = v[i + n];
+      const double give = up ? x : y, keep = up ? y : x;
+      v[i] = keep + __shfl_xor(give, o);
+    }
+  }
+  double t = v[0];
+  for (; o > 0; o >>= 1) t += __shfl_xor(t, o);
+  return t;
+}
+
+// The Dawson table of the small-y core in LDS, one 16-byte entry per node.
+struct DawEntry {
+  float F, F1, E, pad;
+};
+
+// voigt_core_small with its table in LDS.
+__device__ __forceinline__ float core_small(const DawEntry* tab, double xd, float y) {
+  const double ax = fabs(xd);
+  const float kf = rintf(fminf((float)ax, 7.0f) * (float)kDawInvH);
+  const DawEntry e = tab[(int)kf];
+  const float x0 = kf * (float)(1.0 / kDawInvH);   // exact
+  const float d = (float)(ax - (double)x0);
+  const float m2x = -2.0f * x0;
+  const float D0 = e.F, D1 = e.F1;
+  const float D2 = fmaf(m2x, D1, -2.0f * D0);
+  const float D3 = fmaf(m2x, D2, -4.0f * D1);
+  const float D4 = fmaf(m2x, D3, -6.0f * D2);
+  const float D5 = fmaf(m2x, D4, -8.0f * D3);
+  const float D6 = fmaf(m2x, D5, -10.0f * D4);
+  const float d2 = 0.5f * d, d3 = d * (1.0f / 3.0f), d4 = 0.25f * d;
+  const float F1 = fmaf(d, fmaf(d2, fmaf(d3, fmaf(d4, D5, D4), D3), D2), D1);
+  const float F3 = fmaf(d, fmaf(d2, fmaf(d3, D6, D5), D4), D3);
+  const float F5 = fmaf(d, D6, D5);
+  const float y2 = y * y;
+  const float imF = y * fmaf(-y2 * (1.0f / 6.0f), fmaf(-y2 * 0.05f, F5, F3), F1);
+  const float a = 2.0f * (x0 + d) * y;
+  const float a2 = a * a;
+  const float ca = fmaf(a2, fmaf(a2, fmaf(a2, -1.0f / 720.0f, 1.0f / 24.0f), -0.5f), 1.0f);
+  const float g = e.E * exp32(fmaf(-fmaf(2.0f, x0, d), d, y2)) * ca;
+  return fmaf(-2.0f * (float)kInvSqrtPi, imF, g);
+}
+
+// a b + c with c in a scalar register: one instruction (the compiler would copy the scalar
+// pair into the accumulator first, two more per term of the loop below).
+__device__ __forceinline__ double fma_s(double a, double b, double c) {
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+  return r;
+}
+
+// Weideman's series (voigt_core64_n) for a wavefront of lines. The coefficients are real, so
+// the sum follows from the recurrence b_n = a_n + 2 Re(Z) b_(n+1) - |Z|^2 b_(n+2) in real
+// arithmetic, p = a_0 - |Z|^2 b_2 + Z b_1: two operations per term instead of four (|Z| < 1;
+// within 15 % of Horner's rounding, which lies far below the truncation of these term counts).
+template <int N>
+__device__ __forceinline__ double core64(const double* a, double L, double x, double y) {
+  const double lpy = L + y, lmy = L - y;
+  const double x2 = x * x;
+  const double iD = rcp64(fma(lpy, lpy, x2));
+  const double zr = fma(lmy, lpy, -x2) * iD;
+  const double t = zr + zr, u = -fma(lmy, lmy, x2) * iD;
+  double b1 = fma_s(t, a[N - 1], a[N - 2]), b2 = a[N - 1];
+#pragma unroll
+  for (int n = N - 3; n >= 1; --n) {
+    const double b = fma(u, b2, fma_s(t, b1, a[n]));
+    b2 = b1;
+    b1 = b;
+  }
+  // Re[2 p / (L - iz)^2 + 1 / (sqrt(pi) (L - iz))], Im p = 2 L x / D b_1
+  const double pr = fma(u, b2, fma_s(zr, b1, a[0]));
+  const double q = (4.0 * L) * x2 * lpy * iD;
+  const double r = 2.0 * fma(pr, fma(lpy, lpy, -x2), -q * b1) * iD;
+  return fma(lpy, kInvSqrtPi, r) * iD;
+}
+
+// The core form of a chunk of lines, one for the wavefront: none (every y >= 7: no point
+// lies in the core), the FP32 small-y core (every y < 0.1), else the FP64 series with the
+// term count that the chunk's smallest y needs (core_tier; 22 terms go with 24).
+enum { kCoreNone, kCoreSmall, kCore16, kCore20, kCore24, kCoreAny };
+
+// K(x, y) of one line per lane, FP32 path: the tile kernel's forms, outside the core the
+// cheapest of three that serves every lane (the shifted Lorentzian within the launch's error
+// budget eps, 3 terms from |z| = 20, 6 terms).
+template <int CORE>
+__device__ __forceinline__ double lane_k32(const DawEntry* tab, double x, double y, float y32,
+                                           float y2, float eps) {
+  const float xf = (float)x;
+  const float r2 = fmaf(xf, xf, y2);
+  const float c = (float)kInvSqrtPi * y32;
+  if (__ballot(!(r2 >= kT3R2)) == 0ull) {
+    if (__ballot(!shifted_lorentz_ok(y2, r2, eps)) == 0ull) return (double)(c * rcp32(r2 - 1.5f));
+    return (double)(c * asym_scaled<3>(y2, r2));
+  }
+  float k = 0.0f;
+  if constexpr (CORE == kCoreNone) {
+    k = c * asym_scaled<6>(y2, r2);
+  } else {
+    const bool core = r2 < kT6R2;
+    if (!core) k = c * asym_scaled<6>(y2, r2);
+    if (core) {
+      if constexpr (CORE == kCoreSmall) k = core_small(tab, x, y32);
+      else if constexpr (CORE == kCore16) k = (float)core64<16>(kWeidA16, kWeidL16, x, y);
+      else if constexpr (CORE == kCore20) k = (float)core64<20>(kWeidA20, kWeidL20, x, y);
+      else if constexpr (CORE == kCore24) k = (float)core64<24>(kWeidA24, kWeidL24, x, y);
+      else
+        k = y32 < kTaylorY ? core_small(tab, x, y32)
+                           : (float)voigt_core64_tier(core_tier(y), x, y);
+    }
+  }
+  return (double)k;
+}
+
+template <int NM>
+__global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
+  constexpr int R = kPointGroup, NF = node_fields<NM>();
+  __shared__ DawEntry tab[NM == kMomFp32 ? kDawNodes : 1];
+  __shared__ int list[kWavesPerWG][kNodeList];
+  __shared__ int2 rng[kWavesPerWG][kPointRanges];
+  __shared__ int part[kWavesPerWG][2][R];
+  __shared__ double cutl[kWavesPerWG][R][2 * kLeafLines];
+  if constexpr (NM == kMomFp32) {
+    for (int t = threadIdx.x; t < kDawNodes; t += blockDim.x)
+      tab[t] = {kDawF[t], kDawF1[t], kDawE[t], 0.0f};
+    __syncthreads();
+  }
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t item = xcd_logical_wg(blockIdx.x) * kWavesPerWG + wv;
+  if (item >= A.n_groups * A.n_pt * A.split) return;
+  // parts of a group and neighbouring groups of one (P, T) point lie next to each other
+  const int s = (int)(item % A.split);
+  const int64_t gi = item / A.split;
+  const int k = (int)(gi / A.n_groups);
+  const int64_t j0 = (A.g0 + gi % A.n_groups) * R;
+  const int jn = (int)min((int64_t)R, A.n_grid - j0);
+  const double v0 = A.grid[j0], v1 = A.grid[j0 + jn - 1];
+  const int pt = A.pt0 + k;
+  const double kb = make_pt(A.sp, A.pts[2 * pt], A.pts[2 * pt + 1]).dopp / kCLight;
+  const double cut = A.cut;
+  const int rec_n = A.rec_n;
+  const double* nu = A.L.nu0 + A.rec_lo;
+  const LineRec* recs = A.recs + (int64_t)k * rec_n;
+  const double* nodes = A.nodes + (int64_t)k * A.dims.n_nodes * NF;
+  auto node = [&](int l, int q) { return node_at<NM>(nodes, A.dims, l, (int64_t)q); };
+  // the points: lane p (mod R) holds point p, read back as a wave-uniform value
+  const uint64_t vb = __builtin_bit_cast(uint64_t, A.grid[j0 + min(lane & (R - 1), jn - 1)]);
+  auto val = [&](int p) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)vb, p);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(vb >> 32), p);
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+  };
+
+  double acc[R];
+#pragma unroll
+  for (int p = 0; p < R; ++p) acc[p] = 0.0;
+
+  // ---- ranges. Per half-wavefront: lanes 0-31 the lines left of the points, 32-63 right.
+  const bool right = lane >= 32;
+  const int l5 = lane & 31;
+  const double g_near = right ? v1 : v0;
+  auto half = [&](int v, int side) { return __builtin_amdgcn_readlane(v, side * 32); };
+  const double ulp = fabs(g_near) * 0x1p-48;
+  // reachable lines [e0, e1)
+  const int end = pair_search(nu, 0, rec_n,
+                              [&](double c) { return right ? c > v1 + cut + ulp
+                                                           : c >= v0 - cut - ulp; }, lane);
+  const int e0 = half(end, 0), e1 = half(end, 1);
+  // lines inside the cut of every point of the group, in leaves [c0, c1)
+  const int cov = pair_search(nu, e0, e1,
+                              [&](double c) { return right ? c - v0 > cut : v1 - c <= cut; },
+                              lane);
+  const int c0 = (half(cov, 0) + kLeafLines - 1) / kLeafLines, c1 = half(cov, 1) / kLeafLines;
+  // near range, in leaves [a, b): first by the Doppler width, then grown over every leaf
+  // that is not far
+  const double reach = (kFarTheta * far_beta<NM>()) * kb * g_near;
+  const int nr = pair_search(nu, e0, e1,
+                             [&](double c) { return right ? c > v1 + reach : c >= v0 - reach; },
+                             lane);
+  int a = half(nr, 0) / kLeafLines, b = (half(nr, 1) + kLeafLines - 1) / kLeafLines;
+  // distance of a node outwards from the nearest point
+  auto is_far = [&](const NodeRef<NM, const double>& f) {
+    const double c = f.c();
+    return (right ? c - v1 : v0 - c) >= kFarTheta * f.s();
+  };
+  auto grow = [&](int l, int& lo, int& hi, int from, int to) {
+    for (;;) {
+      const int q = right ? hi + l5 : lo - 1 - l5;
+      bool bad = false;
+      if (right ? q < to : q >= from) bad = !is_far(node(l, q));
+      const uint64_t m = __ballot(bad);
+      if (m == 0ull) break;
+      const uint32_t ml = (uint32_t)m, mr = (uint32_t)(m >> 32);
+      lo -= ml ? 32 - __clz((int)ml) : 0;
+      hi += mr ? 32 - __clz((int)mr) : 0;
+    }
+  };
+  grow(0, a, b, c0, c1);
+
+  int n_rng = 1;
+  bool mask = a < c0 || b > c1;   // the near range holds lines outside some point's cut
+  const int n0 = max(e0, min(a * kLeafLines, rec_n)), n1 = min(e1, min(b * kLeafLines, rec_n));
+  if (lane == 0) rng[wv][0] = make_int2(n0, max(n0, n1));
+  if (lane < 2 * R) part[wv][lane >= R][lane & (R - 1)] = -1;
+  wave_sync();
+
+  // ---- tree nodes inside every point's cut, 64 at a time: one per lane
+  bool whole = false;   // too many nodes that are not far: sum every line of the window
+  int n_list = 0, round = 0;
+  auto flush = [&](int n) {
+    wave_sync();
+    const int id = lane < n ? list[wv][lane] : -1;
+    const int l = id >> 27, q = id & 0x7ffffff;
+    const bool in = id >= 0;
+    NodeRef<NM, const double> f{nodes};
+    if (in) f = node(l, q);
+    const double c = f.c(), sc = f.s();
+    const bool bad = in && !(fmax(v0 - c, c - v1) >= kFarTheta * sc);
+    const uint64_t m = __ballot(bad);
+    if (m != 0ull) {
+      const int at = n_rng + __popcll(m & ((1ull << lane) - 1ull));
+      const int add = __popcll(m);
+      if (n_rng + add > kPointRanges) {
+        whole = true;
+      } else {
+        const int i0 = q << (kArityBits * l);
+        if (bad)
+          rng[wv][at] = make_int2(i0 * kLeafLines, min((i0 + (1 << (kArityBits * l))) * kLeafLines,
+                                                       rec_n));
+        n_rng += add;
+      }
+    }
+    if (round++ % A.split == s) {
+      // (lanes without a node: zero moments at a centre that is no grid point)
+      const bool use = in && !bad;
+      const double cc = use ? c : 2.0 * v1 + 1.0;
+      double M[NM];
+#pragma unroll
+      for (int t = 0; t < NM; ++t) M[t] = use ? f.at(kNodeA + t) : 0.0;
+#pragma unroll
+      for (int p = 0; p < R; ++p) {
+        const double rX = rcp64(val(p) - cc), t = sc * rX;
+        double h = M[NM - 1];
+#pragma unroll
+        for (int m2 = NM - 2; m2 >= 0; --m2) h = fma(h, t, M[m2]);
+        acc[p] = fma(h * t, rX, acc[p]);
+      }
+    }
+    // the nodes not taken yet move to the front
+    const int rest = lane + kWave < n_list ? list[wv][kWave + lane] : 0;
+    wave_sync();
+    list[wv][lane] = rest;
+    n_list -= n;
+    wave_sync();
+  };
+  {
+    int al = a, bl = b, lo = c0, hi = c1;   // near and covered ranges in nodes of level l
+    bool on_l = al > lo, on_r = bl < hi;
+    for (int l = 0; (on_l || on_r) && l < A.dims.levels; ++l) {
+      // the next level's ranges: the near range out to whole parents that are not far, the
+      // covered range in to whole parents
+      int pa = al >> kArityBits, pb = (bl + kArity - 1) >> kArityBits;
+      const int plo = (lo + kArity - 1) >> kArityBits, phi = hi >> kArityBits;
+      bool up_l = false, up_r = false;
+      if (l + 1 < A.dims.levels) {
+        grow(l + 1, pa, pb, on_l ? plo : 0x7fffffff, on_r ? phi : -1);
+        up_l = on_l && pa > plo;
+        up_r = on_r && pb < phi;
+      }
+      // left: [lo, plo) and [pa, al) in children where parents go on, else [lo, al)
+      const int s0 = on_l ? (up_l ? (plo << kArityBits) - lo : al - lo) : 0;
+      const int s1 = up_l ? al - (pa << kArityBits) : 0;
+      const int s2 = on_r ? (up_r ? (pb << kArityBits) - bl : hi - bl) : 0;
+      const int s3 = up_r ? hi - (phi << kArityBits) : 0;
+      const int n4 = s0 + s1 + s2 + s3;
+      for (int o = 0; o < n4; o += kWave) {
+        const int i = o + lane;
+        if (i < n4) {
+          const int q = i < s0 ? lo + i
+                        : i < s0 + s1 ? (pa << kArityBits) + (i - s0)
+                        : i < s0 + s1 + s2 ? bl + (i - s0 - s1)
+                                           : (phi << kArityBits) + (i - s0 - s1 - s2);
+          list[wv][n_list + lane] = (l << 27) | q;
+        }
+        n_list += min(kWave, n4 - o);
+        if (n_list >= kWave) flush(kWave);
+      }
+      al = pa;
+      bl = pb;
+      lo = plo;
+      hi = phi;
+      on_l = up_l;
+      on_r = up_r;
+    }
+    if (n_list > 0) flush(n_list);
+  }
+
+  // ---- leaves at the cut: left [e0 / 16, min(a, c0)), right [max(b, c1), e1 / 16 up); a leaf
+  // counts for the points whose cut holds all of it; a leaf that a cut splits is noted
+  {
+    const int la = e0 / kLeafLines, lb = min(a, c0);
+    const int ra = max(b, c1), rb = (e1 + kLeafLines - 1) / kLeafLines;
+    const int nl = max(lb - la, 0), n = nl + max(rb - ra, 0);
+    for (int o = 0; o < n; o += kWave) {
+      const int i = o + lane;
+      const bool in = i < n;
+      const int q = in ? (i < nl ? la + i : ra + (i - nl)) : 0;
+      const NodeRef<NM, const double> f = node(0, q);
+      const double lo = f.lo(), hi = f.hi(), c = f.c(), sc = f.s();
+      const bool bad = in && !(fmax(v0 - c, c - v1) >= kFarTheta * sc);
+      const uint64_t m = __ballot(bad);
+      if (m != 0ull) {
+        // not far: its lines one by one (with the cut test)
+        mask = true;
+        const int at = n_rng + __popcll(m & ((1ull << lane) - 1ull));
+        const int add = __popcll(m);
+        if (n_rng + add > kPointRanges) whole = true;
+        else {
+          if (bad) rng[wv][at] = make_int2(q * kLeafLines, min((q + 1) * kLeafLines, rec_n));
+          n_rng += add;
+        }
+      }
+      const bool mine = round++ % A.split == s;
+      const bool use = in && !bad && mine;
+      double M[NM];
+#pragma unroll
+      for (int t = 0; t < NM; ++t) M[t] = use ? f.at(kNodeA + t) : 0.0;
+#pragma unroll
+      for (int p = 0; p < R; ++p) {
+        const double v = val(p);
+        const bool lo_in = fabs(v - lo) <= cut, hi_in = fabs(v - hi) <= cut;
+        if (in && !bad && lo_in != hi_in) part[wv][i >= nl][p] = q;
+        const double rX = rcp64(v - c), t = sc * rX;
+        double h = M[NM - 1];
+#pragma unroll
+        for (int m2 = NM - 2; m2 >= 0; --m2) h = fma(h, t, M[m2]);
+        if (use && lo_in && hi_in) acc[p] = fma(h * t, rX, acc[p]);
+      }
+    }
+    wave_sync();
+  }
+  if (whole) {
+    // (the same decision in every part of the group)
+#pragma unroll
+    for (int p = 0; p < R; ++p) acc[p] = 0.0;
+    mask = true;
+    n_rng = 1;
+    if (lane == 0) rng[wv][0] = make_int2(e0, e1);
+  } else if (s == 0) {
+    // the split leaves: lanes 0-15 the left one's lines, 16-31 the right one's, per point
+    // (through LDS, so that the sums keep their registers in a loop that is not unrolled)
+#pragma unroll 1
+    for (int p = 0; p < R; ++p) {
+      const int q = lane < 2 * kLeafLines ? part[wv][lane >= kLeafLines][p] : -1;
+      const int i = q * kLeafLines + (lane & (kLeafLines - 1));
+      double t = 0.0;
+      if (q >= 0 && i < rec_n) t = one_line<NM>(val(p), nu[i], recs[i]);
+      if (lane < 2 * kLeafLines) cutl[wv][p][lane] = t;
+    }
+    wave_sync();
+#pragma unroll
+    for (int p = 0; p < R; ++p)
+      if (lane < 2 * kLeafLines) acc[p] += cutl[wv][p][lane];
+  }
+  wave_sync();
+
+  // ---- lines one by one, 64 at a time: one per lane
+  int chunk = 0;
+  for (int r = 0; r < n_rng; ++r) {
+    const int2 ab = rng[wv][r];
+    for (int base = ab.x; base < ab.y; base += kWave) {
+      if (chunk++ % A.split != s) continue;
+      const int i = min(base + lane, ab.y - 1);
+      const double c = nu[i];
+      const LineRec lr = recs[i];
+      const double sc = base + lane < ab.y ? lr.sc : 0.0;
+      // adds the line to every point's sum with the given K
+      auto points = [&](auto k_of) {
+#pragma unroll
+        for (int p = 0; p < R; ++p) {
+          const double d = val(p) - c;
+          const double kk = k_of(d * lr.ib);
+          double w = sc;
+          if (mask) w = fabs(d) <= cut ? sc : 0.0;
+          acc[p] = fma(w, kk, acc[p]);
+        }
+      };
+      if constexpr (NM == kMomFp32) {
+        const float y32 = (float)lr.y, y2 = y32 * y32;
+        auto all = [&](bool t) { return __ballot(!t) == 0ull; };
+        auto with = [&](auto core) {
+          points([&](double x) {
+            return lane_k32<decltype(core)::value>(tab, x, lr.y, y32, y2, A.l1_eps);
+          });
+        };
+        if (all(y32 < kTaylorY)) with(std::integral_constant<int, kCoreSmall>{});
+        else if (all(y2 >= kT6R2)) with(std::integral_constant<int, kCoreNone>{});
+        else if (all(lr.y >= 1.0)) with(std::integral_constant<int, kCore16>{});
+        else if (all(lr.y >= 0.3)) with(std::integral_constant<int, kCore20>{});
+        else if (all(lr.y >= 0.01)) with(std::integral_constant<int, kCore24>{});
+        else with(std::integral_constant<int, kCoreAny>{});
+      } else {
+        points([&](double x) { return voigt_k64(x, lr.y); });
+      }
+    }
+  }
+
+  const double t = wave_sums<R>(acc, lane);
+  constexpr int kRep = kWave / R;
+  const int p = lane / kRep;
+  if (lane % kRep == 0 && p < jn) {
+    if (A.split > 1) {
+      ((double*)A.out)[((int64_t)k * A.split + s) * A.n_grid + j0 + p] = t;
+    } else {
+      const int64_t o = (int64_t)(A.pt0 + k) * A.n_grid + j0 + p;
+      if (A.out_f32) ((float*)A.out)[o] = (float)t;
+      else ((double*)A.out)[o] = t;
+    }
+  }
+}
+
+hipError_t launch_point(const PointArgs& A, int moments, hipStream_t st) {
+  const int64_t items = A.n_groups * A.n_pt * A.split;
+  if (items <= 0) return hipSuccess;
+  const dim3 grid((unsigned)phys_workgroups((items + kWavesPerWG - 1) / kWavesPerWG)),
+      block(kBlock);
+  if (moments == kMomFp32)
+    hipLaunchKernelGGL(xs_point_kernel<kMomFp32>, grid, block, 0, st, A);
+  else
+    hipLaunchKernelGGL(xs_point_kernel<kMomFp64>, grid, block, 0, st, A);
+  return hipGetLastError();
+}
+
+}  // namespace xs

@@ -183,19 +183,32 @@ static void line_range(const LinesRes& L, const GridRes& G, const xs_opts& o, in
   line_range_nu(L, G.first, G.last, o.cut_cm1, lo, hi);
 }
 
-// Far field by moments, chosen where a tile's window holds enough lines beyond its near
+// Lines per wavenumber around the grid's middle, times the cut's full width.
+static int64_t window_lines(const LinesRes& L, const GridRes& G, const xs_opts& o) {
+  const double mid = G.host[G.n / 2];
+  const std::vector<double>& sm = L.sample;
+  return (int64_t)(std::upper_bound(sm.begin(), sm.end(), mid + o.cut_cm1) -
+                   std::lower_bound(sm.begin(), sm.end(), mid - o.cut_cm1)) *
+         kSampleStride;
+}
+
+// Far field by moments, chosen where a point's window holds enough lines beyond its near
 // range: with a fixed cut (every line of a group then ends at the same distance), no
 // selection (which drops lines one by one) and the automatic tile_group.
 static bool use_moments(const LinesRes& L, const GridRes& G, const xs_opts& o) {
-  if (o.tile_group != 0 || o.cutoff_kind != XS_CUT_FIXED || o.select_eps > 0.0 || L.n == 0)
+  if (o.tile_group != 0 || o.cutoff_kind != XS_CUT_FIXED || o.select_eps > 0.0 ||
+      L.n >= ((size_t)1 << 30))
     return false;
-  // lines within the cut of the grid's middle
-  const double mid = G.host[G.n / 2];
-  const std::vector<double>& sm = L.sample;
-  const int64_t w = (int64_t)(std::upper_bound(sm.begin(), sm.end(), mid + o.cut_cm1) -
-                              std::lower_bound(sm.begin(), sm.end(), mid - o.cut_cm1)) *
-                    kSampleStride;
-  return w >= kMomentLines;
+  return window_lines(L, G, o) >= kMomentLines;
+}
+
+// Distance from a point within which its lines are summed one by one, at (P, T): theta
+// (gamma + beta b) with the list's largest width and the Doppler width at the grid's middle.
+static double near_distance(const LinesRes& L, const GridRes& G, const xs_pt& pt, bool f64) {
+  const double pf = pt.P_bar / L.sp.P_ref, tr = L.sp.T_ref / pt.T_K;
+  const double g = L.sp.gam_max * pf * std::max(pow(tr, L.sp.n_min), pow(tr, L.sp.n_max));
+  const double b = G.host[G.n / 2] / kCLight * sqrt(2.0 * kKBoltz * pt.T_K / (L.sp.mass_amu * kAmu));
+  return kFarTheta * (g + (f64 ? kBetaFp64 : kBetaFp32) * b);
 }
 
 void Plan::set_tree() {
@@ -204,15 +217,15 @@ void Plan::set_tree() {
   for (int l = 0; l < kTreeLevels; ++l) {
     dims.off[l] = dims.n_nodes;
     dims.cnt[l] = std::max<int64_t>(1, (n + span - 1) / span);
-    dims.n_nodes += dims.cnt[l];
+    dims.n_nodes += (dims.cnt[l] + kNodeBlock - 1) / kNodeBlock * kNodeBlock;
     dims.levels = l + 1;
     if (dims.cnt[l] < kArity) break;   // no full node above
     span *= kArity;
   }
 }
 
-Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const xs_opts& o,
-               size_t cap_bytes, int64_t max_item_lines, int items_per_slot, bool far_moments) {
+Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, size_t npts,
+               const xs_opts& o, size_t cap_bytes, int64_t max_item_lines, int items_per_slot, bool far_moments) {
   Plan p;
   p.n_grid = (int64_t)G.n;
   if (far_moments && use_moments(L, G, o))
@@ -268,14 +281,41 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const x
     max_cost = std::max(max_cost, cost[t]);
   }
   int64_t max_window = (max_cost + 1) * kSampleStride;   // lines, upper estimate
-  if (p.moments && p.n_units > 0) {
-    // of which a tile walks its near range: its own span and about half of that around it
-    const double span = (G.last - G.first) / (double)p.n_units;
-    max_window = (int64_t)((double)max_window *
-                           std::min(1.0, 1.5 * span / (span + 2.0 * o.cut_cm1))) + kLeafLines;
+  if (p.moments) {
+    // points whose near range spans many tiles go by tiles: there the polynomial of a tile
+    // takes the near lines that are far from it (about 2 instructions per line and 64
+    // points, against 30 in the point kernel)
+    const size_t m = std::min<size_t>(G.n / 2, G.n >= 2 ? G.n - 2 : 0);
+    const double step = G.n >= 2 ? G.host[m + 1] - G.host[m] : 0.0;
+    double widest = 0.0;
+    p.by_tile.resize(npts);
+    for (size_t k = 0; k < npts; ++k) {
+      const double d = near_distance(L, G, pts[k], f64);
+      p.by_tile[k] = d > kWideTiles * (double)tile * step;
+      p.any_tile = p.any_tile || p.by_tile[k];
+      widest = std::max(widest, d);
+    }
+    // lines that one group of points sums one by one
+    const double width = 2.0 * std::min(widest, o.cut_cm1) + kPointGroup * step;
+    max_window = (int64_t)((double)window_lines(L, G, o) * std::min(1.0, width / (2.0 * o.cut_cm1)));
   }
   if (o.split) {
-    p.split = o.split;
+    p.split = p.tile_split = o.split;
+  } else if (p.moments) {
+    // about 32 wavefronts per CU, of at least two 64-line chunks each
+    const int64_t groups = ((int64_t)G.n + kPointGroup - 1) / kPointGroup;
+    int64_t sp = ((int64_t)c.n_cu * 32 + groups * (int64_t)npts - 1) / (groups * (int64_t)npts);
+    if (max_item_lines > 0)
+      sp = std::max<int64_t>(sp, (max_window + max_item_lines - 1) / max_item_lines);
+    sp = std::min<int64_t>(sp, std::max<int64_t>(1, max_window / (2 * kWave)));
+    p.split = (int)std::max<int64_t>(1, std::min<int64_t>(sp, 64));
+    if (p.any_tile) {
+      // points by tiles: two rounds of wavefront slots, of at least four chunks each
+      const int64_t wide = std::count(p.by_tile.begin(), p.by_tile.end(), 1);
+      sp = ((int64_t)c.n_cu * 56 + p.n_units * wide - 1) / (p.n_units * wide);
+      sp = std::min<int64_t>(sp, std::max<int64_t>(1, max_window / (4 * kWave)));
+      p.tile_split = (int)std::max<int64_t>(1, std::min<int64_t>(sp, kMaxSplit));
+    }
   } else {
     // a few work items per resident wavefront slot (4 SIMDs x 7 waves per CU; 4 by
     // default, or the tuned count), so the last round of waves is short; a grouped item
@@ -303,7 +343,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const x
     cap = std::min<size_t>((size_t)64 << 30, free_b / 3);
   }
   const size_t per_pt = std::max<size_t>(
-      1, (size_t)p.rec_n * 32 + (p.split > 1 ? (size_t)p.split * G.n * 8 : 0) +
+      1, (size_t)p.rec_n * 32 + (p.max_split() > 1 ? (size_t)p.max_split() * G.n * 8 : 0) +
              p.extra_bytes());
   p.pt_batch = (int)std::max<size_t>(1, std::min<size_t>(npts, cap / per_pt));
   // issue order: tiles by decreasing number of lines within the largest cut, so the most
@@ -315,6 +355,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const x
     cls[t] = (int)std::floor(4.0 * std::log2(1.0 + (double)cost[t]));
   p.tile_order.resize(p.n_units);
   std::iota(p.tile_order.begin(), p.tile_order.end(), 0);
+  if (p.moments) return p;   // near ranges differ little: ascending
   std::stable_sort(p.tile_order.begin(), p.tile_order.end(),
                    [&](int a, int b) { return cls[a] > cls[b]; });
   return p;
@@ -359,8 +400,6 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
   cut.kind = o.cutoff_kind == XS_CUT_FIXED ? kCutFixed : kCutMinFwhm;
   cut.cut = o.cut_cm1;
   cut.mult = o.fwhm_mult;
-  double* far = p.moments ? (double*)((char*)rec_dev + p.far_offset()) : nullptr;
-  NearRange* near = p.moments ? (NearRange*)((char*)rec_dev + p.near_offset()) : nullptr;
   hipError_t e;
   if (with_params) {
     ParamArgs PA;
@@ -375,7 +414,7 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
     PA.n = p.rec_n;
     PA.out = (LineRec*)rec_dev;
     if (p.moments) {
-      PA.nodes = (char*)rec_dev + p.node_offset();
+      PA.nodes = (double*)((char*)rec_dev + p.node_offset());
       PA.dims = p.dims;
       PA.moments = p.moments;
     }
@@ -409,83 +448,131 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       if (e != hipSuccess) return hip_fail(e, "select kernel launch");
     }
   }
-  if (c1 > c0) {
-    TileArgs A;
-    memset(&A, 0, sizeof A);
-    A.L = L.dev;
-    A.sp = L.sp;
-    A.cut = cut;
-    A.grid = G.d;
-    A.n_grid = (int64_t)G.n;
-    A.pts = pts_dev;
-    A.pt0 = pt0;
-    A.n_pt = nb;
-    A.split = counts ? 1 : p.split;
-    A.group = p.group;
-    A.n_tiles = c1 - c0;
-    A.n_items = A.n_tiles * nb * A.split;
-    A.n_wg = p.group > 1 ? A.n_items : (A.n_items + kWavesPerWG - 1) / kWavesPerWG;
-    A.tile_order = order_dev + c0;
-    A.recs = (const LineRec*)rec_dev;
-    A.rec_lo = p.rec_lo;
-    A.rec_n = p.rec_n;
-    A.l1_eps = opts_eps(o);
-    A.far_kappa = far_kappa(A.l1_eps);
-    if (p.select_eps > 0.0) {
-      // main-contributor selection: the kernels drop the lines below their group's
-      // threshold
-      A.tau = (double*)((char*)rec_dev + p.tau_offset());
-      A.tau_stride = p.n_groups();
+  // runs of points that go the same way: by the point kernel, or by tiles
+  for (int k0 = 0, k1; k0 < nb; k0 = k1) {
+    const bool tiles = !p.moments || counts || p.by_tile[pt0 + k0];
+    k1 = nb;
+    if (p.moments && !counts && p.any_tile) {
+      k1 = k0 + 1;
+      while (k1 < nb && (p.by_tile[pt0 + k1] != 0) == tiles) ++k1;
     }
-    const int64_t phys = phys_workgroups(A.n_wg);
-    int rc = tm ? tm->record(st) : XS_OK;
-    if (rc) return rc;
-    if (p.moments && !counts) {
-      FarArgs F;
-      memset(&F, 0, sizeof F);
-      F.L = L.dev;
-      F.sp = L.sp;
-      F.cut = o.cut_cm1;
-      F.grid = G.d;
-      F.n_grid = (int64_t)G.n;
-      F.pts = pts_dev;
-      F.pt0 = pt0;
-      F.n_pt = nb;
-      F.P = p.P;
-      F.n_items = (c1 - c0) * nb;
-      F.tile_order = A.tile_order;
-      F.n_tiles = p.n_tiles;
-      F.recs = (const LineRec*)rec_dev;
-      F.rec_lo = p.rec_lo;
-      F.rec_n = p.rec_n;
-      F.nodes = (char*)rec_dev + p.node_offset();
-      F.dims = p.dims;
-      F.out = far;
-      F.near = near;
-      e = launch_far(F, p.moments, st);
-      if (e != hipSuccess) return hip_fail(e, "far kernel launch");
-      A.near = near;
-      A.near_stride = p.n_tiles;
-      A.far = far;
+    const int nk = k1 - k0;
+    const LineRec* recs = (const LineRec*)rec_dev + (size_t)k0 * p.rec_n;
+    const double* nodes = p.moments ? (const double*)((char*)rec_dev + p.node_offset() +
+                                                      (size_t)k0 * p.dims.n_nodes *
+                                                          node_bytes(p.moments))
+                                    : nullptr;
+    const bool with_far = tiles && p.moments && !counts;
+    double* far = with_far ? (double*)((char*)rec_dev + p.far_offset()) + (size_t)k0 * G.n : nullptr;
+    const int split = tiles && p.moments ? p.tile_split : p.split;
+    double* part = split > 1 ? (double*)part_dev + (size_t)k0 * p.max_split() * G.n : nullptr;
+    if (c1 > c0 && !tiles) {
+      PointArgs A;
+      memset(&A, 0, sizeof A);
+      A.L = L.dev;
+      A.sp = L.sp;
+      A.cut = o.cut_cm1;
+      A.grid = G.d;
+      A.n_grid = (int64_t)G.n;
+      A.pts = pts_dev;
+      A.pt0 = pt0 + k0;
+      A.n_pt = nk;
+      A.split = split;
+      const int64_t per_unit = (int64_t)kWave * p.P / kPointGroup;
+      A.g0 = c0 * per_unit;
+      A.n_groups = std::min(c1 * per_unit, ((int64_t)G.n + kPointGroup - 1) / kPointGroup) - A.g0;
+      A.recs = recs;
+      A.rec_lo = p.rec_lo;
+      A.rec_n = (int)p.rec_n;
+      A.nodes = nodes;
+      A.dims = p.dims;
+      A.out = split > 1 ? (void*)part : out_dev;
+      A.l1_eps = opts_eps(o);
+      A.out_f32 = o.out_dtype == XS_F32;
+      int rc = tm ? tm->record(st) : XS_OK;
+      if (rc) return rc;
+      e = launch_point(A, p.moments, st);
+      if (e != hipSuccess) return hip_fail(e, "point kernel launch");
+      rc = tm ? tm->record(st) : XS_OK;
+      if (rc) return rc;
     }
-    if (counts) {
-      A.counts = counts;
-      e = launch_count(A, p.P, st, phys);
-      if (e != hipSuccess) return hip_fail(e, "count kernel launch");
-    } else {
-      A.out = (A.split == 1) ? (double*)out_dev : (double*)part_dev;
-      A.out_f32 = A.split == 1 && o.out_dtype == XS_F32;
-      e = launch_tile(A, p.P, f64, p.W, st, phys);
-      if (e != hipSuccess) return hip_fail(e, "tile kernel launch");
+    if (c1 > c0 && tiles) {
+      TileArgs A;
+      memset(&A, 0, sizeof A);
+      A.L = L.dev;
+      A.sp = L.sp;
+      A.cut = cut;
+      A.grid = G.d;
+      A.n_grid = (int64_t)G.n;
+      A.pts = pts_dev;
+      A.pt0 = pt0 + k0;
+      A.n_pt = nk;
+      A.split = counts ? 1 : split;
+      A.group = p.group;
+      A.n_tiles = c1 - c0;
+      A.n_items = A.n_tiles * nk * A.split;
+      A.n_wg = p.group > 1 ? A.n_items : (A.n_items + kWavesPerWG - 1) / kWavesPerWG;
+      A.tile_order = order_dev ? order_dev + c0 : nullptr;
+      A.recs = recs;
+      A.rec_lo = p.rec_lo;
+      A.rec_n = p.rec_n;
+      A.l1_eps = opts_eps(o);
+      A.far_kappa = far_kappa(A.l1_eps);
+      if (p.select_eps > 0.0) {
+        // main-contributor selection: the kernels drop the lines below their group's
+        // threshold
+        A.tau = (double*)((char*)rec_dev + p.tau_offset());
+        A.tau_stride = p.n_groups();
+      }
+      const int64_t phys = phys_workgroups(A.n_wg);
+      int rc = tm ? tm->record(st) : XS_OK;
+      if (rc) return rc;
+      if (with_far) {
+        FarArgs F;
+        memset(&F, 0, sizeof F);
+        F.L = L.dev;
+        F.sp = L.sp;
+        F.cut = o.cut_cm1;
+        F.grid = G.d;
+        F.n_grid = (int64_t)G.n;
+        F.pts = pts_dev;
+        F.pt0 = pt0 + k0;
+        F.n_pt = nk;
+        F.P = p.P;
+        F.n_items = A.n_tiles * nk;
+        F.tile_order = A.tile_order;
+        F.n_tiles = p.n_tiles;
+        F.recs = recs;
+        F.rec_lo = p.rec_lo;
+        F.rec_n = p.rec_n;
+        F.nodes = nodes;
+        F.dims = p.dims;
+        F.out = far;
+        F.near = (NearRange*)((char*)rec_dev + p.near_offset()) + (size_t)k0 * p.n_tiles;
+        e = launch_far(F, p.moments, st);
+        if (e != hipSuccess) return hip_fail(e, "far kernel launch");
+        A.near = F.near;
+        A.near_stride = p.n_tiles;
+        A.far = far;
+      }
+      if (counts) {
+        A.counts = counts;
+        e = launch_count(A, p.P, st, phys);
+        if (e != hipSuccess) return hip_fail(e, "count kernel launch");
+      } else {
+        A.out = (A.split == 1) ? (double*)out_dev : part;
+        A.out_f32 = A.split == 1 && o.out_dtype == XS_F32;
+        e = launch_tile(A, p.P, f64, p.W, st, phys);
+        if (e != hipSuccess) return hip_fail(e, "tile kernel launch");
+      }
+      rc = tm ? tm->record(st) : XS_OK;
+      if (rc) return rc;
     }
-    rc = tm ? tm->record(st) : XS_OK;
-    if (rc) return rc;
-  }
-  if (with_reduce && !counts && p.split > 1) {
-    e = launch_reduce((const double*)part_dev, far,
-                      (char*)out_dev + (size_t)pt0 * G.n * out_elem_bytes(o),
-                      o.out_dtype == XS_F32, (int64_t)G.n, nb, p.split, st);
-    if (e != hipSuccess) return hip_fail(e, "reduce kernel launch");
+    if (with_reduce && !counts && split > 1) {
+      e = launch_reduce(part, far, (char*)out_dev + (size_t)(pt0 + k0) * G.n * out_elem_bytes(o),
+                        o.out_dtype == XS_F32, (int64_t)G.n, nk, split, st);
+      if (e != hipSuccess) return hip_fail(e, "reduce kernel launch");
+    }
   }
   return XS_OK;
 }
@@ -995,25 +1082,25 @@ int xs_compute(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, size_t 
     e = hipEventSynchronize(c->pts_event);
     if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
   }
-  Plan p = make_plan(*c, *L, *G, npts, *opts);
+  Plan p = make_plan(*c, *L, *G, pts, npts, *opts);
   rc = upload_pts(*c, pts, npts, st);
   if (rc) return rc;
   const size_t out_bytes = npts * G->n * out_elem_bytes(*opts);
   // records and partials; a call whose moments do not fit the budget goes line by line
   auto buffers = [&]() {
     int r = c->scratch(c->rec_buf, p.rec_bytes(), "line records");
-    if (r == XS_OK && p.split > 1)
+    if (r == XS_OK && p.max_split() > 1)
       r = c->scratch(c->part_buf, p.part_bytes(G->n), "split partials");
     if (r == XS_OK && !out_on_device) r = c->scratch(c->out_buf, out_bytes, "output staging");
     return r;
   };
   rc = buffers();
   if (rc == XS_ENOMEM && p.moments) {
-    p = make_plan(*c, *L, *G, npts, *opts, 0, 0, 0, false);
+    p = make_plan(*c, *L, *G, pts, npts, *opts, 0, 0, 0, false);
     rc = buffers();
   }
   if (rc) return rc;
-  void* part = p.split > 1 ? c->part_buf.ptr : nullptr;
+  void* part = p.max_split() > 1 ? c->part_buf.ptr : nullptr;
   void* out_dev = out_on_device ? sigma_out : c->out_buf.ptr;
   rc = upload_order(*c, p, st);
   if (rc) return rc;
@@ -1060,12 +1147,12 @@ int xs_compute_noalloc(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts,
   if (pts_area >= kNoAllocScratchBytes)
     return fail(XS_ENOMEM, "%zu P-T points exceed the scratch of %zu bytes", npts,
                 kNoAllocScratchBytes);
-  Plan p = make_plan(*c, *L, *G, npts, *opts, kNoAllocScratchBytes - pts_area);
+  Plan p = make_plan(*c, *L, *G, pts, npts, *opts, kNoAllocScratchBytes - pts_area);
   size_t rec_area = al(p.rec_bytes());
   size_t need = pts_area + rec_area + p.part_bytes(G->n);
   if (need > kNoAllocScratchBytes && p.moments) {
     // one point fits only without the moments: line by line
-    p = make_plan(*c, *L, *G, npts, *opts, kNoAllocScratchBytes - pts_area, 0, 0, false);
+    p = make_plan(*c, *L, *G, pts, npts, *opts, kNoAllocScratchBytes - pts_area, 0, 0, false);
     rec_area = al(p.rec_bytes());
     need = pts_area + rec_area + p.part_bytes(G->n);
   }
@@ -1086,7 +1173,7 @@ int xs_compute_noalloc(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts,
   if (e != hipSuccess) return hip_fail(e, "point table fill");
   // tiles in ascending order (no order table to upload; results do not depend on it)
   return enqueue_path(*L, *G, *opts, p, (const double*)base, nullptr, sigma_dev,
-                      base + pts_area, p.split > 1 ? base + pts_area + rec_area : nullptr, st);
+                      base + pts_area, p.max_split() > 1 ? base + pts_area + rec_area : nullptr, st);
 }
 
 static_assert(XS_N_EVAL_TIERS == kNEvalTiers, "evaluation tiers of the ABI and the kernels");
@@ -1130,7 +1217,7 @@ int xs_count_evals_by_tier(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* 
   xs_opts o = *opts;
   o.split = 1;
   o.tile_group = 1;   // the count kernel walks single tiles
-  const Plan p = make_plan(*c, *L, *G, npts, o);
+  const Plan p = make_plan(*c, *L, *G, pts, npts, o);
   rc = upload_pts(*c, pts, npts, st);
   if (rc) return rc;
   const size_t ncnt = npts * kNEvalTiers;
@@ -1242,7 +1329,7 @@ int xs_graph_create(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, si
   };
   hipError_t e = hipSetDevice(c->device);
   if (e != hipSuccess) return give_up(hip_fail(e, "hipSetDevice"));
-  Plan p = make_plan(*c, *L, *G, npts, *opts);
+  Plan p = make_plan(*c, *L, *G, pts, npts, *opts);
   g->pts_bytes = npts * 2 * sizeof(double);
   rc = c->dev_alloc(&g->pts, g->pts_bytes, "graph point table");
   if (rc) return give_up(rc);
@@ -1258,7 +1345,7 @@ int xs_graph_create(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, si
     g->rec_bytes = p.rec_bytes();
     int r = c->dev_alloc(&g->rec, g->rec_bytes, "graph line records");
     if (r != XS_OK) g->rec = nullptr;
-    if (r == XS_OK && p.split > 1) {
+    if (r == XS_OK && p.max_split() > 1) {
       g->part_bytes = p.part_bytes(G->n);
       r = c->dev_alloc(&g->part, g->part_bytes, "graph partials");
       if (r != XS_OK) g->part = nullptr;
@@ -1269,7 +1356,7 @@ int xs_graph_create(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, si
   if (rc == XS_ENOMEM && p.moments) {
     if (g->rec) c->dev_free(g->rec, g->rec_bytes);
     g->rec = nullptr;
-    p = make_plan(*c, *L, *G, npts, *opts, 0, 0, 0, false);
+    p = make_plan(*c, *L, *G, pts, npts, *opts, 0, 0, 0, false);
     rc = buffers();
   }
   if (rc) return give_up(rc);

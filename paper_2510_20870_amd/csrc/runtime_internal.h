@@ -39,6 +39,8 @@ constexpr int64_t kServeItemLines = 4096;
 
 // Lines within the cut of the grid's middle from which the far field goes by moments.
 constexpr int64_t kMomentLines = 16384;
+// (P, T) points whose near range reaches this many tiles on each side go by tiles.
+constexpr double kWideTiles = 6.0;
 
 struct GridRes {
   double* d = nullptr;
@@ -66,35 +68,40 @@ struct Plan {
   double select_eps = 0.0;         // main-contributor selection (0: off)
   // Far field by moments (far_tree.h): the tree over the records, 0 moments: off.
   int moments = 0;
+  std::vector<uint8_t> by_tile;   // per (P, T) point: the tile kernel walks the near range
+                                  // (else the point kernel)
+  bool any_tile = false;
+  int tile_split = 1;             // line splits of the points by tiles
+  int max_split() const { return any_tile && tile_split > split ? tile_split : split; }
   TreeDims dims{};
   int64_t n_grid = 0;
-  size_t node_bytes() const {
-    return moments == kMomFp32 ? sizeof(FarNode<kMomFp32>) : sizeof(FarNode<kMomFp64>);
-  }
   void set_tree();   // dims from rec_n
   // line records [pt_batch][rec_n] (32 B), then with selection the thresholds of the
   // groups of kSelGroup tiles [pt_batch][n_groups()] (8 B), or with the far field by moments
-  // the tree [pt_batch][n_nodes], the far sums [pt_batch][n_grid] (8 B) and the near ranges
-  // [pt_batch][n_tiles] (16 B)
+  // the tree [pt_batch][n_nodes] and, when any point goes by tiles, the far sums
+  // [pt_batch][n_grid] (8 B) and the near ranges [pt_batch][n_tiles] (16 B)
   int64_t n_groups() const { return (n_tiles + kSelGroup - 1) / kSelGroup; }
   size_t tau_offset() const { return (size_t)rec_n * pt_batch * 32; }
   size_t node_offset() const { return tau_offset(); }
   size_t far_offset() const {
-    return node_offset() + (size_t)pt_batch * dims.n_nodes * node_bytes();
+    return node_offset() + (size_t)pt_batch * dims.n_nodes * node_bytes(moments);
   }
-  size_t near_offset() const { return far_offset() + ((size_t)pt_batch * n_grid * 8 + 15) / 16 * 16; }
+  size_t near_offset() const {
+    return far_offset() + (any_tile ? ((size_t)pt_batch * n_grid * 8 + 15) / 16 * 16 : 0);
+  }
   // bytes per P-T point beside the records
   size_t extra_bytes() const {
-    return moments ? (size_t)dims.n_nodes * node_bytes() + (size_t)n_grid * 8 +
-                         (size_t)n_tiles * sizeof(NearRange)
+    return moments ? (size_t)dims.n_nodes * node_bytes(moments) +
+                         (any_tile ? (size_t)n_grid * 8 + (size_t)n_tiles * sizeof(NearRange) : 0)
            : select_eps > 0.0 ? (size_t)n_groups() * 8 : 0;
   }
   size_t rec_bytes() const {
-    if (moments) return near_offset() + (size_t)pt_batch * n_tiles * sizeof(NearRange);
+    if (moments)
+      return near_offset() + (any_tile ? (size_t)pt_batch * n_tiles * sizeof(NearRange) : 0);
     return tau_offset() + (select_eps > 0.0 ? (size_t)pt_batch * n_groups() * 8 : 0);
   }
   size_t part_bytes(size_t n_grid) const {
-    return split > 1 ? (size_t)pt_batch * split * n_grid * sizeof(double) : 0;
+    return max_split() > 1 ? (size_t)pt_batch * max_split() * n_grid * sizeof(double) : 0;
   }
 };
 
@@ -161,8 +168,8 @@ int validate_pts(const xs_pt* pts, size_t npts);
 // split (default 4). With pts_per_lane, split and waves_per_simd all 0 the shape comes
 // from the tuning cache when it holds the workload's class. far_moments false: every line by
 // the tile kernel (the callers' second choice where memory for the moments is missing).
-Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, size_t npts, const xs_opts& o,
-               size_t cap_bytes = 0, int64_t max_item_lines = 0, int items_per_slot = 0,
+Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, size_t npts,
+               const xs_opts& o, size_t cap_bytes = 0, int64_t max_item_lines = 0, int items_per_slot = 0,
                bool far_moments = true);
 
 // Lines [lo, hi) that can reach [first, last] within cut (from the sampled index; the

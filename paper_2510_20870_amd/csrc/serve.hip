@@ -271,7 +271,7 @@ int Server::enqueue_next(Request& r, Lane& ln) {
   }
   const Step& s = r.steps[r.next];
   void* out_dev = r.out_dev ? r.out : (void*)(blk + r.o_out);
-  void* part = r.plan.split > 1 ? (void*)(blk + r.o_part) : nullptr;
+  void* part = r.plan.max_split() > 1 ? (void*)(blk + r.o_part) : nullptr;
   int rc = enqueue_step(*r.L, *r.G, r.o, r.plan, (const double*)(blk + r.o_pts),
                         (const int*)(blk + r.o_order), out_dev, blk + r.o_rec, part, ln.st,
                         s.pt0, s.nb, s.c0, s.c1, s.params, s.reduce);
@@ -569,7 +569,7 @@ static int submit(Ctx* c, xs_lines_t lh, xs_grid_t gh, bool window, double nu_st
   const size_t n = r->G->n;
   // the launch plan and the parts of the request's arena block
   auto lay_out = [&](bool far_moments) {
-    r->plan = make_plan(*c, *r->L, *r->G, npts, *opts, s->mem / 4, kServeItemLines, 0, far_moments);
+    r->plan = make_plan(*c, *r->L, *r->G, pts, npts, *opts, s->mem / 4, kServeItemLines, 0, far_moments);
     size_t at = 0;
     auto part = [&](size_t bytes) {
       const size_t o = at;

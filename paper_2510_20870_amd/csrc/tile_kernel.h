@@ -170,6 +170,7 @@ struct ItemInfo {
   int k;             // (P, T) index within the batch
   int s;             // split index
   int64_t b, e;      // line range of this item (global line indices)
+  int step;          // distance of the item's 64-line chunks (kWave: all of the range)
 };
 
 // Lines [lo, hi) whose cut can reach the grid range [nu_first, nu_last] at (P, T) point k
@@ -294,6 +295,15 @@ __device__ __forceinline__ bool decode_item(const TileArgs& A, int lane, ItemInf
   } else {
     line_window(A, it.k, A.grid[it.j0], it.nu_last, lane, &lo, &hi);
   }
+  it.step = kWave;
+  if (A.near) {
+    // the parts of a near range take its chunks in turn: the lines beside the tile, which
+    // cost several times the others, fall to all of them
+    it.b = lo + (int64_t)kWave * it.s;
+    it.e = hi;
+    it.step = kWave * A.split;
+    return true;
+  }
   const int64_t cnt = hi > lo ? hi - lo : 0;
   it.b = lo + cnt * it.s / A.split;
   it.e = lo + cnt * (it.s + 1) / A.split;
@@ -378,6 +388,7 @@ __device__ __forceinline__ bool decode_group(const TileArgs& A, int lane, int wa
   const int64_t cnt = hi > lo ? hi - lo : 0;
   gg.fb = A.rec_lo + lo + cnt * it.s / A.split;
   gg.fe = A.rec_lo + lo + cnt * (it.s + 1) / A.split;
+  it.step = kWave;
   // this wave's part of its own tile's window (none for a spare wave past the grid)
   it.b = it.e = 0;
   if (it.j0 < A.n_grid) {
@@ -841,7 +852,7 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
         const double scd = ldexp(sc, kScaleTarget - e_ref);
         const float c1 = j < e_cur ? (float)(scd * (double)y * (double)kInvSqrtPi) : 0.0f;
         far_add(acc, c1, fx0, fh0, j < e_cur ? y * y : 0.0f, __ballot(ds) != 0ull);
-        b += kWave;
+        b += it.step;
         if (++nrun == kFarRun) {
           far_flush(acc);
           far_zero(acc);
@@ -1020,7 +1031,7 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
   // lines are staged, 64 at a time. Without selection the chunks are consecutive lines.
   [[maybe_unused]] int q0 = 0, q1 = 0, nq = 0;
   auto walk = [&](int64_t first) {
-  for (int64_t base = first; SEL || base < e_cur; base += SEL ? 0 : kWave) {
+  for (int64_t base = first; SEL || base < e_cur; base += SEL ? 0 : it.step) {
     if constexpr (!F64 && !SEL) {
       far_run(base);
       if (base >= e_cur) break;

@@ -215,7 +215,6 @@ int time_candidate(Ctx& c, const LinesRes& L, const GridRes& G, const xs_opts& o
     p.rec_n = b.rec_n;
     p.npts = nprobe;
     p.pt_batch = nprobe;
-    if (p.moments) p.set_tree();
     const int64_t t0 = b.j0 / tile, t1 = (b.j1 + tile - 1) / tile;
     const int64_t nt = t1 - t0;
     int64_t sp = std::max<int64_t>(p.split, (round_items + nt * nprobe - 1) / (nt * nprobe));
@@ -371,7 +370,8 @@ int xs_autotune(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, size_t
     o.pts_per_lane = P;
     o.split = 0;
     o.waves_per_simd = W;
-    const Plan full = make_plan(*c, *L, *G, npts, o, 0, 0, ips);
+    // (the shape is the tile kernel's: timed line by line)
+    const Plan full = make_plan(*c, *L, *G, pts, npts, o, 0, 0, ips, false);
     double ms = 0.0;
     const int r = time_candidate(*c, *L, *G, o, blocks, nprobe, full, tm, &ms);
     if (r == XS_OK) tried.push_back({P, ips, waves_option(full.W), ms});
@@ -424,7 +424,7 @@ int xs_autotune(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, size_t
   o.pts_per_lane = 0;
   o.split = 0;
   o.waves_per_simd = 0;
-  const Plan p = make_plan(*c, *L, *G, npts, o);
+  const Plan p = make_plan(*c, *L, *G, pts, npts, o);
   memset(out, 0, sizeof *out);
   out->pts_per_lane = p.P;
   out->split = p.split;

@@ -62,17 +62,17 @@ def test_moments_vs_oracle(ctx, case, f64):
     pts = [(1e-4, 500.0), (0.3, 1500.0), (80.0, 700.0)]
     ref = [O.sigma(L, grid, P, T, 16.0, cut_cm1=cut) for P, T in pts]
     prec = X.XS_FP64 if f64 else X.XS_FP32_KAHAN
-    for lane_pts, split in ((0, 0), (1, 1), (2, 3)):
-        o = ctx.opts(X.XS_CUT_FIXED, cut, precision=prec, pts_per_lane=lane_pts, split=split)
+    for split in (0, 1, 3):
+        o = ctx.opts(X.XS_CUT_FIXED, cut, precision=prec, split=split)
         sig = ctx.compute(h, g, pts, o)
         for k, r in enumerate(ref):
             st = O.compare(sig[k], r, rel_tol=2e-8 if f64 else 2e-6)
-            print(f"[moments] {case} f64={f64} P={pts[k][0]} pts/lane {lane_pts} split {split} "
+            print(f"[moments] {case} f64={f64} P={pts[k][0]} split {split} "
                   f"max_rel {st['max_rel']:.2e}", flush=True)
             assert st["violations"] == 0, st
         assert np.array_equal(ctx.compute(h, g, pts, o), sig)   # bitwise repeatable
     # one point of the batch alone gives the same bits
-    o = ctx.opts(X.XS_CUT_FIXED, cut, precision=prec, pts_per_lane=1, split=1)
+    o = ctx.opts(X.XS_CUT_FIXED, cut, precision=prec, split=1)
     assert np.array_equal(ctx.compute(h, g, pts[1:2], o)[0], ctx.compute(h, g, pts, o)[1])
     ctx.unload_lines(h)
     ctx.free_grid(g)
@@ -89,7 +89,7 @@ def test_moments_entry_points_agree(ctx):
     pts = [(0.01, 900.0), (5.0, 1500.0)]
     h = ctx.load_lines(L, 16.0)
     g = ctx.set_grid(grid)
-    o = ctx.opts(X.XS_CUT_FIXED, 25.0, pts_per_lane=1, split=2)
+    o = ctx.opts(X.XS_CUT_FIXED, 25.0, split=2)
     want = ctx.compute(h, g, pts, o)
     out = torch.empty((2, 700), dtype=torch.float64, device="cuda")
     gr = ctx.graph_create(h, g, pts, o, out)
@@ -108,16 +108,16 @@ def test_moments_entry_points_agree(ctx):
     r = ctx.submit(h, g, pts, o)
     assert np.array_equal(r.wait(60.0), want)
     r.release()
-    # list 1.56 MB + grid; one point's records are 1.92 MB, its moments 0.17 MB more
+    # list 1.56 MB + grid; one point's records are 1.7 MB, its moments 0.7 MB more
     small = X.Context(0, hbm_budget_bytes=3_560_000)
     hs = small.load_lines(L, 16.0)
     gs = small.set_grid(grid)
-    o1 = ctx.opts(X.XS_CUT_FIXED, 25.0, pts_per_lane=1, split=1, out_dtype=X.XS_F32)
+    o1 = ctx.opts(X.XS_CUT_FIXED, 25.0, split=1, out_dtype=X.XS_F32)
     out32 = torch.empty((1, 700), dtype=torch.float32, device="cuda")
     small.compute(hs, gs, pts[:1], o1, out=out32, stream=torch.cuda.current_stream())
     torch.cuda.synchronize()
     used, budget = small.memory_used()
-    assert budget - used < 170_000
+    assert budget - used < 400_000   # the moments need 0.7 MB (13 bytes per line)
     st = O.compare(out32.cpu().numpy()[0].astype(np.float64), want[0], rel_tol=2e-6)
     assert st["violations"] == 0, st
     small.close()
