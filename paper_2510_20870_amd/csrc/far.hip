@@ -12,113 +12,95 @@
 
 namespace xs {
 
-// 1/n! and n! for n <= kMomFp64
+// n!, n <= kMomFp64
 struct Factorials {
-  double inv[kMomFp64 + 1], val[kMomFp64 + 1];
+  double v[kMomFp64 + 1];
 };
 constexpr Factorials make_factorials() {
   Factorials f{};
-  f.inv[0] = f.val[0] = 1.0;
-  for (int n = 1; n <= kMomFp64; ++n) {
-    f.val[n] = f.val[n - 1] * n;
-    f.inv[n] = 1.0 / f.val[n];
-  }
+  f.v[0] = 1.0;
+  for (int n = 1; n <= kMomFp64; ++n) f.v[n] = f.v[n - 1] * n;
   return f;
 }
-static __device__ const Factorials kFact = make_factorials();
+constexpr Factorials kFactorial = make_factorials();
 
-// Three levels at once: a workgroup takes 64 nodes of level l, writes their 16 parents and,
-// where those levels exist, the 4 parents of those and the one above. A child's moments move
-// to the parent's centre and scale by the binomial theorem, which for moments divided by m!
-// is a plain product of series: T'_m / m! = sum_k (R^k A_k / k!) (D^(m-k) / (m-k)!), D the
-// distance of the centres and R the child's scale, in parent scales. Both series are
-// written to LDS first, one thread per term, so that the products run without a chain.
-// Latency sets its time (one workgroup per 1024 lines, three short dependent phases per
-// level).
+// One parent from its n children (nodes q0 .. q0 + n - 1 of the level below). A child's
+// moments move to the parent's centre and scale by the binomial theorem, which for moments
+// divided by m! is a plain product of series: T'_m / m! = sum_k (R^k A_k / k!) (D^(m-k) /
+// (m-k)!), D the distance of the centres and R the child's scale, in parent scales. One thread
+// holds the whole parent in registers, so the term products (136 for 16 moments) are a
+// straight run with no table, no shared memory and neighbouring threads reading
+// neighbouring nodes.
 template <int NM>
-__global__ __launch_bounds__(256) void xs_tree_up_kernel(ParamArgs A, int l) {
-  constexpr int kChild = 64, NF = node_fields<NM>(), kPad = NF + 1;
-  __shared__ double ch[kChild][kPad];        // the children's fields
-  __shared__ double ra[kChild][NM + 1], ed[kChild][NM];   // R^k A_k / k!, D^j / j!
-  const int k = blockIdx.y;
-  double* nodes = A.nodes + (int64_t)k * A.dims.n_nodes * NF;
-  const double kb =
-      make_pt(A.sp, A.pts[2 * (A.pt0 + k)], A.pts[2 * (A.pt0 + k) + 1]).dopp / kCLight;
-  const int64_t c0 = (int64_t)blockIdx.x * kChild;
-  int nc = (int)min((int64_t)kChild, A.dims.cnt[l] - c0);
-  {
-    const double* src = nodes + node_pos<NM>(A.dims.off[l] + c0);
-    for (int t = threadIdx.x; t < kChild * NF; t += blockDim.x) {
-      const int blk = t / (kNodeBlock * NF), r = t - blk * (kNodeBlock * NF);
-      const int f = r / kNodeBlock, n = blk * kNodeBlock + r % kNodeBlock;
-      if (n < nc) ch[n][f] = src[t];
+__device__ __forceinline__ void merge_node(const double* nodes, int64_t q0, int n, double kb,
+                                           double* to) {
+  const NodeRef<NM, const double> first{nodes + node_pos<NM>(q0)};
+  const double lo = first.lo();
+  const double hi = NodeRef<NM, const double>{nodes + node_pos<NM>(q0 + n - 1)}.hi();
+  double g = first.at(kNodeG);
+  for (int i = 1; i < n; ++i)
+    g = fmax(g, NodeRef<NM, const double>{nodes + node_pos<NM>(q0 + i)}.at(kNodeG));
+  const double h = 0.5 * (hi - lo), c = 0.5 * (lo + hi);
+  const double s = sqrt(fma(h, h, g * g)) + far_beta<NM>() * (kb * hi);
+  const double is = 1.0 / s;
+  double sum[NM];
+#pragma unroll
+  for (int m = 0; m < NM; ++m) sum[m] = 0.0;
+#pragma unroll 1
+  for (int i = 0; i < n; ++i) {
+    const NodeRef<NM, const double> f{nodes + node_pos<NM>(q0 + i)};
+    const double D = (f.c() - c) * is, R = f.s() * is;
+    double a[NM], e[NM];   // R^k A_k / k! (k = index + 1), D^j / j!
+    double pr = R, pd = 1.0;
+#pragma unroll
+    for (int k = 0; k < NM; ++k) {
+      a[k] = pr * f.at(kNodeA + k);
+      e[k] = pd;
+      pr *= R * (1.0 / (k + 2));
+      pd *= D * (1.0 / (k + 1));
     }
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+      for (int k = 0; k <= m; ++k) sum[m] = fma(a[k], e[m - k], sum[m]);
   }
-  __syncthreads();
-  int per = kChild / kArity;   // parents of a whole workgroup at the next level
+  const NodeRef<NM, double> p{to};
+  p.at(kNodeLo) = lo;
+  p.at(kNodeHi) = hi;
+  p.at(kNodeS) = s;
+  p.at(kNodeG) = g;
+#pragma unroll
+  for (int m = 0; m < NM; ++m) p.at(kNodeA + m) = sum[m] * kFactorial.v[m + 1];
+}
+
+// Three levels at once: a workgroup takes 4 kBlock nodes of level l, writes their parents, one
+// per thread, and, where those levels exist, the two levels above those. The first of the
+// three levels reads nearly all the bytes; the other two run on a quarter and a sixteenth of
+// the threads, whose latency (about 900 dependent-free instructions each) is what a small
+// list waits for.
+template <int NM>
+__global__ __launch_bounds__(kBlock) void xs_tree_up_kernel(ParamArgs A, int l) {
+  const int k = blockIdx.y;
+  double* nodes = A.nodes + (int64_t)k * A.dims.n_nodes * node_fields<NM>();
+  const double kb = A.bounds[k].kb;
+  int per = kBlock;   // parents of a whole workgroup
+#pragma unroll 1
   for (int up = l + 1; up <= l + 3 && up < A.dims.levels; ++up, per /= kArity) {
-    const int np = (nc + kArity - 1) / kArity;
-    // a parent's extent, largest width and scale, from its children in LDS
-    auto parent = [&](int q, double* lo, double* hi, double* g, double* sc) {
-      const int c1 = min(kArity * q + kArity, nc) - 1;
-      *lo = ch[kArity * q][kNodeLo];
-      *hi = ch[c1][kNodeHi];
-      double gm = 0.0;
-      for (int i = kArity * q; i <= c1; ++i) gm = fmax(gm, ch[i][kNodeG]);
-      *g = gm;
-      const double h = 0.5 * (*hi - *lo);
-      *sc = sqrt(fma(h, h, gm * gm)) + far_beta<NM>() * (kb * *hi);
-    };
-    for (int t = threadIdx.x; t < nc * NM; t += blockDim.x) {
-      const int i = t / NM, j = t - i * NM;
-      double lo, hi, g, sc;
-      parent(i / kArity, &lo, &hi, &g, &sc);
-      const double is = 1.0 / sc;
-      const double D = (0.5 * (ch[i][kNodeLo] + ch[i][kNodeHi]) - 0.5 * (lo + hi)) * is;
-      const double R = ch[i][kNodeS] * is;
-      double pd = 1.0, pr = R;
-      for (int q = 0; q < j; ++q) {
-        pd *= D;
-        pr *= R;
-      }
-      ed[i][j] = pd * kFact.inv[j];
-      ra[i][j + 1] = pr * kFact.inv[j + 1] * ch[i][kNodeA + j];
+    const int64_t q = (int64_t)blockIdx.x * per + threadIdx.x;
+    if ((int)threadIdx.x < per && q < A.dims.cnt[up]) {
+      const int n = (int)min((int64_t)kArity, A.dims.cnt[up - 1] - q * kArity);
+      merge_node<NM>(nodes, A.dims.off[up - 1] + q * kArity, n, kb,
+                     nodes + node_pos<NM>(A.dims.off[up] + q));
     }
-    // (the parents' headers stay in registers over the barrier: ch is overwritten)
-    double hlo = 0.0, hhi = 0.0, hg = 0.0, hs = 0.0;
-    if ((int)threadIdx.x < np) parent((int)threadIdx.x, &hlo, &hhi, &hg, &hs);
-    __syncthreads();
-    const int64_t q0 = (int64_t)blockIdx.x * per;
-    for (int t = threadIdx.x; t < np * NM; t += blockDim.x) {
-      const int q = t / NM, m = t - q * NM + 1;
-      const int c1 = min(kArity * q + kArity, nc);
-      double sum = 0.0;
-      for (int i = kArity * q; i < c1; ++i) {
-        double a = 0.0;
-        for (int j = 1; j <= m; ++j) a = fma(ra[i][j], ed[i][m - j], a);
-        sum += a;
-      }
-      sum *= kFact.val[m];
-      ch[q][kNodeA + m - 1] = sum;
-      nodes[node_pos<NM>(A.dims.off[up] + q0 + q) + (kNodeA + m - 1) * kNodeBlock] = sum;
-    }
-    if ((int)threadIdx.x < np) {
-      const int q = threadIdx.x;
-      const NodeRef<NM, double> nd{nodes + node_pos<NM>(A.dims.off[up] + q0 + q)};
-      ch[q][kNodeLo] = nd.at(kNodeLo) = hlo;
-      ch[q][kNodeHi] = nd.at(kNodeHi) = hhi;
-      ch[q][kNodeS] = nd.at(kNodeS) = hs;
-      ch[q][kNodeG] = nd.at(kNodeG) = hg;
-    }
-    nc = np;
-    __syncthreads();
+    __syncthreads();   // (the next level reads what this one wrote)
   }
 }
 
 hipError_t launch_tree_up(const ParamArgs& A, hipStream_t st) {
   if (A.n <= 0 || A.n_pt <= 0) return hipSuccess;
   for (int l = 0; l + 1 < A.dims.levels; l += 3) {
-    const dim3 grid((unsigned)((A.dims.cnt[l] + 63) / 64), (unsigned)A.n_pt), block(256);
+    const dim3 grid((unsigned)((A.dims.cnt[l + 1] + kBlock - 1) / kBlock), (unsigned)A.n_pt);
+    const dim3 block(kBlock);
     if (A.moments == kMomFp32)
       hipLaunchKernelGGL(xs_tree_up_kernel<kMomFp32>, grid, block, 0, st, A, l);
     else

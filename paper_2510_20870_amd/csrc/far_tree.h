@@ -39,11 +39,11 @@ constexpr double kBetaFp32 = 2.05, kBetaFp64 = 2.35;
 template <int NM> constexpr double far_beta() { return NM == kMomFp32 ? kBetaFp32 : kBetaFp64; }
 
 // A node's fields: centres of the group's first and last line, scale s, largest Lorentz
-// width, moments. Nodes are stored eight by eight, field by field (kNodeBlock nodes of a
+// width, smallest and largest cut (leaves only), moments. Nodes are stored eight by eight, field by field (kNodeBlock nodes of a
 // field side by side), so that wavefronts reading one field of neighbouring nodes read
 // whole lines of the cache; every level starts at a multiple of kNodeBlock.
 constexpr int kNodeBlock = 8;
-enum { kNodeLo = 0, kNodeHi = 1, kNodeS = 2, kNodeG = 3, kNodeA = 4 };
+enum { kNodeLo, kNodeHi, kNodeS, kNodeG, kNodeCutMin, kNodeCutMax, kNodeA };
 template <int NM> constexpr int node_fields() { return kNodeA + NM; }
 constexpr size_t node_bytes(int moments) { return (size_t)(kNodeA + moments) * sizeof(double); }
 template <int NM>
@@ -117,9 +117,9 @@ __device__ __forceinline__ void row_halve(double (&v)[kV], bool up) {
 // width). Each lane forms the moments of its line; the sums over the row go by halving: at
 // every step a lane keeps half of the values and adds its partner's, so 16 sums over 16 lanes
 // take 15 exchanges, and lane i ends with moment i + 1 (28 moments: 2 i + 1 and 2 i + 2).
-template <int NM>
+template <int NM, bool FW>
 __device__ __forceinline__ void leaf_moments(double* nodes, int64_t leaf, double nu0, double w,
-                                             double b, double g, int lane) {
+                                             double b, double g, double cut, int lane) {
   constexpr int kV = NM <= 16 ? 16 : 32;
   static_assert(NM <= 32 && kLeafLines == 16, "a leaf is a DPP row");
   const int row = lane & ~15, i = lane & 15;
@@ -129,9 +129,20 @@ __device__ __forceinline__ void leaf_moments(double* nodes, int64_t leaf, double
   gm = fmax(gm, row_swap<kRowX7>(gm));
   gm = fmax(gm, row_swap<kRowX2>(gm));
   gm = fmax(gm, row_swap<kRowX1>(gm));
+  double cmin = cut, cmax = cut;
+  if constexpr (FW) {
+    cmin = fmin(cmin, row_swap<kRowX8>(cmin));
+    cmax = fmax(cmax, row_swap<kRowX8>(cmax));
+    cmin = fmin(cmin, row_swap<kRowX7>(cmin));
+    cmax = fmax(cmax, row_swap<kRowX7>(cmax));
+    cmin = fmin(cmin, row_swap<kRowX2>(cmin));
+    cmax = fmax(cmax, row_swap<kRowX2>(cmax));
+    cmin = fmin(cmin, row_swap<kRowX1>(cmin));
+    cmax = fmax(cmax, row_swap<kRowX1>(cmax));
+  }
   const double h = 0.5 * (hi - lo);
   const double s = sqrt(fma(h, h, gm * gm)) + far_beta<NM>() * bm;
-  const double is = 1.0 / s;
+  const double is = rcp64(s);
   double v[kV];
   {
     double A[NM];
@@ -149,7 +160,9 @@ __device__ __forceinline__ void leaf_moments(double* nodes, int64_t leaf, double
 #pragma unroll
   for (int m = 0; m < kPer; ++m)
     if (kPer * i + m < NM) nd.at(kNodeA + kPer * i + m) = v[m];
-  if (i < kNodeA) nd.at(i) = i == 0 ? lo : i == 1 ? hi : i == 2 ? s : gm;
+  if (i < kNodeA)
+    nd.at(i) = i == kNodeLo ? lo : i == kNodeHi ? hi : i == kNodeS ? s : i == kNodeG ? gm
+               : i == kNodeCutMin ? cmin : cmax;
 }
 // One line at one point, with the cut test: the sums of the ragged ends of the far ranges
 // (lines of a leaf that the cut of a point splits) and of the few leaves that are neither far

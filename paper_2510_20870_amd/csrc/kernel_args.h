@@ -63,6 +63,7 @@ struct ParamArgs {
   double* nodes;          // tree nodes [n_pt][dims.n_nodes] (nullptr: no tree)
   TreeDims dims;
   int moments;            // kMomFp32 or kMomFp64
+  PtBounds* bounds;       // [n_pt] (with a tree)
 };
 
 // The far kernel: per (tile, P-T point) the sum over the lines outside the tile's near
@@ -90,11 +91,10 @@ struct FarArgs {
 // The point kernel: whole sums at kPointGroup neighbouring grid points per wavefront.
 struct PointArgs {
   LinesDev L;
-  SpeciesDev sp;
-  double cut;             // the fixed cut
+  CutDev cut;
+  const PtBounds* bounds; // [n_pt]
   const double* grid;
   int64_t n_grid;
-  const double* pts;      // [n_pts][2], whole table
   int pt0, n_pt;          // points of this launch
   int split;              // parts of a group's work, each a wavefront of its own
   int64_t g0, n_groups;   // groups of kPointGroup grid points

@@ -58,10 +58,12 @@ namespace xs {
 // One thread per line; each row of 16 lanes is one leaf of the tree (NM > 0: with NM
 // moments), whose moments it sums while the parameters are in registers, so the tree costs
 // no pass of its own over the lines.
-template <int NM>
+// FW: the lines' cuts differ, so a leaf notes their range.
+template <int NM, bool FW>
 __global__ __launch_bounds__(256) void xs_params_kernel(ParamArgs A) {
   const int k = blockIdx.y;
   const PtConst pc = make_pt(A.sp, A.pts[2 * (A.pt0 + k)], A.pts[2 * (A.pt0 + k) + 1]);
+  if (NM > 0 && blockIdx.x == 0 && threadIdx.x == 0) A.bounds[k] = pt_bounds(A.sp, pc);
   LineRec* out = A.out + (int64_t)k * A.n;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane);
@@ -74,13 +76,14 @@ __global__ __launch_bounds__(256) void xs_params_kernel(ParamArgs A) {
                                       A.L.nT[i], A.L.g[i], A.L.J ? A.L.J[i] : (uint16_t)0);
     LineRec r;
     r.cut = lp.cut;
-    r.ib = 1.0 / lp.bD;
+    r.ib = lp.ib;
     r.sc = lp.S * r.ib * (1.0 / kSqrtPiD);
     r.y = lp.gL * r.ib;
     if (ok) out[t] = r;
     if constexpr (NM > 0)
-      leaf_moments<NM>(A.nodes + (int64_t)k * A.dims.n_nodes * node_fields<NM>(),
-                       (base + lane) / kLeafLines, nu0, ok ? lp.S * (1.0 / kPiD) : 0.0, lp.bD, lp.gL, lane);
+      leaf_moments<NM, FW>(A.nodes + (int64_t)k * A.dims.n_nodes * node_fields<NM>(),
+                       (base + lane) / kLeafLines, nu0, ok ? lp.S * (1.0 / kPiD) : 0.0, lp.bD,
+                       lp.gL, lp.cut, lane);
   }
 }
 
@@ -322,11 +325,16 @@ hipError_t launch_params(const ParamArgs& A, hipStream_t st) {
   int64_t blocks = (A.n + 255) / 256;
   if (blocks > 8192) blocks = 8192;
   const dim3 grid((unsigned)blocks, (unsigned)A.n_pt), block(256);
-  if (!A.nodes) hipLaunchKernelGGL(xs_params_kernel<0>, grid, block, 0, st, A);
+  const bool fw = A.cut.kind != kCutFixed;
+  if (!A.nodes) hipLaunchKernelGGL((xs_params_kernel<0, false>), grid, block, 0, st, A);
+  else if (A.moments == kMomFp32 && !fw)
+    hipLaunchKernelGGL((xs_params_kernel<kMomFp32, false>), grid, block, 0, st, A);
   else if (A.moments == kMomFp32)
-    hipLaunchKernelGGL(xs_params_kernel<kMomFp32>, grid, block, 0, st, A);
+    hipLaunchKernelGGL((xs_params_kernel<kMomFp32, true>), grid, block, 0, st, A);
+  else if (!fw)
+    hipLaunchKernelGGL((xs_params_kernel<kMomFp64, false>), grid, block, 0, st, A);
   else
-    hipLaunchKernelGGL(xs_params_kernel<kMomFp64>, grid, block, 0, st, A);
+    hipLaunchKernelGGL((xs_params_kernel<kMomFp64, true>), grid, block, 0, st, A);
   return hipGetLastError();
 }
 

@@ -8,7 +8,7 @@
 // is computed in the same operation order as a plain evaluation of the textbook formula,
 // with contraction disabled for the whole library (-ffp-contract=off) and IEEE sqrt, so
 // that it agrees with any other careful FP64 evaluation to the last bit except where the
-// power function itself differs by an ulp.
+// power function (here exp(n ln(T_ref/T))) itself differs by an ulp.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -48,8 +48,8 @@ struct SpeciesDev {
   const double* broad_gam;
   const double* broad_n;
   // list statistics for the per-tile cutoff bound: gamma_L <= (P/P_ref) gam_max
-  // (T_ref/T)^n for some n in [n_min, n_max]
-  double gam_max, n_min, n_max;
+  // (T_ref/T)^n for some n in [n_min, n_max], and at least gam_min in gam_max's place
+  double gam_max, gam_min, n_min, n_max;
 };
 
 struct CutDev {
@@ -81,6 +81,10 @@ struct PtConst {
   double dopp;        // sqrt(2 k_B T / (m amu)); b_D = (nu0 / c) * dopp
   double pfac;        // P / P_ref
   double tratio;      // T_ref / T
+  double lnt;         // ln(T_ref / T)
+  double c2t;         // c2 / T
+  double s_ein;       // 1 / (8 pi c Q(T))
+  double inv_kb;      // c / dopp: 1 / b_D = inv_kb / nu0
 };
 
 __host__ __device__ inline PtConst make_pt(const SpeciesDev& sp, double P, double T) {
@@ -93,12 +97,17 @@ __host__ __device__ inline PtConst make_pt(const SpeciesDev& sp, double P, doubl
   c.dopp = sqrt(2.0 * kKBoltz * T / (sp.mass_amu * kAmu));
   c.pfac = P / sp.P_ref;
   c.tratio = sp.T_ref / T;
+  c.lnt = log(c.tratio);
+  c.c2t = kC2 / T;
+  c.s_ein = c.inv_q / (8.0 * kPiD * kCcgs);
+  c.inv_kb = kCLight / c.dopp;
   return c;
 }
 
 struct LineParams {
   double S;      // strength [cm/molecule]
   double bD;     // Doppler 1/e half-width [cm^-1]
+  double ib;     // 1 / bD
   double gL;     // Lorentz HWHM [cm^-1]
   double cut;    // cutoff half-width [cm^-1]
 };
@@ -115,25 +124,30 @@ __host__ __device__ inline LineParams line_params(const SpeciesDev& sp, const Pt
                                                   uint16_t g, uint16_t J) {
   LineParams lp;
   const double e = (double)E;
+  // (one division per line; the constants of the (P, T) point carry the others)
+  const double inv = 1.0 / nu0;
   if (sp.form == kEinstein) {
-    const double boltz = exp(-kC2 * e / pc.T);
-    const double stim = -expm1(-kC2 * nu0 / pc.T);
-    lp.S = (double)g * (double)A / (8.0 * kPiD * kCcgs * nu0 * nu0) * boltz * stim * pc.inv_q;
+    const double x = pc.c2t * nu0;
+    const double boltz = exp(-pc.c2t * e);
+    // 1 - exp(-x), by expm1 where the difference would cancel
+    const double stim = x >= 0.5 ? 1.0 - exp(-x) : -expm1(-x);
+    lp.S = (double)g * (double)A * pc.s_ein * (inv * inv) * (boltz * stim);
   } else {
     const double boltz = exp(-kC2 * e / pc.T) / exp(-kC2 * e / sp.T_ref);
     const double stim = expm1(-kC2 * nu0 / pc.T) / expm1(-kC2 * nu0 / sp.T_ref);
     lp.S = (double)A * pc.q_ratio * boltz * stim;
   }
   lp.bD = nu0 / kCLight * pc.dopp;
+  lp.ib = inv * pc.inv_kb;
   if (sp.n_broad == 0) {
-    lp.gL = (double)gam * pc.pfac * pow(pc.tratio, (double)nT);
+    lp.gL = (double)gam * pc.pfac * exp((double)nT * pc.lnt);
   } else {
     // the partners' widths at the line's J, weighted by their mixing ratios
     const int j = (int)J < sp.broad_nj ? (int)J : sp.broad_nj - 1;
     double s = 0.0;
     for (int b = 0; b < sp.n_broad; ++b) {
       const int t = b * sp.broad_nj + j;
-      s += sp.broad_vmr[b] * sp.broad_gam[t] * pow(pc.tratio, sp.broad_n[t]);
+      s += sp.broad_vmr[b] * sp.broad_gam[t] * exp(sp.broad_n[t] * pc.lnt);
     }
     lp.gL = s * pc.pfac;
   }
@@ -156,6 +170,25 @@ __host__ __device__ inline double cut_bound(const SpeciesDev& sp, const PtConst&
   const double bmax = (fabs(nu_last) + cd.cut) / kCLight * pc.dopp;
   const double b = fmin(cd.cut, cd.mult * voigt_fwhm(gmax, bmax));
   return b * (1.0 + 1e-12);
+}
+
+// Bounds over the lines at one (P, T) point: b_D = kb nu0, gamma_L in [gmin, gmax] (widened
+// by rounding).
+struct PtBounds {
+  double kb, gmin, gmax;
+};
+__host__ __device__ inline PtBounds pt_bounds(const SpeciesDev& sp, const PtConst& pc) {
+  const double t1 = pow(pc.tratio, sp.n_min), t2 = pow(pc.tratio, sp.n_max);
+  PtBounds b;
+  b.kb = pc.dopp / kCLight;
+  b.gmin = sp.gam_min * pc.pfac * fmin(t1, t2) * (1.0 - 1e-12);
+  b.gmax = sp.gam_max * pc.pfac * fmax(t1, t2) * (1.0 + 1e-12);
+  return b;
+}
+// The cut of a line of widths (g, b) rounded down (up = false) or up.
+__host__ __device__ inline double cut_at(const CutDev& cd, double g, double b, bool up) {
+  if (cd.kind == kCutFixed) return cd.cut;
+  return fmin(cd.cut, cd.mult * voigt_fwhm(g, b) * (up ? 1.0 + 1e-12 : 1.0 - 1e-12));
 }
 
 }  // namespace xs

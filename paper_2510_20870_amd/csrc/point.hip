@@ -23,6 +23,7 @@
 
 namespace xs {
 
+constexpr int kEdgeQueue = 16;   // most leaves at the cut that go through the queue
 constexpr int kPointRanges = 32;    // line ranges summed one by one, per wavefront
 constexpr int kNodeList = 128;      // pending tree nodes, per wavefront
 
@@ -122,7 +123,7 @@ __device__ __forceinline__ double core64(const double* a, double L, double x, do
   double b1 = fma_s(t, a[N - 1], a[N - 2]), b2 = a[N - 1];
 #pragma unroll
   for (int n = N - 3; n >= 1; --n) {
-    const double b = fma(u, b2, fma_s(t, b1, a[n]));
+    const double b = fma(t, b1, fma_s(u, b2, a[n]));   // (one step of the chain per term)
     b2 = b1;
     b1 = b;
   }
@@ -170,7 +171,10 @@ __device__ __forceinline__ double lane_k32(const DawEntry* tab, double x, double
   return (double)k;
 }
 
-template <int NM>
+// FW: the lines' cuts differ (min(cap, mult FWHM)). The covered and the reachable lines then
+// follow from bounds of the cut; between them lie leaves of which some lines reach a point and
+// some do not.
+template <int NM, bool FW>
 __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   constexpr int R = kPointGroup, NF = node_fields<NM>();
   __shared__ DawEntry tab[NM == kMomFp32 ? kDawNodes : 1];
@@ -194,9 +198,9 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   const int64_t j0 = (A.g0 + gi % A.n_groups) * R;
   const int jn = (int)min((int64_t)R, A.n_grid - j0);
   const double v0 = A.grid[j0], v1 = A.grid[j0 + jn - 1];
-  const int pt = A.pt0 + k;
-  const double kb = make_pt(A.sp, A.pts[2 * pt], A.pts[2 * pt + 1]).dopp / kCLight;
-  const double cut = A.cut;
+  const PtBounds pb = A.bounds[k];
+  const double kb = pb.kb;
+  const double cap = A.cut.cut;
   const int rec_n = A.rec_n;
   const double* nu = A.L.nu0 + A.rec_lo;
   const LineRec* recs = A.recs + (int64_t)k * rec_n;
@@ -220,14 +224,22 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   const double g_near = right ? v1 : v0;
   auto half = [&](int v, int side) { return __builtin_amdgcn_readlane(v, side * 32); };
   const double ulp = fabs(g_near) * 0x1p-48;
+  // the largest cut of the lines on this side that can reach the points, and the smallest of
+  // those (b_D grows with the centre)
+  double cut_hi = cap, cut_lo = cap;
+  if constexpr (FW) {
+    cut_hi = cut_at(A.cut, pb.gmax, kb * (right ? v1 + cap : v1), true);
+    cut_lo = cut_at(A.cut, pb.gmin, kb * (right ? v0 : fmax(v0 - cut_hi, 0.0)), false);
+  }
+  const bool one_cut = !FW || __ballot(cut_lo < cap) == 0ull;
   // reachable lines [e0, e1)
   const int end = pair_search(nu, 0, rec_n,
-                              [&](double c) { return right ? c > v1 + cut + ulp
-                                                           : c >= v0 - cut - ulp; }, lane);
+                              [&](double c) { return right ? c > v1 + cut_hi + ulp
+                                                           : c >= v0 - cut_hi - ulp; }, lane);
   const int e0 = half(end, 0), e1 = half(end, 1);
   // lines inside the cut of every point of the group, in leaves [c0, c1)
   const int cov = pair_search(nu, e0, e1,
-                              [&](double c) { return right ? c - v0 > cut : v1 - c <= cut; },
+                              [&](double c) { return right ? c - v0 > cut_lo : v1 - c <= cut_lo; },
                               lane);
   const int c0 = (half(cov, 0) + kLeafLines - 1) / kLeafLines, c1 = half(cov, 1) / kLeafLines;
   // near range, in leaves [a, b): first by the Doppler width, then grown over every leaf
@@ -252,6 +264,8 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
       const uint32_t ml = (uint32_t)m, mr = (uint32_t)(m >> 32);
       lo -= ml ? 32 - __clz((int)ml) : 0;
       hi += mr ? 32 - __clz((int)mr) : 0;
+      // (the rest of the 32 are far; a node beyond that is not is found when it is taken)
+      if (((ml | mr) >> 16) == 0u) break;
     }
   };
   grow(0, a, b, c0, c1);
@@ -266,6 +280,37 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   // ---- tree nodes inside every point's cut, 64 at a time: one per lane
   bool whole = false;   // too many nodes that are not far: sum every line of the window
   int n_list = 0, round = 0;
+  // adds the lane's node (use: it has one) to every point's sum; lanes without a node take
+  // zero moments at a centre that is no grid point
+  auto add_node = [&](const NodeRef<NM, const double>& f, double c, double sc, bool use) {
+    const double cc = use ? c : 2.0 * v1 + 1.0;
+    double M[NM];
+#pragma unroll
+    for (int t = 0; t < NM; ++t) M[t] = use ? f.at(kNodeA + t) : 0.0;
+#pragma unroll
+    for (int p = 0; p < R; ++p) {
+      const double rX = rcp64(val(p) - cc), t = sc * rX;
+      double h = M[NM - 1];
+#pragma unroll
+      for (int m2 = NM - 2; m2 >= 0; --m2) h = fma(h, t, M[m2]);
+      acc[p] = fma(h * t, rX, acc[p]);
+    }
+  };
+  // lanes with `bad`: node (l, q) is summed line by line
+  auto to_ranges = [&](bool bad, int l, int q) {
+    const uint64_t m = __ballot(bad);
+    if (m == 0ull) return;
+    const int add = __popcll(m);
+    if (n_rng + add > kPointRanges) {
+      whole = true;
+      return;
+    }
+    const int i0 = q << (kArityBits * l), i1 = (q + 1) << (kArityBits * l);
+    if (bad)
+      rng[wv][n_rng + __popcll(m & ((1ull << lane) - 1ull))] =
+          make_int2(i0 * kLeafLines, min(i1 * kLeafLines, rec_n));
+    n_rng += add;
+  };
   auto flush = [&](int n) {
     wave_sync();
     const int id = lane < n ? list[wv][lane] : -1;
@@ -275,36 +320,8 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
     if (in) f = node(l, q);
     const double c = f.c(), sc = f.s();
     const bool bad = in && !(fmax(v0 - c, c - v1) >= kFarTheta * sc);
-    const uint64_t m = __ballot(bad);
-    if (m != 0ull) {
-      const int at = n_rng + __popcll(m & ((1ull << lane) - 1ull));
-      const int add = __popcll(m);
-      if (n_rng + add > kPointRanges) {
-        whole = true;
-      } else {
-        const int i0 = q << (kArityBits * l);
-        if (bad)
-          rng[wv][at] = make_int2(i0 * kLeafLines, min((i0 + (1 << (kArityBits * l))) * kLeafLines,
-                                                       rec_n));
-        n_rng += add;
-      }
-    }
-    if (round++ % A.split == s) {
-      // (lanes without a node: zero moments at a centre that is no grid point)
-      const bool use = in && !bad;
-      const double cc = use ? c : 2.0 * v1 + 1.0;
-      double M[NM];
-#pragma unroll
-      for (int t = 0; t < NM; ++t) M[t] = use ? f.at(kNodeA + t) : 0.0;
-#pragma unroll
-      for (int p = 0; p < R; ++p) {
-        const double rX = rcp64(val(p) - cc), t = sc * rX;
-        double h = M[NM - 1];
-#pragma unroll
-        for (int m2 = NM - 2; m2 >= 0; --m2) h = fma(h, t, M[m2]);
-        acc[p] = fma(h * t, rX, acc[p]);
-      }
-    }
+    to_ranges(bad, l, q);
+    if (round++ % A.split == s) add_node(f, c, sc, in && !bad);
     // the nodes not taken yet move to the front
     const int rest = lane + kWave < n_list ? list[wv][kWave + lane] : 0;
     wave_sync();
@@ -354,30 +371,30 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
     if (n_list > 0) flush(n_list);
   }
 
-  // ---- leaves at the cut: left [e0 / 16, min(a, c0)), right [max(b, c1), e1 / 16 up); a leaf
-  // counts for the points whose cut holds all of it; a leaf that a cut splits is noted
-  {
-    const int la = e0 / kLeafLines, lb = min(a, c0);
-    const int ra = max(b, c1), rb = (e1 + kLeafLines - 1) / kLeafLines;
-    const int nl = max(lb - la, 0), n = nl + max(rb - ra, 0);
-    for (int o = 0; o < n; o += kWave) {
+  // ---- leaves at the cut: left [e0 / 16, min(a, c0)), right [max(b, c1), e1 / 16 up)
+  const int la = e0 / kLeafLines, lb = min(a, c0);
+  const int ra = max(b, c1), rb = (e1 + kLeafLines - 1) / kLeafLines;
+  const int nl = max(lb - la, 0), n_edge = nl + max(rb - ra, 0);
+  auto edge_leaf = [&](int i) { return i < nl ? la + i : ra + (i - nl); };
+  // One cut and more than kEdgeQueue leaves (a dense list): a leaf counts for the points whose
+  // cut holds all of it, and the leaf that a cut splits is noted. Few leaves, or different
+  // cuts: below, line by line where a leaf is not inside every cut. (The
+  // queue sums a leaf's 16 lines at every point, 64 leaves by their moments cost one node per
+  // lane and the lines of the two split leaves. A 250 cm^-1 window of 8696 lines/cm^-1 takes
+  // 257 us by leaf and 302 us with the queue.)
+  const bool by_leaf = one_cut && n_edge > kEdgeQueue;
+  if (by_leaf) {
+    const double cut = cap;
+    for (int o = 0; o < n_edge; o += kWave) {
       const int i = o + lane;
-      const bool in = i < n;
-      const int q = in ? (i < nl ? la + i : ra + (i - nl)) : 0;
+      const bool in = i < n_edge;
+      const int q = in ? edge_leaf(i) : 0;
       const NodeRef<NM, const double> f = node(0, q);
       const double lo = f.lo(), hi = f.hi(), c = f.c(), sc = f.s();
       const bool bad = in && !(fmax(v0 - c, c - v1) >= kFarTheta * sc);
-      const uint64_t m = __ballot(bad);
-      if (m != 0ull) {
-        // not far: its lines one by one (with the cut test)
+      if (__ballot(bad) != 0ull) {
         mask = true;
-        const int at = n_rng + __popcll(m & ((1ull << lane) - 1ull));
-        const int add = __popcll(m);
-        if (n_rng + add > kPointRanges) whole = true;
-        else {
-          if (bad) rng[wv][at] = make_int2(q * kLeafLines, min((q + 1) * kLeafLines, rec_n));
-          n_rng += add;
-        }
+        to_ranges(bad, 0, q);
       }
       const bool mine = round++ % A.split == s;
       const bool use = in && !bad && mine;
@@ -398,6 +415,105 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
     }
     wave_sync();
   }
+  // Few leaves or different cuts: the lines that reach some point are gathered in a queue and
+  // summed 64 at a time, one per lane.
+  int turn = 0;   // the part that takes the next chunk
+  auto my_turn = [&]() {
+    const bool mine = turn == s;
+    turn = turn + 1 == A.split ? 0 : turn + 1;
+    return mine;
+  };
+  if (!by_leaf && !whole) {
+    int n_q = 0;
+    auto sum_queue = [&](int n) {
+      wave_sync();
+      const bool ok = lane < n;
+      const int i = list[wv][ok ? lane : 0];
+      const int rest = lane + kWave < n_q ? list[wv][kWave + lane] : 0;
+      wave_sync();
+      list[wv][lane] = rest;
+      n_q -= n;
+      wave_sync();
+      if (!my_turn()) return;
+      const double c = nu[i];
+      const LineRec lr = recs[i];
+      // the shifted or the doubly shifted Lorentzian within the error budget at both ends
+      // of the group, else the six-term series (x and r^2 in FP64, the reciprocals in
+      // FP32); FP64 path: voigt_k64, which is outside its core here
+      const double w = ok ? lr.sc : 0.0, y2 = lr.y * lr.y;
+      auto far_points = [&](double w1, double add, auto k_of) {
+#pragma unroll
+        for (int p = 0; p < R; ++p) {
+          const double d = val(p) - c, x = d * lr.ib;
+          const double wp = fabs(d) <= lr.cut ? w1 : 0.0;
+          acc[p] = fma(k_of(fma(x, x, add)), wp, acc[p]);
+        }
+      };
+      if constexpr (NM == kMomFp32) {
+        const double xa = (v0 - c) * lr.ib, xb = (v1 - c) * lr.ib;
+        const float y2f = (float)y2, rn = (float)(fmin(xa * xa, xb * xb) + y2);
+        const double w1 = w * lr.y * kInvSqrtPi;
+        if (__ballot(!shifted_lorentz_ok(y2f, rn, A.l1_eps)) == 0ull)
+          far_points(w1, y2 - 1.5, [&](double r) { return (double)rcp32((float)r); });
+        else if (__ballot(!dshift_ok(rn, A.l1_eps)) == 0ull)
+          far_points(w1, y2, [&](double r2) {
+            const float r = (float)r2;
+            return (double)rcp32(fmaf(2.0f * y2f, rcp32(r), r - 1.5f));
+          });
+        else
+          far_points(w1, y2,
+                     [&](double r2) { return (double)asym_scaled<6>(y2f, (float)r2); });
+      } else {
+        far_points(w, y2, [&](double r2) {
+          return r2 >= kFarR2_64 ? voigt_far64(r2, lr.y) : voigt_mid64(r2, lr.y);
+        });
+      }
+    };
+    for (int o = 0; o < n_edge; o += kWave) {
+      const int e = o + lane;
+      const bool in = e < n_edge;
+      const int leaf = in ? edge_leaf(e) : 0;
+      const NodeRef<NM, const double> f = node(0, leaf);
+      const double lo = f.lo(), hi = f.hi(), c = f.c(), sc = f.s();
+      const bool is_left = e < nl;
+      const double cmax = FW ? f.at(kNodeCutMax) : cap, cmin = FW ? f.at(kNodeCutMin) : cap;
+      const bool out = !in || (is_left ? v0 - hi : lo - v1) > cmax;
+      const bool far = fmax(v0 - c, c - v1) >= kFarTheta * sc;
+      // inside every line's cut at every point: by its moments
+      const bool all = !out && far && (is_left ? v1 - lo : hi - v0) <= cmin;
+      if (__ballot(all) != 0ull && round++ % A.split == s) add_node(f, c, sc, all);
+      const bool near = !out && !far;
+      if (__ballot(near) != 0ull) {
+        mask = true;
+        to_ranges(near, 0, leaf);
+      }
+      // the others four at a time, one per row of 16 lanes
+      uint64_t m4 = __ballot(!out && far && !all);
+      while (m4 != 0ull) {
+        int q = -1;
+#pragma unroll
+        for (int t = 0; t < kWave / kLeafLines; ++t) {
+          if (m4 != 0ull) {
+            const int id = __builtin_amdgcn_readlane(leaf, __builtin_ctzll(m4));
+            m4 &= m4 - 1ull;
+            if (lane / kLeafLines == t) q = id;
+          }
+        }
+        const int i = q * kLeafLines + (lane & (kLeafLines - 1));
+        bool take = false;
+        if (q >= 0 && i < rec_n) {
+          const double ci = nu[i];
+          const double ct = FW ? recs[i].cut : cap;
+          take = fabs(v0 - ci) <= ct || fabs(v1 - ci) <= ct;
+        }
+        const uint64_t m = __ballot(take);
+        if (take) list[wv][n_q + __popcll(m & ((1ull << lane) - 1ull))] = i;
+        n_q += __popcll(m);
+        if (n_q >= kWave) sum_queue(kWave);
+      }
+    }
+    if (n_q > 0) sum_queue(n_q);
+  }
   if (whole) {
     // (the same decision in every part of the group)
 #pragma unroll
@@ -405,7 +521,7 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
     mask = true;
     n_rng = 1;
     if (lane == 0) rng[wv][0] = make_int2(e0, e1);
-  } else if (s == 0) {
+  } else if (by_leaf && s == 0) {
     // the split leaves: lanes 0-15 the left one's lines, 16-31 the right one's, per point
     // (through LDS, so that the sums keep their registers in a loop that is not unrolled)
 #pragma unroll 1
@@ -423,16 +539,17 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   }
   wave_sync();
 
-  // ---- lines one by one, 64 at a time: one per lane
-  int chunk = 0;
+  // ---- lines of the ranges, 64 at a time: one per lane
   for (int r = 0; r < n_rng; ++r) {
-    const int2 ab = rng[wv][r];
-    for (int base = ab.x; base < ab.y; base += kWave) {
-      if (chunk++ % A.split != s) continue;
-      const int i = min(base + lane, ab.y - 1);
+    // (the walk's state in scalar registers)
+    const int first = __builtin_amdgcn_readfirstlane(rng[wv][r].x);
+    const int last = __builtin_amdgcn_readfirstlane(rng[wv][r].y) - 1;
+    for (int base = first; base <= last; base += kWave) {
+      if (!my_turn()) continue;
+      const int i = min(base + lane, last);
       const double c = nu[i];
       const LineRec lr = recs[i];
-      const double sc = base + lane < ab.y ? lr.sc : 0.0;
+      const double sc = base + lane <= last ? lr.sc : 0.0;
       // adds the line to every point's sum with the given K
       auto points = [&](auto k_of) {
 #pragma unroll
@@ -440,7 +557,7 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
           const double d = val(p) - c;
           const double kk = k_of(d * lr.ib);
           double w = sc;
-          if (mask) w = fabs(d) <= cut ? sc : 0.0;
+          if (mask) w = fabs(d) <= lr.cut ? sc : 0.0;
           acc[p] = fma(w, kk, acc[p]);
         }
       };
@@ -452,8 +569,8 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
             return lane_k32<decltype(core)::value>(tab, x, lr.y, y32, y2, A.l1_eps);
           });
         };
-        if (all(y32 < kTaylorY)) with(std::integral_constant<int, kCoreSmall>{});
-        else if (all(y2 >= kT6R2)) with(std::integral_constant<int, kCoreNone>{});
+        if (all(y2 >= kT6R2)) with(std::integral_constant<int, kCoreNone>{});
+        else if (all(y32 < kTaylorY)) with(std::integral_constant<int, kCoreSmall>{});
         else if (all(lr.y >= 1.0)) with(std::integral_constant<int, kCore16>{});
         else if (all(lr.y >= 0.3)) with(std::integral_constant<int, kCore20>{});
         else if (all(lr.y >= 0.01)) with(std::integral_constant<int, kCore24>{});
@@ -483,10 +600,14 @@ hipError_t launch_point(const PointArgs& A, int moments, hipStream_t st) {
   if (items <= 0) return hipSuccess;
   const dim3 grid((unsigned)phys_workgroups((items + kWavesPerWG - 1) / kWavesPerWG)),
       block(kBlock);
-  if (moments == kMomFp32)
-    hipLaunchKernelGGL(xs_point_kernel<kMomFp32>, grid, block, 0, st, A);
-  else
-    hipLaunchKernelGGL(xs_point_kernel<kMomFp64>, grid, block, 0, st, A);
+  const bool fw = A.cut.kind != kCutFixed;
+  if (moments == kMomFp32) {
+    if (fw) hipLaunchKernelGGL((xs_point_kernel<kMomFp32, true>), grid, block, 0, st, A);
+    else hipLaunchKernelGGL((xs_point_kernel<kMomFp32, false>), grid, block, 0, st, A);
+  } else {
+    if (fw) hipLaunchKernelGGL((xs_point_kernel<kMomFp64, true>), grid, block, 0, st, A);
+    else hipLaunchKernelGGL((xs_point_kernel<kMomFp64, false>), grid, block, 0, st, A);
+  }
   return hipGetLastError();
 }
 

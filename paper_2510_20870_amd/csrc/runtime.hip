@@ -183,6 +183,14 @@ static void line_range(const LinesRes& L, const GridRes& G, const xs_opts& o, in
   line_range_nu(L, G.first, G.last, o.cut_cm1, lo, hi);
 }
 
+static CutDev cut_dev(const xs_opts& o) {
+  CutDev c;
+  c.kind = o.cutoff_kind == XS_CUT_FIXED ? kCutFixed : kCutMinFwhm;
+  c.cut = o.cut_cm1;
+  c.mult = o.fwhm_mult;
+  return c;
+}
+
 // Lines per wavenumber around the grid's middle, times the cut's full width.
 static int64_t window_lines(const LinesRes& L, const GridRes& G, const xs_opts& o) {
   const double mid = G.host[G.n / 2];
@@ -193,22 +201,20 @@ static int64_t window_lines(const LinesRes& L, const GridRes& G, const xs_opts& 
 }
 
 // Far field by moments, chosen where a point's window holds enough lines beyond its near
-// range: with a fixed cut (every line of a group then ends at the same distance), no
-// selection (which drops lines one by one) and the automatic tile_group.
+// range: without selection (which drops lines one by one) and with the automatic tile_group.
 static bool use_moments(const LinesRes& L, const GridRes& G, const xs_opts& o) {
-  if (o.tile_group != 0 || o.cutoff_kind != XS_CUT_FIXED || o.select_eps > 0.0 ||
-      L.n >= ((size_t)1 << 30))
-    return false;
+  if (o.tile_group != 0 || o.select_eps > 0.0 || L.n >= ((size_t)1 << 30)) return false;
   return window_lines(L, G, o) >= kMomentLines;
 }
 
-// Distance from a point within which its lines are summed one by one, at (P, T): theta
-// (gamma + beta b) with the list's largest width and the Doppler width at the grid's middle.
-static double near_distance(const LinesRes& L, const GridRes& G, const xs_pt& pt, bool f64) {
-  const double pf = pt.P_bar / L.sp.P_ref, tr = L.sp.T_ref / pt.T_K;
-  const double g = L.sp.gam_max * pf * std::max(pow(tr, L.sp.n_min), pow(tr, L.sp.n_max));
-  const double b = G.host[G.n / 2] / kCLight * sqrt(2.0 * kKBoltz * pt.T_K / (L.sp.mass_amu * kAmu));
-  return kFarTheta * (g + (f64 ? kBetaFp64 : kBetaFp32) * b);
+// The lines' bounds at (P, T) for planning (without the partition function, which may lie in
+// device memory).
+static PtBounds plan_bounds(const LinesRes& L, const xs_pt& pt) {
+  PtConst pc{};
+  pc.dopp = sqrt(2.0 * kKBoltz * pt.T_K / (L.sp.mass_amu * kAmu));
+  pc.pfac = pt.P_bar / L.sp.P_ref;
+  pc.tratio = L.sp.T_ref / pt.T_K;
+  return pt_bounds(L.sp, pc);
 }
 
 void Plan::set_tree() {
@@ -290,8 +296,15 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     double widest = 0.0;
     p.by_tile.resize(npts);
     for (size_t k = 0; k < npts; ++k) {
-      const double d = near_distance(L, G, pts[k], f64);
-      p.by_tile[k] = d > kWideTiles * (double)tile * step;
+      // distance within which lines are summed one by one; by tiles only with one cut for
+      // every line (the far kernel's rule)
+      const PtBounds pb = plan_bounds(L, pts[k]);
+      const double bm = pb.kb * G.host[m];
+      const double d = kFarTheta * (pb.gmax + (f64 ? kBetaFp64 : kBetaFp32) * bm);
+      const CutDev cd = cut_dev(o);
+      p.by_tile[k] = d > kWideTiles * (double)tile * step &&
+                     cut_at(cd, pb.gmin, pb.kb * std::max(0.0, G.first - o.cut_cm1), false) >=
+                         o.cut_cm1;
       p.any_tile = p.any_tile || p.by_tile[k];
       widest = std::max(widest, d);
     }
@@ -396,10 +409,8 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
                  bool with_params, bool with_reduce, unsigned long long* counts,
                  KernelTimer* tm) {
   const bool f64 = o.precision == XS_FP64;
-  CutDev cut;
-  cut.kind = o.cutoff_kind == XS_CUT_FIXED ? kCutFixed : kCutMinFwhm;
-  cut.cut = o.cut_cm1;
-  cut.mult = o.fwhm_mult;
+  const CutDev cut = cut_dev(o);
+  PtBounds* bounds = p.moments ? (PtBounds*)((char*)rec_dev + p.bounds_offset()) : nullptr;
   hipError_t e;
   if (with_params) {
     ParamArgs PA;
@@ -417,6 +428,7 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       PA.nodes = (double*)((char*)rec_dev + p.node_offset());
       PA.dims = p.dims;
       PA.moments = p.moments;
+      PA.bounds = bounds;
     }
     e = launch_params(PA, st);
     if (e != hipSuccess) return hip_fail(e, "parameter kernel launch");
@@ -470,11 +482,10 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       PointArgs A;
       memset(&A, 0, sizeof A);
       A.L = L.dev;
-      A.sp = L.sp;
-      A.cut = o.cut_cm1;
+      A.cut = cut;
+      A.bounds = bounds + k0;
       A.grid = G.d;
       A.n_grid = (int64_t)G.n;
-      A.pts = pts_dev;
       A.pt0 = pt0 + k0;
       A.n_pt = nk;
       A.split = split;
@@ -795,7 +806,7 @@ int xs_load_lines(xs_ctx* c, const xs_lines_desc* d, const xs_species_desc* sp, 
   // broadening partners: mixing ratios and tables over J
   const int nb = sp->n_broad;
   const size_t nj = nb > 0 ? sp->broad_nj : 0;
-  double bg_max = 0.0, bn_min = 0.0, bn_max = 0.0;
+  double bg_max = 0.0, bg_min = 0.0, bn_min = 0.0, bn_max = 0.0;
   if (nb < 0 || nb > 8) return fail(XS_EINVAL, "n_broad must be in [0, 8] (got %d)", nb);
   if (nb > 0) {
     if (nj < 1 || nj > 4096 || !sp->broad_vmr || !sp->broad_gamma || !sp->broad_n)
@@ -804,22 +815,24 @@ int xs_load_lines(xs_ctx* c, const xs_lines_desc* d, const xs_species_desc* sp, 
     for (int b = 0; b < nb; ++b) {
       if (!(sp->broad_vmr[b] >= 0.0) || !isfinite(sp->broad_vmr[b]))
         return fail(XS_EINVAL, "broad_vmr[%d] invalid", b);
-      double gb = 0.0;
+      double gb = 0.0, gs = sp->broad_gamma[b * nj];
       for (size_t j = 0; j < nj; ++j) {
         const double g = sp->broad_gamma[b * nj + j], nn = sp->broad_n[b * nj + j];
         if (!(g >= 0.0) || !isfinite(g) || !isfinite(nn))
           return fail(XS_EINVAL, "broadening table %d entry %zu invalid", b, j);
         gb = std::max(gb, g);
+        gs = std::min(gs, g);
         if (b == 0 && j == 0) bn_min = bn_max = nn;
         bn_min = std::min(bn_min, nn);
         bn_max = std::max(bn_max, nn);
       }
       bg_max += sp->broad_vmr[b] * gb;
+      bg_min += sp->broad_vmr[b] * gs;
     }
   }
   // validate records; find whether they are sorted
   bool sorted = true;
-  double gmax = 0.0, nmin = 0.0, nmax = 0.0;
+  double gmax = 0.0, gmin = n > 0 ? (double)d->gamma_ref[0] : 0.0, nmin = 0.0, nmax = 0.0;
   for (size_t i = 0; i < n; ++i) {
     const double nu = d->nu0[i];
     const float A = d->A_or_Sref[i], E = d->E_low[i], g = d->gamma_ref[i], nt = d->n_T[i];
@@ -832,6 +845,7 @@ int xs_load_lines(xs_ctx* c, const xs_lines_desc* d, const xs_species_desc* sp, 
       return fail(XS_EINVAL, "g_up[%zu] = 0", i);
     if (i && nu < d->nu0[i - 1]) sorted = false;
     gmax = std::max(gmax, (double)g);
+    gmin = std::min(gmin, (double)g);
     if (i == 0) nmin = nmax = nt;
     nmin = std::min(nmin, (double)nt);
     nmax = std::max(nmax, (double)nt);
@@ -926,6 +940,7 @@ int xs_load_lines(xs_ctx* c, const xs_lines_desc* d, const xs_species_desc* sp, 
   // bounds of gamma_L for the per-tile cutoff bound: the lines' own gamma_ref and n_T, or
   // with partners sum_b vmr_b max_j gamma_b and the tables' range of n
   L->sp.gam_max = nb > 0 ? bg_max : gmax;
+  L->sp.gam_min = nb > 0 ? bg_min : gmin;
   L->sp.n_min = nb > 0 ? bn_min : nmin;
   L->sp.n_max = nb > 0 ? bn_max : nmax;
   // host index: every kSampleStride-th centre of the sorted list

@@ -79,7 +79,8 @@ struct Plan {
   // line records [pt_batch][rec_n] (32 B), then with selection the thresholds of the
   // groups of kSelGroup tiles [pt_batch][n_groups()] (8 B), or with the far field by moments
   // the tree [pt_batch][n_nodes] and, when any point goes by tiles, the far sums
-  // [pt_batch][n_grid] (8 B) and the near ranges [pt_batch][n_tiles] (16 B)
+  // [pt_batch][n_grid] (8 B) and the near ranges [pt_batch][n_tiles] (16 B), then the lines'
+  // bounds [pt_batch]
   int64_t n_groups() const { return (n_tiles + kSelGroup - 1) / kSelGroup; }
   size_t tau_offset() const { return (size_t)rec_n * pt_batch * 32; }
   size_t node_offset() const { return tau_offset(); }
@@ -89,15 +90,17 @@ struct Plan {
   size_t near_offset() const {
     return far_offset() + (any_tile ? ((size_t)pt_batch * n_grid * 8 + 15) / 16 * 16 : 0);
   }
+  size_t bounds_offset() const {
+    return near_offset() + (any_tile ? (size_t)pt_batch * n_tiles * sizeof(NearRange) : 0);
+  }
   // bytes per P-T point beside the records
   size_t extra_bytes() const {
-    return moments ? (size_t)dims.n_nodes * node_bytes(moments) +
+    return moments ? (size_t)dims.n_nodes * node_bytes(moments) + sizeof(PtBounds) +
                          (any_tile ? (size_t)n_grid * 8 + (size_t)n_tiles * sizeof(NearRange) : 0)
            : select_eps > 0.0 ? (size_t)n_groups() * 8 : 0;
   }
   size_t rec_bytes() const {
-    if (moments)
-      return near_offset() + (any_tile ? (size_t)pt_batch * n_tiles * sizeof(NearRange) : 0);
+    if (moments) return bounds_offset() + (size_t)pt_batch * sizeof(PtBounds);
     return tau_offset() + (select_eps > 0.0 ? (size_t)pt_batch * n_groups() * 8 : 0);
   }
   size_t part_bytes(size_t n_grid) const {

@@ -47,6 +47,10 @@ CASES = {
     "coincident": ("coincident", 50_000, (970.0, 1035.0), (1000.0, 0.015, 260), 25.0),
     "short_cut": ("uniform", 90_000, (1000.0, 1004.0), (1001.0, 0.02, 100), 0.6),
     "wide_tiles": ("uniform", 60_000, (970.0, 1035.0), (980.0, 0.4, 130), 25.0),
+    # the FWHM cut: from a few Doppler widths over cuts that differ by line to the common cap
+    "fwhm": ("uniform", 60_000, (970.0, 1035.0), (1000.0, 0.01, 5 * 64 + 1), 25.0),
+    "fwhm_clusters": ("clusters", 50_000, (970.0, 1035.0), (997.0, 0.02, 390), 25.0),
+    "fwhm_past_ends": ("coincident", 40_000, (1000.0, 1020.0), (985.0, 0.25, 200), 25.0),
 }
 
 
@@ -60,10 +64,16 @@ def test_moments_vs_oracle(ctx, case, f64):
     h = ctx.load_lines(L, 16.0)
     g = ctx.set_grid(grid)
     pts = [(1e-4, 500.0), (0.3, 1500.0), (80.0, 700.0)]
-    ref = [O.sigma(L, grid, P, T, 16.0, cut_cm1=cut) for P, T in pts]
+    fwhm = case.startswith("fwhm")
+    if fwhm:
+        pts.append((3.0, 900.0))
+    rule = "min_fwhm" if fwhm else "fixed"
+    ref = [O.sigma(L, grid, P, T, 16.0, cut_kind=rule, cut_cm1=cut, fwhm_mult=100.0)
+           for P, T in pts]
+    kind = X.XS_CUT_MIN_FWHM if fwhm else X.XS_CUT_FIXED
     prec = X.XS_FP64 if f64 else X.XS_FP32_KAHAN
     for split in (0, 1, 3):
-        o = ctx.opts(X.XS_CUT_FIXED, cut, precision=prec, split=split)
+        o = ctx.opts(kind, cut, 100.0, precision=prec, split=split)
         sig = ctx.compute(h, g, pts, o)
         for k, r in enumerate(ref):
             st = O.compare(sig[k], r, rel_tol=2e-8 if f64 else 2e-6)
@@ -72,8 +82,29 @@ def test_moments_vs_oracle(ctx, case, f64):
             assert st["violations"] == 0, st
         assert np.array_equal(ctx.compute(h, g, pts, o), sig)   # bitwise repeatable
     # one point of the batch alone gives the same bits
-    o = ctx.opts(X.XS_CUT_FIXED, cut, precision=prec, split=1)
+    o = ctx.opts(kind, cut, 100.0, precision=prec, split=1)
     assert np.array_equal(ctx.compute(h, g, pts[1:2], o)[0], ctx.compute(h, g, pts, o)[1])
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
+
+
+def test_moments_fwhm_partners(ctx):
+    """Broadening partners: the bounds of the cut come from the partners' tables."""
+    from paper_2510_20870_amd import xsec as X
+    L = _lists("uniform", 60_000, 970.0, 1035.0, 93)
+    L["J_low"] = synth.j_low(L["E_low"])
+    B = synth.broadening_partners()
+    grid = 1000.0 + 0.015 * np.arange(200, dtype=np.float64)
+    pts = [(1e-3, 800.0), (0.5, 1500.0), (20.0, 600.0)]
+    h = ctx.load_lines(L, 16.0, broadening=B)
+    g = ctx.set_grid(grid)
+    sig = ctx.compute(h, g, pts, ctx.opts(X.XS_CUT_MIN_FWHM, 25.0, 100.0))
+    for k, (P, T) in enumerate(pts):
+        ref = O.sigma(L, grid, P, T, 16.0, cut_kind="min_fwhm", cut_cm1=25.0, fwhm_mult=100.0,
+                      broadening=B)
+        st = O.compare(sig[k], ref, rel_tol=2e-6)
+        print(f"[moments] partners P={P} max_rel {st['max_rel']:.2e}", flush=True)
+        assert st["violations"] == 0, st
     ctx.unload_lines(h)
     ctx.free_grid(g)
 
