@@ -111,6 +111,143 @@ hipError_t launch_tree_up(const ParamArgs& A, hipStream_t st) {
   return hipSuccess;
 }
 
+// Values of the lane whose index differs by the mask kX: inside a row of 16 by DPP (4 as 7
+// then 3).
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xf, 0xf, true);
+}
+template <int kX>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if constexpr (kX == 1) return dpp_u32<kRowX1>(v);
+  else if constexpr (kX == 2) return dpp_u32<kRowX2>(v);
+  else if constexpr (kX == 4) return dpp_u32<0x1b>(dpp_u32<kRowX7>(v));
+  else if constexpr (kX == 8) return dpp_u32<kRowX8>(v);
+  else return (uint32_t)__shfl_xor((int)v, kX);
+}
+// v of the lane d below inside the row of 16, 0 where there is none (row_shr:d)
+template <int d>
+__device__ __forceinline__ double row_below(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = dpp_u32<0x110 + d>((uint32_t)u), hi = dpp_u32<0x110 + d>((uint32_t)(u >> 32));
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+// v of one lane, wave-uniform
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+// One stage of the bitonic network over e = 16 lane + r: e against e ^ j, in runs of w.
+template <int w, int j>
+__device__ __forceinline__ void sort_stage(uint32_t (&v)[16], int lane) {
+  if constexpr (j >= 16) {
+    const bool big = ((lane & (j / 16)) == 0) == ((lane & (w / 16)) == 0);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const uint32_t o = lane_xor<j / 16>(v[r]);
+      v[r] = big ? max(v[r], o) : min(v[r], o);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if ((r & j) != 0) continue;
+      const bool falling = w < 16 ? (r & w) == 0 : (lane & (w / 16)) == 0;
+      const uint32_t hi = max(v[r], v[r + j]), lo = min(v[r], v[r + j]);
+      v[r] = falling ? hi : lo;
+      v[r + j] = falling ? lo : hi;
+    }
+  }
+  if constexpr (j > 1) sort_stage<w, j / 2>(v, lane);
+}
+
+// The order by cut of one block (far_tree.h), by one wavefront: lane i holds sorted places
+// 16 i to 16 i + 15 in registers (a bitonic network; strides below 16 stay in the lane), then
+// the moments of its 16 lines about the block's centre, and a scan over the lanes adds those
+// before it. What bounds it is reading the records twice, in order for the cuts and gathered
+// for the moments: 2.1e6 lines x 12 (P, T) points take 676 us (0.8 GB of records, 0.4 GB
+// written; exchanges by DPP instead of LDS gave 30 us of that). With it the point kernel takes
+// 3.1 ms instead of 6.2 on 25147 grid points: up to 1.7e5 lines lie between a point's
+// smallest and largest cut, and were tested and summed one by one.
+template <int NM>
+__global__ __launch_bounds__(kBlock) void xs_cut_order_kernel(ParamArgs A) {
+  constexpr int kPer = kCutBlock / kWave;
+  static_assert(kPer == kLeafLines && kCutBlock == kLeafLines << (kArityBits * kCutLevel),
+                "a lane is a group, a block is a node");
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int blk = blockIdx.x * kWavesPerWG + wv, k = blockIdx.y;
+  if (blk >= A.order.blocks) return;
+  // (the point kernel asks for no order where every line's cut is the cap)
+  if (A.cut.mult * voigt_fwhm(A.bounds[k].gmin, 0.0) >= A.cut.cut * (1.0 + 1e-9)) return;
+  const int64_t l0 = (int64_t)blk * kCutBlock;
+  const LineRec* recs = A.out + (int64_t)k * A.n + l0;
+  const double* nu = A.L.nu0 + A.lo + l0;
+  uint32_t v[kPer];
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) v[r] = cut_key(recs[r * kWave + lane].cut, A.cut.cut, r * kWave + lane);
+  sort_stage<2, 1>(v, lane);
+  sort_stage<4, 2>(v, lane);
+  sort_stage<8, 4>(v, lane);
+  sort_stage<16, 8>(v, lane);
+  sort_stage<32, 16>(v, lane);
+  sort_stage<64, 32>(v, lane);
+  sort_stage<128, 64>(v, lane);
+  sort_stage<256, 128>(v, lane);
+  sort_stage<512, 256>(v, lane);
+  sort_stage<1024, 512>(v, lane);
+  const int64_t at = (int64_t)k * A.order.blocks + blk;
+  uint4* keys = (uint4*)(A.order.keys + at * kCutBlock + lane * kPer);
+#pragma unroll
+  for (int r = 0; r < kPer; r += 4) keys[r / 4] = make_uint4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+  const NodeRef<NM, const double> f =
+      node_at<NM>(A.nodes + (int64_t)k * A.dims.n_nodes * node_fields<NM>(), A.dims, kCutLevel, blk);
+  const double c = f.c(), is = 1.0 / f.s();
+  double sum[NM];
+#pragma unroll
+  for (int m = 0; m < NM; ++m) sum[m] = 0.0;
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) {
+    const int i = (int)(v[r] & (kCutBlock - 1));
+    const LineRec lr = recs[i];
+    const double b = rcp64(lr.ib), bs = b * is;
+    double M[NM];
+    // (S/pi from the record's S / (b sqrt(pi)))
+    line_moments<NM>(lr.sc * b * kInvSqrtPi, (nu[i] - c) * is, lr.y * bs, 0.5 * bs * bs, M);
+#pragma unroll
+    for (int m = 0; m < NM; ++m) sum[m] += M[m];
+  }
+  double2* pre = (double2*)(A.order.pre + (at * kWave + lane) * NM);
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    double t = sum[m];
+    t += row_below<1>(t);
+    t += row_below<2>(t);
+    t += row_below<4>(t);
+    t += row_below<8>(t);
+    // the rows before this one
+    const double r0 = lane_value(t, 15), r1 = lane_value(t, 31), r2 = lane_value(t, 47);
+    t += lane < 16 ? 0.0 : lane < 32 ? r0 : lane < 48 ? r0 + r1 : r0 + r1 + r2;
+    sum[m] = t;
+  }
+#pragma unroll
+  for (int m = 0; m < NM; m += 2) pre[m / 2] = make_double2(sum[m], sum[m + 1]);
+}
+
+hipError_t launch_cut_order(const ParamArgs& A, hipStream_t st) {
+  if (A.order.blocks <= 0 || A.n_pt <= 0) return hipSuccess;
+  const dim3 grid((unsigned)((A.order.blocks + kWavesPerWG - 1) / kWavesPerWG), (unsigned)A.n_pt);
+  const dim3 block(kBlock);
+  if (A.moments == kMomFp32)
+    hipLaunchKernelGGL(xs_cut_order_kernel<kMomFp32>, grid, block, 0, st, A);
+  else
+    hipLaunchKernelGGL(xs_cut_order_kernel<kMomFp64>, grid, block, 0, st, A);
+  return hipGetLastError();
+}
+
 // Far kernel. One workgroup per (tile, P-T point): wavefronts 0 and 1 take the groups left
 // and right of the near range that are inside the cut of every point of the tile (the same
 // nodes for all lanes), wavefronts 2 and 3 the lines beyond, up to each point's own cut

@@ -86,6 +86,23 @@ __host__ __device__ __forceinline__ void line_moments(double w, double d, double
   }
 }
 
+// Order by cut (cuts of so many FWHM differ from line to line, in a block as much as over the
+// list). A point at distance d from a block of kCutBlock lines takes those whose cut is at
+// least d: with the block's lines in order of falling cut, its first so many. Their moments up
+// to every 16th are kept as running sums, so a block costs a point one series and the lines
+// around the boundary. A key holds the cut in units of cap / 4194303, rounded down, above
+// the line's index in the block; the two bounds of a key's cut are a unit wider than that.
+constexpr double kCutUnits = 4194303.0;
+__host__ __device__ __forceinline__ uint32_t cut_key(double cut, double cap, int i) {
+  return ((uint32_t)(cut / cap * kCutUnits) << 10) | (uint32_t)i;
+}
+__host__ __device__ __forceinline__ double cut_key_lower(uint32_t key, double unit) {
+  return ((double)(key >> 10) - 1.0) * unit;
+}
+__host__ __device__ __forceinline__ double cut_key_upper(uint32_t key, double unit) {
+  return ((double)(key >> 10) + 2.0) * unit;
+}
+
 #if defined(__HIPCC__)
 // Exchange with the lane whose index differs by the mask 8, 7, 2 or 1 inside a row of 16
 // lanes (row_ror:8, row_half_mirror, two quad permutations).

@@ -52,6 +52,17 @@ struct NearRange {
   int64_t n0, n1;
 };
 
+// The lines of every whole block of kCutBlock lines (a tree node of level kCutLevel) in order
+// of falling cut, 16 to a group (far_tree.h): per (P, T) point and block the sorted keys
+// (cut, line of the block) and per group the moments of the lines up to its end.
+constexpr int kCutLevel = 3;
+constexpr int kCutBlock = 1024;
+struct CutOrder {
+  int blocks;             // per (P, T) point; 0: cuts are one, or too few lines
+  uint32_t* keys;         // [n_pt][blocks][kCutBlock]
+  double* pre;            // [n_pt][blocks][kCutBlock / 16][moments]
+};
+
 struct ParamArgs {
   LinesDev L;
   SpeciesDev sp;
@@ -64,6 +75,7 @@ struct ParamArgs {
   TreeDims dims;
   int moments;            // kMomFp32 or kMomFp64
   PtBounds* bounds;       // [n_pt] (with a tree)
+  CutOrder order;         // blocks == 0: none
 };
 
 // The far kernel: per (tile, P-T point) the sum over the lines outside the tile's near
@@ -103,6 +115,7 @@ struct PointArgs {
   int rec_n;
   const double* nodes;
   TreeDims dims;
+  CutOrder order;         // of this launch's first point
   void* out;              // split == 1: sigma rows [n_pts][n_grid] (row pt0 + k); else
                           // partials [n_pt][split][n_grid] (double)
   int out_f32;
@@ -163,6 +176,8 @@ hipError_t launch_tile_p4(const TileArgs& A, bool f64, int W, hipStream_t st, di
 hipError_t launch_tile_p8(const TileArgs& A, bool f64, int W, hipStream_t st, dim3 grid);
 // the moments of every level above the leaves (launch_params writes those)
 hipError_t launch_tree_up(const ParamArgs& A, hipStream_t st);
+// the blocks' orders by cut (A.order)
+hipError_t launch_cut_order(const ParamArgs& A, hipStream_t st);
 hipError_t launch_far(const FarArgs& A, int moments, hipStream_t st);
 hipError_t launch_point(const PointArgs& A, int moments, hipStream_t st);
 // out: float rows when out_f32, else double rows; far (may be nullptr): one more partial

@@ -280,13 +280,13 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   // ---- tree nodes inside every point's cut, 64 at a time: one per lane
   bool whole = false;   // too many nodes that are not far: sum every line of the window
   int n_list = 0, round = 0;
-  // adds the lane's node (use: it has one) to every point's sum; lanes without a node take
-  // zero moments at a centre that is no grid point
-  auto add_node = [&](const NodeRef<NM, const double>& f, double c, double sc, bool use) {
+  // adds the lane's moments (use: it has some) about c, scale sc, to every point's sum; lanes
+  // without take zeros about a centre that is no grid point
+  auto add_moments = [&](double c, double sc, bool use, auto moment) {
     const double cc = use ? c : 2.0 * v1 + 1.0;
     double M[NM];
 #pragma unroll
-    for (int t = 0; t < NM; ++t) M[t] = use ? f.at(kNodeA + t) : 0.0;
+    for (int t = 0; t < NM; ++t) M[t] = use ? moment(t) : 0.0;
 #pragma unroll
     for (int p = 0; p < R; ++p) {
       const double rX = rcp64(val(p) - cc), t = sc * rX;
@@ -321,7 +321,8 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
     const double c = f.c(), sc = f.s();
     const bool bad = in && !(fmax(v0 - c, c - v1) >= kFarTheta * sc);
     to_ranges(bad, l, q);
-    if (round++ % A.split == s) add_node(f, c, sc, in && !bad);
+    if (round++ % A.split == s)
+      add_moments(c, sc, in && !bad, [&](int t) { return f.at(kNodeA + t); });
     // the nodes not taken yet move to the front
     const int rest = lane + kWave < n_list ? list[wv][kWave + lane] : 0;
     wave_sync();
@@ -469,37 +470,121 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
         });
       }
     };
-    for (int o = 0; o < n_edge; o += kWave) {
-      const int e = o + lane;
-      const bool in = e < n_edge;
-      const int leaf = in ? edge_leaf(e) : 0;
-      const NodeRef<NM, const double> f = node(0, leaf);
-      const double lo = f.lo(), hi = f.hi(), c = f.c(), sc = f.s();
-      const bool is_left = e < nl;
-      const double cmax = FW ? f.at(kNodeCutMax) : cap, cmin = FW ? f.at(kNodeCutMin) : cap;
-      const bool out = !in || (is_left ? v0 - hi : lo - v1) > cmax;
-      const bool far = fmax(v0 - c, c - v1) >= kFarTheta * sc;
-      // inside every line's cut at every point: by its moments
-      const bool all = !out && far && (is_left ? v1 - lo : hi - v0) <= cmin;
-      if (__ballot(all) != 0ull && round++ % A.split == s) add_node(f, c, sc, all);
-      const bool near = !out && !far;
-      if (__ballot(near) != 0ull) {
-        mask = true;
-        to_ranges(near, 0, leaf);
+    // The leaves one round of 64 after the other; first, where the lines' cuts differ, the
+    // whole blocks of kCutBlock lines that are far and ordered by cut, 64 at a time. (A block
+    // that is not far goes leaf by leaf.)
+    const int lx = max(la, lb), ry = max(ra, rb);
+    int x0 = lx, x1 = lx, y0 = ry, y1 = ry;   // left and right whole blocks, in leaves
+    constexpr int kPer = kCutBlock / kLeafLines;
+    if constexpr (FW) {
+      const int p0 = (la + kPer - 1) / kPer * kPer, p1 = min(lb / kPer, A.order.blocks) * kPer;
+      if (p0 < p1) x0 = p0, x1 = p1;
+      const int q0 = (ra + kPer - 1) / kPer * kPer, q1 = min(rb / kPer, A.order.blocks) * kPer;
+      if (q0 < q1) y0 = q0, y1 = q1;
+    }
+    const int nx = (x1 - x0) / kPer, n_blk = A.order.blocks ? nx + (y1 - y0) / kPer : 0;
+    const int n_leaf = n_blk ? n_edge - n_blk * kPer : n_edge;
+    auto edge_rest = [&](int i) {   // leaf i of those outside the blocks
+      if (!FW || n_blk == 0) return edge_leaf(i);
+      if (i < x0 - la) return la + i;
+      i -= x0 - la;
+      if (i < lx - x1) return x1 + i;
+      i -= lx - x1;
+      return i < y0 - ra ? ra + i : y1 + (i - (y0 - ra));
+    };
+    const uint32_t* keys = A.order.keys + (int64_t)k * A.order.blocks * kCutBlock;
+    const double* pre = A.order.pre + (int64_t)k * A.order.blocks * (kPer * NM);
+    const double unit = cap * (1.0 / kCutUnits);
+    int blk = 0;            // the lane's block of the last round of blocks
+    uint64_t todo = 0ull;   // lanes whose block is still to go leaf by leaf
+    for (int o_blk = 0, o_leaf = 0;;) {
+      // per lane: groups [ent, ent + cnt) of 16 lines whose lines are tested one by one
+      int ent = 0, cnt = 0;
+      bool sorted = false;
+      if (FW && todo == 0ull && o_blk < n_blk) {
+        const int e = o_blk + lane;
+        o_blk += kWave;
+        const bool in = e < n_blk, is_left = e < nx;
+        blk = !in ? 0 : is_left ? x0 / kPer + e : y0 / kPer + (e - nx);
+        const NodeRef<NM, const double> f = node(kCutLevel, blk);
+        const double lo = f.lo(), hi = f.hi(), c = f.c(), sc = f.s();
+        const bool far = fmax(v0 - c, c - v1) >= kFarTheta * sc;
+        todo = __ballot(in && !far);
+        const double dmin = is_left ? v0 - hi : lo - v1, dmax = is_left ? v1 - lo : hi - v0;
+        // groups inside every point's cut, and groups that reach some point
+        const uint32_t* kb_ = keys + (int64_t)blk * kCutBlock;
+        int n_in = 0, n_reach = 0;
+        if (in && far) {
+#pragma unroll
+          for (int st = kPer; st >= 1; st /= 2) {
+            if (n_in + st <= kPer &&
+                cut_key_lower(kb_[(n_in + st) * kLeafLines - 1], unit) >= dmax)
+              n_in += st;
+            if (n_reach + st <= kPer &&
+                cut_key_upper(kb_[(n_reach + st - 1) * kLeafLines], unit) >= dmin)
+              n_reach += st;
+          }
+          ent = blk * kPer + n_in;
+          cnt = max(n_reach - n_in, 0);
+        }
+        sorted = true;
+        if (__ballot(n_in > 0) != 0ull && round++ % A.split == s) {
+          const double* row = pre + ((int64_t)blk * kPer + max(n_in - 1, 0)) * NM;
+          add_moments(c, sc, n_in > 0, [&](int t) { return row[t]; });
+        }
+      } else {
+        bool in = true, is_left;
+        int leaf;
+        if (FW && todo != 0ull) {
+          const int id = __builtin_amdgcn_readlane(blk, __builtin_ctzll(todo));
+          todo &= todo - 1ull;
+          leaf = id * kPer + lane;
+          is_left = leaf < lx;
+        } else if (o_leaf < n_leaf) {
+          const int e = o_leaf + lane;
+          o_leaf += kWave;
+          in = e < n_leaf;
+          leaf = in ? edge_rest(e) : 0;
+          is_left = leaf < lx;
+        } else {
+          break;
+        }
+        const NodeRef<NM, const double> f = node(0, leaf);
+        const double lo = f.lo(), hi = f.hi(), c = f.c(), sc = f.s();
+        const double cmax = FW ? f.at(kNodeCutMax) : cap, cmin = FW ? f.at(kNodeCutMin) : cap;
+        const bool out = !in || (is_left ? v0 - hi : lo - v1) > cmax;
+        const bool far = fmax(v0 - c, c - v1) >= kFarTheta * sc;
+        // inside every line's cut at every point: by its moments
+        const bool all = !out && far && (is_left ? v1 - lo : hi - v0) <= cmin;
+        if (__ballot(all) != 0ull && round++ % A.split == s)
+          add_moments(c, sc, all, [&](int t) { return f.at(kNodeA + t); });
+        const bool near = !out && !far;
+        if (__ballot(near) != 0ull) {
+          mask = true;
+          to_ranges(near, 0, leaf);
+        }
+        ent = leaf;
+        cnt = !out && far && !all ? 1 : 0;
       }
-      // the others four at a time, one per row of 16 lanes
-      uint64_t m4 = __ballot(!out && far && !all);
+      // four groups at a time, one per row of 16 lanes
+      uint64_t m4 = __ballot(cnt > 0);
       while (m4 != 0ull) {
         int q = -1;
 #pragma unroll
         for (int t = 0; t < kWave / kLeafLines; ++t) {
           if (m4 != 0ull) {
-            const int id = __builtin_amdgcn_readlane(leaf, __builtin_ctzll(m4));
-            m4 &= m4 - 1ull;
+            const int src = __builtin_ctzll(m4);
+            const int id = __builtin_amdgcn_readlane(ent, src);
+            if (__builtin_amdgcn_readlane(cnt, src) == 1) m4 &= m4 - 1ull;
+            if (lane == src) {
+              ++ent;
+              --cnt;
+            }
             if (lane / kLeafLines == t) q = id;
           }
         }
-        const int i = q * kLeafLines + (lane & (kLeafLines - 1));
+        int i = q * kLeafLines + (lane & (kLeafLines - 1));
+        if (FW && sorted && q >= 0) i = (i & -kCutBlock) | (int)(keys[i] & (kCutBlock - 1));
         bool take = false;
         if (q >= 0 && i < rec_n) {
           const double ci = nu[i];

@@ -274,6 +274,8 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   line_range(L, G, o, &p.rec_lo, &hi);
   p.rec_n = hi - p.rec_lo;
   if (p.moments) p.set_tree();
+  if (p.moments && o.cutoff_kind != XS_CUT_FIXED && p.dims.levels > kCutLevel)
+    p.cut_blocks = (int)(p.rec_n / kCutBlock);
   // line windows of the units (from the sampled index, within the largest cut)
   const std::vector<double>& sm = L.sample;
   std::vector<int64_t>& cost = p.tile_cost;
@@ -411,6 +413,11 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
   const bool f64 = o.precision == XS_FP64;
   const CutDev cut = cut_dev(o);
   PtBounds* bounds = p.moments ? (PtBounds*)((char*)rec_dev + p.bounds_offset()) : nullptr;
+  CutOrder order{p.cut_blocks, nullptr, nullptr};
+  if (p.cut_blocks) {
+    order.pre = (double*)((char*)rec_dev + p.pre_offset());
+    order.keys = (uint32_t*)((char*)rec_dev + p.keys_offset());
+  }
   hipError_t e;
   if (with_params) {
     ParamArgs PA;
@@ -429,12 +436,15 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       PA.dims = p.dims;
       PA.moments = p.moments;
       PA.bounds = bounds;
+      PA.order = order;
     }
     e = launch_params(PA, st);
     if (e != hipSuccess) return hip_fail(e, "parameter kernel launch");
     if (p.moments) {
       e = launch_tree_up(PA, st);
       if (e != hipSuccess) return hip_fail(e, "moment kernel launch");
+      e = launch_cut_order(PA, st);
+      if (e != hipSuccess) return hip_fail(e, "cut order kernel launch");
     }
     if (p.select_eps > 0.0) {
       // main-contributor selection: the thresholds of every tile group of the grid
@@ -497,6 +507,9 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       A.rec_n = (int)p.rec_n;
       A.nodes = nodes;
       A.dims = p.dims;
+      if (p.cut_blocks)
+        A.order = {p.cut_blocks, order.keys + (size_t)k0 * p.cut_blocks * kCutBlock,
+                   order.pre + (size_t)k0 * (p.pre_bytes() / sizeof(double))};
       A.out = split > 1 ? (void*)part : out_dev;
       A.l1_eps = opts_eps(o);
       A.out_f32 = o.out_dtype == XS_F32;

@@ -74,13 +74,14 @@ struct Plan {
   int tile_split = 1;             // line splits of the points by tiles
   int max_split() const { return any_tile && tile_split > split ? tile_split : split; }
   TreeDims dims{};
+  int cut_blocks = 0;             // blocks ordered by cut (CutOrder)
   int64_t n_grid = 0;
   void set_tree();   // dims from rec_n
   // line records [pt_batch][rec_n] (32 B), then with selection the thresholds of the
   // groups of kSelGroup tiles [pt_batch][n_groups()] (8 B), or with the far field by moments
   // the tree [pt_batch][n_nodes] and, when any point goes by tiles, the far sums
   // [pt_batch][n_grid] (8 B) and the near ranges [pt_batch][n_tiles] (16 B), then the lines'
-  // bounds [pt_batch]
+  // bounds [pt_batch] and the orders by cut: moments, then keys
   int64_t n_groups() const { return (n_tiles + kSelGroup - 1) / kSelGroup; }
   size_t tau_offset() const { return (size_t)rec_n * pt_batch * 32; }
   size_t node_offset() const { return tau_offset(); }
@@ -93,14 +94,23 @@ struct Plan {
   size_t bounds_offset() const {
     return near_offset() + (any_tile ? (size_t)pt_batch * n_tiles * sizeof(NearRange) : 0);
   }
+  size_t pre_offset() const {   // (128 B: a row of moments lies in whole cache lines)
+    return (bounds_offset() + (size_t)pt_batch * sizeof(PtBounds) + 127) / 128 * 128;
+  }
+  size_t pre_bytes() const {    // per point
+    return (size_t)cut_blocks * (kCutBlock / 16) * moments * sizeof(double);
+  }
+  size_t keys_offset() const { return pre_offset() + (size_t)pt_batch * pre_bytes(); }
+  size_t keys_bytes() const { return (size_t)cut_blocks * kCutBlock * sizeof(uint32_t); }
   // bytes per P-T point beside the records
   size_t extra_bytes() const {
     return moments ? (size_t)dims.n_nodes * node_bytes(moments) + sizeof(PtBounds) +
+                         pre_bytes() + keys_bytes() +
                          (any_tile ? (size_t)n_grid * 8 + (size_t)n_tiles * sizeof(NearRange) : 0)
            : select_eps > 0.0 ? (size_t)n_groups() * 8 : 0;
   }
   size_t rec_bytes() const {
-    if (moments) return bounds_offset() + (size_t)pt_batch * sizeof(PtBounds);
+    if (moments) return keys_offset() + (size_t)pt_batch * keys_bytes();
     return tau_offset() + (select_eps > 0.0 ? (size_t)pt_batch * n_groups() * 8 : 0);
   }
   size_t part_bytes(size_t n_grid) const {

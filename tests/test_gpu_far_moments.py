@@ -50,6 +50,10 @@ CASES = {
     # the FWHM cut: from a few Doppler widths over cuts that differ by line to the common cap
     "fwhm": ("uniform", 60_000, (970.0, 1035.0), (1000.0, 0.01, 5 * 64 + 1), 25.0),
     "fwhm_clusters": ("clusters", 50_000, (970.0, 1035.0), (997.0, 0.02, 390), 25.0),
+    # dense lists, whole blocks of 1024 lines between the smallest and the largest cut; the
+    # last block of the second lacks a few lines
+    "fwhm_blocks": ("uniform", 120_000, (990.0, 1030.0), (1005.0, 0.003, 150), 25.0),
+    "fwhm_block_end": ("uniform", 64 * 1024 - 5, (1000.0, 1012.0), (1001.0, 0.05, 200), 25.0),
     "fwhm_past_ends": ("coincident", 40_000, (1000.0, 1020.0), (985.0, 0.25, 200), 25.0),
 }
 
