@@ -133,14 +133,6 @@ __device__ __forceinline__ double row_below(double v) {
   return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
 }
 
-// v of one lane, wave-uniform
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
-  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
-}
-
 // One stage of the bitonic network over e = 16 lane + r: e against e ^ j, in runs of w.
 template <int w, int j>
 __device__ __forceinline__ void sort_stage(uint32_t (&v)[16], int lane) {

@@ -181,6 +181,57 @@ __device__ __forceinline__ void leaf_moments(double* nodes, int64_t leaf, double
     nd.at(i) = i == kNodeLo ? lo : i == kNodeHi ? hi : i == kNodeS ? s : i == kNodeG ? gm
                : i == kNodeCutMin ? cmin : cmax;
 }
+
+// Moments of the wavefront's 64 lines (w = 0: none), for the FP64 path: lane i of every row
+// of 16 ends with moments i + 1 (a) and i + 17 (b, 0 from moment 29 on). By halves, so that
+// 16 values are held at a time.
+__device__ __forceinline__ void wave_moments(double w, double d, double g, double q, int lane,
+                                             double* a, double* b) {
+  const int i = lane & 15;
+  double u0 = 1.0, v0 = 0.0, u1 = d, v1 = g;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    double v[16];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      const int k = 16 * half + m + 1;   // moment k is w v1
+      v[m] = k <= kMomFp64 ? w * v1 : 0.0;
+      if (k < kMomFp64) {
+        const double mq = (double)k * q;
+        const double u2 = fma(d, u1, fma(-g, v1, mq * u0));
+        const double v2 = fma(d, v1, fma(g, u1, mq * v0));
+        u0 = u1;
+        v0 = v1;
+        u1 = u2;
+        v1 = v2;
+      }
+    }
+    row_halve<kRowX8, 8>(v, (i & 8) != 0);
+    row_halve<kRowX7, 4>(v, (i & 4) != 0);
+    row_halve<kRowX2, 2>(v, (i & 2) != 0);
+    row_halve<kRowX1, 1>(v, (i & 1) != 0);
+    double t = v[0];
+    t += __shfl_xor(t, 16);
+    t += __shfl_xor(t, 32);
+    *(half ? b : a) = t;
+  }
+}
+// v of one lane (wave-uniform index), as a wave-uniform value
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+// The largest v of the wavefront, wave-uniform.
+__device__ __forceinline__ double wave_fmax(double v) {
+  v = fmax(v, row_swap<kRowX8>(v));
+  v = fmax(v, row_swap<kRowX7>(v));
+  v = fmax(v, row_swap<kRowX2>(v));
+  v = fmax(v, row_swap<kRowX1>(v));
+  return fmax(fmax(lane_value(v, 0), lane_value(v, 16)),
+              fmax(lane_value(v, 32), lane_value(v, 48)));
+}
 // One line at one point, with the cut test: the sums of the ragged ends of the far ranges
 // (lines of a leaf that the cut of a point splits) and of the few leaves that are neither far
 // nor inside the near range. FP32 path (NM = 16): the doubly shifted Lorentzian in FP64 where

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kBlock) void xs_count_kernel(TileArgs A) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = threadIdx.x >> 6;
   ItemInfo it;
-  if (!decode_item<P>(A, lane, it)) return;
+  if (!decode_item<P, false>(A, lane, it)) return;
   double nu[P];
 #pragma unroll
   for (int p = 0; p < P; ++p) {
@@ -188,10 +188,13 @@ __global__ __launch_bounds__(kBlock) void xs_count_kernel(TileArgs A) {
 // One workgroup per (group, point), its waves taking interleaved 64-line slices of the
 // window: A.n_tiles counts groups here. L is the sum of the waves' partial sums in wave
 // order, and the histogram is shared (integer additions), so tau depends on the data only.
+// 16 waves, because a grid has few groups and a wave waits for its loads most of the time: 59
+// groups of 5.4e4 lines take 225 us with 4 waves each, 112 us with 16.
+constexpr int kSelBlock = 1024;
 template <int P>
-__global__ __launch_bounds__(kBlock) void xs_select_kernel(TileArgs A) {
+__global__ __launch_bounds__(kSelBlock) void xs_select_kernel(TileArgs A) {
   __shared__ unsigned long long hist[kWave];
-  __shared__ double part[kWavesPerWG];
+  __shared__ double part[kSelBlock / kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t item = blockIdx.x;
@@ -204,7 +207,8 @@ __global__ __launch_bounds__(kBlock) void xs_select_kernel(TileArgs A) {
   line_window(A, k, t_first, t_last, lane, &lo, &hi);
   const LineRec* rec = A.recs + (int64_t)k * A.rec_n - A.rec_lo;
   double acc = 0.0;
-  for (int64_t i = lo + (int64_t)wv * kWave + lane; i < hi; i += kBlock)
+#pragma unroll 4
+  for (int64_t i = lo + (int64_t)wv * kWave + lane; i < hi; i += kSelBlock)
     acc += contrib_lower(A.L.nu0[i], rec[i], t_first, t_last);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
@@ -213,7 +217,7 @@ __global__ __launch_bounds__(kBlock) void xs_select_kernel(TileArgs A) {
   __syncthreads();
   double L = part[0];
 #pragma unroll
-  for (int w = 1; w < kWavesPerWG; ++w) L += part[w];
+  for (int w = 1; w < kSelBlock / kWave; ++w) L += part[w];
   double tau = 0.0;
   const double budget = A.select_eps * L;
   // (a budget so small that its fixed-point unit would overflow drops nothing; the test
@@ -224,7 +228,8 @@ __global__ __launch_bounds__(kBlock) void xs_select_kernel(TileArgs A) {
     const int elo = eL - 62;
     const double top = ldexp(1.0, eL), low = ldexp(1.0, elo);
     const double unit = ldexp(1.0, 40) / budget;   // histogram units per unit of sigma
-    for (int64_t i = lo + (int64_t)wv * kWave + lane; i < hi; i += kBlock) {
+#pragma unroll 4
+    for (int64_t i = lo + (int64_t)wv * kWave + lane; i < hi; i += kSelBlock) {
       const double c = contrib_upper(A.L.nu0[i], rec[i], t_first, t_last);
       if (c < top) {
         const int bin = c < low ? 0 : ilogb(c) - elo + 1;
@@ -365,7 +370,7 @@ hipError_t launch_count(const TileArgs& A, int P, hipStream_t st, int64_t phys_w
 hipError_t launch_select(const TileArgs& A, int P, hipStream_t st) {
   const int64_t items = A.n_tiles * A.n_pt;
   if (items <= 0) return hipSuccess;
-  const dim3 grid((unsigned)items), block(kBlock);
+  const dim3 grid((unsigned)items), block(kSelBlock);
   switch (P) {
     case 1: hipLaunchKernelGGL((xs_select_kernel<1>), grid, block, 0, st, A); break;
     case 2: hipLaunchKernelGGL((xs_select_kernel<2>), grid, block, 0, st, A); break;

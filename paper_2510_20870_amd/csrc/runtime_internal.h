@@ -72,6 +72,7 @@ struct Plan {
                                   // (else the point kernel)
   bool any_tile = false;
   int tile_split = 1;             // line splits of the points by tiles
+  bool chunks = false;            // FP64 tile kernel: chunks of lines by their moments
   int max_split() const { return any_tile && tile_split > split ? tile_split : split; }
   TreeDims dims{};
   int cut_blocks = 0;             // blocks ordered by cut (CutOrder)

@@ -9,6 +9,7 @@
 
 #include <type_traits>
 
+#include "far_tree.h"
 #include "kernel_args.h"
 #include "physics.h"
 #include "voigt.h"
@@ -173,6 +174,16 @@ struct ItemInfo {
   int step;          // distance of the item's 64-line chunks (kWave: all of the range)
 };
 
+// FP64 path: a part's lines. Those near the tile, which cost 10 to 100 times the others
+// (chunk_rows), fall to all parts, chunk by chunk in turn; the others are cut into runs, so
+// that a chunk's lines lie side by side. (With the whole window cut into runs the two or three
+// parts beside the tile took 1.9 ms on a 30001-point grid of 1050 lines/cm^-1, with the near
+// lines dealt out it is 0.69 ms.)
+struct Parts {
+  int64_t l0, l1, r0, r1;   // runs left and right of the near range
+  int64_t n0, n1;           // near range; this part's chunks from n0 in steps of it.step
+};
+
 // Lines [lo, hi) whose cut can reach the grid range [nu_first, nu_last] at (P, T) point k
 // of the batch: two 64-ary wave searches with the range's widest possible cut.
 __device__ __forceinline__ void line_window(const TileArgs& A, int k, double nu_first,
@@ -269,7 +280,7 @@ __device__ __forceinline__ FarLine far_line(const FarTile& ft, double nu0, const
   return FarLine{far, ds, far ? x : 1.0f, far ? h : 0.0f};
 }
 
-template <int P>
+template <int P, bool kParts>
 __device__ __forceinline__ bool decode_item(const TileArgs& A, int lane, ItemInfo& it) {
   const int64_t phys = blockIdx.x;
   const int64_t wg = xcd_logical_wg(phys);
@@ -292,10 +303,11 @@ __device__ __forceinline__ bool decode_item(const TileArgs& A, int lane, ItemInf
     const NearRange nr = A.near[(int64_t)it.k * A.near_stride + tile];
     lo = A.rec_lo + nr.n0;
     hi = A.rec_lo + nr.n1;
-  } else {
+  } else if (!kParts) {
     line_window(A, it.k, A.grid[it.j0], it.nu_last, lane, &lo, &hi);
   }
   it.step = kWave;
+  if (kParts) return true;   // the ranges follow (decode_parts)
   if (A.near) {
     // the parts of a near range take its chunks in turn: the lines beside the tile, which
     // cost several times the others, fall to all of them
@@ -308,6 +320,31 @@ __device__ __forceinline__ bool decode_item(const TileArgs& A, int lane, ItemInf
   it.b = lo + cnt * it.s / A.split;
   it.e = lo + cnt * (it.s + 1) / A.split;
   return true;
+}
+
+
+// The near range: lines of which no chunk, however narrow, is far from the whole tile.
+template <int P>
+__device__ __forceinline__ Parts decode_parts(const TileArgs& A, int lane, ItemInfo& it) {
+  const double g0 = A.grid[it.j0];
+  line_window(A, it.k, g0, it.nu_last, lane, &it.b, &it.e);
+  it.e = max(it.e, it.b);
+  const int64_t lo = it.b, hi = it.e;
+  const int pt = A.pt0 + it.k;
+  const PtBounds pb = pt_bounds(A.sp, make_pt(A.sp, A.pts[2 * pt], A.pts[2 * pt + 1]));
+  const double d = kFarTheta * (pb.gmax + kBetaFp64 * pb.kb * it.nu_last);
+  const double* nu = A.L.nu0 + lo;
+  Parts q;
+  q.n0 = lo + wave_search<false>(nu, hi - lo, g0 - d, lane);
+  q.n1 = max(lo + wave_search<true>(nu, hi - lo, it.nu_last + d, lane), q.n0);
+  const int64_t nl = q.n0 - lo, nf = nl + (hi - q.n1);
+  const int64_t f0 = nf * it.s / A.split, f1 = nf * (it.s + 1) / A.split;
+  q.l0 = lo + min(f0, nl);
+  q.l1 = lo + min(f1, nl);
+  q.r0 = q.n1 + max(f0 - nl, (int64_t)0);
+  q.r1 = q.n1 + max(f1 - nl, (int64_t)0);
+  q.n0 += (int64_t)kWave * it.s;
+  return q;
 }
 
 // Grouped far field (tile_group = kGroup): the kGroup wavefronts of a workgroup take
@@ -637,13 +674,69 @@ __device__ __forceinline__ float series_row(int var, const Rec<false, P>& q, flo
 // partial of at most kChunk positive terms carries a relative error below kChunk u32.
 constexpr int kChunk = 16;
 
+// FP64 path: a chunk's lines as one group about its middle, for the rows of the tile that are
+// far from it and inside every line's cut at both ends: their moments cost some 400
+// instructions for 64 lines and each row's series 40, where the lines themselves cost 40 per
+// line and row (30001 points, 1050 lines/cm^-1, selection of 1e-4: 2.66 ms line by line, 0.69
+// with this and the parts above). in: the lane holds a line that reaches some point. Adds to
+// s; returns the bits of cls of the rows taken (the same for all lanes; 0: none).
+constexpr int kChunkMinLines = 16;   // fewer go line by line
+template <int P>
+__device__ __forceinline__ int chunk_rows(const TileArgs& A, const Rows<P>& rows,
+                                          const Rec<true, P>& r, bool in, int lane,
+                                          const double* rowv, double (&s)[P]) {
+  const uint64_t m = __ballot(in);
+  if (__popcll(m) < kChunkMinLines) return 0;
+  const int l0 = __builtin_ctzll(m), l1 = 63 - __builtin_clzll(m);
+  const double lo = lane_value(r.nu0, l0), hi = lane_value(r.nu0, l1);
+  const double c = 0.5 * (lo + hi), h = 0.5 * (hi - lo);
+  const double b = in ? rcp64(r.ib) : 0.0, g = in ? r.y * b : 0.0;
+  const double gm = wave_fmax(g);
+  const double sc = sqrt(fma(h, h, gm * gm)) + kBetaFp64 * lane_value(b, l1);
+  const double cut = A.cut.kind == kCutFixed ? A.cut.cut : -wave_fmax(in ? -r.cut : -A.cut.cut);
+  int taken = 0;
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const double ra = rows.ra[p], rb = rows.rb[p];
+    const bool far = ra - c >= kFarTheta * sc || c - rb >= kFarTheta * sc;
+    const bool all = fmax(fabs(ra - lo), fabs(ra - hi)) <= cut &&
+                     fmax(fabs(rb - lo), fabs(rb - hi)) <= cut;
+    if (rows.valid[p] && far && all) taken |= 3 << (2 * p);
+  }
+  taken = __builtin_amdgcn_readfirstlane(taken);
+  if (taken == 0) return 0;
+  const double is = rcp64(sc), bs = b * is;
+  double a16, b16;
+  wave_moments(in ? r.sc * b * kInvSqrtPi : 0.0, in ? (r.nu0 - c) * is : 0.0, g * is,
+               0.5 * bs * bs, lane, &a16, &b16);
+  double t[P], u[P], k[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    u[p] = rcp64(rowv[kWave * p + lane] - c);
+    t[p] = sc * u[p];
+    k[p] = 0.0;
+  }
+#pragma unroll
+  for (int i = kMomFp64 - 1; i >= 0; --i) {
+    const double M = lane_value(i < 16 ? a16 : b16, i & 15);
+#pragma unroll
+    for (int p = 0; p < P; ++p) k[p] = fma(k[p], t[p], M);
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if ((taken >> (2 * p)) & 1) s[p] = fma(k[p] * t[p], u[p], s[p]);
+  return taken;
+}
+
 // W > 0 asks the compiler for at least W waves per SIMD (capping VGPRs at 512/W).
 // SEL: main-contributor selection (a variant of its own, so that the kernel without it
 // keeps its register allocation).
-// GRP: the grouped far field (tile_group = kGroup; FP32 path without selection only).
-template <int P, bool F64, int W, bool SEL, bool GRP = false>
+// EXT: FP32 path: the grouped far field (tile_group = kGroup; without selection only); FP64
+// path: windows of many chunks per part, chunk by chunk (decode_parts, chunk_rows).
+template <int P, bool F64, int W, bool SEL, bool EXT = false>
 __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileArgs A) {
-  static_assert(!GRP || (!F64 && !SEL && P <= 2), "grouped far field: FP32, P <= 2");
+  constexpr bool GRP = EXT && !F64, kChunks = EXT && F64;
+  static_assert(!GRP || (!SEL && P <= 2), "grouped far field: no selection, P <= 2");
   __shared__ Rec<F64, P> recs[kWavesPerWG][kWave];
   __shared__ double rowvals[kWavesPerWG][kWave * P];
   __shared__ int incl[kWavesPerWG][kWave];           // packed core points, inclusive prefix
@@ -664,7 +757,7 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
   if constexpr (GRP) {
     if (!decode_group<P>(A, lane, wvu, it, gg)) return;   // the whole workgroup
   } else {
-    if (!decode_item<P>(A, lane, it)) return;
+    if (!decode_item<P, kChunks>(A, lane, it)) return;
   }
   // a spare wave of the last group has no tile (its reads below use a valid index)
   const bool tile_ok = it.j0 < A.n_grid;
@@ -1030,8 +1123,9 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
   // overflow; compacted through incl, which is free between passes), so that only kept
   // lines are staged, 64 at a time. Without selection the chunks are consecutive lines.
   [[maybe_unused]] int q0 = 0, q1 = 0, nq = 0;
+  int step = it.step;
   auto walk = [&](int64_t first) {
-  for (int64_t base = first; SEL || base < e_cur; base += SEL ? 0 : it.step) {
+  for (int64_t base = first; SEL || base < e_cur; base += SEL ? 0 : step) {
     if constexpr (!F64 && !SEL) {
       far_run(base);
       if (base >= e_cur) break;
@@ -1057,7 +1151,7 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
         if (lane < nq && lane + kWave - nq < cnt) q1 = q;
         wave_sync();
         nq += cnt;
-        base += kWave;
+        base += step;
       }
       if (nq == 0) break;
       i = lane < nq ? it.b + q0 : e_cur;
@@ -1090,6 +1184,13 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
       r.cls = 0;
     }
     set_scale(r, sc64);
+    // FP64 path: rows that are far from the chunk (far_tree.h) and inside all of its lines'
+    // cuts take its lines by their moments
+    if constexpr (kChunks) {
+      const int taken = chunk_rows(A, rows, r, mode != kSkip, lane, rowvals[wv], s);
+      r.cls &= ~taken;
+      if (r.cls == 0) mode = kSkip;
+    }
     // FP32 path: lines of the unmasked series modes far enough from the tile (far_ok at
     // the tile's centre, the doubly shifted Lorentzian valid at its nearest point) are
     // summed as one polynomial when the chunk holds enough of them; they then leave the
@@ -1218,6 +1319,15 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
       e_cur = r1[q];
       if (r0[q] < e_cur) walk(r0[q]);
     }
+  } else if constexpr (kChunks) {
+    const Parts q = decode_parts<P>(A, lane, it);
+    const int64_t at[3] = {q.l0, q.r0, q.n0}, to[3] = {q.l1, q.r1, q.n1};
+#pragma unroll 1
+    for (int t = 0; t < 3; ++t) {
+      e_cur = to[t];
+      step = t == 2 ? kWave * A.split : kWave;
+      if (at[t] < e_cur) walk(at[t]);
+    }
   } else {
     walk(it.b);
   }
@@ -1334,24 +1444,24 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
   }
 }
 
-template <int P, bool F64, bool SEL, bool GRP = false>
+template <int P, bool F64, bool SEL, bool EXT = false>
 static hipError_t launch_tile_ws(const TileArgs& A, int W, hipStream_t st, dim3 grid) {
   const dim3 block(kBlock);
   switch (W) {
     case 0:
-      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 0, SEL, GRP>), grid, block, 0, st, A);
+      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 0, SEL, EXT>), grid, block, 0, st, A);
       break;
     case 3:
-      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 3, SEL, GRP>), grid, block, 0, st, A);
+      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 3, SEL, EXT>), grid, block, 0, st, A);
       break;
     case 4:
-      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 4, SEL, GRP>), grid, block, 0, st, A);
+      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 4, SEL, EXT>), grid, block, 0, st, A);
       break;
     case 5:
-      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 5, SEL, GRP>), grid, block, 0, st, A);
+      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 5, SEL, EXT>), grid, block, 0, st, A);
       break;
     case 6:
-      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 6, SEL, GRP>), grid, block, 0, st, A);
+      hipLaunchKernelGGL((xs_tile_kernel<P, F64, 6, SEL, EXT>), grid, block, 0, st, A);
       break;
     default: return hipErrorInvalidValue;
   }
@@ -1368,6 +1478,11 @@ static hipError_t launch_tile_w(const TileArgs& A, int W, hipStream_t st, dim3 g
       if (!A.tau) return launch_tile_ws<P, false, false, true>(A, W, st, grid);
     }
     return hipErrorInvalidValue;
+  }
+  if constexpr (F64) {
+    if (A.chunks)
+      return A.tau ? launch_tile_ws<P, true, true, true>(A, W, st, grid)
+                   : launch_tile_ws<P, true, false, true>(A, W, st, grid);
   }
   return A.tau ? launch_tile_ws<P, F64, true>(A, W, st, grid)
                : launch_tile_ws<P, F64, false>(A, W, st, grid);
