@@ -101,8 +101,8 @@ __device__ __forceinline__ float wave_total(float v) {
 // least this many of its lines qualify (fewer cost less on the per-line walk).
 constexpr int kFarMinLines = 16;
 // Consecutive chunks of far lines only add their coefficients per lane for at most this
-// many chunks before the sum over the wavefront (plain FP32 sums of terms of one sign:
-// the lines of such a run all lie on one side of the tile).
+// many chunks before the sum over the wavefront (plain FP32 sums; the constant terms, which
+// bound the others, all have one sign).
 constexpr int kFarRun = 8;
 
 // Workgroups are dispatched round-robin over the 8 XCDs. Logical workgroups are grouped in
@@ -254,9 +254,9 @@ __device__ __forceinline__ FarTile far_tile(const TileArgs& A, int64_t j0, doubl
   return t;
 }
 // Whether a line (centre nu0, record lr) is a far line of the tile: the tests of stage_line
-// and of the far split of the tile kernel's chunk loop, on the tile's first or last point:
-// the whole tile inside the cut, the doubly shifted Lorentzian valid at the nearest point,
-// far_ok at the centre; with x at the centre and H (Doppler units), and whether the line
+// on the tile's first or last point: the whole tile inside the cut, the doubly shifted
+// Lorentzian valid at the nearest point, far_line_ok at the centre (a line broad enough may lie
+// inside the tile); with x at the centre and H (Doppler units), and whether the line
 // needs the doubly shifted expansion (ds: the shifted Lorentzian fails at the nearest
 // point).
 struct FarLine {
@@ -266,16 +266,16 @@ struct FarLine {
 // (every test is evaluated and combined with &, so that the code has no branches)
 __device__ __forceinline__ FarLine far_line(const FarTile& ft, double nu0, const LineRec& lr) {
   const double da = ft.ra0 - nu0, db = ft.rbl - nu0;
-  const bool left = da > 0.0;
-  const bool in_cut = left ? db <= lr.cut : ((db < 0.0) & (da >= -lr.cut));
+  const bool left = da > 0.0, inside = (da <= 0.0) & (db >= 0.0);
+  const bool in_cut = (db <= lr.cut) & (da >= -lr.cut);
   const float y = (float)lr.y;
   const float y2 = y * y;
   const float ib32 = (float)lr.ib;
   const float xn = (float)((left ? da : db) * lr.ib);
-  const float r2n = fmaf(xn, xn, y2);
+  const float r2n = inside ? y2 : fmaf(xn, xn, y2);
   const float h = ft.h * ib32;
   const float x = fmaf(ib32, left ? ft.ca : ft.cb, xn);
-  const bool far = ft.ok & in_cut & dshift_ok(r2n, ft.eps) & far_ok(x, h, ft.kappa);
+  const bool far = ft.ok & in_cut & dshift_ok(r2n, ft.eps) & far_line_ok(x, h, y2, ft.kappa);
   const bool ds = far & !shifted_lorentz_ok(y2, r2n, ft.eps);
   return FarLine{far, ds, far ? x : 1.0f, far ? h : 0.0f};
 }
@@ -1178,11 +1178,23 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
         sc64 = 0.0;
       }
     }
-    if (i < e_cur) {
-      r = stage_line<F64, P>(A, recs_k, rows, rowvals[wv], i, &sc64, &mode, &npairs, false);
-    } else {
-      r.cls = 0;
+    // FP32 path: far lines (far_line) are summed as one polynomial over the tile when the
+    // chunk holds enough of them; the others are staged
+    [[maybe_unused]] float fx = 1.0f, fhl = 0.0f;
+    [[maybe_unused]] bool far = false, far_chunk = false, far_ds = false;
+    if constexpr (!F64) {
+      float fy = 0.0f;
+      bool ds = false;
+      if (i < e_cur) far = far_line_j(i, fx, fhl, fy, sc64, ds);
+      far_chunk = __popcll(__ballot(far)) >= kFarMinLines;
+      far = far && far_chunk;
+      far_ds = __ballot(far && ds) != 0ull;
+      r.y = fy;
+      r.y2 = fy * fy;
     }
+    r.cls = 0;
+    if (i < e_cur && !far)
+      r = stage_line<F64, P>(A, recs_k, rows, rowvals[wv], i, &sc64, &mode, &npairs, false);
     set_scale(r, sc64);
     // FP64 path: rows that are far from the chunk (far_tree.h) and inside all of its lines'
     // cuts take its lines by their moments
@@ -1190,35 +1202,6 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
       const int taken = chunk_rows(A, rows, r, mode != kSkip, lane, rowvals[wv], s);
       r.cls &= ~taken;
       if (r.cls == 0) mode = kSkip;
-    }
-    // FP32 path: lines of the unmasked series modes far enough from the tile (far_ok at
-    // the tile's centre, the doubly shifted Lorentzian valid at its nearest point) are
-    // summed as one polynomial when the chunk holds enough of them; they then leave the
-    // per-line walk
-    [[maybe_unused]] float fc1 = 0.0f, fx = 1.0f, fhl = 0.0f, fy2 = 0.0f;
-    [[maybe_unused]] bool far_chunk = false, far_ds = false;
-    if constexpr (!F64) {
-      bool far = false, ds = false;
-      const int ms = mode - kSeries;   // series modes: side * 2 kNVar + masked * kNVar + var
-      if (ms >= 0 && ms % (2 * kNVar) < kNVar) {
-        const bool left = ms < 2 * kNVar;
-        const float hl = ft.h * r.ib32;
-        const float xn = left ? r.xr[0] : r.xr[P - 1];
-        const float x = fmaf(r.ib32, left ? ft.ca : ft.cb, xn);
-        const float y2 = r.y * r.y;
-        const float r2n = fmaf(xn, xn, y2);
-        if (dshift_ok(r2n, A.l1_eps) && far_ok(x, hl, A.far_kappa)) {
-          far = true;
-          ds = !shifted_lorentz_ok(y2, r2n, A.l1_eps);
-          fc1 = r.c1;
-          fx = x;
-          fhl = hl;
-          fy2 = y2;
-        }
-      }
-      far_chunk = __popcll(__ballot(far)) >= kFarMinLines;
-      far_ds = __ballot(ds) != 0ull;
-      if (far_chunk && far) mode = kSkip;
     }
     // Group the chunk's lines by mode (stable inside each mode) so that the walk below
     // runs every mode's lines in a loop of its own with no per-line dispatch; lines with
@@ -1253,7 +1236,7 @@ __global__ __launch_bounds__(kBlock, (W > 0 ? W : 1)) void xs_tile_kernel(TileAr
     }
     wave_sync();
     if constexpr (!F64) {
-      if (far_chunk) far_sum(fc1, fx, fhl, fy2, far_ds);
+      if (far_chunk) far_sum(far ? r.c1 : 0.0f, fx, fhl, far ? r.y2 : 0.0f, far_ds);
     }
     if constexpr (F64) {
       for (int kk = gstart[kRows]; kk < gstart[kRows + 1]; ++kk) {

@@ -192,7 +192,11 @@ XS_HD float asym_scaled_v(int v, float y2, float r2) {
 // rho = H / (|X| - sqrt(max(-y2s, 0))), which bounds |b_k| <= 1.05 (k + 1) rho^k b_0, and
 // the sum truncated after degree kFarDeg is within
 // (1 + rho)^2 (kFarDeg + 2) rho^(kFarDeg + 1) / (1 - rho)^2 (x 1.05) of f on the range.
-// A line qualifies where |X| >= kappa H + 1.25 (rho <= 1 / kappa, as y2s >= -3/2), kappa =
+// A line with y^2 <= 3/2 qualifies where |X| >= kappa H + 1.25 (rho <= 1 / kappa, as y2s >=
+// -3/2). A broad line's roots are off the real axis, at |H t|^2 = X^2 + y2s, so there rho = H /
+// sqrt(X^2 + y2s) (with |b_k| <= (k + 1) rho^k b_0 and the same bound), and it qualifies where
+// (|X| - 1.25)^2 + y2s >= (kappa H)^2, be it beside the range or inside it (far_line_ok).
+// kappa =
 // far_kappa(eps) keeping the bound within 0.65 eps of the error budget eps: 4.09 at the
 // default 2e-7, 3.16 at 1e-5 (degree 13). The coefficients of many lines add up, so a sum
 // of such lines costs one polynomial per point instead of one evaluation per line and
@@ -203,6 +207,12 @@ constexpr float kFarMargin = 1.25f;   // >= sqrt(3/2)
 // Whether a line at tile-centre x and half-width h (both Doppler units) may be expanded.
 XS_HD bool far_ok(float x, float h, float kappa) {
   return fabsf(x) >= fmaf(kappa, h, kFarMargin);
+}
+
+// The same for a line of any width (y2 = y^2).
+XS_HD bool far_line_ok(float x, float h, float y2, float kappa) {
+  const float ax = fmaxf(fabsf(x) - kFarMargin, 0.0f), kh = kappa * h;
+  return fmaf(ax, ax, fmaxf(y2 - 1.5f, 0.0f)) >= kh * kh;
 }
 
 // The truncation bound above at rho, with the factor 1.05 raised to 1.15: at a looser
@@ -261,7 +271,8 @@ XS_HD void far_coeffs(float c1, float x, float h, float y2s, float (&b)[kFarDeg 
 // for y^2 < 9/32, else complex with |R| = sqrt(2) y; the four poles in t solve
 // (X + H t)^2 = R - y^2, and every such X + H t has a real part of magnitude at most
 // sqrt(3/2) (below 0.71 in the complex case), so |X| >= kappa H + 1.25 keeps them at
-// |t| >= kappa as for the shifted Lorentzian, and the same truncation bound holds. FP32
+// |t| >= kappa as for the shifted Lorentzian, and the same truncation bound holds; in the
+// complex case their imaginary part squared is at least y^2 - 3/8, which far_line_ok uses. FP32
 // rounding of the four-term recurrence (13 steps, terms up to 2.7 times the value at the
 // default kappa) keeps the polynomial within 6.6e-7 of the closed form over tile
 // half-widths of 0.1-1e4 Doppler widths and y up to 3e4.
