@@ -184,19 +184,23 @@ typedef struct { double P_bar, T_K; } xs_pt;
  * tiles, and the lines far from the whole four-tile span, with that span inside their
  * cut, are expanded once about the span's centre, the expansion split among the four
  * wavefronts and added in a fixed order (FP32 path, fixed cut, no selection, 1 or 2
- * points per lane; XS_EINVAL otherwise). 0: automatic. With a fixed cut, no selection and
- * enough lines inside the cut, the lines far from a grid point enter by moments of line
- * groups (FP64, within 5e-8 of each line's contribution on the FP32 path and 1e-13 on the
- * FP64 path) and only those near it one by one (pts_per_lane and waves_per_simd then shape
- * only the (P, T) points whose lines are so broad that tiles take them); where the memory for the moments (about 13 bytes per line and (P, T) point, FP64 path
- * 21) is missing, and everywhere else, 4 where it applies and the cut spans at least 3 kappa half-widths of a four-tile span at the grid's
- * middle, kappa the far threshold below, else 1.
+ * points per lane; XS_EINVAL otherwise). 0: automatic. Without selection, the lines far
+ * from a grid point enter by moments of line groups (FP64, within 5e-8 of each line's
+ * contribution on the FP32 path and 1e-13 on the FP64 path) and only those near it one by
+ * one: for every cut from 16384 lines within the cut, for a fixed cut also with fewer, from a
+ * list of 512 lines on and unless lines are broad. pts_per_lane and waves_per_simd then shape
+ * only the (P, T) points whose lines are so broad that tiles take them. The moments take about
+ * 13 bytes per line and (P, T) point (FP64 path 21; a FWHM cut 12 or 18 more); where that
+ * memory is missing, and everywhere else, 4 where it applies and the cut spans at least 3
+ * kappa half-widths of a four-tile span at the grid's middle, kappa the far threshold below,
+ * else 1.
  * tol: the error budget of the FP32 path's cheaper far forms, relative to each line's
  * contribution at each point (section "Functionality of pyROX" leaves the accuracy of the
  * profile to the implementation): 0 is the default budget 2e-7; otherwise tol must lie
  * in [2e-7, 1e-5] (XS_EINVAL). It sets where the shifted Lorentzian
  * (3/2 + 2 y^2) / r^4 <= tol, the doubly shifted Lorentzian 3/2 / r^4 <= tol and the
- * far-line polynomials |X| >= kappa H + 1.25 take over, kappa = 4.09 at the default and
+ * far-line polynomials |X| >= kappa H + 1.25 (for lines with y^2 > 3/2: (|X| - 1.25)^2 + y^2
+ * - 3/2 >= (kappa H)^2) take over, kappa = 4.09 at the default and
  * 3.16 at 1e-5 (the polynomial's truncation within 0.65 tol, the rest for its FP32
  * recurrence); the other forms keep their own error (within 6e-7), and the FP32 sums add
  * theirs (below 1e-6). So sigma's relative error stays below tol + 2e-6. The FP64 path

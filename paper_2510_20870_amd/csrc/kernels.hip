@@ -3,7 +3,13 @@
 // bullets "Compute line-strengths and -widths", "Compute line profiles", "Combine and
 // save").
 //
-// Two kernels carry the path:
+// Two ways lead from the line records to sigma. By moments (far_tree.h; the usual way, chosen
+// by make_plan): lines far from a grid point enter group by group, and the point kernel
+// (point.hip) sums the others with lanes being lines; (P, T) points whose lines are so broad
+// that tiles serve them better take the far kernel (far.hip) and the tile kernel over each
+// tile's near range. Line by line: the tile kernel over the whole window, with main-contributor
+// selection, an explicit tile_group, lists of fewer than 512 lines, or too little memory for
+// the moments. The kernels of the second way:
 //
 // 1. xs_params_kernel (HBM-bound): for every line in the range a grid can reach and every
 //    (P, T) point of a batch, the FP64 line parameters (cutoff, 1/b_D, S/(b_D sqrt(pi)),
@@ -32,8 +38,8 @@
 // 6 terms) and the cut as a lane bound found at staging time with the FP64 test; rows a
 // line reaches inside |z| = 7 take x from the FP64 difference, the six-term series for
 // their points outside |z| = 7 and the FP64 Weideman core inside. Lines far from the
-// tile on the FP32 path (the whole tile inside the cut, shifted Lorentzian, |x| at the
-// tile's centre at least five half-widths away) are not evaluated per point: their Taylor
+// tile on the FP32 path (the whole tile inside the cut, shifted Lorentzian, the line's poles
+// at least four half-widths from the tile's centre: far_line) are not evaluated per point: their Taylor
 // coefficients in the tile coordinate are summed over the wavefront and the polynomial is
 // evaluated once per point (voigt.h, far_coeffs). Contributions are summed in FP32 over
 // blocks of 16 lines, each block added to a Kahan-compensated FP32 sum (a plain FP64 sum

@@ -200,13 +200,6 @@ static int64_t window_lines(const LinesRes& L, const GridRes& G, const xs_opts& 
          kSampleStride;
 }
 
-// Far field by moments, chosen where a point's window holds enough lines beyond its near
-// range: without selection (which drops lines one by one) and with the automatic tile_group.
-static bool use_moments(const LinesRes& L, const GridRes& G, const xs_opts& o) {
-  if (o.tile_group != 0 || o.select_eps > 0.0 || L.n >= ((size_t)1 << 30)) return false;
-  return window_lines(L, G, o) >= kMomentLines;
-}
-
 // The lines' bounds at (P, T) for planning (without the partition function, which may lie in
 // device memory).
 static PtBounds plan_bounds(const LinesRes& L, const xs_pt& pt) {
@@ -217,10 +210,10 @@ static PtBounds plan_bounds(const LinesRes& L, const xs_pt& pt) {
   return pt_bounds(L.sp, pc);
 }
 
-void Plan::set_tree() {
+void Plan::set_tree(int max_levels) {
   int64_t n = rec_n, span = kLeafLines;
   dims = TreeDims{};
-  for (int l = 0; l < kTreeLevels; ++l) {
+  for (int l = 0; l < max_levels; ++l) {
     dims.off[l] = dims.n_nodes;
     dims.cnt[l] = std::max<int64_t>(1, (n + span - 1) / span);
     dims.n_nodes += (dims.cnt[l] + kNodeBlock - 1) / kNodeBlock * kNodeBlock;
@@ -230,11 +223,39 @@ void Plan::set_tree() {
   }
 }
 
+// The grid step at the grid's middle.
+static double mid_step(const GridRes& G) {
+  const size_t m = std::min<size_t>(G.n / 2, G.n >= 2 ? G.n - 2 : 0);
+  return G.n >= 2 ? G.host[m + 1] - G.host[m] : 0.0;
+}
+// Distance within which the lines at (P, T) are summed one by one, at the grid's middle, and
+// whether that is many tiles.
+static double near_distance(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
+  const size_t m = std::min<size_t>(G.n / 2, G.n >= 2 ? G.n - 2 : 0);
+  return kFarTheta * (pb.gmax + (o.precision == XS_FP64 ? kBetaFp64 : kBetaFp32) * pb.kb * G.host[m]);
+}
+static bool is_wide(const GridRes& G, const xs_opts& o, const PtBounds& pb, int64_t tile) {
+  return near_distance(G, o, pb) > kWideTiles * (double)tile * mid_step(G);
+}
+
+// Far field by moments, chosen where a point's window holds enough lines beyond its near
+// range: without selection (which drops lines one by one) and with the automatic tile_group.
+static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, size_t npts,
+                        const xs_opts& o) {
+  if (o.tile_group != 0 || o.select_eps > 0.0 || L.n >= ((size_t)1 << 30)) return false;
+  if (window_lines(L, G, o) >= kMomentLines) return true;
+  if (o.cutoff_kind != XS_CUT_FIXED || (int64_t)L.n < kMomentList) return false;
+  const int64_t tile = (int64_t)kWave * (o.pts_per_lane ? o.pts_per_lane : 1);
+  for (size_t k = 0; k < npts; ++k)
+    if (is_wide(G, o, plan_bounds(L, pts[k]), tile)) return false;
+  return true;
+}
+
 Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, size_t npts,
                const xs_opts& o, size_t cap_bytes, int64_t max_item_lines, int items_per_slot, bool far_moments) {
   Plan p;
   p.n_grid = (int64_t)G.n;
-  if (far_moments && use_moments(L, G, o))
+  if (far_moments && use_moments(L, G, pts, npts, o))
     p.moments = o.precision == XS_FP64 ? kMomFp64 : kMomFp32;
   p.P = o.pts_per_lane ? o.pts_per_lane : p.moments ? 1 : 2;
   p.select_eps = o.select_eps;
@@ -273,7 +294,14 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   int64_t hi = 0;
   line_range(L, G, o, &p.rec_lo, &hi);
   p.rec_n = hi - p.rec_lo;
-  if (p.moments) p.set_tree();
+  if (p.moments) {
+    const int64_t lines = window_lines(L, G, o);
+    const int64_t groups = ((int64_t)G.n + kPointGroup - 1) / kPointGroup;
+    int levels = kTreeLevels;
+    if (lines < kMomentLines && groups * (int64_t)npts <= kFewGroups)
+      for (levels = 1; (lines / kLeafLines) >> (kArityBits * (levels - 1)) > kTopNodes;) ++levels;
+    p.set_tree(levels);
+  }
   if (p.moments && o.cutoff_kind != XS_CUT_FIXED && p.dims.levels > kCutLevel)
     p.cut_blocks = (int)(p.rec_n / kCutBlock);
   // line windows of the units (from the sampled index, within the largest cut)
@@ -293,18 +321,15 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     // points whose near range spans many tiles go by tiles: there the polynomial of a tile
     // takes the near lines that are far from it (about 2 instructions per line and 64
     // points, against 30 in the point kernel)
-    const size_t m = std::min<size_t>(G.n / 2, G.n >= 2 ? G.n - 2 : 0);
-    const double step = G.n >= 2 ? G.host[m + 1] - G.host[m] : 0.0;
+    // (only with one cut for every line: the far kernel's rule)
+    const double step = mid_step(G);
     double widest = 0.0;
     p.by_tile.resize(npts);
     for (size_t k = 0; k < npts; ++k) {
-      // distance within which lines are summed one by one; by tiles only with one cut for
-      // every line (the far kernel's rule)
       const PtBounds pb = plan_bounds(L, pts[k]);
-      const double bm = pb.kb * G.host[m];
-      const double d = kFarTheta * (pb.gmax + (f64 ? kBetaFp64 : kBetaFp32) * bm);
+      const double d = near_distance(G, o, pb);
       const CutDev cd = cut_dev(o);
-      p.by_tile[k] = d > kWideTiles * (double)tile * step &&
+      p.by_tile[k] = is_wide(G, o, pb, tile) &&
                      cut_at(cd, pb.gmin, pb.kb * std::max(0.0, G.first - o.cut_cm1), false) >=
                          o.cut_cm1;
       p.any_tile = p.any_tile || p.by_tile[k];

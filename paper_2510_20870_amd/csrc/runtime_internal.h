@@ -37,8 +37,17 @@ constexpr int64_t kSampleStride = 1024;
 // at or under it, so that a new request's kernels find free wavefront slots quickly).
 constexpr int64_t kServeItemLines = 4096;
 
-// Lines within the cut of the grid's middle from which the far field goes by moments.
-constexpr int64_t kMomentLines = 16384;
+// Far field by moments: from this many lines within the cut of the grid's middle with any
+// options that allow it; with fewer, for a fixed cut and no wide point (kWideTiles), from this
+// many lines in the list. Measured with a fixed cut (us, tile kernel alone / by moments): 526
+// lines in the window 36 / 24, 2000 lines 51 / 26, 5263 lines 79 / 31, 15000 lines 254 / 42. A
+// FWHM cut with 6550 lines goes from 224 to 417 (the lines that only some points reach are far
+// too few per block), a wide point has nearly all lines beside it.
+constexpr int64_t kMomentLines = 16384, kMomentList = 512;
+// Small calls of that kind keep the tree low, as each three of its levels are a launch of some
+// 20 us: the fewest levels that leave at most kTopNodes nodes in a window, for at most
+// kFewGroups groups of points.
+constexpr int64_t kFewGroups = 16384, kTopNodes = 512;
 // (P, T) points whose near range reaches this many tiles on each side go by tiles.
 constexpr double kWideTiles = 6.0;
 
@@ -77,7 +86,7 @@ struct Plan {
   TreeDims dims{};
   int cut_blocks = 0;             // blocks ordered by cut (CutOrder)
   int64_t n_grid = 0;
-  void set_tree();   // dims from rec_n
+  void set_tree(int max_levels);   // dims from rec_n
   // line records [pt_batch][rec_n] (32 B), then with selection the thresholds of the
   // groups of kSelGroup tiles [pt_batch][n_groups()] (8 B), or with the far field by moments
   // the tree [pt_batch][n_nodes] and, when any point goes by tiles, the far sums
