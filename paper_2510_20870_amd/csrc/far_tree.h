@@ -39,9 +39,10 @@ constexpr double kBetaFp32 = 2.05, kBetaFp64 = 2.35;
 template <int NM> constexpr double far_beta() { return NM == kMomFp32 ? kBetaFp32 : kBetaFp64; }
 
 // A node's fields: centres of the group's first and last line, scale s, largest Lorentz
-// width, smallest and largest cut (leaves only), moments. Nodes are stored eight by eight, field by field (kNodeBlock nodes of a
-// field side by side), so that wavefronts reading one field of neighbouring nodes read
-// whole lines of the cache; every level starts at a multiple of kNodeBlock.
+// width, smallest and largest cut (leaves only), moments. Nodes are stored eight by eight,
+// field by field (kNodeBlock nodes of a field side by side), so that wavefronts reading one
+// field of neighbouring nodes read whole lines of the cache; every level starts at a multiple
+// of kNodeBlock.
 constexpr int kNodeBlock = 8;
 enum { kNodeLo, kNodeHi, kNodeS, kNodeG, kNodeCutMin, kNodeCutMax, kNodeA };
 template <int NM> constexpr int node_fields() { return kNodeA + NM; }

@@ -17,7 +17,9 @@
 // chunk of 64 neighbouring lines lies in the core or outside is nearly uniform. The group's
 // width trades the loads and the tree walk, paid once per group, against the lines that only
 // some of its points need. VALU-bound: about 55 instructions per 64 core pairs with y < 0.1,
-// 30 outside the core.
+// 30 outside the core. 20011 points of a list of 8700 lines/cm^-1 (0.3 bar, 435000 lines within
+// the cut): 257 us at 66 % of the issue rate, 8.5 ms by the tile kernel over the whole window;
+// FP64 path, 100003 points, 53000 lines within the cut: 300 us against 9.7 ms.
 #include "far_tree.h"
 #include "tile_kernel.h"
 
