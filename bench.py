@@ -63,9 +63,9 @@ PEAK_ALU_TFLOPS = 256 * 64 * 2 * 2.4e9 / 1e12
 PEAK_VALU_LANE_INSTR = 256 * 64 * 2.4e9
 PEAK_HBM_GBS = 8000.0
 KERNEL_SOURCES = ("tile_kernel.h", "voigt.h", "physics.h", "kernel_args.h", "weideman_coef.h",
-                  "dawson_table.h")
+                  "dawson_table.h", "far_tree.h", "far.hip", "point.hip")
 PROFILE_DIR = os.path.join(ROOT, "profiles")
-COUNTER_PROFILE = os.path.join(PROFILE_DIR, "tile_kernel_large_counters.md")
+COUNTER_PROFILE = os.path.join(PROFILE_DIR, "moments_large_counters.md")
 METRIC = "Voigt line-point evals/s at <=1e-4 rel err vs FP64; p50/p99 request latency"
 
 
@@ -79,7 +79,7 @@ def _code_only(text: str) -> str:
 
 
 def kernel_source_hash() -> str:
-    """sha256 over the code of the tile kernel's sources (comments left out), in
+    """sha256 over the code of the sum kernels' sources (comments left out), in
     KERNEL_SOURCES order."""
     import hashlib
     h = hashlib.sha256()
@@ -90,7 +90,7 @@ def kernel_source_hash() -> str:
 
 
 def counter_profile(path=None):
-    """Figures of the committed counter profile of the tile kernel ("key: value" lines),
+    """Figures of the committed counter profile of the sum's kernels ("key: value" lines),
     or None when it is missing or the kernel sources changed since it was taken."""
     try:
         with open(path or COUNTER_PROFILE) as fh:
@@ -401,12 +401,13 @@ def timed_steps(torch, ctx, h, g, pts, order, opts, out_rows, steps, warmup):
 
 
 def roofline(prof, evals_per_launch, kernel_ms, flops_model):
-    """The tile kernel's position: counter-derived VALU FLOP/s (from the committed profile
+    """The sum's kernels' position: counter-derived VALU FLOP/s (from the committed profile
     of the current kernel sources) against the published FP32 vector peak, the VALU issue
     fraction, and HBM traffic; the tier model's FLOPs only when no such profile exists."""
     sec = kernel_ms * 1e-3
     r = {"bound": "alu", "unit": "TFLOP/s", "peak": PEAK_FP32_PACKED_TFLOPS,
-         "kernel": "xs_tile_kernel", "kernel_ms_per_launch": kernel_ms,
+         "kernel": "xs_point_kernel, xs_far_kernel + xs_tile_kernel (by (P, T) point)",
+         "kernel_ms_per_launch": kernel_ms,
          "evals_per_launch": evals_per_launch}
     if prof and prof.get("evals_per_launch"):
         fpe = prof["valu_flops_per_launch"] / prof["evals_per_launch"]
