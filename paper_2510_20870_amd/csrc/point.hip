@@ -227,11 +227,11 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   auto half = [&](int v, int side) { return __builtin_amdgcn_readlane(v, side * 32); };
   const double ulp = fabs(g_near) * 0x1p-48;
   // the largest cut of the lines on this side that can reach the points, and the smallest of
-  // those (b_D grows with the centre)
+  // those (b_D grows with the centre, which is above zero also where a point is not)
   double cut_hi = cap, cut_lo = cap;
   if constexpr (FW) {
     cut_hi = cut_at(A.cut, pb.gmax, kb * (right ? v1 + cap : v1), true);
-    cut_lo = cut_at(A.cut, pb.gmin, kb * (right ? v0 : fmax(v0 - cut_hi, 0.0)), false);
+    cut_lo = cut_at(A.cut, pb.gmin, kb * fmax(right ? v0 : v0 - cut_hi, 0.0), false);
   }
   const bool one_cut = !FW || __ballot(cut_lo < cap) == 0ull;
   // reachable lines [e0, e1)
@@ -283,9 +283,9 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   bool whole = false;   // too many nodes that are not far: sum every line of the window
   int n_list = 0, round = 0;
   // adds the lane's moments (use: it has some) about c, scale sc, to every point's sum; lanes
-  // without take zeros about a centre that is no grid point
+  // without take zeros about a centre beyond the last point (which may be below zero)
   auto add_moments = [&](double c, double sc, bool use, auto moment) {
-    const double cc = use ? c : 2.0 * v1 + 1.0;
+    const double cc = use ? c : v1 + fabs(v1) + 1.0;
     double M[NM];
 #pragma unroll
     for (int t = 0; t < NM; ++t) M[t] = use ? moment(t) : 0.0;

@@ -1,0 +1,47 @@
+"""The point kernel at the edges of what its callers may pass, against the FP64 oracle: grid
+points at and below zero. Tolerances: the FP32 path's own error (K within 6e-7, sums below
+1e-6, moments within 5e-8 of each contribution) stays below 2e-6; the FP64 path's core (8.5e-9)
+below 2e-8."""
+import numpy as np
+import pytest
+
+from oracle import xsec_oracle as O
+from paper_2510_20870_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2510_20870_amd import xsec
+    c = xsec.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("rule,lo,grid,pt,mult", [
+    # the group from -4 to -2.25 holds a point at 2 v - 1 of its last one
+    ("fixed", 0.01, -8.0 + 0.25 * np.arange(80), (0.1, 800.0), 100.0),
+    ("min_fwhm", 0.01, -8.0 + 0.25 * np.arange(80), (1.0, 800.0), 100.0),
+    # cuts of several times the line's own centre, so that lines close to zero reach no point
+    # below it while those further up do
+    ("min_fwhm", 0.001, -1.0 + 0.02 * np.arange(49), (1e-12, 1000.0), 1e6),
+])
+def test_points_below_zero(ctx, rule, lo, grid, pt, mult, f64):
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(40_000, lo, 2.0 if lo < 0.01 else 20.0, 31))
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    ref = O.sigma(L, grid, pt[0], pt[1], 16.0, cut_kind=rule, cut_cm1=25.0, fwhm_mult=mult)
+    kind = X.XS_CUT_FIXED if rule == "fixed" else X.XS_CUT_MIN_FWHM
+    o = ctx.opts(kind, 25.0, mult, precision=X.XS_FP64 if f64 else X.XS_FP32_KAHAN)
+    sig = ctx.compute(h, g, [pt], o)[0]
+    assert np.all(np.isfinite(sig)), np.nonzero(~np.isfinite(sig))[0]
+    st = O.compare(sig, ref, rel_tol=2e-8 if f64 else 2e-6)
+    print(f"[below zero] {rule} f64={f64} max_rel {st['max_rel']:.2e}", flush=True)
+    assert st["violations"] == 0, st
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
