@@ -247,6 +247,8 @@ __device__ __forceinline__ double one_line(double nu, double nu0, const LineRec&
     const double r2 = fma(x, x, y2);
     if (r2 >= 74.0 * 74.0)
       return kInvSqrtPi * r.sc * r.y * r2 * rcp64(fma(r2, r2 - 1.5, 2.0 * y2));
+    if (r2 >= kT6R2)   // (y in FP64: K may lie below FP32's range)
+      return kInvSqrtPi * r.sc * r.y * (double)asym_scaled<6>((float)y2, (float)r2);
     return r.sc * (double)voigt_k32(x, (float)r.y);
   } else {
     return r.sc * voigt_k64(x, r.y);

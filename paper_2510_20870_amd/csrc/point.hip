@@ -173,6 +173,18 @@ __device__ __forceinline__ double lane_k32(const DawEntry* tab, double x, double
   return (double)k;
 }
 
+// The same for lines of so small a y that the products above leave FP32's range (K falls below
+// 1e-38 in the wing): y enters the wing's forms in FP64.
+constexpr float kTinyY = 1e-20f;
+__device__ __forceinline__ double lane_k32_tiny(const DawEntry* tab, double x, double y,
+                                                float y32, float y2) {
+  const float xf = (float)x;
+  const float r2 = fmaf(xf, xf, y2);
+  if (r2 >= kT6R2) return kInvSqrtPi * y * (double)asym_scaled<6>(y2, r2);
+  return (double)(y32 < kTaylorY ? core_small(tab, x, y32)
+                                 : (float)voigt_core64_tier(core_tier(y), x, y));
+}
+
 // FW: the lines' cuts differ (min(cap, mult FWHM)). The covered and the reachable lines then
 // follow from bounds of the cut; between them lie leaves of which some lines reach a point and
 // some do not.
@@ -656,7 +668,9 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
             return lane_k32<decltype(core)::value>(tab, x, lr.y, y32, y2, A.l1_eps);
           });
         };
-        if (all(y2 >= kT6R2)) with(std::integral_constant<int, kCoreNone>{});
+        if (!all(y32 >= kTinyY))
+          points([&](double x) { return lane_k32_tiny(tab, x, lr.y, y32, y2); });
+        else if (all(y2 >= kT6R2)) with(std::integral_constant<int, kCoreNone>{});
         else if (all(y32 < kTaylorY)) with(std::integral_constant<int, kCoreSmall>{});
         else if (all(lr.y >= 1.0)) with(std::integral_constant<int, kCore16>{});
         else if (all(lr.y >= 0.3)) with(std::integral_constant<int, kCore20>{});

@@ -1,5 +1,6 @@
 """The point kernel at the edges of what its callers may pass, against the FP64 oracle: grid
-points at and below zero. Tolerances: the FP32 path's own error (K within 6e-7, sums below
+points at and below zero, pressures so low that a profile's wing leaves FP32's range.
+Tolerances: the FP32 path's own error (K within 6e-7, sums below
 1e-6, moments within 5e-8 of each contribution) stays below 2e-6; the FP64 path's core (8.5e-9)
 below 2e-8."""
 import numpy as np
@@ -42,6 +43,29 @@ def test_points_below_zero(ctx, rule, lo, grid, pt, mult, f64):
     assert np.all(np.isfinite(sig)), np.nonzero(~np.isfinite(sig))[0]
     st = O.compare(sig, ref, rel_tol=2e-8 if f64 else 2e-6)
     print(f"[below zero] {rule} f64={f64} max_rel {st['max_rel']:.2e}", flush=True)
+    assert st["violations"] == 0, st
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("P", [1e-28, 1e-36, 1e-40])
+def test_tiny_pressures(ctx, P):
+    """Every point outside the Doppler cores (there the Lorentz wing is all there is, K down to
+    1e-48), whatever its size beside the maximum."""
+    n = 600
+    L = synth.make_lines(synth.ListSpec(n, 1000.0, 1400.0, 5))
+    grid = 1000.0 + 0.05 * np.arange(600, dtype=np.float64)
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    ref = O.sigma(L, grid, P, 800.0, 16.0, cut_cm1=25.0)
+    sig = ctx.compute(h, g, [(P, 800.0)], ctx.opts(0, 25.0))[0]
+    # 12 half-widths from every centre the Gaussian is below 1e-62
+    b = O.doppler_width(grid, 800.0, 16.0)
+    i = np.clip(np.searchsorted(L["nu0"], grid), 1, n - 1)
+    wing = np.minimum(np.abs(grid - L["nu0"][i - 1]), np.abs(grid - L["nu0"][i])) > 12.0 * b
+    rel = np.abs(sig - ref)[wing] / ref[wing]
+    print(f"[tiny P] P={P} {int(wing.sum())} wing points max_rel {rel.max():.2e}", flush=True)
+    assert rel.max() < 2e-6
+    st = O.compare(sig, ref, rel_tol=2e-6)
     assert st["violations"] == 0, st
     ctx.unload_lines(h)
     ctx.free_grid(g)
