@@ -255,7 +255,7 @@ template <int NM>
 __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t item = xcd_logical_wg(blockIdx.x);
+  const int64_t item = logical_wg();
   if (item >= A.n_items) return;   // the whole workgroup
   const int k = (int)(item % A.n_pt);
   const int64_t tile = A.tile_order ? (int64_t)A.tile_order[item / A.n_pt] : item / A.n_pt;
@@ -407,7 +407,7 @@ __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
 
 hipError_t launch_far(const FarArgs& A, int moments, hipStream_t st) {
   if (A.n_items <= 0) return hipSuccess;
-  const dim3 grid((unsigned)phys_workgroups(A.n_items)), block(kBlock);
+  const dim3 grid = wg_grid(phys_workgroups(A.n_items)), block(kBlock);
   if (moments == kMomFp32)
     hipLaunchKernelGGL(xs_far_kernel<kMomFp32>, grid, block, 0, st, A);
   else

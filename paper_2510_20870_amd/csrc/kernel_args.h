@@ -164,6 +164,14 @@ struct TileArgs {
 // Launchers (kernels.hip). phys_wg = number of workgroups launched: n_wg rounded up to a
 // multiple of 8 * 16 (whole XCD blocks).
 inline int64_t phys_workgroups(int64_t n_wg) { return (n_wg + 127) / 128 * 128; }
+// The launch grid of n workgroups of at most 1024 threads: a dimension holds at most 2^32 - 1
+// threads, so more than kMaxGridX of them go into rows of kMaxGridX (a multiple of 128; the last
+// row may hold workgroups past n, which have no work).
+constexpr int64_t kMaxGridX = (int64_t)1 << 21;
+inline dim3 wg_grid(int64_t n) {
+  return n <= kMaxGridX ? dim3((unsigned)n)
+                        : dim3((unsigned)kMaxGridX, (unsigned)((n + kMaxGridX - 1) / kMaxGridX));
+}
 hipError_t launch_params(const ParamArgs& A, hipStream_t st);
 hipError_t launch_tile(const TileArgs& A, int P, bool f64, int W, hipStream_t st,
                        int64_t phys_wg);

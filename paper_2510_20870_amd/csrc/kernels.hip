@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kSelBlock) void xs_select_kernel(TileArgs A) {
   __shared__ double part[kSelBlock / kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t item = blockIdx.x;
+  const int64_t item = launched_wg();
   if (item >= A.n_tiles * A.n_pt) return;   // the whole workgroup
   const int k = (int)(item % A.n_pt);
   const int64_t group = item / A.n_pt;
@@ -362,7 +362,7 @@ hipError_t launch_params(const ParamArgs& A, hipStream_t st) {
 
 hipError_t launch_tile(const TileArgs& A, int P, bool f64, int W, hipStream_t st,
                        int64_t phys_wg) {
-  const dim3 grid((unsigned)phys_wg);
+  const dim3 grid = wg_grid(phys_wg);
   switch (P) {
     case 1: return launch_tile_p1(A, f64, W, st, grid);
     case 2: return launch_tile_p2(A, f64, W, st, grid);
@@ -373,7 +373,7 @@ hipError_t launch_tile(const TileArgs& A, int P, bool f64, int W, hipStream_t st
 }
 
 hipError_t launch_count(const TileArgs& A, int P, hipStream_t st, int64_t phys_wg) {
-  const dim3 grid((unsigned)phys_wg), block(kBlock);
+  const dim3 grid = wg_grid(phys_wg), block(kBlock);
   switch (P) {
     case 1: hipLaunchKernelGGL((xs_count_kernel<1>), grid, block, 0, st, A); break;
     case 2: hipLaunchKernelGGL((xs_count_kernel<2>), grid, block, 0, st, A); break;
@@ -387,7 +387,7 @@ hipError_t launch_count(const TileArgs& A, int P, hipStream_t st, int64_t phys_w
 hipError_t launch_select(const TileArgs& A, int P, hipStream_t st) {
   const int64_t items = A.n_tiles * A.n_pt;
   if (items <= 0) return hipSuccess;
-  const dim3 grid((unsigned)items), block(kSelBlock);
+  const dim3 grid = wg_grid(items), block(kSelBlock);
   switch (P) {
     case 1: hipLaunchKernelGGL((xs_select_kernel<1>), grid, block, 0, st, A); break;
     case 2: hipLaunchKernelGGL((xs_select_kernel<2>), grid, block, 0, st, A); break;

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   }
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t item = xcd_logical_wg(blockIdx.x) * kWavesPerWG + wv;
+  const int64_t item = logical_wg() * kWavesPerWG + wv;
   if (item >= A.n_groups * A.n_pt * A.split) return;
   // parts of a group and neighbouring groups of one (P, T) point lie next to each other
   const int s = (int)(item % A.split);
@@ -699,8 +699,8 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
 hipError_t launch_point(const PointArgs& A, int moments, hipStream_t st) {
   const int64_t items = A.n_groups * A.n_pt * A.split;
   if (items <= 0) return hipSuccess;
-  const dim3 grid((unsigned)phys_workgroups((items + kWavesPerWG - 1) / kWavesPerWG)),
-      block(kBlock);
+  const dim3 grid = wg_grid(phys_workgroups((items + kWavesPerWG - 1) / kWavesPerWG)),
+             block(kBlock);
   const bool fw = A.cut.kind != kCutFixed;
   if (moments == kMomFp32) {
     if (fw) hipLaunchKernelGGL((xs_point_kernel<kMomFp32, true>), grid, block, 0, st, A);

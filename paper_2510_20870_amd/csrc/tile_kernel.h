@@ -115,6 +115,12 @@ __device__ __forceinline__ int64_t xcd_logical_wg(int64_t phys) {
   return (slot / kXcdBlock) * (8 * kXcdBlock) + xcd * kXcdBlock + (slot % kXcdBlock);
 }
 
+// This workgroup's number in a launch of wg_grid, and its logical number.
+__device__ __forceinline__ int64_t launched_wg() {
+  return (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+}
+__device__ __forceinline__ int64_t logical_wg() { return xcd_logical_wg(launched_wg()); }
+
 // First index i in [0, n) with a[i] >= key (n if none); LE selects a[i] > key instead.
 // 64-ary search: every lane probes one position per level.
 template <bool LE>
@@ -282,8 +288,7 @@ __device__ __forceinline__ FarLine far_line(const FarTile& ft, double nu0, const
 
 template <int P, bool kParts>
 __device__ __forceinline__ bool decode_item(const TileArgs& A, int lane, ItemInfo& it) {
-  const int64_t phys = blockIdx.x;
-  const int64_t wg = xcd_logical_wg(phys);
+  const int64_t wg = logical_wg();
   // the wave index is wave-uniform; say so, so that everything derived from it is scalar
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t item = wg * kWavesPerWG + wave;
@@ -376,7 +381,7 @@ struct GroupGeo {
 template <int P>
 __device__ __forceinline__ bool decode_group(const TileArgs& A, int lane, int wave,
                                              ItemInfo& it, GroupGeo& gg) {
-  const int64_t wg = xcd_logical_wg(blockIdx.x);
+  const int64_t wg = logical_wg();
   if (wg >= A.n_items) return false;   // one work item per workgroup
   it.s = (int)(wg % A.split);
   const int64_t r = wg / A.split;
