@@ -85,6 +85,15 @@ int xs_ctx::scratch(xs::Scratch& s, size_t bytes, const char* what) {
   return XS_OK;
 }
 
+void xs_ctx::drop_scratch() {
+  if (pts_event_valid) (void)hipEventSynchronize(pts_event);
+  for (xs::Scratch* s : {&part_buf, &out_buf, &count_buf, &rec_buf, &order_buf}) {
+    if (s->ptr) dev_free(s->ptr, s->cap);
+    *s = xs::Scratch{};
+  }
+  order_host.clear();
+}
+
 xs::LinesRes* xs_ctx::find_lines(xs_lines_t h) {
   auto it = lines.find(h);
   return it == lines.end() ? nullptr : it->second;
@@ -416,6 +425,21 @@ int KernelTimer::record(hipStream_t st) {
   if (r != hipSuccess) return hip_fail(r, "hipEventRecord");
   ++used;
   return XS_OK;
+}
+
+// Room for the plan's records, partials (with_part), output staging (out_bytes, 0: none) and
+// tile order.
+static int plan_buffers(Ctx& c, const Plan& p, size_t n_grid, bool with_part, size_t out_bytes) {
+  int rc = c.scratch(c.rec_buf, p.rec_bytes(), "line records");
+  if (rc == XS_OK && with_part && p.max_split() > 1)
+    rc = c.scratch(c.part_buf, p.part_bytes(n_grid), "split partials");
+  if (rc == XS_OK && out_bytes) rc = c.scratch(c.out_buf, out_bytes, "output staging");
+  const size_t bytes = p.tile_order.size() * sizeof(int);
+  if (rc == XS_OK && c.order_buf.cap < bytes) {
+    c.order_host.clear();   // (the content goes with the buffer)
+    rc = c.scratch(c.order_buf, bytes, "tile order");
+  }
+  return rc;
 }
 
 int upload_order(Ctx& c, const Plan& p, hipStream_t st) {
@@ -1141,19 +1165,20 @@ int xs_compute(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, size_t 
     if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
   }
   Plan p = make_plan(*c, *L, *G, pts, npts, *opts);
-  rc = upload_pts(*c, pts, npts, st);
-  if (rc) return rc;
   const size_t out_bytes = npts * G->n * out_elem_bytes(*opts);
-  // records and partials; a call whose moments do not fit the budget goes line by line
   auto buffers = [&]() {
-    int r = c->scratch(c->rec_buf, p.rec_bytes(), "line records");
-    if (r == XS_OK && p.max_split() > 1)
-      r = c->scratch(c->part_buf, p.part_bytes(G->n), "split partials");
-    if (r == XS_OK && !out_on_device) r = c->scratch(c->out_buf, out_bytes, "output staging");
-    return r;
+    const int r = upload_pts(*c, pts, npts, st);
+    return r ? r : plan_buffers(*c, p, G->n, true, out_on_device ? 0 : out_bytes);
   };
+  // first beside what earlier calls left, then without it; a call whose moments do not fit the
+  // budget goes line by line
   rc = buffers();
+  if (rc == XS_ENOMEM) {
+    c->drop_scratch();
+    rc = buffers();
+  }
   if (rc == XS_ENOMEM && p.moments) {
+    c->drop_scratch();
     p = make_plan(*c, *L, *G, pts, npts, *opts, 0, 0, 0, false);
     rc = buffers();
   }
@@ -1276,12 +1301,17 @@ int xs_count_evals_by_tier(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* 
   o.split = 1;
   o.tile_group = 1;   // the count kernel walks single tiles
   const Plan p = make_plan(*c, *L, *G, pts, npts, o);
-  rc = upload_pts(*c, pts, npts, st);
-  if (rc) return rc;
   const size_t ncnt = npts * kNEvalTiers;
-  rc = c->scratch(c->count_buf, ncnt * sizeof(uint64_t), "counters");
-  if (rc) return rc;
-  rc = c->scratch(c->rec_buf, p.rec_bytes(), "line records");
+  auto buffers = [&]() {
+    int r = upload_pts(*c, pts, npts, st);
+    if (r == XS_OK) r = c->scratch(c->count_buf, ncnt * sizeof(uint64_t), "counters");
+    return r ? r : plan_buffers(*c, p, G->n, false, 0);
+  };
+  rc = buffers();
+  if (rc == XS_ENOMEM) {
+    c->drop_scratch();
+    rc = buffers();
+  }
   if (rc) return rc;
   e = launch_fill_u64((unsigned long long*)c->count_buf.ptr, (int64_t)ncnt, st);
   if (e != hipSuccess) return hip_fail(e, "counter clear");

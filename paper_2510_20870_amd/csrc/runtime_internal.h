@@ -171,6 +171,9 @@ struct xs_ctx {
   int dev_alloc(void** p, size_t bytes, const char* what);
   void dev_free(void* p, size_t bytes);
   int scratch(xs::Scratch& s, size_t bytes, const char* what);
+  // Gives back the scratch of finished calls (all but the point table), after the last launch
+  // that reads it.
+  void drop_scratch();
   xs::LinesRes* find_lines(xs_lines_t h);
   xs::GridRes* find_grid(xs_grid_t h);
 };

@@ -373,7 +373,11 @@ int xs_autotune(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, size_t
     // (the shape is the tile kernel's: timed line by line)
     const Plan full = make_plan(*c, *L, *G, pts, npts, o, 0, 0, ips, false);
     double ms = 0.0;
-    const int r = time_candidate(*c, *L, *G, o, blocks, nprobe, full, tm, &ms);
+    int r = time_candidate(*c, *L, *G, o, blocks, nprobe, full, tm, &ms);
+    if (r == XS_ENOMEM) {   // without what earlier calls left
+      c->drop_scratch();
+      r = time_candidate(*c, *L, *G, o, blocks, nprobe, full, tm, &ms);
+    }
     if (r == XS_OK) tried.push_back({P, ips, waves_option(full.W), ms});
     return r;
   };
