@@ -226,7 +226,7 @@ extern "C" int xs_regrid(xs_ctx* c, xs_grid_t src_h, xs_grid_t dst_h, const doub
   double* out_dev = out;
   if (!on_device) {
     const size_t in_al = (in_bytes + 255) & ~(size_t)255;
-    int rc = c->dev_alloc(&buf, in_al + out_bytes, "regrid staging");
+    int rc = c->dev_alloc_again(&buf, in_al + out_bytes, "regrid staging");
     if (rc) return rc;
     e = hipMemcpyAsync(buf, sigma_src, in_bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) {

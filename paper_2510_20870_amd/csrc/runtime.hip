@@ -94,6 +94,15 @@ void xs_ctx::drop_scratch() {
   order_host.clear();
 }
 
+int xs_ctx::dev_alloc_again(void** p, size_t bytes, const char* what) {
+  int rc = dev_alloc(p, bytes, what);
+  if (rc == XS_ENOMEM) {
+    drop_scratch();
+    rc = dev_alloc(p, bytes, what);
+  }
+  return rc;
+}
+
 xs::LinesRes* xs_ctx::find_lines(xs_lines_t h) {
   auto it = lines.find(h);
   return it == lines.end() ? nullptr : it->second;
@@ -935,7 +944,7 @@ int xs_load_lines(xs_ctx* c, const xs_lines_desc* d, const xs_species_desc* sp, 
   const size_t b_j = has_j ? b_g : 0;
   const size_t b_bv = al((size_t)nb * 8), b_bt = al((size_t)nb * nj * 8);
   L->bytes = b_nu + 4 * b_f + b_g + 2 * b_q + b_j + b_bv + 2 * b_bt;
-  int rc = c->dev_alloc(&L->base, L->bytes, "line list");
+  int rc = c->dev_alloc_again(&L->base, L->bytes, "line list");
   if (rc) {
     delete L;
     return rc;
@@ -1062,7 +1071,7 @@ int xs_set_grid(xs_ctx* c, const double* nu, size_t n, xs_grid_t* out) {
   G->first = nu[0];
   G->last = nu[n - 1];
   G->host.assign(nu, nu + n);
-  int rc = c->dev_alloc((void**)&G->d, G->bytes, "grid");
+  int rc = c->dev_alloc_again((void**)&G->d, G->bytes, "grid");
   if (rc) {
     delete G;
     return rc;
@@ -1419,7 +1428,7 @@ int xs_graph_create(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, si
   if (e != hipSuccess) return give_up(hip_fail(e, "hipSetDevice"));
   Plan p = make_plan(*c, *L, *G, pts, npts, *opts);
   g->pts_bytes = npts * 2 * sizeof(double);
-  rc = c->dev_alloc(&g->pts, g->pts_bytes, "graph point table");
+  rc = c->dev_alloc_again(&g->pts, g->pts_bytes, "graph point table");
   if (rc) return give_up(rc);
   std::vector<double> h(2 * npts);
   for (size_t k = 0; k < npts; ++k) {
@@ -1431,11 +1440,11 @@ int xs_graph_create(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, si
   // records and partials; a graph whose moments do not fit the budget goes line by line
   auto buffers = [&]() {
     g->rec_bytes = p.rec_bytes();
-    int r = c->dev_alloc(&g->rec, g->rec_bytes, "graph line records");
+    int r = c->dev_alloc_again(&g->rec, g->rec_bytes, "graph line records");
     if (r != XS_OK) g->rec = nullptr;
     if (r == XS_OK && p.max_split() > 1) {
       g->part_bytes = p.part_bytes(G->n);
-      r = c->dev_alloc(&g->part, g->part_bytes, "graph partials");
+      r = c->dev_alloc_again(&g->part, g->part_bytes, "graph partials");
       if (r != XS_OK) g->part = nullptr;
     }
     return r;
@@ -1449,7 +1458,7 @@ int xs_graph_create(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, si
   }
   if (rc) return give_up(rc);
   g->order_bytes = p.tile_order.size() * sizeof(int);
-  rc = c->dev_alloc(&g->order, g->order_bytes, "graph tile order");
+  rc = c->dev_alloc_again(&g->order, g->order_bytes, "graph tile order");
   if (rc) return give_up(rc);
   e = hipMemcpy(g->order, p.tile_order.data(), g->order_bytes, hipMemcpyHostToDevice);
   if (e != hipSuccess) return give_up(hip_fail(e, "graph tile order upload"));
@@ -1530,7 +1539,7 @@ int xs_cia_regrid(xs_ctx* c, xs_grid_t gh, const size_t* off, size_t nb, const d
   const size_t b_out = (size_t)nb * G->n * 8;
   const size_t total = b_off + 2 * b_nodes + b_out;
   void* buf = nullptr;
-  int rc = c->dev_alloc(&buf, total, "CIA buffers");
+  int rc = c->dev_alloc_again(&buf, total, "CIA buffers");
   if (rc) return rc;
   char* p = (char*)buf;
   int64_t* d_off = (int64_t*)p;
@@ -1560,7 +1569,7 @@ int xs_eval_voigt(xs_ctx* c, const double* x, const double* y, size_t n, int pre
   if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
   void* buf = nullptr;
   const size_t b = n * sizeof(double);
-  int rc = c->dev_alloc(&buf, 3 * b, "voigt evaluation buffers");
+  int rc = c->dev_alloc_again(&buf, 3 * b, "voigt evaluation buffers");
   if (rc) return rc;
   double* dx = (double*)buf;
   double* dy = dx + n;

@@ -169,6 +169,9 @@ struct xs_ctx {
   bool reserve(size_t bytes);
   void release(size_t bytes);
   int dev_alloc(void** p, size_t bytes, const char* what);
+  // dev_alloc, and where the budget is short, again without the scratch that finished calls
+  // left (not from the serving calls: the scratch belongs to the context's own thread)
+  int dev_alloc_again(void** p, size_t bytes, const char* what);
   void dev_free(void* p, size_t bytes);
   int scratch(xs::Scratch& s, size_t bytes, const char* what);
   // Gives back the scratch of finished calls (all but the point table), after the last launch

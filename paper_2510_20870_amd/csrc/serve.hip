@@ -443,7 +443,8 @@ void serve_shutdown(Ctx* c) {
   c->server = nullptr;
 }
 
-static int serve_start_locked(Ctx* c, const xs_serve_opts* o) {
+// own_thread: called on the context's own thread (not from a submitter's)
+static int serve_start_locked(Ctx* c, const xs_serve_opts* o, bool own_thread) {
   xs_serve_opts d{};
   if (!o) o = &d;
   if (o->max_inflight < 0 || o->max_inflight > 64)
@@ -472,7 +473,8 @@ static int serve_start_locked(Ctx* c, const xs_serve_opts* o) {
     delete s;
     return fail(XS_ENOMEM, "serving arena of %zu bytes is too small", mem);
   }
-  int rc = c->dev_alloc((void**)&s->base, mem, "serving arena");
+  int rc = own_thread ? c->dev_alloc_again((void**)&s->base, mem, "serving arena")
+                      : c->dev_alloc((void**)&s->base, mem, "serving arena");
   if (rc) {
     delete s;
     return rc;
@@ -504,7 +506,7 @@ static int serve_start_locked(Ctx* c, const xs_serve_opts* o) {
 static int ensure_server(Ctx* c) {
   std::lock_guard<std::mutex> lk(c->serve_mu);
   if (c->server) return XS_OK;
-  return serve_start_locked(c, nullptr);
+  return serve_start_locked(c, nullptr, false);
 }
 
 static Request* find_req(Server* s, xs_req_t id) {
@@ -669,7 +671,7 @@ int xs_serve_start(xs_ctx* c, const xs_serve_opts* opts) {
   if (!c) return fail(XS_EINVAL, "ctx is NULL");
   std::lock_guard<std::mutex> lk(c->serve_mu);
   if (c->server) return fail(XS_EBUSY, "the server is already running");
-  return serve_start_locked(c, opts);
+  return serve_start_locked(c, opts, true);
 }
 
 int xs_serve_pause(xs_ctx* c, int paused) {
