@@ -261,10 +261,13 @@ static bool is_wide(const GridRes& G, const xs_opts& o, const PtBounds& pb, int6
 static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, size_t npts,
                         const xs_opts& o) {
   if (o.tile_group != 0 || o.select_eps > 0.0 || L.n >= ((size_t)1 << 30)) return false;
-  if (window_lines(L, G, o) >= kMomentLines) return true;
+  const int64_t lines = window_lines(L, G, o);
+  if (lines >= kMomentLines) return true;
   // fewer lines: by a rule on the whole call, so only where the split follows from the whole
   // call too (with a given split a row's bits are its own point's alone)
   if (o.split || o.cutoff_kind != XS_CUT_FIXED || (int64_t)L.n < kMomentList) return false;
+  const int64_t groups = ((int64_t)G.n + kPointGroup - 1) / kPointGroup;
+  if (lines < kMomentFewLines && groups * (int64_t)npts > kMomentGroups) return false;
   const int64_t tile = (int64_t)kWave * (o.pts_per_lane ? o.pts_per_lane : 1);
   for (size_t k = 0; k < npts; ++k)
     if (is_wide(G, o, plan_bounds(L, pts[k]), tile)) return false;

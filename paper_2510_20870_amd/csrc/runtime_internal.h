@@ -37,13 +37,19 @@ constexpr int64_t kSampleStride = 1024;
 // at or under it, so that a new request's kernels find free wavefront slots quickly).
 constexpr int64_t kServeItemLines = 4096;
 
-// Far field by moments: from this many lines within the cut of the grid's middle with any
-// options that allow it; with fewer, for a fixed cut and no wide point (kWideTiles), from this
-// many lines in the list. Measured with a fixed cut (us, tile kernel alone / by moments): 526
-// lines in the window 36 / 24, 2000 lines 51 / 26, 5263 lines 79 / 31, 15000 lines 254 / 42. A
-// FWHM cut with 6550 lines goes from 224 to 417 (the lines that only some points reach are far
-// too few per block), a wide point has nearly all lines beside it.
-constexpr int64_t kMomentLines = 16384, kMomentList = 512;
+// Far field by moments: from kMomentLines lines within the cut of the grid's middle with any
+// options that allow it; with fewer, for a fixed cut and no wide point (kWideTiles), from
+// kMomentList lines in the list. There a call that does not fill the device wins by its shorter
+// chains, a large one only where a window holds so many lines that walking them costs more than
+// the point kernel's searches and sums (some 0.5 ns per point): with fewer than kMomentFewLines,
+// up to kMomentGroups groups of points in all. Measured with a fixed cut (us, tile kernel alone /
+// by moments; 3e4, 2e5 and 1e6 points): 100 lines in the window 68 / 41, 151 / 140, 251 / 550;
+// 500 lines 82 / 46, 181 / 173, 377 / 687; 2000 lines 147 / 51, 255 / 201, 748 / 810; 5000 lines
+// 217 / 64, 401 / 225, 1502 / 943; 15000 lines 404 / 79, 848 / 275, 3787 / 1466. A FWHM cut with
+// 6550 lines goes from 224 to 417 (the lines that only some points reach are far too few per
+// block), a wide point has nearly all lines beside it.
+constexpr int64_t kMomentLines = 16384, kMomentFewLines = 4096, kMomentList = 512;
+constexpr int64_t kMomentGroups = 25000;
 // Small calls of that kind keep the tree low, as each three of its levels are a launch of some
 // 20 us: the fewest levels that leave at most kTopNodes nodes in a window, for at most
 // kFewGroups groups of points.

@@ -1,0 +1,59 @@
+"""The rules that choose between the point kernel, the far kernel and tiles over the whole window:
+both sides of each line against the FP64 oracle (FP32 path: below 2e-6; FP64 path: its core, 8.5e-9,
+below 2e-8), and the side taken, told from the bits: those of the tile kernel are the ones of
+an explicit tile_group of 1."""
+import numpy as np
+import pytest
+
+from oracle import xsec_oracle as O
+from paper_2510_20870_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2510_20870_amd import xsec
+    c = xsec.Context(0)
+    yield c
+    c.close()
+
+
+def _check(ctx, L, grid, pts, o, idx=None, tol=2e-6, rule="fixed"):
+    """The call's rows, checked at grid[idx]."""
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    sig = ctx.compute(h, g, pts, o)
+    idx = np.arange(len(grid)) if idx is None else idx
+    for k, (P, T) in enumerate(pts):
+        ref = O.sigma(L, grid, P, T, 16.0, cut_kind=rule, cut_cm1=o.cut_cm1, fwhm_mult=100.0,
+                      points=idx)
+        st = O.compare(sig[k][idx], ref, rel_tol=tol)
+        assert st["violations"] == 0, (pts[k], st)
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
+    return sig
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("n,m,moments", [
+    (2000, 200_000, True), (2000, 200_001, False),     # 10 lines in a window: by the groups
+    (950_000, 200_001, True),                          # 5000 lines: by moments all the same
+])
+def test_few_lines_many_points(ctx, n, m, moments, f64):
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(n, 500.0, 10000.0, 3))
+    grid = 2000.0 + 0.005 * np.arange(m, dtype=np.float64)
+    prec = X.XS_FP64 if f64 else X.XS_FP32_KAHAN
+    idx = np.linspace(0, m - 1, 300).astype(np.int64)
+    pts = [(0.1, 900.0)]
+    sig = _check(ctx, L, grid, pts, ctx.opts(0, 25.0, 100.0, prec), idx, 2e-8 if f64 else 2e-6)
+    # by the tile kernel (a cut this wide groups tiles on the FP32 path) with any split
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    line = any(np.array_equal(sig, ctx.compute(h, g, pts, ctx.opts(
+        0, 25.0, 100.0, prec, 2, split, tile_group=1 if f64 else 4))) for split in range(1, 65))
+    assert line == (not moments)
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
