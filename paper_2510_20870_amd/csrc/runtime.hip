@@ -397,8 +397,11 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   }
   // FP64 tile kernel: by chunks where a part has more than two of them. (Code that runs once
   // or twice is fetched for longer than it saves: a window of 1160 lines on 1349 points takes
-  // 23 us line by line, 37 by chunks.)
-  p.chunks = f64 && !p.moments && max_window > 2 * (int64_t)kWave * p.split;
+  // 23 us line by line, 37 by chunks.) max_window is rounded up to whole samples, so with
+  // one or two samples in every window there may be a few lines only (10 lines, 1e6 points: 217 us
+  // line by line, 249 by chunks; 1000 lines, 2e5 points with selection 319 and 338; 2500: 640
+  // and 555).
+  p.chunks = f64 && !p.moments && max_cost > 2 && max_window > 2 * (int64_t)kWave * p.split;
   // (P, T) points per batch: the records of a batch (32 B per line and point) and its
   // partials stay under a third of the free budget and 64 GiB (fewer, longer launches:
   // the tail of each tile launch, where the last work items run alone, is paid once

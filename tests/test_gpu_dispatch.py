@@ -57,3 +57,42 @@ def test_few_lines_many_points(ctx, n, m, moments, f64):
     assert line == (not moments)
     ctx.unload_lines(h)
     ctx.free_grid(g)
+
+
+def _chunk_list(kind):
+    """Lists with more than two thousand lines in a window (FP64 tile kernel by chunks)."""
+    if kind == "sparse":        # a chunk of 64 lines is 64 cm^-1 wide
+        return synth.make_lines(synth.ListSpec(9000, 100.0, 9100.0, 17)), 2500.0
+    L = synth.make_lines(synth.ListSpec(4200, 960.0, 1050.0, 17))
+    rng = np.random.default_rng(17)
+    if kind == "cluster":       # nearly all lines in one narrow band, a few thin ones around
+        L["nu0"] = np.where(np.arange(4200) < 4160, 1011.0 + 0.02 * rng.random(4200), L["nu0"])
+    elif kind == "short_cut":   # the cut splits chunks, rows and the tile
+        L["nu0"] = 1000.0 + 2.0 * rng.random(4200)
+    order = np.argsort(L["nu0"], kind="stable")
+    return {k: v[order] for k, v in L.items()}, {"cluster": 25.0, "short_cut": 0.9}[kind]
+
+
+@pytest.mark.parametrize("rule", ["fixed", "min_fwhm"])
+@pytest.mark.parametrize("kind", ["sparse", "cluster", "short_cut"])
+def test_fp64_chunks(ctx, kind, rule):
+    from paper_2510_20870_amd import xsec as X
+    L, cut = _chunk_list(kind)
+    grid = (3000.0 if kind == "sparse" else 1000.0) + 0.01 * np.arange(261, dtype=np.float64)
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    pts = [(1e-4, 500.0), (0.3, 1500.0), (80.0, 700.0)]
+    cutk = X.XS_CUT_FIXED if rule == "fixed" else X.XS_CUT_MIN_FWHM
+    for P in (1, 2, 4):
+        for split in (1, 3):
+            o = ctx.opts(cutk, cut, 100.0, X.XS_FP64, P, split)
+            full = ctx.compute(h, g, pts, o)
+            o.select_eps = 1e-4
+            part = ctx.compute(h, g, pts, o)
+            for k, (p, t) in enumerate(pts):
+                ref = O.sigma(L, grid, p, t, 16.0, cut_kind=rule, cut_cm1=cut, fwhm_mult=100.0)
+                st = O.compare(full[k], ref, rel_tol=2e-8)
+                assert st["violations"] == 0, (P, split, pts[k], st)
+                assert np.all(part[k] <= ref * (1.0 + 2e-8)), (P, split, pts[k])
+                assert np.all(part[k] >= ref * (1.0 - 1e-4 - 2e-8)), (P, split, pts[k])
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
