@@ -1,5 +1,6 @@
 """The point kernel at the edges of what its callers may pass, against the FP64 oracle: grid
-points at and below zero, pressures so low that a profile's wing leaves FP32's range.
+points at and below zero, pressures so low that a profile's wing leaves FP32's range, gaps
+between the points of a group.
 Tolerances: the FP32 path's own error (K within 6e-7, sums below
 1e-6, moments within 5e-8 of each contribution) stays below 2e-6; the FP64 path's core (8.5e-9)
 below 2e-8."""
@@ -67,5 +68,32 @@ def test_tiny_pressures(ctx, P):
     assert rel.max() < 2e-6
     st = O.compare(sig, ref, rel_tol=2e-6)
     assert st["violations"] == 0, st
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("rule", ["fixed", "min_fwhm"])
+@pytest.mark.parametrize("split", [0, 1, 3])
+def test_seams_of_a_grid(ctx, rule, split, f64):
+    """Groups of points that span gaps of the grid: two bands that meet inside a group, a lone
+    point between bands, gaps of just under and just over two cuts, steps wider than two cuts."""
+    from paper_2510_20870_amd import xsec as X
+    cut = 4.0
+    L = synth.make_lines(synth.ListSpec(500_000, 1000.0, 1200.0, 12))
+    grid = np.concatenate([1001.0 + 0.01 * np.arange(21), 1050.0 + 0.01 * np.arange(10), [1061.0],
+                           1070.0 + 0.01 * np.arange(30), 1078.29 + 8.0 * np.arange(3),
+                           1103.0 + 0.01 * np.arange(9) + 8.01 * np.arange(9), [1199.0, 1202.0]])
+    pts = [(1e-3, 500.0), (0.3, 1500.0), (60.0, 700.0)]
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    kind = X.XS_CUT_FIXED if rule == "fixed" else X.XS_CUT_MIN_FWHM
+    o = ctx.opts(kind, cut, 100.0, X.XS_FP64 if f64 else X.XS_FP32_KAHAN, split=split)
+    sig = ctx.compute(h, g, pts, o)
+    for k, (P, T) in enumerate(pts):
+        ref = O.sigma(L, grid, P, T, 16.0, cut_kind=rule, cut_cm1=cut, fwhm_mult=100.0)
+        st = O.compare(sig[k], ref, rel_tol=2e-8 if f64 else 2e-6)
+        print(f"[seams] {rule} f64={f64} split {split} P={P} max_rel {st['max_rel']:.2e}",
+              flush=True)
+        assert st["violations"] == 0, (pts[k], st)
     ctx.unload_lines(h)
     ctx.free_grid(g)
