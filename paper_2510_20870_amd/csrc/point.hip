@@ -251,6 +251,25 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
                               [&](double c) { return right ? c > v1 + cut_hi + ulp
                                                            : c >= v0 - cut_hi - ulp; }, lane);
   const int e0 = half(end, 0), e1 = half(end, 1);
+  // lane kRep p holds point p's sum
+  constexpr int kRep = kWave / R;
+  auto put = [&](double t) {
+    const int p = lane / kRep;
+    if (lane % kRep != 0 || p >= jn) return;
+    if (A.split > 1) {
+      ((double*)A.out)[((int64_t)k * A.split + s) * A.n_grid + j0 + p] = t;
+    } else {
+      const int64_t o = (int64_t)(A.pt0 + k) * A.n_grid + j0 + p;
+      if (A.out_f32) ((float*)A.out)[o] = (float)t;
+      else ((double*)A.out)[o] = t;
+    }
+  };
+  // No line in reach (a grid beyond its list's ends or in a gap of it). (24 (P, T) points of 1e5
+  // points, 40 % of them past the list: 1.02 ms with the walks below, 0.97 so.)
+  if (e0 >= e1) {
+    put(0.0);
+    return;
+  }
   // A group across a gap of the grid wider than two cuts (the seam of two bands): most lines
   // between its points reach none, and nothing is inside every cut, so the lines within each
   // point's own cut are summed one by one. (4004 points in two bands 4000 cm^-1 apart, 1050
@@ -714,18 +733,7 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
     }
   }
 
-  const double t = wave_sums<R>(acc, lane);
-  constexpr int kRep = kWave / R;
-  const int p = lane / kRep;
-  if (lane % kRep == 0 && p < jn) {
-    if (A.split > 1) {
-      ((double*)A.out)[((int64_t)k * A.split + s) * A.n_grid + j0 + p] = t;
-    } else {
-      const int64_t o = (int64_t)(A.pt0 + k) * A.n_grid + j0 + p;
-      if (A.out_f32) ((float*)A.out)[o] = (float)t;
-      else ((double*)A.out)[o] = t;
-    }
-  }
+  put(wave_sums<R>(acc, lane));
 }
 
 hipError_t launch_point(const PointArgs& A, int moments, hipStream_t st) {

@@ -97,3 +97,24 @@ def test_seams_of_a_grid(ctx, rule, split, f64):
         assert st["violations"] == 0, (pts[k], st)
     ctx.unload_lines(h)
     ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("split", [0, 2])
+def test_beyond_the_list(ctx, split, f64):
+    """Points with no line in reach read 0, those at the edge of the cut do not; float32 and
+    float64 rows."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(40_000, 1000.0, 1010.0, 12))
+    grid = 985.0 + 0.03 * np.arange(2001, dtype=np.float64)
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    ref = O.sigma(L, grid, 0.1, 700.0, 16.0, cut_cm1=8.0)
+    for out in (X.XS_F64, X.XS_F32):
+        o = ctx.opts(0, 8.0, 100.0, X.XS_FP64 if f64 else X.XS_FP32_KAHAN, split=split,
+                     out_dtype=out)
+        sig = ctx.compute(h, g, [(0.1, 700.0)], o)[0].astype(np.float64)
+        assert np.array_equal(sig == 0.0, ref == 0.0) and np.sum(ref == 0.0) > 500
+        st = O.compare(sig, ref, rel_tol=2e-8 if f64 and out == X.XS_F64 else 2e-6)
+        assert st["violations"] == 0, st
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
