@@ -266,8 +266,9 @@ static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, s
   // fewer lines: by a rule on the whole call, so only where the split follows from the whole
   // call too (with a given split a row's bits are its own point's alone)
   if (o.split || o.cutoff_kind != XS_CUT_FIXED || (int64_t)L.n < kMomentList) return false;
-  const int64_t groups = ((int64_t)G.n + kPointGroup - 1) / kPointGroup;
-  if (lines < kMomentFewLines && groups * (int64_t)npts > kMomentGroups) return false;
+  const int64_t groups = ((int64_t)G.n + kPointGroup - 1) / kPointGroup * (int64_t)npts;
+  if (lines < kMomentLines1 && groups > kMomentGroups1) return false;
+  if (lines < kMomentLines2 && groups > kMomentGroups2) return false;
   const int64_t tile = (int64_t)kWave * (o.pts_per_lane ? o.pts_per_lane : 1);
   for (size_t k = 0; k < npts; ++k)
     if (is_wide(G, o, plan_bounds(L, pts[k]), tile)) return false;

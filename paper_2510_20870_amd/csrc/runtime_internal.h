@@ -40,16 +40,20 @@ constexpr int64_t kServeItemLines = 4096;
 // Far field by moments: from kMomentLines lines within the cut of the grid's middle with any
 // options that allow it; with fewer, for a fixed cut and no wide point (kWideTiles), from
 // kMomentList lines in the list. There a call that does not fill the device wins by its shorter
-// chains, a large one only where a window holds so many lines that walking them costs more than
-// the point kernel's searches and sums (some 0.5 ns per point): with fewer than kMomentFewLines,
-// up to kMomentGroups groups of points in all. Measured with a fixed cut (us, tile kernel alone /
-// by moments; 3e4, 2e5 and 1e6 points): 100 lines in the window 68 / 41, 151 / 140, 251 / 550;
-// 500 lines 82 / 46, 181 / 173, 377 / 687; 2000 lines 147 / 51, 255 / 201, 748 / 810; 5000 lines
-// 217 / 64, 401 / 225, 1502 / 943; 15000 lines 404 / 79, 848 / 275, 3787 / 1466. A FWHM cut with
-// 6550 lines goes from 224 to 417 (the lines that only some points reach are far too few per
-// block), a wide point has nearly all lines beside it.
-constexpr int64_t kMomentLines = 16384, kMomentFewLines = 4096, kMomentList = 512;
-constexpr int64_t kMomentGroups = 25000;
+// chains, a larger one only where a window holds so many lines that walking them costs more
+// than the point kernel's searches and sums (some 0.5 ns per point): beyond kMomentGroups1 groups
+// of points in all from kMomentLines1 lines on, beyond kMomentGroups2 from kMomentLines2.
+// Measured with a fixed cut (us, tile kernel alone / by moments; one (P, T) point of 3e4, 2e5, 1e6
+// grid points): 100 lines in the window 68 / 41, 151 / 140, 251 / 550; 500 lines 82 / 46,
+// 181 / 173, 377 / 687; 2000 lines 147 / 51, 255 / 201, 748 / 810; 5000 lines 217 / 64, 401 / 225,
+// 1502 / 943; 15000 lines 404 / 79, 848 / 275, 3787 / 1466; tables of 8 x 1e5, 24 x 1e5 and
+// 8 x 4e5: 3000 lines 612 / 498, 1075 / 1332, 1066 / 1726; 5000 lines 936 / 535, 1696 / 1438,
+// 1553 / 1857; 8000 lines 1412 / 582, 2640 / 1599, 2284 / 2017. A FWHM cut with 6550 lines goes
+// from 224 to 417 (the lines that only some points reach are far too few per block), a wide point
+// has nearly all lines beside it.
+constexpr int64_t kMomentLines = 16384, kMomentList = 512;
+constexpr int64_t kMomentLines1 = 3072, kMomentGroups1 = 25000;
+constexpr int64_t kMomentLines2 = 6144, kMomentGroups2 = 125000;
 // Small calls of that kind keep the tree low, as each three of its levels are a launch of some
 // 20 us: the fewest levels that leave at most kTopNodes nodes in a window, for at most
 // kFewGroups groups of points.

@@ -38,17 +38,18 @@ def _check(ctx, L, grid, pts, o, idx=None, tol=2e-6, rule="fixed"):
 
 
 @pytest.mark.parametrize("f64", [False, True])
-@pytest.mark.parametrize("n,m,moments", [
-    (2000, 200_000, True), (2000, 200_001, False),     # 10 lines in a window: by the groups
-    (950_000, 200_001, True),                          # 5000 lines: by moments all the same
+@pytest.mark.parametrize("n,m,rows,moments", [
+    (2000, 200_000, 1, True), (2000, 200_001, 1, False),   # 10 lines in a window
+    (950_000, 200_001, 1, True),                           # 5000 lines
+    (950_000, 100_000, 10, True), (950_000, 100_000, 11, False),
 ])
-def test_few_lines_many_points(ctx, n, m, moments, f64):
+def test_few_lines_many_points(ctx, n, m, rows, moments, f64):
     from paper_2510_20870_amd import xsec as X
     L = synth.make_lines(synth.ListSpec(n, 500.0, 10000.0, 3))
     grid = 2000.0 + 0.005 * np.arange(m, dtype=np.float64)
     prec = X.XS_FP64 if f64 else X.XS_FP32_KAHAN
     idx = np.linspace(0, m - 1, 300).astype(np.int64)
-    pts = [(0.1, 900.0)]
+    pts = [(0.1, 900.0 + k) for k in range(rows)]
     sig = _check(ctx, L, grid, pts, ctx.opts(0, 25.0, 100.0, prec), idx, 2e-8 if f64 else 2e-6)
     # by the tile kernel (a cut this wide groups tiles on the FP32 path) with any split
     h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
