@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <set>
@@ -91,6 +92,10 @@ struct Plan {
                                   // (else the point kernel)
   bool any_tile = false;
   int tile_split = 1;             // line splits of the points by tiles
+  // the point kernel's groups of points in a tile of 64 P points
+  int64_t groups_per_tile() const {
+    return std::max<int64_t>(1, std::min<int64_t>(kWave * P, n_grid + kPointGroup - 1) / kPointGroup);
+  }
   bool chunks = false;            // FP64 tile kernel: chunks of lines by their moments
   int max_split() const { return any_tile && tile_split > split ? tile_split : split; }
   TreeDims dims{};

@@ -431,7 +431,8 @@ int xs_autotune(xs_ctx* c, xs_lines_t lh, xs_grid_t gh, const xs_pt* pts, size_t
   const Plan p = make_plan(*c, *L, *G, pts, npts, o);
   memset(out, 0, sizeof *out);
   out->pts_per_lane = p.P;
-  out->split = p.split;
+  // (as an option: per tile)
+  out->split = (int)std::min<int64_t>(kMaxSplit, p.split * (p.moments ? p.groups_per_tile() : 1));
   out->waves_per_simd = waves_option(p.W);
   out->items_per_slot = v.ips;
   out->probe_ms = best.ms;

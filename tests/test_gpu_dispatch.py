@@ -97,3 +97,31 @@ def test_fp64_chunks(ctx, kind, rule):
                 assert np.all(part[k] >= ref * (1.0 - 1e-4 - 2e-8)), (P, split, pts[k])
     ctx.unload_lines(h)
     ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("m", [5, 13, 700])
+def test_given_splits(ctx, m, f64):
+    """A given split counts the parts of a tile of 64 points per lane; the point kernel's groups of
+    8 points are parts of it already."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(40_000, 970.0, 1035.0, 91))
+    grid = 1000.0 + 0.01 * np.arange(m, dtype=np.float64)
+    prec = X.XS_FP64 if f64 else X.XS_FP32_KAHAN
+    pts = [(0.3, 1500.0), (80.0, 700.0)]   # 0.3 bar: by the point kernel
+    ref = [O.sigma(L, grid, p, t, 16.0, cut_cm1=25.0) for p, t in pts]
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    rows = {}
+    for P in (1, 2):
+        for split in (1, 2, 8, 9, 17, 256):
+            sig = ctx.compute(h, g, pts, ctx.opts(0, 25.0, 100.0, prec, P, split))
+            for k in range(2):
+                st = O.compare(sig[k], ref[k], rel_tol=2e-8 if f64 else 2e-6)
+                assert st["violations"] == 0, (P, split, pts[k], st)
+            rows[P, split] = sig[0]
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
+    for P, split in ((1, 2), (1, 8), (1, 9), (2, 17)):
+        c = min(8 * P, (m + 7) // 8)
+        one = -(-split // c) == 1
+        assert np.array_equal(rows[P, split], rows[P, 1]) == one, (P, split)
