@@ -241,10 +241,16 @@ void Plan::set_tree(int max_levels) {
   }
 }
 
-// The grid step at the grid's middle.
-static double mid_step(const GridRes& G) {
-  const size_t m = std::min<size_t>(G.n / 2, G.n >= 2 ? G.n - 2 : 0);
-  return G.n >= 2 ? G.host[m + 1] - G.host[m] : 0.0;
+// The grid's step: the median of five, so that a gap at one of them does not count.
+static double usual_step(const GridRes& G) {
+  if (G.n < 2) return 0.0;
+  double d[5];
+  for (size_t i = 0; i < 5; ++i) {
+    const size_t m = std::min<size_t>(G.n * (2 * i + 1) / 10, G.n - 2);
+    d[i] = G.host[m + 1] - G.host[m];
+  }
+  std::nth_element(d, d + 2, d + 5);
+  return d[2];
 }
 // Distance within which the lines at (P, T) are summed one by one, at the grid's middle, and
 // whether that is many tiles.
@@ -252,8 +258,8 @@ static double near_distance(const GridRes& G, const xs_opts& o, const PtBounds& 
   const size_t m = std::min<size_t>(G.n / 2, G.n >= 2 ? G.n - 2 : 0);
   return kFarTheta * (pb.gmax + (o.precision == XS_FP64 ? kBetaFp64 : kBetaFp32) * pb.kb * G.host[m]);
 }
-static bool is_wide(const GridRes& G, const xs_opts& o, const PtBounds& pb, int64_t tile) {
-  return near_distance(G, o, pb) > kWideTiles * (double)tile * mid_step(G);
+static bool is_wide(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
+  return near_distance(G, o, pb) > kWideSteps * usual_step(G);
 }
 
 // Far field by moments, chosen where a point's window holds enough lines beyond its near
@@ -269,9 +275,8 @@ static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, s
   const int64_t groups = ((int64_t)G.n + kPointGroup - 1) / kPointGroup * (int64_t)npts;
   if (lines < kMomentLines1 && groups > kMomentGroups1) return false;
   if (lines < kMomentLines2 && groups > kMomentGroups2) return false;
-  const int64_t tile = (int64_t)kWave * (o.pts_per_lane ? o.pts_per_lane : 1);
   for (size_t k = 0; k < npts; ++k)
-    if (is_wide(G, o, plan_bounds(L, pts[k]), tile)) return false;
+    if (is_wide(G, o, plan_bounds(L, pts[k]))) return false;
   return true;
 }
 
@@ -346,14 +351,14 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     // takes the near lines that are far from it (about 2 instructions per line and 64
     // points, against 30 in the point kernel)
     // (only with one cut for every line: the far kernel's rule)
-    const double step = mid_step(G);
+    const double step = usual_step(G);
     double widest = 0.0;
     p.by_tile.resize(npts);
     for (size_t k = 0; k < npts; ++k) {
       const PtBounds pb = plan_bounds(L, pts[k]);
       const double d = near_distance(G, o, pb);
       const CutDev cd = cut_dev(o);
-      p.by_tile[k] = is_wide(G, o, pb, tile) &&
+      p.by_tile[k] = is_wide(G, o, pb) &&
                      cut_at(cd, pb.gmin, pb.kb * std::max(0.0, G.first - o.cut_cm1), false) >=
                          o.cut_cm1;
       p.any_tile = p.any_tile || p.by_tile[k];

@@ -39,7 +39,7 @@ constexpr int64_t kSampleStride = 1024;
 constexpr int64_t kServeItemLines = 4096;
 
 // Far field by moments: from kMomentLines lines within the cut of the grid's middle with any
-// options that allow it; with fewer, for a fixed cut and no wide point (kWideTiles), from
+// options that allow it; with fewer, for a fixed cut and no wide point (kWideSteps), from
 // kMomentList lines in the list. There a call that does not fill the device wins by its shorter
 // chains, a larger one only where a window holds so many lines that walking them costs more
 // than the point kernel's searches and sums (some 0.5 ns per point): beyond kMomentGroups1 groups
@@ -59,8 +59,10 @@ constexpr int64_t kMomentLines2 = 6144, kMomentGroups2 = 125000;
 // 20 us: the fewest levels that leave at most kTopNodes nodes in a window, for at most
 // kFewGroups groups of points.
 constexpr int64_t kFewGroups = 16384, kTopNodes = 512;
-// (P, T) points whose near range reaches this many tiles on each side go by tiles.
-constexpr double kWideTiles = 6.0;
+// (P, T) points whose near range reaches this many grid steps on each side go by tiles, whatever
+// the tile's size (with 4 or 8 points per lane a limit of so many tiles kept points at 50 bar in
+// the point kernel: 10000 points, 3750 lines/cm^-1, 1057 us, by tiles of 4 points per lane 588).
+constexpr double kWideSteps = 384.0;
 
 struct GridRes {
   double* d = nullptr;

@@ -125,3 +125,30 @@ def test_given_splits(ctx, m, f64):
         c = min(8 * P, (m + 7) // 8)
         one = -(-split // c) == 1
         assert np.array_equal(rows[P, split], rows[P, 1]) == one, (P, split)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("kind", ["uniform", "gap"])
+def test_broad_points_whatever_the_tile(ctx, kind, f64):
+    """(P, T) points with broad lines go by tiles for every number of points per lane (ragged
+    tiles, two points of which one is narrow), a gap at the grid's middle or not: rows against
+    the oracle, and the same with more parts."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(60_000, 970.0, 1060.0, 91))
+    grid = 1000.0 + 0.01 * np.arange(700, dtype=np.float64)
+    if kind == "gap":
+        grid[350:] += 20.0
+    prec = X.XS_FP64 if f64 else X.XS_FP32_KAHAN
+    pts = [(80.0, 700.0), (0.3, 1500.0), (100.0, 400.0)]
+    ref = [O.sigma(L, grid, p, t, 16.0, cut_cm1=25.0) for p, t in pts]
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    for P in (1, 2, 4, 8):
+        for split in (0, 1, 3):
+            sig = ctx.compute(h, g, pts, ctx.opts(0, 25.0, 100.0, prec, P, split))
+            for k in range(len(pts)):
+                st = O.compare(sig[k], ref[k], rel_tol=2e-8 if f64 else 2e-6)
+                print(f"[broad points] {kind} f64={f64} P={P} split {split} {pts[k]} "
+                      f"max_rel {st['max_rel']:.2e}", flush=True)
+                assert st["violations"] == 0, (P, split, pts[k], st)
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
