@@ -259,7 +259,10 @@ static double near_distance(const GridRes& G, const xs_opts& o, const PtBounds& 
   return kFarTheta * (pb.gmax + (o.precision == XS_FP64 ? kBetaFp64 : kBetaFp32) * pb.kb * G.host[m]);
 }
 static bool is_wide(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
-  return near_distance(G, o, pb) > kWideSteps * usual_step(G);
+  // (one point has no step: by what the point kernel would sum one by one. 1050 lines/cm^-1 within
+  // 25 cm^-1: 0.1 bar 70 us by the point kernel, 209 by tiles; 100 bar 134 and 82)
+  const double d = near_distance(G, o, pb);
+  return G.n > 1 ? d > kWideSteps * usual_step(G) : d > 0.25 * o.cut_cm1;
 }
 
 // Far field by moments, chosen where a point's window holds enough lines beyond its near

@@ -152,3 +152,18 @@ def test_broad_points_whatever_the_tile(ctx, kind, f64):
                 assert st["violations"] == 0, (P, split, pts[k], st)
     ctx.unload_lines(h)
     ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("rule", ["fixed", "min_fwhm"])
+def test_one_point(ctx, rule, f64):
+    """Grids of one point, narrow and broad lines."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(60_000, 970.0, 1035.0, 91))
+    kind = X.XS_CUT_FIXED if rule == "fixed" else X.XS_CUT_MIN_FWHM
+    for nu in (1003.3, 946.0, 1020.25):
+        for split in (0, 1, 5):
+            o = ctx.opts(kind, 25.0, 100.0, X.XS_FP64 if f64 else X.XS_FP32_KAHAN, split=split)
+            _check(ctx, L, np.array([nu]), [(1e-3, 500.0), (0.1, 900.0), (20.0, 800.0),
+                                            (100.0, 400.0)], o, tol=2e-8 if f64 else 2e-6,
+                   rule=rule)
