@@ -390,6 +390,8 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
       // points by tiles: two rounds of wavefront slots, of at least four chunks each
       const int64_t wide = std::count(p.by_tile.begin(), p.by_tile.end(), 1);
       sp = ((int64_t)c.n_cu * 56 + p.n_units * wide - 1) / (p.n_units * wide);
+      if (max_item_lines > 0)
+        sp = std::max<int64_t>(sp, (max_window + max_item_lines - 1) / max_item_lines);
       sp = std::min<int64_t>(sp, std::max<int64_t>(1, max_window / (4 * kWave)));
       p.tile_split = (int)std::max<int64_t>(1, std::min<int64_t>(sp, kMaxSplit));
     }

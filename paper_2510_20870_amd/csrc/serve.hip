@@ -207,7 +207,11 @@ void Server::build_steps(Request& r) const {
   const double pts_per_unit = (double)(kWave * p.P * p.group);
   for (int pt0 = 0; pt0 < p.npts; pt0 += p.pt_batch) {
     const int nb = std::min(p.pt_batch, p.npts - pt0);
-    const int64_t items_per_unit = (int64_t)nb * p.split * p.group;
+    // (the point kernel's groups of a tile count as one: together they do a tile's work)
+    int64_t items_per_unit = (int64_t)nb * p.split * p.group;
+    if (p.any_tile)
+      for (int k = 0; k < nb; ++k)
+        if (p.by_tile[pt0 + k]) items_per_unit += p.tile_split - p.split;
     int64_t c0 = 0;
     double acc = 0.0;
     bool first = true;
