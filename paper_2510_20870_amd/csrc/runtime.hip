@@ -370,6 +370,9 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     // lines that one group of points sums one by one
     const double width = 2.0 * std::min(widest, o.cut_cm1) + kPointGroup * step;
     max_window = (int64_t)((double)window_lines(L, G, o) * std::min(1.0, width / (2.0 * o.cut_cm1)));
+    // what a unit costs is the near lines and, for the searches and the tree, as much as some
+    // 3000 lines more
+    for (int64_t& t : cost) t = std::min(t, (max_window + 3000) / kSampleStride + 1);
   }
   if (o.split) {
     // work items per tile of 64 P points, of which the point kernel has as many as the tile has

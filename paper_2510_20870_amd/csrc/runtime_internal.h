@@ -85,7 +85,8 @@ struct Plan {
   int npts = 0;
   int pt_batch = 1;        // (P, T) points per parameter/tile launch pair
   std::vector<int> tile_order;   // units by decreasing estimated work
-  std::vector<int64_t> tile_cost;  // sampled line count in each unit's window (x 1024)
+  std::vector<int64_t> tile_cost;  // estimated lines of each unit (x 1024): in its window, or
+                                   // by moments near it
   bool tuned = false;              // launch shape from the tuning cache
   double select_eps = 0.0;         // main-contributor selection (0: off)
   // Far field by moments (far_tree.h): the tree over the records, 0 moments: off.

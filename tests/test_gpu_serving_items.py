@@ -1,5 +1,6 @@
-"""Work items of served requests with broad lines: at most 4096 lines each, as for the others.
-The number of parts is told from the bits of calls with that split given."""
+"""Served requests by moments. Work items of broad lines: at most 4096 lines each, as for the
+others (the number of parts is told from the bits of calls with that split given). Order: the
+request with the least work left goes first, a request by moments counting what it costs."""
 import numpy as np
 import pytest
 
@@ -45,3 +46,25 @@ def test_broad_requests_in_short_items(ctx):
     assert st["violations"] == 0, st
     ctx.unload_lines(h)
     ctx.free_grid(g)
+
+
+def test_least_work_first(ctx):
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(600_000, 970.0, 1130.0, 5))
+    h = ctx.load_lines(L, 16.0)
+    ctx.serve_start(max_inflight=1, mem_bytes=4 << 30, paused=True)
+    pts = [(0.1, 900.0)]
+    # selection walks all 190000 lines of every window; the full sum on four times the points
+    # goes by moments and takes a tenth of the time
+    slow = ctx.submit_window(h, 1030.0, 0.002, 10_000, pts,
+                             ctx.opts(X.XS_CUT_FIXED, 25.0, select_eps=1e-4))
+    fast = ctx.submit_window(h, 1030.0, 0.0005, 40_000, pts, ctx.opts(X.XS_CUT_FIXED, 25.0))
+    ctx.serve_pause(False)
+    a, b = slow.wait(60.0), fast.wait(60.0)
+    assert np.all(np.isfinite(a)) and np.all(np.isfinite(b))
+    t_slow, t_fast = slow.times(), fast.times()
+    print(f"[order] slow {t_slow} fast {t_fast}", flush=True)
+    assert t_fast[2] < t_slow[2]
+    slow.release()
+    fast.release()
+    ctx.unload_lines(h)
