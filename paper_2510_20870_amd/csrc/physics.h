@@ -8,7 +8,8 @@
 // is computed in the same operation order as a plain evaluation of the textbook formula,
 // with contraction disabled for the whole library (-ffp-contract=off) and IEEE sqrt, so
 // that it agrees with any other careful FP64 evaluation to the last bit except where the
-// power function (here exp(n ln(T_ref/T))) itself differs by an ulp.
+// power function (here exp of n ln(T_ref/T), the logarithm in two parts: power_ln) itself
+// differs by an ulp.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -73,6 +74,42 @@ __host__ __device__ inline double partition_q(const SpeciesDev& sp, double T) {
   return sp.q_val[lo] + t * (sp.q_val[hi] - sp.q_val[lo]);
 }
 
+// ln(t), t > 0 and finite, as hi + lo to 2^-59: t = 2^k m with m in [sqrt(1/2), sqrt(2)),
+// ln m = 2 atanh(s) = 2 s + 2 s^3 / 3 + 2 s^5 / 5 + ..., s = (m - 1)/(m + 1) (|s| < 0.172: the terms
+// to s^23 leave 1e-19), the quotient's and the cube's rounding errors carried along.
+__host__ __device__ inline void log_two(double t, double* hi, double* lo) {
+  constexpr double kLn2Hi = 0x1.62e42fefa2000p-1;   // 13 zero bits at the end: k kLn2Hi is exact
+  constexpr double kLn2Lo = 0x1.9ef35793c7673p-41;  // ln 2 - kLn2Hi
+  int k;
+  double m = frexp(t, &k);
+  if (m < 0.70710678118654752440) {
+    m *= 2.0;
+    --k;
+  }
+  const double f = m - 1.0;                        // exact
+  const double d = m + 1.0, dl = m - (d - 1.0);    // d + dl = m + 1
+  const double s = f / d, sl = (fma(-s, d, f) - s * dl) / d;
+  const double z = s * s, c = z * s;
+  const double cl = fma(z, s, -c) + fma(s, s, -z) * s;   // c + cl = s^3
+  double p = 2.0 / 23.0;
+  for (int j = 21; j >= 5; j -= 2) p = fma(p, z, 2.0 / j);
+  constexpr double kC = 2.0 / 3.0, kCl = 0x1.5555555555555p-55;   // kC + kCl = 2/3
+  const double q = kC * c, ql = fma(kC, c, -q) + fma(kC, cl, kCl * c);
+  const double a = k * kLn2Hi, b = 2.0 * s, h = a + b, v = h - a;
+  // smallest first; the quotient's error enters with the derivative 2 / (1 - s^2)
+  const double l = ((k * kLn2Lo + fma(z * c, p, ql)) + 2.0 * fma(sl, z, sl)) + q +
+                   ((a - (h - v)) + (b - v));
+  *hi = h + l;
+  *lo = l - (*hi - h);
+}
+// t^n from ln(t) = hi + lo, as exact as the power function (a logarithm rounded to one double
+// would add |n ln t| half-units in the last place), at the cost of exp.
+__host__ __device__ inline double power_ln(double n, double hi, double lo) {
+  const double x = n * hi, e = fma(n, hi, -x) + n * lo;
+  const double y = exp(x);
+  return y < HUGE_VAL ? fma(y, e, y) : y;
+}
+
 // Constants of one (P, T) point shared by every line.
 struct PtConst {
   double T, P;
@@ -81,7 +118,7 @@ struct PtConst {
   double dopp;        // sqrt(2 k_B T / (m amu)); b_D = (nu0 / c) * dopp
   double pfac;        // P / P_ref
   double tratio;      // T_ref / T
-  double lnt;         // ln(T_ref / T)
+  double lnt, lnt_lo; // ln(T_ref / T) = lnt + lnt_lo
   double c2t;         // c2 / T
   double s_ein;       // 1 / (8 pi c Q(T))
   double inv_kb;      // c / dopp: 1 / b_D = inv_kb / nu0
@@ -97,7 +134,7 @@ __host__ __device__ inline PtConst make_pt(const SpeciesDev& sp, double P, doubl
   c.dopp = sqrt(2.0 * kKBoltz * T / (sp.mass_amu * kAmu));
   c.pfac = P / sp.P_ref;
   c.tratio = sp.T_ref / T;
-  c.lnt = log(c.tratio);
+  log_two(c.tratio, &c.lnt, &c.lnt_lo);
   c.c2t = kC2 / T;
   c.s_ein = c.inv_q / (8.0 * kPiD * kCcgs);
   c.inv_kb = kCLight / c.dopp;
@@ -140,14 +177,14 @@ __host__ __device__ inline LineParams line_params(const SpeciesDev& sp, const Pt
   lp.bD = nu0 / kCLight * pc.dopp;
   lp.ib = inv * pc.inv_kb;
   if (sp.n_broad == 0) {
-    lp.gL = (double)gam * pc.pfac * exp((double)nT * pc.lnt);
+    lp.gL = (double)gam * pc.pfac * power_ln((double)nT, pc.lnt, pc.lnt_lo);
   } else {
     // the partners' widths at the line's J, weighted by their mixing ratios
     const int j = (int)J < sp.broad_nj ? (int)J : sp.broad_nj - 1;
     double s = 0.0;
     for (int b = 0; b < sp.n_broad; ++b) {
       const int t = b * sp.broad_nj + j;
-      s += sp.broad_vmr[b] * sp.broad_gam[t] * exp(sp.broad_n[t] * pc.lnt);
+      s += sp.broad_vmr[b] * sp.broad_gam[t] * power_ln(sp.broad_n[t], pc.lnt, pc.lnt_lo);
     }
     lp.gL = s * pc.pfac;
   }
