@@ -479,7 +479,8 @@ int xs_eval_bounds_host(const double *x, const double *y, size_t n, double *K_lo
  * its nearest point, any y: r^2 >= 2738.6 at the default budget), with every point of the
  * tile inside the cut, is summed as a polynomial of degree 13 in the tile coordinate
  * t in [-1, 1] when |X| >= kappa H + 1.25, X being x at the tile's centre and H the tile's
- * half-width in Doppler units; eps and kappa are those of budget `tol` (as xs_opts.tol: 0
+ * half-width in Doppler units, or for a line with y^2 > 3/2, which may then lie inside the tile
+ * (nearest point x = 0), when max(|X| - 1.25, 0)^2 + y^2 - 3/2 >= (kappa H)^2; eps and kappa are those of budget `tol` (as xs_opts.tol: 0
  * the default, eps = 2e-7 and kappa = 4.09) (section
  * "Functionality of pyROX": the profile of every line inside the cutoff, here summed per
  * tile instead of per point). Where the shifted Lorentzian (y / sqrt(pi)) /

@@ -157,7 +157,7 @@ struct TileArgs {
   const double* far;
   int chunks;             // FP64 path without near: chunks of lines by their moments
   // error budget of the shifted forms (shifted_lorentz_ok, dshift_ok) and the far-line
-  // threshold kappa (far_ok) for that budget
+  // threshold kappa (far_line_ok) for that budget
   float l1_eps, far_kappa;
 };
 

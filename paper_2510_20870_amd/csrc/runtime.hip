@@ -1659,10 +1659,10 @@ int xs_eval_far_host(const double* X, const double* H, const double* y, const do
   for (size_t i = 0; i < n; ++i) {
     const float xf = (float)X[i], hf = (float)H[i], yf = (float)y[i], tf = (float)t[i];
     const float y2 = yf * yf;
-    const float xn = fabsf(xf) - hf;   // the nearest point of the tile
+    const float xn = fmaxf(fabsf(xf) - hf, 0.0f);   // the nearest point of the tile
     const float r2n = fmaf(xn, xn, y2);
-    if (!(yf > 0.0f) || !(hf >= 0.0f) || !(fabsf(tf) <= 1.0f) || !far_ok(xf, hf, kappa) ||
-        !(xn >= 0.0f) || !dshift_ok(r2n, eps))
+    if (!(yf > 0.0f) || !(hf >= 0.0f) || !(fabsf(tf) <= 1.0f) || !far_line_ok(xf, hf, y2, kappa) ||
+        !dshift_ok(r2n, eps))
       return fail(XS_EINVAL, "case %zu (X %g, H %g, y %g, t %g) is not a far line", i, X[i],
                   H[i], y[i], t[i]);
     const bool ds = !shifted_lorentz_ok(y2, r2n, eps);

@@ -204,12 +204,7 @@ XS_HD float asym_scaled_v(int v, float y2, float r2) {
 constexpr int kFarDeg = 13;
 constexpr float kFarMargin = 1.25f;   // >= sqrt(3/2)
 
-// Whether a line at tile-centre x and half-width h (both Doppler units) may be expanded.
-XS_HD bool far_ok(float x, float h, float kappa) {
-  return fabsf(x) >= fmaf(kappa, h, kFarMargin);
-}
-
-// The same for a line of any width (y2 = y^2).
+// Whether a line at tile-centre x and half-width h (both Doppler units), y2 = y^2, may be expanded.
 XS_HD bool far_line_ok(float x, float h, float y2, float kappa) {
   const float ax = fmaxf(fabsf(x) - kFarMargin, 0.0f), kh = kappa * h;
   return fmaf(ax, ax, fmaxf(y2 - 1.5f, 0.0f)) >= kh * kh;

@@ -499,3 +499,42 @@ def test_fixed_resolving_power_grid():
                 (1.0, 1e6, 1e9)):
         with pytest.raises(xsec.XsError):
             xsec.wavelength_grid(*bad)
+
+
+@pytest.mark.parametrize("tol", [0.0, LOOSE_TOL])
+def test_far_line_polynomial_broad(tol):
+    # lines that qualify by their width alone, beside the tile and inside it, at the edge of the
+    # condition and well past it: against the closed form that is expanded. Truncation within
+    # 0.65 of the budget, FP32 rounding as for the lines beside the tile (1e-6 with the loose
+    # budget, else 5.7e-7 of a total of 7e-7)
+    eps, kappa = (tol or 2e-7), (LOOSE_KAPPA if tol else DEFAULT_KAPPA)
+    rng = np.random.default_rng(57)
+    n = 600_000
+    H = 10 ** rng.uniform(-1, 4, n)
+    X = kappa * H * rng.uniform(0, 1, n) ** rng.choice([0.3, 1.0, 3.0], n)
+    X[:2000] = 0.0
+    need = (kappa * H) ** 2 - np.maximum(X - 1.25, 0.0) ** 2 + 1.5
+    y = np.sqrt(np.maximum(need, 2.0)) * (1.0 + 10 ** rng.uniform(-5, 0.7, n))
+    X *= np.where(rng.random(n) < 0.5, -1.0, 1.0)
+    t = rng.uniform(-1, 1, n)
+    t[:4000:4], t[1:4000:4], t[2:4000:4] = -1.0, 1.0, 0.0
+    f32 = lambda a: a.astype(np.float32).astype(np.float64)
+    Xf, Hf, yf, tf = f32(X), f32(H), f32(y), f32(t)
+    r2n = np.maximum(np.abs(Xf) - Hf, 0.0) ** 2 + yf ** 2
+    ok = (np.maximum(np.abs(Xf) - 1.25, 0.0) ** 2 + yf ** 2 - 1.5 >=
+          (kappa * Hf) ** 2 * (1.0 + 1e-5)) & (r2n ** 2 * eps >= 1.5 * (1.0 + 1e-5))
+    ok &= np.abs(Xf) < kappa * Hf + 1.25      # not by their distance
+    Xf, Hf, yf, tf = Xf[ok], Hf[ok], yf[ok], tf[ok]
+    assert np.sum(np.abs(Xf) < Hf) > 100_000 and np.sum(np.abs(Xf) > Hf) > 50_000
+    K, kind = xsec.eval_far_host(Xf, Hf, yf, tf, with_kind=True, tol=tol)
+    r2 = (Xf + Hf * tf) ** 2 + yf ** 2
+    closed = (yf / np.sqrt(np.pi)) / np.where(kind == 1, r2 - 1.5 + 2 * yf * yf / r2, r2 - 1.5)
+    rel = np.abs(K / closed - 1)
+    for k in (0, 1):
+        print(f"broad far polynomial, budget {eps:g}, kind {k}: max {rel[kind == k].max():.3e} "
+              f"of {np.sum(kind == k)}")
+        assert np.sum(kind == k) > 10_000
+    assert rel.max() < (0.65 * tol + 1e-6 if tol else 7e-7)
+    # a line too narrow for its tile is refused
+    with pytest.raises(xsec.XsError):
+        xsec.eval_far_host(0.0, 100.0, kappa * 100.0 * 0.998, 0.5, tol=tol)
