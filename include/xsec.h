@@ -372,9 +372,11 @@ int xs_sched_simulate(size_t n, const double *arrive, const double *duration,
  * grid middle (power of two of the lines within the cut) and the number of P-T points
  * (1, 2..16, more). Every later call with pts_per_lane, split and waves_per_simd all 0
  * uses the cached shape of its class (results then follow that shape, so they agree with
- * untuned runs to FP32 rounding, and bitwise among runs with the same cache). */
+ * untuned runs to FP32 rounding, and bitwise among runs with the same cache). The shape is
+ * that of a walk over whole windows, and timed as such; a call that goes by moments (xs_opts,
+ * tile_group) has a shape of its own, which the cache does not change. */
 typedef struct {
-  int pts_per_lane, split, waves_per_simd;  /* the tuned shape (waves_per_simd 2..6)    */
+  int pts_per_lane, split, waves_per_simd;  /* the shape the call now gets (waves 2..6) */
   int items_per_slot;                       /* the cached class parameter               */
   double probe_ms;                          /* probe time of the tuned shape            */
   double default_probe_ms;                  /* probe time of the untuned default        */

@@ -293,8 +293,12 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   p.select_eps = o.select_eps;
   const bool f64 = o.precision == XS_FP64;
   p.W = waves_target(o.waves_per_simd, p.P, f64);
+  // By moments the shape is that of the tiles of broad (P, T) points: 1 point per lane at 6 waves
+  // per SIMD (10413 points of a 1e9-line list at 100 bar 1567 us, with 5 waves 1617, with 2 points per
+  // lane 2476 to 2633), whatever shape was tuned for walking whole windows.
+  if (p.moments && !f64 && p.P == 1 && o.waves_per_simd == 0) p.W = 6;
   int ips = items_per_slot > 0 ? items_per_slot : 4;
-  if (o.pts_per_lane == 0 && o.split == 0 && o.waves_per_simd == 0) {
+  if (!p.moments && o.pts_per_lane == 0 && o.split == 0 && o.waves_per_simd == 0) {
     // fully automatic launch shape: the tuned one of this workload class, if any
     TuneVal tv;
     if (tune_get(tune_key(c, L, G, npts, o), &tv)) {

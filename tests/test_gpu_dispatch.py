@@ -167,3 +167,23 @@ def test_one_point(ctx, rule, f64):
             _check(ctx, L, np.array([nu]), [(1e-3, 500.0), (0.1, 900.0), (20.0, 800.0),
                                             (100.0, 400.0)], o, tol=2e-8 if f64 else 2e-6,
                    rule=rule)
+
+
+def test_tuned_shapes_are_for_whole_windows(ctx):
+    """A tuned shape changes the calls that walk whole windows; those by moments, also their broad
+    points, keep their own."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(40_000, 970.0, 1035.0, 91))
+    grid = 1000.0 + 0.01 * np.arange(900, dtype=np.float64)
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    pts = [(0.3, 1500.0), (80.0, 700.0)]
+    moments, walk = ctx.opts(0, 25.0), ctx.opts(0, 25.0, tile_group=1)
+    try:
+        a, b = ctx.compute(h, g, pts, moments), ctx.compute(h, g, pts, walk)
+        X.tune_cache_put(ctx.tune_key(h, g, len(pts), moments), 4, 3, 16, 1.0)
+        assert np.array_equal(ctx.compute(h, g, pts, moments), a)
+        assert not np.array_equal(ctx.compute(h, g, pts, walk), b)
+    finally:
+        X.tune_cache_clear()
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
