@@ -88,7 +88,7 @@ __host__ __device__ inline void log_two(double t, double* hi, double* lo) {
   }
   const double f = m - 1.0;                        // exact
   const double d = m + 1.0, dl = m - (d - 1.0);    // d + dl = m + 1
-  const double s = f / d, sl = (fma(-s, d, f) - s * dl) / d;
+  const double id = 1.0 / d, s = f * id, sl = (fma(-s, d, f) - s * dl) * id;
   const double z = s * s, c = z * s;
   const double cl = fma(z, s, -c) + fma(s, s, -z) * s;   // c + cl = s^3
   double p = 2.0 / 23.0;
