@@ -185,33 +185,32 @@ __device__ __forceinline__ double lane_k32_tiny(const DawEntry* tab, double x, d
                                  : (float)voigt_core64_tier(core_tier(y), x, y));
 }
 
+// The LDS of a workgroup, per wavefront but for the table.
+template <int NM>
+struct PointLds {
+  DawEntry tab[NM == kMomFp32 ? kDawNodes : 1];
+  int list[kWavesPerWG][kNodeList];
+  int2 rng[kWavesPerWG][kPointRanges];
+  int part[kWavesPerWG][2][kPointGroup];
+  double cutl[kWavesPerWG][kPointGroup][2 * kLeafLines];
+};
+
+// The sums at the points [r0, r1) of the group from j0 (part s), true when they are stored. RUNS:
+// where a gap between two of them holds more than kGapLines lines that are near neither, the
+// run ends there: r1 is lowered, nothing is stored, and the caller asks again.
 // FW: the lines' cuts differ (min(cap, mult FWHM)). The covered and the reachable lines then
 // follow from bounds of the cut; between them lie leaves of which some lines reach a point and
 // some do not.
-template <int NM, bool FW>
-__global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
+template <int NM, bool FW, bool RUNS>
+__device__ __forceinline__ bool point_run(const PointArgs& A, PointLds<NM>& lds, int lane, int wv,
+                                          int64_t j0, int k, int s, int r0, int& r1) {
   constexpr int R = kPointGroup, NF = node_fields<NM>();
-  __shared__ DawEntry tab[NM == kMomFp32 ? kDawNodes : 1];
-  __shared__ int list[kWavesPerWG][kNodeList];
-  __shared__ int2 rng[kWavesPerWG][kPointRanges];
-  __shared__ int part[kWavesPerWG][2][R];
-  __shared__ double cutl[kWavesPerWG][R][2 * kLeafLines];
-  if constexpr (NM == kMomFp32) {
-    for (int t = threadIdx.x; t < kDawNodes; t += blockDim.x)
-      tab[t] = {kDawF[t], kDawF1[t], kDawE[t], 0.0f};
-    __syncthreads();
-  }
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t item = logical_wg() * kWavesPerWG + wv;
-  if (item >= A.n_groups * A.n_pt * A.split) return;
-  // parts of a group and neighbouring groups of one (P, T) point lie next to each other
-  const int s = (int)(item % A.split);
-  const int64_t gi = item / A.split;
-  const int k = (int)(gi / A.n_groups);
-  const int64_t j0 = (A.g0 + gi % A.n_groups) * R;
-  const int jn = (int)min((int64_t)R, A.n_grid - j0);
-  const double v0 = A.grid[j0], v1 = A.grid[j0 + jn - 1];
+  auto& tab = lds.tab;
+  auto& list = lds.list;
+  auto& rng = lds.rng;
+  auto& part = lds.part;
+  auto& cutl = lds.cutl;
+  const double v0 = A.grid[j0 + r0], v1 = A.grid[j0 + r1 - 1];
   const PtBounds pb = A.bounds[k];
   const double kb = pb.kb;
   const double cap = A.cut.cut;
@@ -221,7 +220,8 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   const double* nodes = A.nodes + (int64_t)k * A.dims.n_nodes * NF;
   auto node = [&](int l, int q) { return node_at<NM>(nodes, A.dims, l, (int64_t)q); };
   // the points: lane p (mod R) holds point p, read back as a wave-uniform value
-  const uint64_t vb = __builtin_bit_cast(uint64_t, A.grid[j0 + min(lane & (R - 1), jn - 1)]);
+  const uint64_t vb =
+      __builtin_bit_cast(uint64_t, A.grid[j0 + min(max(lane & (R - 1), r0), r1 - 1)]);
   auto val = [&](int p) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)vb, p);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(vb >> 32), p);
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   constexpr int kRep = kWave / R;
   auto put = [&](double t) {
     const int p = lane / kRep;
-    if (lane % kRep != 0 || p >= jn) return;
+    if (lane % kRep != 0 || p < r0 || p >= r1) return;
     if (A.split > 1) {
       ((double*)A.out)[((int64_t)k * A.split + s) * A.n_grid + j0 + p] = t;
     } else {
@@ -268,17 +268,8 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   // points, 40 % of them past the list: 1.02 ms with the walks below, 0.97 so.)
   if (e0 >= e1) {
     put(0.0);
-    return;
+    return true;
   }
-  // A group across a gap of the grid wider than two cuts (the seam of two bands): most lines
-  // between its points reach none, and nothing is inside every cut, so the lines within each
-  // point's own cut are summed one by one. (4004 points in two bands 4000 cm^-1 apart, 1050
-  // lines/cm^-1: 85 ms with the lines of the gap in the near range of one group, 2.3 ms so, 19.7
-  // by tiles.)
-  const double c2 = FW ? 2.0 * fmax(lane_value(cut_hi, 0), lane_value(cut_hi, 32)) : 2.0 * cap;
-  bool seam = false;
-  if (v1 - v0 > c2)
-    for (int p = 1; p < jn; ++p) seam = seam || val(p) - val(p - 1) > c2;
   // lines inside the cut of every point of the group, in leaves [c0, c1)
   const int cov = pair_search(nu, e0, e1,
                               [&](double c) { return right ? c - v0 > cut_lo : v1 - c <= cut_lo; },
@@ -290,6 +281,20 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   const int nr = pair_search(nu, e0, e1,
                              [&](double c) { return right ? c > v1 + reach : c >= v0 - reach; },
                              lane);
+  if constexpr (RUNS) {
+    // (4004 points in two bands 4000 cm^-1 apart, 1050 lines/cm^-1: 85 ms with the lines of the
+    // gap summed at every point of one group, 0.24 so, 19.7 by tiles)
+    const int n_near = half(nr, 1) - half(nr, 0);
+    const double wide = 2.0 * kFarTheta * (pb.gmax + far_beta<NM>() * kb * fabs(v1));
+    if (n_near > kGapLines && v1 - v0 > wide) {
+      const double per = (double)n_near / (v1 - v0);   // lines per wavenumber, rather too many
+      for (int p = r0 + 1; p < r1; ++p)
+        if ((val(p) - val(p - 1) - wide) * per > (double)kGapLines) {
+          r1 = p;
+          return false;
+        }
+    }
+  }
   int a = half(nr, 0) / kLeafLines, b = (half(nr, 1) + kLeafLines - 1) / kLeafLines;
   // distance of a node outwards from the nearest point
   auto is_far = [&](const NodeRef<NM, const double>& f) {
@@ -320,9 +325,7 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   wave_sync();
 
   // ---- tree nodes inside every point's cut, 64 at a time: one per lane
-  // too many nodes that are not far (or none that are inside every cut): sum every line of the
-  // window
-  bool whole = seam;
+  bool whole = false;   // too many nodes that are not far: sum every line of the window
   int n_list = 0, round = 0;
   // adds the lane's moments (use: it has some) about c, scale sc, to every point's sum; lanes
   // without take zeros about a centre beyond the last point (which may be below zero)
@@ -374,7 +377,7 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
     n_list -= n;
     wave_sync();
   };
-  if (!seam) {
+  {
     int al = a, bl = b, lo = c0, hi = c1;   // near and covered ranges in nodes of level l
     bool on_l = al > lo, on_r = bl < hi;
     for (int l = 0; (on_l || on_r) && l < A.dims.levels; ++l) {
@@ -427,7 +430,7 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   // queue sums a leaf's 16 lines at every point, 64 leaves by their moments cost one node per
   // lane and the lines of the two split leaves. A 250 cm^-1 window of 8696 lines/cm^-1 takes
   // 257 us by leaf and 302 us with the queue.)
-  const bool by_leaf = !seam && one_cut && n_edge > kEdgeQueue;
+  const bool by_leaf = one_cut && n_edge > kEdgeQueue;
   if (by_leaf) {
     const double cut = cap;
     for (int o = 0; o < n_edge; o += kWave) {
@@ -649,28 +652,7 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
     for (int p = 0; p < R; ++p) acc[p] = 0.0;
     mask = true;
     n_rng = 1;
-    if (!seam) {
-      if (lane == 0) rng[wv][0] = make_int2(e0, e1);
-    } else {
-      // the points' windows, those that overlap as one
-      int f = e0, l = e0;
-      n_rng = 0;
-      for (int p = 0; p < jn; ++p) {
-        const double v = val(p);
-        const int w = pair_search(nu, e0, e1,
-                                  [&](double c) { return right ? c > v + cut_hi + ulp
-                                                               : c >= v - cut_hi - ulp; }, lane);
-        const int w0 = half(w, 0), w1 = half(w, 1);
-        if (w0 > l) {
-          if (lane == 0) rng[wv][n_rng] = make_int2(f, l);
-          ++n_rng;
-          f = w0;
-        }
-        l = max(l, w1);
-      }
-      if (lane == 0) rng[wv][n_rng] = make_int2(f, l);
-      ++n_rng;
-    }
+    if (lane == 0) rng[wv][0] = make_int2(e0, e1);
   } else if (by_leaf && s == 0) {
     // the split leaves: lanes 0-15 the left one's lines, 16-31 the right one's, per point
     // (through LDS, so that the sums keep their registers in a loop that is not unrolled)
@@ -734,6 +716,46 @@ __global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
   }
 
   put(wave_sums<R>(acc, lane));
+  return true;
+}
+
+// RUNS: grids with gaps of many lines (a variant of its own, as the loop costs the others spills
+// and 9 % of their time).
+template <int NM, bool FW, bool RUNS>
+__global__ __launch_bounds__(kBlock, 4) void xs_point_kernel(PointArgs A) {
+  constexpr int R = kPointGroup;
+  __shared__ PointLds<NM> lds;
+  if constexpr (NM == kMomFp32) {
+    for (int t = threadIdx.x; t < kDawNodes; t += blockDim.x)
+      lds.tab[t] = {kDawF[t], kDawF1[t], kDawE[t], 0.0f};
+    __syncthreads();
+  }
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t item = logical_wg() * kWavesPerWG + wv;
+  if (item >= A.n_groups * A.n_pt * A.split) return;
+  // parts of a group and neighbouring groups of one (P, T) point lie next to each other
+  const int s = (int)(item % A.split);
+  const int64_t gi = item / A.split;
+  const int k = (int)(gi / A.n_groups);
+  const int64_t j0 = (A.g0 + gi % A.n_groups) * R;
+  const int jn = (int)min((int64_t)R, A.n_grid - j0);
+  int r1 = jn;
+  if constexpr (!RUNS) {
+    point_run<NM, FW, false>(A, lds, lane, wv, j0, k, s, 0, r1);
+  } else {
+    for (int r0 = 0; r0 < jn;)
+      if (point_run<NM, FW, true>(A, lds, lane, wv, j0, k, s, r0, r1)) {
+        r0 = r1;
+        r1 = jn;
+      }
+  }
+}
+
+template <int NM, bool FW>
+static void launch_point_as(const PointArgs& A, dim3 grid, dim3 block, hipStream_t st) {
+  if (A.runs) hipLaunchKernelGGL((xs_point_kernel<NM, FW, true>), grid, block, 0, st, A);
+  else hipLaunchKernelGGL((xs_point_kernel<NM, FW, false>), grid, block, 0, st, A);
 }
 
 hipError_t launch_point(const PointArgs& A, int moments, hipStream_t st) {
@@ -742,13 +764,10 @@ hipError_t launch_point(const PointArgs& A, int moments, hipStream_t st) {
   const dim3 grid = wg_grid(phys_workgroups((items + kWavesPerWG - 1) / kWavesPerWG)),
              block(kBlock);
   const bool fw = A.cut.kind != kCutFixed;
-  if (moments == kMomFp32) {
-    if (fw) hipLaunchKernelGGL((xs_point_kernel<kMomFp32, true>), grid, block, 0, st, A);
-    else hipLaunchKernelGGL((xs_point_kernel<kMomFp32, false>), grid, block, 0, st, A);
-  } else {
-    if (fw) hipLaunchKernelGGL((xs_point_kernel<kMomFp64, true>), grid, block, 0, st, A);
-    else hipLaunchKernelGGL((xs_point_kernel<kMomFp64, false>), grid, block, 0, st, A);
-  }
+  if (moments == kMomFp32 && fw) launch_point_as<kMomFp32, true>(A, grid, block, st);
+  else if (moments == kMomFp32) launch_point_as<kMomFp32, false>(A, grid, block, st);
+  else if (fw) launch_point_as<kMomFp64, true>(A, grid, block, st);
+  else launch_point_as<kMomFp64, false>(A, grid, block, st);
   return hipGetLastError();
 }
 

@@ -371,6 +371,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
       p.any_tile = p.any_tile || p.by_tile[k];
       widest = std::max(widest, d);
     }
+    p.runs = G.max_step * (double)window_lines(L, G, o) > 2.0 * o.cut_cm1 * kGapLines;
     // lines that one group of points sums one by one
     const double width = 2.0 * std::min(widest, o.cut_cm1) + kPointGroup * step;
     max_window = (int64_t)((double)window_lines(L, G, o) * std::min(1.0, width / (2.0 * o.cut_cm1)));
@@ -606,6 +607,7 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       A.out = split > 1 ? (void*)part : out_dev;
       A.l1_eps = opts_eps(o);
       A.out_f32 = o.out_dtype == XS_F32;
+      A.runs = p.runs;
       int rc = tm ? tm->record(st) : XS_OK;
       if (rc) return rc;
       e = launch_point(A, p.moments, st);
@@ -1102,6 +1104,7 @@ int xs_set_grid(xs_ctx* c, const double* nu, size_t n, xs_grid_t* out) {
   G->first = nu[0];
   G->last = nu[n - 1];
   G->host.assign(nu, nu + n);
+  for (size_t j = 1; j < n; ++j) G->max_step = std::max(G->max_step, nu[j] - nu[j - 1]);
   int rc = c->dev_alloc_again((void**)&G->d, G->bytes, "grid");
   if (rc) {
     delete G;

@@ -69,6 +69,7 @@ struct GridRes {
   size_t n = 0;
   size_t bytes = 0;
   double first = 0.0, last = 0.0;   // host copies of the end points
+  double max_step = 0.0;            // the widest gap between neighbouring points
   std::vector<double> host;         // host copy of the grid
   std::atomic<int> refs{0};         // pending serving requests and live graphs
 };
@@ -94,6 +95,7 @@ struct Plan {
   std::vector<uint8_t> by_tile;   // per (P, T) point: the tile kernel walks the near range
                                   // (else the point kernel)
   bool any_tile = false;
+  bool runs = false;              // the grid has gaps of many lines (kGapLines)
   int tile_split = 1;             // line splits of the points by tiles
   // the point kernel's groups of points in a tile of 64 P points
   int64_t groups_per_tile() const {
