@@ -209,13 +209,65 @@ static CutDev cut_dev(const xs_opts& o) {
   return c;
 }
 
-// Lines per wavenumber around the grid's middle, times the cut's full width.
-static int64_t window_lines(const LinesRes& L, const GridRes& G, const xs_opts& o) {
-  const double mid = G.host[G.n / 2];
+// The grid's step: the median of five, so that a gap at one of them does not count.
+static double usual_step(const GridRes& G) {
+  if (G.n < 2) return 0.0;
+  double d[5];
+  for (size_t i = 0; i < 5; ++i) {
+    const size_t m = std::min<size_t>(G.n * (2 * i + 1) / 10, G.n - 2);
+    d[i] = G.host[m + 1] - G.host[m];
+  }
+  std::nth_element(d, d + 2, d + 5);
+  return d[2];
+}
+// Lines with centres below nu, from the sampled centres (evenly spread between two samples).
+static double lines_below(const LinesRes& L, double nu) {
   const std::vector<double>& sm = L.sample;
-  return (int64_t)(std::upper_bound(sm.begin(), sm.end(), mid + o.cut_cm1) -
-                   std::lower_bound(sm.begin(), sm.end(), mid - o.cut_cm1)) *
-         kSampleStride;
+  if (sm.empty() || nu <= sm[0]) return 0.0;
+  if (nu > L.nu_last) return (double)L.n;
+  const size_t k = (size_t)(std::upper_bound(sm.begin(), sm.end(), nu) - sm.begin()) - 1;
+  const bool last = k + 1 == sm.size();
+  const double a = sm[k], b = last ? L.nu_last : sm[k + 1];
+  const double i0 = (double)k * kSampleStride, i1 = last ? (double)L.n : i0 + kSampleStride;
+  return b > a ? i0 + (i1 - i0) * (nu - a) / (b - a) : i0;
+}
+static double lines_within(const LinesRes& L, double nu, double d) {
+  return lines_below(L, nu + d) - lines_below(L, nu - d);
+}
+
+// Lines within d (the cut, or less) of a grid point where the list is densest: the most at nine lines spread
+// evenly over those in reach (a grid may end outside its list, or have its middle in a gap).
+static int64_t window_lines(const LinesRes& L, const GridRes& G, const xs_opts& o, double d) {
+  int64_t lo, hi;
+  line_range(L, G, o, &lo, &hi);
+  const std::vector<double>& sm = L.sample;
+  const size_t k0 = (size_t)(lo / kSampleStride), k1 = (size_t)((hi + kSampleStride - 1) / kSampleStride);
+  double most = 0.0;
+  for (int q = 0; q < 9 && k0 < k1; ++q) {
+    // a tenth of the way between two samples at a time
+    const double at = (double)k0 + (double)(k1 - k0) * (q + 0.5) / 9.0;
+    const size_t k = std::min((size_t)at, sm.size() - 1);
+    const double next = k + 1 < sm.size() ? sm[k + 1] : L.nu_last;
+    const double nu = sm[k] + (next - sm[k]) * (at - (double)k);
+    most = std::max(most, lines_within(L, std::min(std::max(nu, G.first), G.last), d));
+  }
+  return (int64_t)most;
+}
+
+// Grid points with a line in reach of the cut, at most.
+static int64_t points_in_reach(const LinesRes& L, const GridRes& G, const xs_opts& o) {
+  if (L.n == 0) return 0;
+  return (int64_t)(std::upper_bound(G.host.begin(), G.host.end(), L.nu_last + o.cut_cm1) -
+                   std::lower_bound(G.host.begin(), G.host.end(), L.sample[0] - o.cut_cm1));
+}
+
+// Lines that a tile of 64 points adds to the window of one point, at most: by its usual span, or
+// where it spans the grid's widest gap; w lines lie within d of a point.
+static double tile_lines(const LinesRes& L, const GridRes& G, double w, double d) {
+  const double span = (double)std::min<size_t>(kWave, G.n - 1) * usual_step(G);
+  const double gap = G.n < 2 ? 0.0 : lines_below(L, G.host[G.max_at + 1]) -
+                                     lines_below(L, G.host[G.max_at]);
+  return std::min((double)L.n, std::max(w * span / (2.0 * d), gap));
 }
 
 // The lines' bounds at (P, T) for planning (without the partition function, which may lie in
@@ -241,28 +293,22 @@ void Plan::set_tree(int max_levels) {
   }
 }
 
-// The grid's step: the median of five, so that a gap at one of them does not count.
-static double usual_step(const GridRes& G) {
-  if (G.n < 2) return 0.0;
-  double d[5];
-  for (size_t i = 0; i < 5; ++i) {
-    const size_t m = std::min<size_t>(G.n * (2 * i + 1) / 10, G.n - 2);
-    d[i] = G.host[m + 1] - G.host[m];
-  }
-  std::nth_element(d, d + 2, d + 5);
-  return d[2];
-}
 // Distance within which the lines at (P, T) are summed one by one, at the grid's middle, and
 // whether that is many tiles.
 static double near_distance(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
   const size_t m = std::min<size_t>(G.n / 2, G.n >= 2 ? G.n - 2 : 0);
   return kFarTheta * (pb.gmax + (o.precision == XS_FP64 ? kBetaFp64 : kBetaFp32) * pb.kb * G.host[m]);
 }
-static bool is_wide(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
-  // (one point has no step: by what the point kernel would sum one by one. 1050 lines/cm^-1 within
-  // 25 cm^-1: 0.1 bar 70 us by the point kernel, 209 by tiles; 100 bar 134 and 82)
+static bool is_wide(const LinesRes& L, const GridRes& G, const xs_opts& o, const PtBounds& pb) {
+  // (one point has no step: by what the point kernel would sum one by one)
   const double d = near_distance(G, o, pb);
-  return G.n > 1 ? d > kWideSteps * usual_step(G) : d > 0.25 * o.cut_cm1;
+  return G.n > 1 ? d > kWideSteps * usual_step(G) : lines_within(L, G.first, std::min(d, o.cut_cm1)) > kWideLines;
+}
+
+// Whether every line's cut at (P, T) is the fixed cut or the cap.
+static bool one_cut(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
+  const double b = pb.kb * std::max(0.0, G.first - o.cut_cm1);
+  return cut_at(cut_dev(o), pb.gmin, b, false) >= o.cut_cm1;
 }
 
 // Far field by moments, chosen where a point's window holds enough lines beyond its near
@@ -270,16 +316,34 @@ static bool is_wide(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
 static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, size_t npts,
                         const xs_opts& o) {
   if (o.tile_group != 0 || o.select_eps > 0.0 || L.n >= ((size_t)1 << 30)) return false;
-  const int64_t lines = window_lines(L, G, o);
+  const int64_t window = window_lines(L, G, o, o.cut_cm1);
+  const int64_t lines = window + (int64_t)tile_lines(L, G, (double)window, o.cut_cm1);
+  // groups of points (of all (P, T) points where the split follows from them too: with a given
+  // split a row's bits are its own point's alone)
+  const int64_t groups = (points_in_reach(L, G, o) + kPointGroup - 1) / kPointGroup *
+                         (int64_t)(o.split ? 1 : npts);
+  if (o.cutoff_kind != XS_CUT_FIXED) {
+    if (lines < kMomentLines) return false;
+    if (o.split || groups >= kFwhmGroups) return true;   // (by the grid alone with a given split)
+    bool one = true;
+    double widest = 0.0;
+    for (size_t k = 0; k < npts; ++k) {
+      const PtBounds pb = plan_bounds(L, pts[k]);
+      one = one && one_cut(G, o, pb);   // no order by cut where every line's cut is the cap
+      widest = std::max(widest, cut_at(cut_dev(o), pb.gmax, pb.kb * std::max(G.last, 0.0), true));
+    }
+    if (one) return true;
+    const double w = (double)window_lines(L, G, o, widest);
+    return w + tile_lines(L, G, w, widest) >= (double)kFwhmLines;
+  }
   if (lines >= kMomentLines) return true;
-  // fewer lines: by a rule on the whole call, so only where the split follows from the whole
-  // call too (with a given split a row's bits are its own point's alone)
-  if (o.split || o.cutoff_kind != XS_CUT_FIXED || (int64_t)L.n < kMomentList) return false;
-  const int64_t groups = ((int64_t)G.n + kPointGroup - 1) / kPointGroup * (int64_t)npts;
+  // fewer lines: by a rule on the whole call, so only with the automatic split
+  if (o.split || (int64_t)L.n < kMomentList) return false;
+  if (o.precision == XS_FP64 && lines < kMomentLines64) return false;
   if (lines < kMomentLines1 && groups > kMomentGroups1) return false;
   if (lines < kMomentLines2 && groups > kMomentGroups2) return false;
   for (size_t k = 0; k < npts; ++k)
-    if (is_wide(G, o, plan_bounds(L, pts[k]))) return false;
+    if (is_wide(L, G, o, plan_bounds(L, pts[k]))) return false;
   return true;
 }
 
@@ -331,7 +395,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   line_range(L, G, o, &p.rec_lo, &hi);
   p.rec_n = hi - p.rec_lo;
   if (p.moments) {
-    const int64_t lines = window_lines(L, G, o);
+    const int64_t lines = window_lines(L, G, o, o.cut_cm1);
     const int64_t groups = ((int64_t)G.n + kPointGroup - 1) / kPointGroup;
     int levels = kTreeLevels;
     if (lines < kMomentLines && groups * (int64_t)npts <= kFewGroups)
@@ -359,22 +423,23 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     // points, against 30 in the point kernel)
     // (only with one cut for every line: the far kernel's rule)
     const double step = usual_step(G);
+    const double per = (double)window_lines(L, G, o, o.cut_cm1) / (2.0 * o.cut_cm1);
     double widest = 0.0;
+    p.runs = G.max_step * per > (double)kGapLines;
+    // (a tile across such a gap walks its lines alone; on a small grid that is longer than the
+    // near lines of all points by the point kernel: 4004 points at 100 bar 7.3 ms and @)
+    const bool tiles = !p.runs || G.n > kSeamPoints;
     p.by_tile.resize(npts);
     for (size_t k = 0; k < npts; ++k) {
       const PtBounds pb = plan_bounds(L, pts[k]);
       const double d = near_distance(G, o, pb);
-      const CutDev cd = cut_dev(o);
-      p.by_tile[k] = is_wide(G, o, pb) &&
-                     cut_at(cd, pb.gmin, pb.kb * std::max(0.0, G.first - o.cut_cm1), false) >=
-                         o.cut_cm1;
+      p.by_tile[k] = tiles && is_wide(L, G, o, pb) && one_cut(G, o, pb);
       p.any_tile = p.any_tile || p.by_tile[k];
       widest = std::max(widest, d);
     }
-    p.runs = G.max_step * (double)window_lines(L, G, o) > 2.0 * o.cut_cm1 * kGapLines;
     // lines that one group of points sums one by one
     const double width = 2.0 * std::min(widest, o.cut_cm1) + kPointGroup * step;
-    max_window = (int64_t)((double)window_lines(L, G, o) * std::min(1.0, width / (2.0 * o.cut_cm1)));
+    max_window = std::min<int64_t>(p.rec_n, (int64_t)(per * width));
     // what a unit costs is the near lines and, for the searches and the tree, as much as some
     // 3000 lines more
     for (int64_t& t : cost) t = std::min(t, (max_window + 3000) / kSampleStride + 1);
@@ -1055,6 +1120,7 @@ int xs_load_lines(xs_ctx* c, const xs_lines_desc* d, const xs_species_desc* sp, 
   // host index: every kSampleStride-th centre of the sorted list
   for (size_t i = 0; i < n; i += (size_t)kSampleStride)
     L->sample.push_back(sorted ? d->nu0[i] : d->nu0[order[i]]);
+  if (n) L->nu_last = sorted ? d->nu0[n - 1] : d->nu0[order[n - 1]];
   // host copy of the species for host-side Q evaluation (tables on the host)
   L->q_T_host.assign(sp->q_T ? sp->q_T : nullptr, sp->q_T ? sp->q_T + qn : nullptr);
   L->q_val_host.assign(sp->q_val ? sp->q_val : nullptr, sp->q_val ? sp->q_val + qn : nullptr);
@@ -1104,7 +1170,11 @@ int xs_set_grid(xs_ctx* c, const double* nu, size_t n, xs_grid_t* out) {
   G->first = nu[0];
   G->last = nu[n - 1];
   G->host.assign(nu, nu + n);
-  for (size_t j = 1; j < n; ++j) G->max_step = std::max(G->max_step, nu[j] - nu[j - 1]);
+  for (size_t j = 1; j < n; ++j)
+    if (nu[j] - nu[j - 1] > G->max_step) {
+      G->max_step = nu[j] - nu[j - 1];
+      G->max_at = j - 1;
+    }
   int rc = c->dev_alloc_again((void**)&G->d, G->bytes, "grid");
   if (rc) {
     delete G;

@@ -31,6 +31,7 @@ struct LinesRes {
   std::atomic<int> refs{0}; // pending serving requests and live graphs
   std::vector<double> q_T_host, q_val_host;
   std::vector<double> sample;   // nu0 of every kSampleStride-th line (host index)
+  double nu_last = 0.0;         // nu0 of the last line
 };
 
 constexpr int64_t kSampleStride = 1024;
@@ -38,9 +39,9 @@ constexpr int64_t kSampleStride = 1024;
 // at or under it, so that a new request's kernels find free wavefront slots quickly).
 constexpr int64_t kServeItemLines = 4096;
 
-// Far field by moments: from kMomentLines lines within the cut of the grid's middle with any
-// options that allow it; with fewer, for a fixed cut and no wide point (kWideSteps), from
-// kMomentList lines in the list. There a call that does not fill the device wins by its shorter
+// Far field by moments: from kMomentLines lines with a fixed cut (those within the cut where the
+// list is densest, and those that a tile of 64 points spans besides: tile_lines); with fewer, for
+// a fixed cut and no wide point (kWideSteps), from kMomentList lines in the list. There a call that does not fill the device wins by its shorter
 // chains, a larger one only where a window holds so many lines that walking them costs more
 // than the point kernel's searches and sums (some 0.5 ns per point): beyond kMomentGroups1 groups
 // of points in all from kMomentLines1 lines on, beyond kMomentGroups2 from kMomentLines2.
@@ -49,12 +50,20 @@ constexpr int64_t kServeItemLines = 4096;
 // 181 / 173, 377 / 687; 2000 lines 147 / 51, 255 / 201, 748 / 810; 5000 lines 217 / 64, 401 / 225,
 // 1502 / 943; 15000 lines 404 / 79, 848 / 275, 3787 / 1466; tables of 8 x 1e5, 24 x 1e5 and
 // 8 x 4e5: 3000 lines 612 / 498, 1075 / 1332, 1066 / 1726; 5000 lines 936 / 535, 1696 / 1438,
-// 1553 / 1857; 8000 lines 1412 / 582, 2640 / 1599, 2284 / 2017. A FWHM cut with 6550 lines goes
-// from 224 to 417 (the lines that only some points reach are far too few per block), a wide point
-// has nearly all lines beside it.
-constexpr int64_t kMomentLines = 16384, kMomentList = 512;
+// 1553 / 1857; 8000 lines 1412 / 582, 2640 / 1599, 2284 / 2017. A wide point has nearly all lines
+// beside it. On the FP64 path kMomentLines64 lines at least (28 moments per leaf: 40 points, 100
+// lines 27 / 35, 300 lines 31 / 35, 600 lines 39 / 37).
+constexpr int64_t kMomentLines = 16384, kMomentList = 512, kMomentLines64 = 400;
 constexpr int64_t kMomentLines1 = 3072, kMomentGroups1 = 25000;
 constexpr int64_t kMomentLines2 = 6144, kMomentGroups2 = 125000;
+// With a FWHM cut only from kMomentLines lines (6550 lines go from 224 to 417: those that only
+// some points reach are far too few per block), and, as the orders by cut make the chain of
+// launches longer, on kFwhmGroups groups of points in all or from kFwhmLines lines within the
+// widest of the lines' own cuts. (0.3 bar, about 1700 / 3000 / 6000 such lines, tiles / moments: 40
+// points 54 / 92, 72 / 113, 106 / 122; 3000 points 79 / 96, 106 / 114, 161 / 126; 20000 points
+// 119 / 116, 156 / 143, 241 / 218; 52000 lines: 1 point 330 / 150.) Where every line's cut is the cap
+// there are no orders: 53000 lines at 100 bar, 64 points 230 / 105.
+constexpr int64_t kFwhmGroups = 2048, kFwhmLines = 6144;
 // Small calls of that kind keep the tree low, as each three of its levels are a launch of some
 // 20 us: the fewest levels that leave at most kTopNodes nodes in a window, for at most
 // kFewGroups groups of points.
@@ -63,13 +72,19 @@ constexpr int64_t kFewGroups = 16384, kTopNodes = 512;
 // the tile's size (with 4 or 8 points per lane a limit of so many tiles kept points at 50 bar in
 // the point kernel: 10000 points, 3750 lines/cm^-1, 1057 us, by tiles of 4 points per lane 588).
 constexpr double kWideSteps = 384.0;
+// Grids with gaps of many lines keep broad points in the point kernel up to this many points.
+constexpr size_t kSeamPoints = 65536;
+// Of a grid of one point: those with this many lines in the near range. (1050 lines/cm^-1: 0.1 bar
+// 70 us by the point kernel, 209 by tiles; 30 bar 83 and 92; 100 bar, 47000 near lines, 134 and 82)
+constexpr double kWideLines = 32768.0;
 
 struct GridRes {
   double* d = nullptr;
   size_t n = 0;
   size_t bytes = 0;
   double first = 0.0, last = 0.0;   // host copies of the end points
-  double max_step = 0.0;            // the widest gap between neighbouring points
+  double max_step = 0.0;            // the widest gap between neighbouring points,
+  size_t max_at = 0;                // from this point to the next
   std::vector<double> host;         // host copy of the grid
   std::atomic<int> refs{0};         // pending serving requests and live graphs
 };

@@ -561,7 +561,7 @@ static int submit(Ctx* c, xs_lines_t lh, xs_grid_t gh, bool window, double nu_st
     for (size_t j = 0; j < n_points; ++j) r->own.host[j] = nu_start + (double)j * step;
     r->own.first = r->own.host.front();
     r->own.last = r->own.host.back();
-    r->own.max_step = n_points > 1 ? step : 0.0;
+    r->own.max_step = n_points > 1 ? step : 0.0;   // (from point 0)
     r->own.bytes = n_points * sizeof(double);
     r->G = &r->own;
   }

@@ -39,8 +39,8 @@ def _check(ctx, L, grid, pts, o, idx=None, tol=2e-6, rule="fixed"):
 
 @pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("n,m,rows,moments", [
-    (2000, 200_000, 1, True), (2000, 200_001, 1, False),   # 10 lines in a window
-    (950_000, 200_001, 1, True),                           # 5000 lines
+    (100_000, 200_000, 1, True), (100_000, 200_001, 1, False),   # 526 lines in a window
+    (950_000, 200_001, 1, True),                                 # 5000 lines
     (950_000, 100_000, 10, True), (950_000, 100_000, 11, False),
 ])
 def test_few_lines_many_points(ctx, n, m, rows, moments, f64):
@@ -185,5 +185,67 @@ def test_tuned_shapes_are_for_whole_windows(ctx):
         assert not np.array_equal(ctx.compute(h, g, pts, walk), b)
     finally:
         X.tune_cache_clear()
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("kind", ["uniform", "clusters", "coincident", "end", "past", "partners"])
+def test_fwhm_by_moments(ctx, kind, f64):
+    """FWHM cuts by moments (grids of 16384 points and more), as lists whose leaves and blocks are
+    wide or narrow, lines with one centre, a last block that lacks a few lines, a grid past both
+    ends, partners: at a sample of points, narrow to broad lines."""
+    from paper_2510_20870_amd import xsec as X
+    n, lo, hi, g0, step = {"end": (64 * 1024 - 5, 1000.0, 1012.0, 1001.0, 6e-4),
+                           "past": (40_000, 1000.0, 1020.0, 985.0, 3e-3)}.get(
+        kind, (60_000, 970.0, 1035.0, 1000.0, 3e-4))
+    L = synth.make_lines(synth.ListSpec(n, lo, hi, 91))
+    rng = np.random.default_rng(91)
+    if kind == "clusters":
+        c = lo + (hi - lo) * np.array([0.1, 0.42, 0.55, 0.9])
+        L["nu0"] = np.where(rng.random(n) < 0.67, c[rng.integers(0, 4, n)] + 0.02 * rng.random(n),
+                            L["nu0"])
+    elif kind == "coincident":
+        L["nu0"] = np.round(L["nu0"], 1)
+    order = np.argsort(L["nu0"], kind="stable")
+    L = {k: v[order] for k, v in L.items()}
+    B = None
+    if kind == "partners":
+        L["J_low"], B = synth.j_low(L["E_low"]), synth.broadening_partners()
+    m = 16_500
+    grid = g0 + step * np.arange(m, dtype=np.float64)
+    idx = np.unique(np.concatenate([rng.integers(0, m, 150), [0, m - 1], np.arange(800, 816)]))
+    pts = [(1e-4, 500.0), (0.3, 1500.0), (3.0, 900.0), (80.0, 700.0)]
+    h = ctx.load_lines(L, 16.0, broadening=B) if B else ctx.load_lines(L, 16.0)
+    g = ctx.set_grid(grid)
+    ref = [O.sigma(L, grid, p, t, 16.0, cut_kind="min_fwhm", cut_cm1=25.0, fwhm_mult=100.0,
+                   points=idx, broadening=B) for p, t in pts]
+    prec = X.XS_FP64 if f64 else X.XS_FP32_KAHAN
+    for split in (0, 1, 17):
+        sig = ctx.compute(h, g, pts, ctx.opts(X.XS_CUT_MIN_FWHM, 25.0, 100.0, prec, split=split))
+        for k, r in enumerate(ref):
+            st = O.compare(sig[k][idx], r, rel_tol=2e-8 if f64 else 2e-6)
+            print(f"[fwhm] {kind} f64={f64} split {split} {pts[k]} max_rel {st['max_rel']:.2e}",
+                  flush=True)
+            assert st["violations"] == 0, (split, pts[k], st)
+    walk = ctx.compute(h, g, pts, ctx.opts(X.XS_CUT_MIN_FWHM, 25.0, 100.0, prec, 2, 1,
+                                           tile_group=1))
+    assert not np.array_equal(walk[0], sig[0])
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+def test_grid_beyond_its_list(ctx, f64):
+    """A grid whose middle lies far outside its list: the rule looks at the lines in reach."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(60_000, 1000.0, 1060.0, 4))
+    grid = 1030.0 + 0.5 * np.arange(3000, dtype=np.float64)
+    prec = X.XS_FP64 if f64 else X.XS_FP32_KAHAN
+    o = ctx.opts(0, 25.0, 100.0, prec, 2, 1)
+    sig = _check(ctx, L, grid, [(0.1, 900.0)], o, tol=2e-8 if f64 else 2e-6)
+    o.tile_group = 1
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    assert not np.array_equal(ctx.compute(h, g, [(0.1, 900.0)], o), sig)
     ctx.unload_lines(h)
     ctx.free_grid(g)
