@@ -41,9 +41,10 @@ struct LineRec {
 constexpr int kPointGroup = 8;   // grid points per wavefront of the point kernel
 constexpr int kTreeLevels = 7;
 // A group of points is cut in runs at a gap that holds more lines than this beyond the near
-// ranges beside it: they cost more than the runs' own searches (steps of 1 cm^-1, 1050
-// lines/cm^-1: 509 us as one group, 729 in runs; steps of 10 cm^-1: 657 and 646).
-constexpr int kGapLines = 8192;
+// ranges beside it, as they cost more than the runs' own searches: one gap of many small steps
+// (more than half of the group), or steps that are all that wide (1050 lines/cm^-1, steps of 1 cm^-1:
+// 509 us as one group, 729 in runs; steps of 10 cm^-1: 657 and 646).
+constexpr int kGapLines = 1024, kStepLines = 8192;
 struct TreeDims {
   int64_t off[kTreeLevels];
   int64_t cnt[kTreeLevels];
@@ -123,7 +124,7 @@ struct PointArgs {
   void* out;              // split == 1: sigma rows [n_pts][n_grid] (row pt0 + k); else
                           // partials [n_pt][split][n_grid] (double)
   int out_f32;
-  int runs;               // the grid has gaps of more than kGapLines lines
+  int runs;               // the grid has gaps of many lines (kGapLines)
   float l1_eps;           // error budget of the shifted Lorentzian
 };
 

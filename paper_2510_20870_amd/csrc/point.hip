@@ -196,7 +196,7 @@ struct PointLds {
 };
 
 // The sums at the points [r0, r1) of the group from j0 (part s), true when they are stored. RUNS:
-// where a gap between two of them holds more than kGapLines lines that are near neither, the
+// where a gap between two of them holds many lines that are near neither (kGapLines), the
 // run ends there: r1 is lowered, nothing is stored, and the caller asks again.
 // FW: the lines' cuts differ (min(cap, mult FWHM)). The covered and the reachable lines then
 // follow from bounds of the cut; between them lie leaves of which some lines reach a point and
@@ -288,11 +288,14 @@ __device__ __forceinline__ bool point_run(const PointArgs& A, PointLds<NM>& lds,
     const double wide = 2.0 * kFarTheta * (pb.gmax + far_beta<NM>() * kb * fabs(v1));
     if (n_near > kGapLines && v1 - v0 > wide) {
       const double per = (double)n_near / (v1 - v0);   // lines per wavenumber, rather too many
-      for (int p = r0 + 1; p < r1; ++p)
-        if ((val(p) - val(p - 1) - wide) * per > (double)kGapLines) {
+      for (int p = r0 + 1; p < r1; ++p) {
+        const double gap = val(p) - val(p - 1);
+        const int most = gap > 0.5 * (v1 - v0) ? kGapLines : kStepLines;
+        if ((gap - wide) * per > (double)most) {
           r1 = p;
           return false;
         }
+      }
     }
   }
   int a = half(nr, 0) / kLeafLines, b = (half(nr, 1) + kLeafLines - 1) / kLeafLines;

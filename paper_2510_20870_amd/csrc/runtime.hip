@@ -261,13 +261,16 @@ static int64_t points_in_reach(const LinesRes& L, const GridRes& G, const xs_opt
                    std::lower_bound(G.host.begin(), G.host.end(), L.sample[0] - o.cut_cm1));
 }
 
+// Lines in the grid's widest gap.
+static double gap_lines(const LinesRes& L, const GridRes& G) {
+  return G.n < 2 ? 0.0 : lines_below(L, G.host[G.max_at + 1]) - lines_below(L, G.host[G.max_at]);
+}
+
 // Lines that a tile of 64 points adds to the window of one point, at most: by its usual span, or
 // where it spans the grid's widest gap; w lines lie within d of a point.
 static double tile_lines(const LinesRes& L, const GridRes& G, double w, double d) {
   const double span = (double)std::min<size_t>(kWave, G.n - 1) * usual_step(G);
-  const double gap = G.n < 2 ? 0.0 : lines_below(L, G.host[G.max_at + 1]) -
-                                     lines_below(L, G.host[G.max_at]);
-  return std::min((double)L.n, std::max(w * span / (2.0 * d), gap));
+  return std::min((double)L.n, std::max(w * span / (2.0 * d), gap_lines(L, G)));
 }
 
 // The lines' bounds at (P, T) for planning (without the partition function, which may lie in
@@ -425,9 +428,10 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     const double step = usual_step(G);
     const double per = (double)window_lines(L, G, o, o.cut_cm1) / (2.0 * o.cut_cm1);
     double widest = 0.0;
-    p.runs = G.max_step * per > (double)kGapLines;
+    const double gap = gap_lines(L, G);
+    p.runs = gap > (double)(G.max_step > 4.0 * kPointGroup * step ? kGapLines : kStepLines);
     // (a tile across such a gap walks its lines alone; on a small grid that is longer than the
-    // near lines of all points by the point kernel: 4004 points at 100 bar 7.3 ms and @)
+    // near lines of all points by the point kernel: 4004 points at 100 bar 7.5 ms and 0.5)
     const bool tiles = !p.runs || G.n > kSeamPoints;
     p.by_tile.resize(npts);
     for (size_t k = 0; k < npts; ++k) {

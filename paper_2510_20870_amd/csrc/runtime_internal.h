@@ -53,7 +53,7 @@ constexpr int64_t kServeItemLines = 4096;
 // 1553 / 1857; 8000 lines 1412 / 582, 2640 / 1599, 2284 / 2017. A wide point has nearly all lines
 // beside it. On the FP64 path kMomentLines64 lines at least (28 moments per leaf: 40 points, 100
 // lines 27 / 35, 300 lines 31 / 35, 600 lines 39 / 37).
-constexpr int64_t kMomentLines = 16384, kMomentList = 512, kMomentLines64 = 400;
+constexpr int64_t kMomentLines = 16384, kMomentList = 512, kMomentLines64 = 512;
 constexpr int64_t kMomentLines1 = 3072, kMomentGroups1 = 25000;
 constexpr int64_t kMomentLines2 = 6144, kMomentGroups2 = 125000;
 // With a FWHM cut only from kMomentLines lines (6550 lines go from 224 to 417: those that only

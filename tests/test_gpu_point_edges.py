@@ -118,3 +118,25 @@ def test_beyond_the_list(ctx, split, f64):
         assert st["violations"] == 0, st
     ctx.unload_lines(h)
     ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("n", [3000, 20_000, 400_000])
+def test_gaps_of_few_lines(ctx, n, f64):
+    """Two bands that meet inside a group and a step's widening, over gaps of less than 1024 lines,
+    of more, and of more than 8192."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(n, 500.0, 1500.0, 12))
+    grid = np.concatenate([600.0 + 0.01 * np.arange(1044), 900.0 + 0.01 * np.arange(90),
+                           1000.0 + 30.0 * np.arange(17)])
+    pts = [(0.01, 1500.0), (5.0, 600.0)]
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    sig = ctx.compute(h, g, pts, ctx.opts(X.XS_CUT_FIXED, 10.0, 0.0,
+                                          X.XS_FP64 if f64 else X.XS_FP32_KAHAN))
+    for k, (P, T) in enumerate(pts):
+        ref = O.sigma(L, grid, P, T, 16.0, cut_cm1=10.0)
+        st = O.compare(sig[k], ref, rel_tol=2e-8 if f64 else 2e-6)
+        print(f"[gaps] n={n} f64={f64} P={P} max_rel {st['max_rel']:.2e}", flush=True)
+        assert st["violations"] == 0, (pts[k], st)
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
