@@ -314,6 +314,12 @@ static bool one_cut(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
   return cut_at(cut_dev(o), pb.gmin, b, false) >= o.cut_cm1;
 }
 
+// The widest of the lines' cuts at (P, T).
+static double widest_cut(const LinesRes& L, const GridRes& G, const xs_opts& o,
+                         const PtBounds& pb) {
+  return std::min(o.cut_cm1, cut_at(cut_dev(o), pb.gmax, pb.kb * (std::max(G.last, 0.0) + o.cut_cm1), true));
+}
+
 // Far field by moments, chosen where a point's window holds enough lines beyond its near
 // range: without selection (which drops lines one by one) and with the automatic tile_group.
 static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, size_t npts,
@@ -333,7 +339,7 @@ static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, s
     for (size_t k = 0; k < npts; ++k) {
       const PtBounds pb = plan_bounds(L, pts[k]);
       one = one && one_cut(G, o, pb);   // no order by cut where every line's cut is the cap
-      widest = std::max(widest, cut_at(cut_dev(o), pb.gmax, pb.kb * std::max(G.last, 0.0), true));
+      widest = std::max(widest, widest_cut(L, G, o, pb));
     }
     if (one) return true;
     const double w = (double)window_lines(L, G, o, widest);
@@ -493,8 +499,24 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   // 23 us line by line, 37 by chunks.) max_window is rounded up to whole samples, so with
   // one or two samples in every window there may be a few lines only (10 lines, 1e6 points: 217 us
   // line by line, 249 by chunks; 1000 lines, 2e5 points with selection 319 and 338; 2500: 640
-  // and 555).
-  p.chunks = f64 && !p.moments && max_cost > 2 && max_window > 2 * (int64_t)kWave * p.split;
+  // and 555). With a FWHM cut each (P, T) point by the window within its own widest cut (1349
+  // points, 34000 lines within the cap, 2000 within the lines' cuts: 117 us line by line, 207 by
+  // chunks).
+  if (f64 && !p.moments) {
+    p.chunks.resize(npts);
+    const double half = 0.5 * (double)tile * usual_step(G);
+    for (size_t k = 0; k < npts; ++k) {
+      const double most = widest_cut(L, G, o, plan_bounds(L, pts[k]));
+      const double w = (double)max_window * ((most + half) / (o.cut_cm1 + half));
+      p.chunks[k] = w > (double)std::max<int64_t>(3 * kSampleStride, 2 * kWave * p.split);
+      p.any_chunks = p.any_chunks || p.chunks[k];
+    }
+    // points of both kinds in turn, each run a launch of its own: all by chunks (with a given
+    // split a row's bits are its own point's alone). 16 such points 239 us, 779 in runs.
+    int runs = 1;
+    for (size_t k = 1; k < npts; ++k) runs += p.chunks[k] != p.chunks[k - 1];
+    if (!o.split && runs > 4) std::fill(p.chunks.begin(), p.chunks.end(), 1);
+  }
   // (P, T) points per batch: the records of a batch (32 B per line and point) and its
   // partials stay under a third of the free budget and 64 GiB (fewer, longer launches:
   // the tail of each tile launch, where the last work items run alone, is paid once
@@ -633,13 +655,15 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       if (e != hipSuccess) return hip_fail(e, "select kernel launch");
     }
   }
-  // runs of points that go the same way: by the point kernel, or by tiles
+  // runs of points that go the same way: by the point kernel, or by tiles; by chunks or not
   for (int k0 = 0, k1; k0 < nb; k0 = k1) {
     const bool tiles = !p.moments || counts || p.by_tile[pt0 + k0];
     k1 = nb;
-    if (p.moments && !counts && p.any_tile) {
+    const std::vector<uint8_t>* way = counts ? nullptr : p.any_tile ? &p.by_tile
+                                             : p.any_chunks ? &p.chunks : nullptr;
+    if (way) {
       k1 = k0 + 1;
-      while (k1 < nb && (p.by_tile[pt0 + k1] != 0) == tiles) ++k1;
+      while (k1 < nb && (*way)[pt0 + k1] == (*way)[pt0 + k0]) ++k1;
     }
     const int nk = k1 - k0;
     const LineRec* recs = (const LineRec*)rec_dev + (size_t)k0 * p.rec_n;
@@ -706,7 +730,7 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       A.rec_n = p.rec_n;
       A.l1_eps = opts_eps(o);
       A.far_kappa = far_kappa(A.l1_eps);
-      A.chunks = p.chunks;
+      A.chunks = p.any_chunks && p.chunks[pt0 + k0];
       if (p.select_eps > 0.0) {
         // main-contributor selection: the kernels drop the lines below their group's
         // threshold

@@ -116,7 +116,8 @@ struct Plan {
   int64_t groups_per_tile() const {
     return std::max<int64_t>(1, std::min<int64_t>(kWave * P, n_grid + kPointGroup - 1) / kPointGroup);
   }
-  bool chunks = false;            // FP64 tile kernel: chunks of lines by their moments
+  std::vector<uint8_t> chunks;    // per (P, T) point: FP64 tile kernel, chunks of lines by their
+  bool any_chunks = false;        // moments
   int max_split() const { return any_tile && tile_split > split ? tile_split : split; }
   TreeDims dims{};
   int cut_blocks = 0;             // blocks ordered by cut (CutOrder)

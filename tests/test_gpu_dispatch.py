@@ -249,3 +249,27 @@ def test_grid_beyond_its_list(ctx, f64):
     assert not np.array_equal(ctx.compute(h, g, [(0.1, 900.0)], o), sig)
     ctx.unload_lines(h)
     ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("split", [0, 2])
+def test_fp64_chunks_of_a_table(ctx, split):
+    """FWHM cuts on the FP64 path: points whose lines' own cuts hold few lines and points with many,
+    alone, in two runs and in turn; with a given split a row is that of its point alone."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(12_000, 990.0, 1030.0, 17))
+    grid = 1008.0 + 0.004 * np.arange(333, dtype=np.float64)
+    narrow, broad = (1e-3, 500.0), (8.0, 700.0)
+    o = ctx.opts(X.XS_CUT_MIN_FWHM, 15.0, 100.0, X.XS_FP64, 2, split)
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    ref = {p: O.sigma(L, grid, *p, 16.0, cut_kind="min_fwhm", cut_cm1=15.0, fwhm_mult=100.0)
+           for p in (narrow, broad)}
+    alone = {p: ctx.compute(h, g, [p], o)[0] for p in ref}
+    for pts in ([narrow, broad], [broad] * 3 + [narrow] * 2, [narrow, broad] * 5):
+        sig = ctx.compute(h, g, pts, o)
+        for k, p in enumerate(pts):
+            st = O.compare(sig[k], ref[p], rel_tol=2e-8)
+            assert st["violations"] == 0, (k, p, st)
+            if split:
+                assert np.array_equal(sig[k], alone[p]), (k, p)
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
