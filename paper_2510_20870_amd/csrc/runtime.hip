@@ -315,8 +315,7 @@ static bool one_cut(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
 }
 
 // The widest of the lines' cuts at (P, T).
-static double widest_cut(const LinesRes& L, const GridRes& G, const xs_opts& o,
-                         const PtBounds& pb) {
+static double widest_cut(const GridRes& G, const xs_opts& o, const PtBounds& pb) {
   return std::min(o.cut_cm1, cut_at(cut_dev(o), pb.gmax, pb.kb * (std::max(G.last, 0.0) + o.cut_cm1), true));
 }
 
@@ -333,24 +332,30 @@ static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, s
                          (int64_t)(o.split ? 1 : npts);
   if (o.cutoff_kind != XS_CUT_FIXED) {
     if (lines < kMomentLines) return false;
-    if (o.split || groups >= kFwhmGroups) return true;   // (by the grid alone with a given split)
-    bool one = true;
+    if (o.split) return lines >= kFwhmLines1;   // (by the grid alone)
+    const bool f64 = o.precision == XS_FP64;
+    if (groups >= kFwhmGroups1 &&
+        (lines >= kFwhmLines2 || (lines >= kFwhmLines1 && (f64 || groups <= kFwhmGroups2))))
+      return true;
     double widest = 0.0;
     for (size_t k = 0; k < npts; ++k) {
       const PtBounds pb = plan_bounds(L, pts[k]);
-      one = one && one_cut(G, o, pb);   // no order by cut where every line's cut is the cap
-      widest = std::max(widest, widest_cut(L, G, o, pb));
+      if (one_cut(G, o, pb)) return true;
+      widest = std::max(widest, widest_cut(G, o, pb));
     }
-    if (one) return true;
     const double w = (double)window_lines(L, G, o, widest);
-    return w + tile_lines(L, G, w, widest) >= (double)kFwhmLines;
+    return w + (f64 ? 4.0 : 2.0) * tile_lines(L, G, w, widest) >=
+           (double)(f64 ? kFwhmOwn64 : groups < kFwhmGroups1 ? kFwhmOwn1 : kFwhmOwn2);
   }
   if (lines >= kMomentLines) return true;
   // fewer lines: by a rule on the whole call, so only with the automatic split
   if (o.split || (int64_t)L.n < kMomentList) return false;
-  if (o.precision == XS_FP64 && lines < kMomentLines64) return false;
-  if (lines < kMomentLines1 && groups > kMomentGroups1) return false;
-  if (lines < kMomentLines2 && groups > kMomentGroups2) return false;
+  if (o.precision == XS_FP64) {
+    if (lines < kMomentLines64) return false;
+  } else if ((lines < kMomentLines1 && groups > kMomentGroups1) ||
+             (lines < kMomentLines2 && groups > kMomentGroups2)) {
+    return false;
+  }
   for (size_t k = 0; k < npts; ++k)
     if (is_wide(L, G, o, plan_bounds(L, pts[k]))) return false;
   return true;
@@ -506,7 +511,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     p.chunks.resize(npts);
     const double half = 0.5 * (double)tile * usual_step(G);
     for (size_t k = 0; k < npts; ++k) {
-      const double most = widest_cut(L, G, o, plan_bounds(L, pts[k]));
+      const double most = widest_cut(G, o, plan_bounds(L, pts[k]));
       const double w = (double)max_window * ((most + half) / (o.cut_cm1 + half));
       p.chunks[k] = w > (double)std::max<int64_t>(3 * kSampleStride, 2 * kWave * p.split);
       p.any_chunks = p.any_chunks || p.chunks[k];

@@ -51,19 +51,31 @@ constexpr int64_t kServeItemLines = 4096;
 // 1502 / 943; 15000 lines 404 / 79, 848 / 275, 3787 / 1466; tables of 8 x 1e5, 24 x 1e5 and
 // 8 x 4e5: 3000 lines 612 / 498, 1075 / 1332, 1066 / 1726; 5000 lines 936 / 535, 1696 / 1438,
 // 1553 / 1857; 8000 lines 1412 / 582, 2640 / 1599, 2284 / 2017. A wide point has nearly all lines
-// beside it. On the FP64 path kMomentLines64 lines at least (28 moments per leaf: 40 points, 100
-// lines 27 / 35, 300 lines 31 / 35, 600 lines 39 / 37).
+// beside it. On the FP64 path only from kMomentLines64 lines on (28 moments per leaf: 40 points, 100
+// lines 27 / 35, 300 lines 31 / 35, 600 lines 39 / 37), which then holds for every size
+// (4 x 3.3e5 points, 730 lines 547 / 445).
 constexpr int64_t kMomentLines = 16384, kMomentList = 512, kMomentLines64 = 512;
 constexpr int64_t kMomentLines1 = 3072, kMomentGroups1 = 25000;
 constexpr int64_t kMomentLines2 = 6144, kMomentGroups2 = 125000;
-// With a FWHM cut only from kMomentLines lines (6550 lines go from 224 to 417: those that only
-// some points reach are far too few per block), and, as the orders by cut make the chain of
-// launches longer, on kFwhmGroups groups of points in all or from kFwhmLines lines within the
-// widest of the lines' own cuts. (0.3 bar, about 1700 / 3000 / 6000 such lines, tiles / moments: 40
-// points 54 / 92, 72 / 113, 106 / 122; 3000 points 79 / 96, 106 / 114, 161 / 126; 20000 points
-// 119 / 116, 156 / 143, 241 / 218; 52000 lines: 1 point 330 / 150.) Where every line's cut is the cap
-// there are no orders: 53000 lines at 100 bar, 64 points 230 / 105.
-constexpr int64_t kFwhmGroups = 2048, kFwhmLines = 6144;
+// With a FWHM cut only from kMomentLines lines within the cap (6550 lines go from 224 to 417: those
+// that only some points reach are far too few per block). The orders by cut make the chain of
+// launches longer, and what tiles cost follows from the lines within their own cuts: so by moments
+// from kFwhmOwn1 lines within the widest of these on (and in a tile's span) up to kFwhmGroups1
+// groups of points in all (more on the FP64 path), from kFwhmOwn2 on more, where every line's
+// cut is the cap at some point (53000 lines at 100 bar, 64 points 230 / 105), and where the cap
+// holds so many that the parameters of all of them are what counts. Measured (us, tiles / moments; one (P, T)
+// point at 1000 K of 0.001, 0.3, 1, 3 bar, for which the widest of the lines' own cuts hold 0.012,
+// 0.15, 0.5 and 1 times the lines within the cap): FP32, 17000 lines, 1349 points 45 / 107, 59 / 113,
+// 102 / 127, 158 / 116; 40000 points 101 / 91, 124 / 134, 140 / 210, 187 / 257; 400000 points
+// 242 / 288, 307 / 644, 509 / 1117, 825 / 1096; 50000 lines, 1349 points 58 / 115, 112 / 126,
+// 227 / 122, 396 / 138; 40000 points 120 / 103, 213 / 222, 244 / 286, 390 / 360; 400000 points
+// 359 / 332, 570 / 1167, 1162 / 1214, 2112 / 1485; 200000 lines, 400000 points 848 / 423,
+// 1704 / 1349, 4126 / 2078, 8036 / 3194. FP64, 17000 lines, 1349 points 49 / 115, 85 / 140, 91 / 190,
+// 146 / 160; 400000 points 300 / 502, 970 / 1071, 1729 / 1828, 2538 / 1651; 50000 lines, 400000 points
+// 612 / 566, 1722 / 1972, 3277 / 1789, 5317 / 2235.
+constexpr int64_t kFwhmGroups1 = 2048, kFwhmGroups2 = 16384;
+constexpr int64_t kFwhmLines1 = 32768, kFwhmLines2 = 65536;
+constexpr int64_t kFwhmOwn1 = 8192, kFwhmOwn2 = 24576, kFwhmOwn64 = 16384;
 // Small calls of that kind keep the tree low, as each three of its levels are a launch of some
 // 20 us: the fewest levels that leave at most kTopNodes nodes in a window, for at most
 // kFewGroups groups of points.

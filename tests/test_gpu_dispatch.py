@@ -273,3 +273,31 @@ def test_fp64_chunks_of_a_table(ctx, split):
                 assert np.array_equal(sig[k], alone[p]), (k, p)
     ctx.unload_lines(h)
     ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("n,m,P,f64,split,moments", [
+    (27_000, 1349, 0.4, False, 0, False), (27_000, 1349, 8.0, False, 0, True),
+    (27_000, 17_000, 8.0, False, 0, False), (60_000, 17_000, 0.1, False, 0, True),
+    (60_000, 140_000, 0.1, False, 0, False), (60_000, 140_000, 8.0, False, 0, True),
+    (120_000, 140_000, 0.1, False, 0, True),
+    (27_000, 1349, 1.0, True, 0, False), (27_000, 1349, 8.0, True, 0, True),
+    (27_000, 17_000, 0.1, True, 0, False), (60_000, 17_000, 0.1, True, 0, True),
+    (27_000, 1349, 8.0, False, 3, False), (60_000, 1349, 0.1, False, 3, True)])
+def test_fwhm_rule(ctx, n, m, P, f64, split, moments):
+    """Both sides of the rule for FWHM cuts; the route shows in the bits (split 1: the automatic
+    split of either is another one)."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(n, 970.0, 1030.0, 8))
+    grid = 999.0 + (2.0 / m) * np.arange(m, dtype=np.float64)
+    idx = np.unique(np.random.default_rng(8).integers(0, m, 60))
+    o = ctx.opts(X.XS_CUT_MIN_FWHM, 25.0, 100.0, X.XS_FP64 if f64 else X.XS_FP32_KAHAN, split=split)
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    sig = ctx.compute(h, g, [(P, 900.0)], o)[0]
+    ref = O.sigma(L, grid, P, 900.0, 16.0, cut_kind="min_fwhm", cut_cm1=25.0, fwhm_mult=100.0,
+                  points=idx)
+    st = O.compare(sig[idx], ref, rel_tol=2e-8 if f64 else 2e-6)
+    assert st["violations"] == 0, st
+    o.tile_group = 1
+    assert np.array_equal(ctx.compute(h, g, [(P, 900.0)], o)[0], sig) != moments
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
