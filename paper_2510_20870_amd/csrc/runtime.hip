@@ -345,18 +345,23 @@ static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, s
     }
     const double w = (double)window_lines(L, G, o, widest);
     return w + (f64 ? 4.0 : 2.0) * tile_lines(L, G, w, widest) >=
-           (double)(f64 ? kFwhmOwn64 : groups < kFwhmGroups1 ? kFwhmOwn1 : kFwhmOwn2);
+           (double)(f64 ? (groups < kFwhmGroups64 ? kFwhmOwn64 : kFwhmOwn3)
+                        : groups < kFwhmGroups1 ? kFwhmOwn1 : kFwhmOwn2);
   }
   if (lines >= kMomentLines) return true;
   // fewer lines: by a rule on the whole call, so only with the automatic split
   if (o.split || (int64_t)L.n < kMomentList) return false;
-  if (o.precision == XS_FP64) {
+  const bool f64 = o.precision == XS_FP64;
+  if (f64) {
     if (lines < kMomentLines64) return false;
-  } else if ((lines < kMomentLines1 && groups > kMomentGroups1) ||
-             (lines < kMomentLines2 && groups > kMomentGroups2)) {
-    return false;
+  } else {
+    // (the lines beside a tile cost it several times what the others do)
+    const int64_t work = window + (int64_t)(16.0 * tile_lines(L, G, (double)window, o.cut_cm1));
+    if ((work < kMomentLines1 && groups > kMomentGroups1) ||
+        (work < kMomentLines2 && groups > kMomentGroups2))
+      return false;
   }
-  for (size_t k = 0; k < npts; ++k)
+  for (size_t k = 0; k < npts && !f64; ++k)
     if (is_wide(L, G, o, plan_bounds(L, pts[k]))) return false;
   return true;
 }
@@ -445,13 +450,34 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     // near lines of all points by the point kernel: 4004 points at 100 bar 7.5 ms and 0.5)
     const bool tiles = !p.runs || G.n > kSeamPoints;
     p.by_tile.resize(npts);
+    bool all_one = true;
     for (size_t k = 0; k < npts; ++k) {
       const PtBounds pb = plan_bounds(L, pts[k]);
       const double d = near_distance(G, o, pb);
-      p.by_tile[k] = tiles && is_wide(L, G, o, pb) && one_cut(G, o, pb);
-      p.any_tile = p.any_tile || p.by_tile[k];
+      const bool one = one_cut(G, o, pb);
+      if (tiles && is_wide(L, G, o, pb)) {
+        // (with cuts that differ the far kernel's rule does not hold: whole windows)
+        const double own = one ? o.cut_cm1 : widest_cut(G, o, pb);
+        const double near = (double)window_lines(L, G, o, std::min(d, own));
+        const double part = near / std::max(1.0, (double)window_lines(L, G, o, own));
+        if (f64 ? part >= kNearAll64 && near >= kNearLines64 : one || part >= kNearAll32)
+          p.by_tile[k] = one ? kTileNear : kTileWhole;
+      }
+      all_one = all_one && one;
       widest = std::max(widest, d);
     }
+    // A small table whose points go both ways in turn, each run in launches of its own: as
+    // one, all by tiles, or all by the point kernel where there is one point alone (24 points of
+    // the table in turn, us: 1270 lines/cm^-1 on 718 points 504 in runs, 245 as one; 610
+    // lines/cm^-1 on 245 points with FWHM cuts 451, 254; one point 847, 442). With a given split
+    // a row's bits are its own point's alone.
+    int ways = 1;
+    for (size_t k = 1; k < npts; ++k) ways += p.by_tile[k] != p.by_tile[k - 1];
+    if (!o.split && ways > 4 &&
+        ((int64_t)G.n + kPointGroup - 1) / kPointGroup * (int64_t)npts <= kTurnGroups)
+      std::fill(p.by_tile.begin(), p.by_tile.end(),
+                G.n == 1 ? kPoint : all_one ? kTileNear : kTileWhole);
+    p.any_tile = std::count(p.by_tile.begin(), p.by_tile.end(), kPoint) < (int64_t)npts;
     // lines that one group of points sums one by one
     const double width = 2.0 * std::min(widest, o.cut_cm1) + kPointGroup * step;
     max_window = std::min<int64_t>(p.rec_n, (int64_t)(per * width));
@@ -476,7 +502,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     p.split = (int)std::max<int64_t>(1, std::min<int64_t>(sp, 64));
     if (p.any_tile) {
       // points by tiles: two rounds of wavefront slots, of at least four chunks each
-      const int64_t wide = std::count(p.by_tile.begin(), p.by_tile.end(), 1);
+      const int64_t wide = (int64_t)npts - std::count(p.by_tile.begin(), p.by_tile.end(), kPoint);
       sp = ((int64_t)c.n_cu * 56 + p.n_units * wide - 1) / (p.n_units * wide);
       if (max_item_lines > 0)
         sp = std::max<int64_t>(sp, (max_window + max_item_lines - 1) / max_item_lines);
@@ -660,9 +686,10 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       if (e != hipSuccess) return hip_fail(e, "select kernel launch");
     }
   }
-  // runs of points that go the same way: by the point kernel, or by tiles; by chunks or not
+  // runs of points that go the same way (PointWay); by chunks or not
   for (int k0 = 0, k1; k0 < nb; k0 = k1) {
-    const bool tiles = !p.moments || counts || p.by_tile[pt0 + k0];
+    const int way_of = p.moments && !counts ? p.by_tile[pt0 + k0] : kTileWhole;
+    const bool tiles = way_of != kPoint;
     k1 = nb;
     const std::vector<uint8_t>* way = counts ? nullptr : p.any_tile ? &p.by_tile
                                              : p.any_chunks ? &p.chunks : nullptr;
@@ -676,7 +703,7 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
                                                       (size_t)k0 * p.dims.n_nodes *
                                                           node_bytes(p.moments))
                                     : nullptr;
-    const bool with_far = tiles && p.moments && !counts;
+    const bool with_far = way_of == kTileNear;
     double* far = with_far ? (double*)((char*)rec_dev + p.far_offset()) + (size_t)k0 * G.n : nullptr;
     const int split = tiles && p.moments ? p.tile_split : p.split;
     double* part = split > 1 ? (double*)part_dev + (size_t)k0 * p.max_split() * G.n : nullptr;

@@ -53,15 +53,17 @@ constexpr int64_t kServeItemLines = 4096;
 // 1553 / 1857; 8000 lines 1412 / 582, 2640 / 1599, 2284 / 2017. A wide point has nearly all lines
 // beside it. On the FP64 path only from kMomentLines64 lines on (28 moments per leaf: 40 points, 100
 // lines 27 / 35, 300 lines 31 / 35, 600 lines 39 / 37), which then holds for every size
-// (4 x 3.3e5 points, 730 lines 547 / 445).
-constexpr int64_t kMomentLines = 16384, kMomentList = 512, kMomentLines64 = 512;
+// (4 x 3.3e5 points, 730 lines 547 / 445). The lines beside a tile weigh 16-fold in the two limits
+// (3.1e5 points of steps of 0.006 cm^-1, 1890 lines within 3 cm^-1: 657 / 339).
+constexpr int64_t kMomentLines = 16384, kMomentList = 512, kMomentLines64 = 384;
 constexpr int64_t kMomentLines1 = 3072, kMomentGroups1 = 25000;
 constexpr int64_t kMomentLines2 = 6144, kMomentGroups2 = 125000;
 // With a FWHM cut only from kMomentLines lines within the cap (6550 lines go from 224 to 417: those
 // that only some points reach are far too few per block). The orders by cut make the chain of
 // launches longer, and what tiles cost follows from the lines within their own cuts: so by moments
 // from kFwhmOwn1 lines within the widest of these on (and in a tile's span) up to kFwhmGroups1
-// groups of points in all (more on the FP64 path), from kFwhmOwn2 on more, where every line's
+// groups of points in all (FP64: kFwhmOwn64 up to
+// kFwhmGroups64, then kFwhmOwn3), from kFwhmOwn2 on more, where every line's
 // cut is the cap at some point (53000 lines at 100 bar, 64 points 230 / 105), and where the cap
 // holds so many that the parameters of all of them are what counts. Measured (us, tiles / moments; one (P, T)
 // point at 1000 K of 0.001, 0.3, 1, 3 bar, for which the widest of the lines' own cuts hold 0.012,
@@ -72,10 +74,11 @@ constexpr int64_t kMomentLines2 = 6144, kMomentGroups2 = 125000;
 // 359 / 332, 570 / 1167, 1162 / 1214, 2112 / 1485; 200000 lines, 400000 points 848 / 423,
 // 1704 / 1349, 4126 / 2078, 8036 / 3194. FP64, 17000 lines, 1349 points 49 / 115, 85 / 140, 91 / 190,
 // 146 / 160; 400000 points 300 / 502, 970 / 1071, 1729 / 1828, 2538 / 1651; 50000 lines, 400000 points
-// 612 / 566, 1722 / 1972, 3277 / 1789, 5317 / 2235.
-constexpr int64_t kFwhmGroups1 = 2048, kFwhmGroups2 = 16384;
+// 612 / 566, 1722 / 1972, 3277 / 1789, 5317 / 2235. At 9000 cm^-1, where the Doppler widths make the
+// cuts, 4300 of 30000 lines, 629 and 9508 points FP32 173 / 79, 210 / 86, FP64 111 / 124, 251 / 145.
+constexpr int64_t kFwhmGroups64 = 512, kFwhmGroups1 = 2048, kFwhmGroups2 = 16384;
 constexpr int64_t kFwhmLines1 = 32768, kFwhmLines2 = 65536;
-constexpr int64_t kFwhmOwn1 = 8192, kFwhmOwn2 = 24576, kFwhmOwn64 = 16384;
+constexpr int64_t kFwhmOwn1 = 4096, kFwhmOwn2 = 24576, kFwhmOwn64 = 16384, kFwhmOwn3 = 3072;
 // Small calls of that kind keep the tree low, as each three of its levels are a launch of some
 // 20 us: the fewest levels that leave at most kTopNodes nodes in a window, for at most
 // kFewGroups groups of points.
@@ -84,6 +87,21 @@ constexpr int64_t kFewGroups = 16384, kTopNodes = 512;
 // the tile's size (with 4 or 8 points per lane a limit of so many tiles kept points at 50 bar in
 // the point kernel: 10000 points, 3750 lines/cm^-1, 1057 us, by tiles of 4 points per lane 588).
 constexpr double kWideSteps = 384.0;
+// Where the lines' cuts differ (FWHM), broad points go by tiles over whole windows: those with at
+// least this part of the lines within their own widest cut in the near range (40600 lines/cm^-1,
+// 12356 points, us by tiles / point kernel: 1 bar 2573 / 1107, 3 bar 1940 / 1020, 10 bar 744 / 4188,
+// 30 bar 548 / 8250; the part is 0.07 at 3 bar, 0.22 at 10).
+constexpr double kNearAll32 = 0.125;
+// On the FP64 path only those whose near range holds at least this part, and so many lines (24
+// points in turn, 2855 lines, 9052 grid points 1727 us, 405 by the point kernel): its tiles gain
+// little from the far field's polynomial. (Tiles / point kernel, us: 17000 lines in the window,
+// 800 points at 3, 30, 60, 100 bar 187 / 89, 178 / 112, 178 / 136, 158 / 151; 5000 points at 60 and
+// 100 bar 224 / 210, 235 / 265; 50000 lines, 2000 points 256 / 305, 267 / 399; 1e5 points at 20 and
+// 100 bar 1995 / 1776, 7177 / 7727. The near range is 0.6 of the cut at 60 bar.)
+constexpr double kNearAll64 = 0.8, kNearLines64 = 16384.0;
+// Tables of up to this many groups of points in all go one way where their points would go two
+// ways in turn.
+constexpr int64_t kTurnGroups = 4096;
 // Grids with gaps of many lines keep broad points in the point kernel up to this many points.
 constexpr size_t kSeamPoints = 65536;
 // Of a grid of one point: those with this many lines in the near range. (1050 lines/cm^-1: 0.1 bar
@@ -100,6 +118,10 @@ struct GridRes {
   std::vector<double> host;         // host copy of the grid
   std::atomic<int> refs{0};         // pending serving requests and live graphs
 };
+
+// How a (P, T) point of a call by moments is summed: the point kernel, tiles over the near ranges
+// beside the far kernel's sums, or tiles over whole windows (without the tree).
+enum PointWay : uint8_t { kPoint = 0, kTileNear = 1, kTileWhole = 2 };
 
 struct Plan {
   int P = 4;               // grid points per lane (tile = 64 P points)
@@ -119,8 +141,7 @@ struct Plan {
   double select_eps = 0.0;         // main-contributor selection (0: off)
   // Far field by moments (far_tree.h): the tree over the records, 0 moments: off.
   int moments = 0;
-  std::vector<uint8_t> by_tile;   // per (P, T) point: the tile kernel walks the near range
-                                  // (else the point kernel)
+  std::vector<uint8_t> by_tile;   // per (P, T) point: a PointWay
   bool any_tile = false;
   bool runs = false;              // the grid has gaps of many lines (kGapLines)
   int tile_split = 1;             // line splits of the points by tiles
