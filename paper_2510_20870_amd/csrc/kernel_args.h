@@ -183,7 +183,7 @@ hipError_t launch_tile(const TileArgs& A, int P, bool f64, int W, hipStream_t st
                        int64_t phys_wg);
 hipError_t launch_count(const TileArgs& A, int P, hipStream_t st, int64_t phys_wg);
 // one wavefront per (group of 4 tiles, P-T point), A.n_tiles groups: writes A.tau
-hipError_t launch_select(const TileArgs& A, int P, hipStream_t st);
+hipError_t launch_select(const TileArgs& A, int P, bool wide, hipStream_t st);
 // per points-per-lane instantiations of the tile kernel (tile_p*.hip)
 hipError_t launch_tile_p1(const TileArgs& A, bool f64, int W, hipStream_t st, dim3 grid);
 hipError_t launch_tile_p2(const TileArgs& A, bool f64, int W, hipStream_t st, dim3 grid);

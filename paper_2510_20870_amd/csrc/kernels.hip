@@ -205,10 +205,10 @@ __global__ __launch_bounds__(kBlock) void xs_count_kernel(TileArgs A) {
 // One workgroup per (group, point), its waves taking interleaved 64-line slices of the
 // window: A.n_tiles counts groups here. L is the sum of the waves' partial sums in wave
 // order, and the histogram is shared (integer additions), so tau depends on the data only.
-// 16 waves, because a grid has few groups and a wave waits for its loads most of the time: 59
-// groups of 5.4e4 lines take 225 us with 4 waves each, 112 us with 16.
-constexpr int kSelBlock = 1024;
-template <int P>
+// 16 waves where a grid has few groups or windows are long, as a wave waits for its loads most of
+// the time (59 groups of 5.4e4 lines take 225 us with 4 waves each, 112 us with 16), else 4
+// (wide_select).
+template <int P, int kSelBlock>
 __global__ __launch_bounds__(kSelBlock) void xs_select_kernel(TileArgs A) {
   __shared__ unsigned long long hist[kWave];
   __shared__ double part[kSelBlock / kWave];
@@ -384,18 +384,24 @@ hipError_t launch_count(const TileArgs& A, int P, hipStream_t st, int64_t phys_w
   return hipGetLastError();
 }
 
-hipError_t launch_select(const TileArgs& A, int P, hipStream_t st) {
-  const int64_t items = A.n_tiles * A.n_pt;
-  if (items <= 0) return hipSuccess;
+template <int kSelBlock>
+static hipError_t launch_select_block(const TileArgs& A, int P, int64_t items, hipStream_t st) {
   const dim3 grid = wg_grid(items), block(kSelBlock);
   switch (P) {
-    case 1: hipLaunchKernelGGL((xs_select_kernel<1>), grid, block, 0, st, A); break;
-    case 2: hipLaunchKernelGGL((xs_select_kernel<2>), grid, block, 0, st, A); break;
-    case 4: hipLaunchKernelGGL((xs_select_kernel<4>), grid, block, 0, st, A); break;
-    case 8: hipLaunchKernelGGL((xs_select_kernel<8>), grid, block, 0, st, A); break;
+    case 1: hipLaunchKernelGGL((xs_select_kernel<1, kSelBlock>), grid, block, 0, st, A); break;
+    case 2: hipLaunchKernelGGL((xs_select_kernel<2, kSelBlock>), grid, block, 0, st, A); break;
+    case 4: hipLaunchKernelGGL((xs_select_kernel<4, kSelBlock>), grid, block, 0, st, A); break;
+    case 8: hipLaunchKernelGGL((xs_select_kernel<8, kSelBlock>), grid, block, 0, st, A); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_select(const TileArgs& A, int P, bool wide, hipStream_t st) {
+  const int64_t items = A.n_tiles * A.n_pt;
+  if (items <= 0) return hipSuccess;
+  return wide ? launch_select_block<1024>(A, P, items, st)
+              : launch_select_block<256>(A, P, items, st);
 }
 
 hipError_t launch_reduce(const double* part, const double* far, void* out, int out_f32,

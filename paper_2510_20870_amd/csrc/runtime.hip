@@ -344,7 +344,8 @@ static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, s
       widest = std::max(widest, widest_cut(G, o, pb));
     }
     const double w = (double)window_lines(L, G, o, widest);
-    return w + (f64 ? 4.0 : 2.0) * tile_lines(L, G, w, widest) >=
+    // (the lines beside a tile cost it more than the others)
+    return w + (f64 ? 4.0 : groups < kFwhmGroups1 ? 2.0 : 32.0) * tile_lines(L, G, w, widest) >=
            (double)(f64 ? (groups < kFwhmGroups64 ? kFwhmOwn64 : kFwhmOwn3)
                         : groups < kFwhmGroups1 ? kFwhmOwn1 : kFwhmOwn2);
   }
@@ -474,7 +475,8 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     int ways = 1;
     for (size_t k = 1; k < npts; ++k) ways += p.by_tile[k] != p.by_tile[k - 1];
     if (!o.split && ways > 4 &&
-        ((int64_t)G.n + kPointGroup - 1) / kPointGroup * (int64_t)npts <= kTurnGroups)
+        ((int64_t)G.n + kPointGroup - 1) / kPointGroup * (int64_t)npts <=
+            (all_one ? kTurnGroups : kTurnGroups / 4))
       std::fill(p.by_tile.begin(), p.by_tile.end(),
                 G.n == 1 ? kPoint : all_one ? kTileNear : kTileWhole);
     p.any_tile = std::count(p.by_tile.begin(), p.by_tile.end(), kPoint) < (int64_t)npts;
@@ -525,6 +527,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     sp = std::min<int64_t>(sp, std::max<int64_t>(1, max_window / 64));
     p.split = (int)std::min<int64_t>(sp, kMaxSplit);
   }
+  p.wide_select = max_window >= kSelLines || p.n_groups() <= kSelGroups;
   // FP64 tile kernel: by chunks where a part has more than two of them. (Code that runs once
   // or twice is fetched for longer than it saves: a window of 1160 lines on 1349 points takes
   // 23 us line by line, 37 by chunks.) max_window is rounded up to whole samples, so with
@@ -682,7 +685,7 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       S.tau = (double*)((char*)rec_dev + p.tau_offset());
       S.tau_stride = p.n_groups();
       S.select_eps = p.select_eps;
-      e = launch_select(S, p.P, st);
+      e = launch_select(S, p.P, p.wide_select, st);
       if (e != hipSuccess) return hip_fail(e, "select kernel launch");
     }
   }

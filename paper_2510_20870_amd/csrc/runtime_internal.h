@@ -78,7 +78,7 @@ constexpr int64_t kMomentLines2 = 6144, kMomentGroups2 = 125000;
 // cuts, 4300 of 30000 lines, 629 and 9508 points FP32 173 / 79, 210 / 86, FP64 111 / 124, 251 / 145.
 constexpr int64_t kFwhmGroups64 = 512, kFwhmGroups1 = 2048, kFwhmGroups2 = 16384;
 constexpr int64_t kFwhmLines1 = 32768, kFwhmLines2 = 65536;
-constexpr int64_t kFwhmOwn1 = 4096, kFwhmOwn2 = 24576, kFwhmOwn64 = 16384, kFwhmOwn3 = 3072;
+constexpr int64_t kFwhmOwn1 = 4096, kFwhmOwn2 = 20480, kFwhmOwn64 = 16384, kFwhmOwn3 = 3072;
 // Small calls of that kind keep the tree low, as each three of its levels are a launch of some
 // 20 us: the fewest levels that leave at most kTopNodes nodes in a window, for at most
 // kFewGroups groups of points.
@@ -91,7 +91,7 @@ constexpr double kWideSteps = 384.0;
 // least this part of the lines within their own widest cut in the near range (40600 lines/cm^-1,
 // 12356 points, us by tiles / point kernel: 1 bar 2573 / 1107, 3 bar 1940 / 1020, 10 bar 744 / 4188,
 // 30 bar 548 / 8250; the part is 0.07 at 3 bar, 0.22 at 10).
-constexpr double kNearAll32 = 0.125;
+constexpr double kNearAll32 = 0.2;
 // On the FP64 path only those whose near range holds at least this part, and so many lines (24
 // points in turn, 2855 lines, 9052 grid points 1727 us, 405 by the point kernel): its tiles gain
 // little from the far field's polynomial. (Tiles / point kernel, us: 17000 lines in the window,
@@ -99,8 +99,16 @@ constexpr double kNearAll32 = 0.125;
 // 100 bar 224 / 210, 235 / 265; 50000 lines, 2000 points 256 / 305, 267 / 399; 1e5 points at 20 and
 // 100 bar 1995 / 1776, 7177 / 7727. The near range is 0.6 of the cut at 60 bar.)
 constexpr double kNearAll64 = 0.8, kNearLines64 = 16384.0;
+// Main-contributor selection's thresholds by workgroups of 16 waves from so many lines in a window
+// on (sampled, so rather more than there are) or up to so many groups of tiles, else of 4 waves.
+// Whole calls, us, 4 / 16 waves: 5 lines, 235 groups, 8 (P, T) points 105 / 116, 586 groups 137 / 165;
+// 500 lines 187 / 200, 284 / 320; 1800 lines, 195 groups 131 / 126, 4 groups 67 / 61; 5000 lines 223 / 203,
+// 405 / 390. The rule looks at the grid and the list alone, as the thresholds' rounding follows the
+// workgroup.
+constexpr int64_t kSelLines = 3072, kSelGroups = 64;
 // Tables of up to this many groups of points in all go one way where their points would go two
-// ways in turn.
+// ways in turn (over whole windows a quarter as many: 24 points of the table with FWHM cuts, 1180
+// lines/cm^-1 on 715 points 443 us in runs, 1071 as one).
 constexpr int64_t kTurnGroups = 4096;
 // Grids with gaps of many lines keep broad points in the point kernel up to this many points.
 constexpr size_t kSeamPoints = 65536;
@@ -139,6 +147,7 @@ struct Plan {
                                    // by moments near it
   bool tuned = false;              // launch shape from the tuning cache
   double select_eps = 0.0;         // main-contributor selection (0: off)
+  bool wide_select = false;        // thresholds by workgroups of 16 waves
   // Far field by moments (far_tree.h): the tree over the records, 0 moments: off.
   int moments = 0;
   std::vector<uint8_t> by_tile;   // per (P, T) point: a PointWay

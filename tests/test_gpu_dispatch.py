@@ -330,3 +330,27 @@ def test_points_that_go_different_ways(ctx, rule, split, f64):
                     assert np.array_equal(sig[k], alone[p]), (len(grid), k, p)
         ctx.unload_lines(h)
         ctx.free_grid(g)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("n,m", [(900, 34_000), (900, 3000), (12_000, 34_000)])
+def test_selection_workgroups(ctx, n, m, f64):
+    """Thresholds by 4 waves (few lines, more than 64 groups of tiles), by 16: dropped lines stay
+    within select_eps, and a row does not depend on the table with a given split."""
+    from paper_2510_20870_amd import xsec as X
+    L = synth.make_lines(synth.ListSpec(n, 1000.0, 1120.0, 6))
+    grid = 1001.0 + 0.003 * np.arange(m, dtype=np.float64)
+    idx = np.unique(np.random.default_rng(6).integers(0, m, 300))
+    o = ctx.opts(X.XS_CUT_FIXED, 25.0, 100.0, X.XS_FP64 if f64 else X.XS_FP32_KAHAN, split=2,
+                 select_eps=1e-3)
+    h, g = ctx.load_lines(L, 16.0), ctx.set_grid(grid)
+    pts = [(0.05, 700.0), (20.0, 500.0)]
+    sig = ctx.compute(h, g, pts, o)
+    tol = 2e-8 if f64 else 2e-6
+    for k, (P, T) in enumerate(pts):
+        ref = O.sigma(L, grid, P, T, 16.0, points=idx)
+        assert np.all(sig[k][idx] <= ref * (1.0 + tol)), (P, T)
+        assert np.all(sig[k][idx] >= ref * (1.0 - 1e-3 - tol)), (P, T)
+        assert np.array_equal(ctx.compute(h, g, [(P, T)], o)[0], sig[k])
+    ctx.unload_lines(h)
+    ctx.free_grid(g)
