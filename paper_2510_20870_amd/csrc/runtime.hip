@@ -538,10 +538,13 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   // chunks).
   if (f64 && !p.moments) {
     p.chunks.resize(npts);
-    const double half = 0.5 * (double)tile * usual_step(G);
     for (size_t k = 0; k < npts; ++k) {
-      const double most = widest_cut(G, o, plan_bounds(L, pts[k]));
-      const double w = (double)max_window * ((most + half) / (o.cut_cm1 + half));
+      double w = (double)max_window;
+      if (o.cutoff_kind != XS_CUT_FIXED) {
+        const double most = widest_cut(G, o, plan_bounds(L, pts[k]));
+        const double in_cut = (double)window_lines(L, G, o, most);
+        w = std::min(w, in_cut + p.P * tile_lines(L, G, in_cut, most));
+      }
       p.chunks[k] = w > (double)std::max<int64_t>(3 * kSampleStride, 2 * kWave * p.split);
       p.any_chunks = p.any_chunks || p.chunks[k];
     }
@@ -769,7 +772,7 @@ int enqueue_step(const LinesRes& L, const GridRes& G, const xs_opts& o, const Pl
       if (p.select_eps > 0.0) {
         // main-contributor selection: the kernels drop the lines below their group's
         // threshold
-        A.tau = (double*)((char*)rec_dev + p.tau_offset());
+        A.tau = (double*)((char*)rec_dev + p.tau_offset()) + (size_t)k0 * p.n_groups();
         A.tau_stride = p.n_groups();
       }
       const int64_t phys = phys_workgroups(A.n_wg);

@@ -91,7 +91,7 @@ constexpr double kWideSteps = 384.0;
 // least this part of the lines within their own widest cut in the near range (40600 lines/cm^-1,
 // 12356 points, us by tiles / point kernel: 1 bar 2573 / 1107, 3 bar 1940 / 1020, 10 bar 744 / 4188,
 // 30 bar 548 / 8250; the part is 0.07 at 3 bar, 0.22 at 10).
-constexpr double kNearAll32 = 0.2;
+constexpr double kNearAll32 = 0.125;
 // On the FP64 path only those whose near range holds at least this part, and so many lines (24
 // points in turn, 2855 lines, 9052 grid points 1727 us, 405 by the point kernel): its tiles gain
 // little from the far field's polynomial. (Tiles / point kernel, us: 17000 lines in the window,

@@ -271,13 +271,20 @@ def test_fp64_chunks_of_a_table(ctx, split):
             assert st["violations"] == 0, (k, p, st)
             if split:
                 assert np.array_equal(sig[k], alone[p]), (k, p)
+    # with selection: each run of points by its own thresholds
+    o.split, o.select_eps = 2, 1e-3
+    sel = ctx.compute(h, g, [broad, narrow, narrow, broad], o)
+    for k, p in enumerate([broad, narrow, narrow, broad]):
+        assert np.array_equal(sel[k], ctx.compute(h, g, [p], o)[0]), (k, p)
+        assert np.all(sel[k] <= ref[p] * (1.0 + 2e-8)), (k, p)
+        assert np.all(sel[k] >= ref[p] * (1.0 - 1e-3 - 2e-8)), (k, p)
     ctx.unload_lines(h)
     ctx.free_grid(g)
 
 
 @pytest.mark.parametrize("n,m,P,f64,split,moments", [
     (27_000, 1349, 0.1, False, 0, False), (27_000, 1349, 8.0, False, 0, True),
-    (27_000, 17_000, 8.0, False, 0, False), (60_000, 17_000, 0.1, False, 0, True),
+    (27_000, 17_000, 1.0, False, 0, False), (60_000, 17_000, 0.1, False, 0, True),
     (60_000, 140_000, 0.1, False, 0, False), (60_000, 140_000, 8.0, False, 0, True),
     (120_000, 140_000, 0.1, False, 0, True),
     (27_000, 1349, 1.0, True, 0, False), (27_000, 1349, 8.0, True, 0, True),
