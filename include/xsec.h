@@ -165,18 +165,26 @@ typedef struct { double P_bar, T_K; } xs_pt;
  * min(cap, fwhm_mult * f_V) (XS_CUT_MIN_FWHM). Launch shape (each 0 = autotuned):
  * pts_per_lane (1, 2, 4 or 8) sets the grid tile of one wavefront to 64 * pts_per_lane
  * points; split (1..256) divides each tile's line window into that many independent work
- * items whose partial sums are added in a fixed order; waves_per_simd is the
+ * items whose partial sums are added in a fixed order (by moments, see tile_group, the groups of
+ * 8 points in a tile count as its items already: a split of up to that many leaves them whole);
+ * waves_per_simd is the
  * occupancy the tile kernel is compiled for: 3..6 waves per SIMD, 2 the compiler's own
  * choice, 0 automatic (the tuned value, else 5 on the FP32 path with 1 or 2 points per
  * lane and the compiler's choice otherwise). The result does not depend on the launch
- * shape beyond FP32 rounding (bitwise for a fixed shape).
+ * shape beyond rounding and, where the shape changes the way a point is summed (tile_group),
+ * the error of its forms. With an explicit split, the same grid and list, and enough memory, a
+ * row's bits depend on its own (P, T) point alone; with an automatic split the shape and the
+ * way also follow from the number of points and from the others. Where too little memory is
+ * left for the moments, a call is summed line by line, which changes its bits.
  * select_eps > 0 turns on main-contributor selection (named in "Functionality of pyROX"
  * as a way to speed up the profile computation; the paper does not define it): per tile of
  * the grid and (P, T) point, lines are dropped when the sum of their contributions' upper
  * bounds over the tile stays within select_eps times a lower bound of sigma over the tile,
  * so that sigma changes by at most select_eps * sigma at every point (plus the FP32
  * rounding and the error budget tol of the kept lines); 0 computes every line. Must be in
- * [0, 1).
+ * [0, 1). Selection walks every line of a tile's window, so it never goes by moments: where
+ * these apply it takes longer than no selection (9.5e5 grid points, 1e7 lines, FP32 10.8 ms
+ * against 2.0, FP64 15.3 against 4.0). It serves where lines are to be dropped.
  * out_dtype: the element type of sigma outputs, XS_F64 (float64) or XS_F32 (float32, the
  * FP64 sum rounded once to nearest); the arithmetic is the same for both.
  * tile_group: how the tiles of a workgroup share work. 1: each wavefront sums the far
@@ -186,12 +194,17 @@ typedef struct { double P_bar, T_K; } xs_pt;
  * wavefronts and added in a fixed order (FP32 path, fixed cut, no selection, 1 or 2
  * points per lane; XS_EINVAL otherwise). 0: automatic. Without selection, the lines far
  * from a grid point enter by moments of line groups (FP64, within 5e-8 of each line's
- * contribution on the FP32 path and 1e-13 on the FP64 path) and only those near it one by
- * one: for every cut from 16384 lines within the cut, for a fixed cut also with fewer, from a
- * list of 512 lines on and unless lines are broad. pts_per_lane and waves_per_simd then shape
- * only the (P, T) points whose lines are so broad that tiles take them. The moments take about
- * 13 bytes per line and (P, T) point (FP64 path 21; a FWHM cut 12 or 18 more); where that
- * memory is missing, and everywhere else, 4 where it applies and the cut spans at least 3
+ * contribution on the FP32 path and 3e-14 on the FP64 path) and only those near it one by
+ * one. So go, with a fixed cut, calls of 16384 lines and more within the cut of a point (and in
+ * the span of a tile) where the list is densest, and with an automatic split those of fewer,
+ * from a list of 512 lines on, unless a point's lines are broad (FP32) or they are so few that
+ * many grid points cost more than their lines; with a FWHM cut, calls of 32768 lines and more
+ * within the cap, with an automatic split of 16384 where the lines' own cuts hold a good part of
+ * them. The measured limits stand in the library's runtime_internal.h. pts_per_lane and
+ * waves_per_simd then shape only the (P, T) points whose lines are so broad that tiles take
+ * them. The moments take about 14.7 bytes per line and (P, T) point (FP64 path 22.7; a FWHM cut
+ * 12 or 18 more) beside the record's 32; where that memory is missing, and everywhere else, 4
+ * where it applies and the cut spans at least 3
  * kappa half-widths of a four-tile span at the grid's middle, kappa the far threshold below,
  * else 1.
  * tol: the error budget of the FP32 path's cheaper far forms, relative to each line's
@@ -225,7 +238,8 @@ typedef struct {
  * sigma_out is device memory, the work is enqueued on `stream` (a hipStream_t, NULL =
  * the null stream) and the call returns without waiting; otherwise sigma_out is host
  * memory and the call returns when it is filled. Each output element is produced by one
- * work item in a fixed line order, so repeated calls give bitwise identical results.
+ * work item in a fixed line order, so repeated calls give bitwise identical results (as long as
+ * the memory left does not change the way they are summed: see tile_group).
  * Errors: XS_EINVAL (P or T <= 0 or not finite, bad options), XS_ENOTFOUND, XS_ENOMEM,
  * XS_EDEVICE. */
 int xs_compute(xs_ctx *ctx, xs_lines_t lines, xs_grid_t grid, const xs_pt *pts, size_t npts,
@@ -234,7 +248,8 @@ int xs_compute(xs_ctx *ctx, xs_lines_t lines, xs_grid_t grid, const xs_pt *pts, 
 /* Allocation-free variant of xs_compute, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid allocation).
  * It computes what xs_compute computes with the same kernels (bitwise the same result
- * for the same launch shape), into device memory sigma_dev (npts * n_grid elements of
+ * for the same launch shape, unless the moments do not fit the array below and the call is
+ * summed line by line), into device memory sigma_dev (npts * n_grid elements of
  * opts->out_dtype), enqueued on `stream` (a hipStream_t, NULL = the null stream); it
  * returns without waiting and calls no allocation routine: the point table, the line
  * records and the split partials live in one static device array of
@@ -242,7 +257,8 @@ int xs_compute(xs_ctx *ctx, xs_lines_t lines, xs_grid_t grid, const xs_pt *pts, 
  * until the process ends, and the tiles are issued in ascending order. Limit: the point
  * table plus the records and partials of one batch of P-T points (32 bytes per line that
  * can reach the grid and per point, plus 8 bytes per grid point and split when the line
- * window of a tile is split) must fit that array, else XS_ENOMEM (larger tables are run
+ * window of a tile is split; the moments beside them only where they fit) must fit that
+ * array, else XS_ENOMEM (larger tables are run
  * in several batches inside the call). Every call on one GPU, from any context or
  * thread, shares that GPU's array, and a call leaves its contents behind: calls whose
  * device work overlaps in time (different streams without ordering between them) race
@@ -299,10 +315,13 @@ void xs_graph_destroy(xs_graph *g);
  * their kernels share the device with the others at step granularity, and short requests
  * do not wait behind long ones. A served request's result depends only on its own
  * inputs and options (the launch shape is planned from them alone), so it is bitwise the
- * same served alone or in any mix. With an automatic split (opts.split = 0) the server
+ * same served alone or in any mix (the moments are left out where they do not fit the whole
+ * arena, never for what else is in it). With an automatic split (opts.split = 0) the server
  * plans shorter work items than xs_compute (at most 4096 lines each), so the two agree to
- * FP32 rounding; with the same explicit split they agree bitwise. Footprint = records (32 B per line that can
- * reach the grid and per P-T point of a batch) + split partials + the output when it
+ * rounding; with the same explicit split they agree bitwise where both go the same way
+ * (tile_group: xs_compute by its budget, a request by its arena). Footprint = records (32 B per
+ * line that can reach the grid and per P-T point of a batch) + the moments where the request
+ * goes by them (14.7 B, FP64 22.7, a FWHM cut 12 or 18 more, likewise) + split partials + the output when it
  * goes to host memory + the grid of a window request + the point table and tile order.
  * The lines (and grid) of a request stay referenced until it is done: unloading them
  * meanwhile fails with XS_EBUSY. */

@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kBlock) void xs_far_kernel(FarArgs A) {
   }
   // a near range that reaches past the covered lines: no groups for the whole tile
   const int64_t stop = left ? min(near_b, cov) : max(near_b, cov);   // end of the groups
-  const int64_t edge_b = left ? min(stop * kLeafLines, A.rec_n) : min(stop * kLeafLines, A.rec_n);
+  const int64_t edge_b = min(stop * kLeafLines, A.rec_n);
   const int64_t near_line = left ? max(end, min(near_b * kLeafLines, A.rec_n))
                                  : min(end, near_b * kLeafLines);
   if (!edge && lane == 0) {

@@ -7,9 +7,11 @@
 // by make_plan): lines far from a grid point enter group by group, and the point kernel
 // (point.hip) sums the others with lanes being lines; (P, T) points whose lines are so broad
 // that tiles serve them better take the far kernel (far.hip) and the tile kernel over each
-// tile's near range. Line by line: the tile kernel over the whole window, with main-contributor
-// selection, an explicit tile_group, lists of fewer than 512 lines, or too little memory for
-// the moments. The kernels of the second way:
+// tile's near range, or, where FWHM cuts differ, the tile kernel over whole windows. Line by line:
+// the tile kernel over the whole window, with main-contributor selection, an explicit
+// tile_group, lists of fewer than 512 lines or too few lines in a window for the number of grid
+// points, FWHM cuts that hold few lines (use_moments), or too little memory for the moments. The
+// kernels of the second way:
 //
 // 1. xs_params_kernel (HBM-bound): for every line in the range a grid can reach and every
 //    (P, T) point of a batch, the FP64 line parameters (cutoff, 1/b_D, S/(b_D sqrt(pi)),

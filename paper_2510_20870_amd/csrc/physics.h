@@ -7,9 +7,9 @@
 // Everything here is FP64. The cutoff width decides which (line, point) pairs exist, so it
 // is computed in the same operation order as a plain evaluation of the textbook formula,
 // with contraction disabled for the whole library (-ffp-contract=off) and IEEE sqrt, so
-// that it agrees with any other careful FP64 evaluation to the last bit except where the
-// power function (here exp of n ln(T_ref/T), the logarithm in two parts: power_ln) itself
-// differs by an ulp.
+// that it agrees with any other careful FP64 evaluation to the last bit except for the power of
+// the temperature ratio (here exp of n ln(T_ref/T), the logarithm in two parts: power_ln), which
+// is within an ulp or two of pow.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -322,9 +322,8 @@ static double widest_cut(const GridRes& G, const xs_opts& o, const PtBounds& pb)
 // Far field by moments, chosen where a point's window holds enough lines beyond its near
 // range: without selection (which drops lines one by one) and with the automatic tile_group.
 static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, size_t npts,
-                        const xs_opts& o) {
+                        const xs_opts& o, int64_t window) {
   if (o.tile_group != 0 || o.select_eps > 0.0 || L.n >= ((size_t)1 << 30)) return false;
-  const int64_t window = window_lines(L, G, o, o.cut_cm1);
   const int64_t lines = window + (int64_t)tile_lines(L, G, (double)window, o.cut_cm1);
   // groups of points (of all (P, T) points where the split follows from them too: with a given
   // split a row's bits are its own point's alone)
@@ -371,7 +370,9 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
                const xs_opts& o, size_t cap_bytes, int64_t max_item_lines, int items_per_slot, bool far_moments) {
   Plan p;
   p.n_grid = (int64_t)G.n;
-  if (far_moments && use_moments(L, G, pts, npts, o))
+  // lines within the cut of a point
+  const int64_t window = far_moments ? window_lines(L, G, o, o.cut_cm1) : 0;
+  if (far_moments && use_moments(L, G, pts, npts, o, window))
     p.moments = o.precision == XS_FP64 ? kMomFp64 : kMomFp32;
   p.P = o.pts_per_lane ? o.pts_per_lane : p.moments ? 1 : 2;
   p.select_eps = o.select_eps;
@@ -415,11 +416,10 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   line_range(L, G, o, &p.rec_lo, &hi);
   p.rec_n = hi - p.rec_lo;
   if (p.moments) {
-    const int64_t lines = window_lines(L, G, o, o.cut_cm1);
     const int64_t groups = ((int64_t)G.n + kPointGroup - 1) / kPointGroup;
     int levels = kTreeLevels;
-    if (lines < kMomentLines && groups * (int64_t)npts <= kFewGroups)
-      for (levels = 1; (lines / kLeafLines) >> (kArityBits * (levels - 1)) > kTopNodes;) ++levels;
+    if (window < kMomentLines && groups * (int64_t)npts <= kFewGroups)
+      for (levels = 1; (window / kLeafLines) >> (kArityBits * (levels - 1)) > kTopNodes;) ++levels;
     p.set_tree(levels);
   }
   if (p.moments && o.cutoff_kind != XS_CUT_FIXED && p.dims.levels > kCutLevel)
@@ -443,7 +443,7 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
     // points, against 30 in the point kernel)
     // (only with one cut for every line: the far kernel's rule)
     const double step = usual_step(G);
-    const double per = (double)window_lines(L, G, o, o.cut_cm1) / (2.0 * o.cut_cm1);
+    const double per = (double)window / (2.0 * o.cut_cm1);
     double widest = 0.0;
     const double gap = gap_lines(L, G);
     p.runs = gap > (double)(G.max_step > 4.0 * kPointGroup * step ? kGapLines : kStepLines);
@@ -568,6 +568,9 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
       1, (size_t)p.rec_n * 32 + (p.max_split() > 1 ? (size_t)p.max_split() * G.n * 8 : 0) +
              p.extra_bytes());
   p.pt_batch = (int)std::max<size_t>(1, std::min<size_t>(npts, cap / per_pt));
+  p.tile_order.resize(p.n_units);
+  std::iota(p.tile_order.begin(), p.tile_order.end(), 0);
+  if (p.moments) return p;   // near ranges differ little: ascending
   // issue order: tiles by decreasing number of lines within the largest cut, so the most
   // expensive work items start first
   // coarse cost classes (ratio 2^(1/4)) keep neighbouring tiles of similar cost together,
@@ -575,9 +578,6 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   std::vector<int> cls(p.n_units);
   for (int64_t t = 0; t < p.n_units; ++t)
     cls[t] = (int)std::floor(4.0 * std::log2(1.0 + (double)cost[t]));
-  p.tile_order.resize(p.n_units);
-  std::iota(p.tile_order.begin(), p.tile_order.end(), 0);
-  if (p.moments) return p;   // near ranges differ little: ascending
   std::stable_sort(p.tile_order.begin(), p.tile_order.end(),
                    [&](int a, int b) { return cls[a] > cls[b]; });
   return p;
@@ -613,6 +613,7 @@ static int plan_buffers(Ctx& c, const Plan& p, size_t n_grid, bool with_part, si
 
 int upload_order(Ctx& c, const Plan& p, hipStream_t st) {
   const size_t bytes = p.tile_order.size() * sizeof(int);
+  if (p.moments && !p.any_tile) return XS_OK;   // the point kernel takes its groups as they come
   if (c.order_host == p.tile_order && c.order_buf.ptr) return XS_OK;
   if (c.pts_event_valid) {
     hipError_t e = hipEventSynchronize(c.pts_event);

@@ -270,7 +270,8 @@ int validate_pts(const xs_pt* pts, size_t npts);
 // Launch plan; cap_bytes bounds the records and partials of one batch of (P, T) points
 // (0: min(64 GiB, a third of the free budget)); max_item_lines > 0 caps the line range
 // of a work item when the split is automatic. The launch shape (P, split) depends only on
-// the inputs, the options and max_item_lines, never on the memory left.
+// the inputs, the options, max_item_lines and far_moments, never on the memory left (which only
+// bounds the points per batch; a caller short of memory asks again with far_moments false).
 // items_per_slot > 0 sets the work items per resident wavefront slot of the automatic
 // split (default 4). With pts_per_lane, split and waves_per_simd all 0 the shape comes
 // from the tuning cache when it holds the workload's class. far_moments false: every line by
