@@ -103,12 +103,32 @@ def counter_profile(path=None):
     out = {}
     for key, val in re.findall(r"^([a-z_0-9]+):\s*([-+0-9.eE]+)\s*$", text, re.M):
         out[key] = float(val)
+    for key, vals in re.findall(r"^([a-z_0-9]+_by_point):\s*([-+0-9.eE ]+)$", text, re.M):
+        out[key] = [float(v) for v in vals.split()]
+    return out
+
+
+def timed_profile(prof, step_points, n_points):
+    """The profile's figures per launch over the points that were timed: means of its figures by
+    point; without these only where every point was timed equally often, else None."""
+    if prof is None:
+        return None
+    keys = [k for k in prof if k.endswith("_by_point")]
+    if not keys:
+        counts = [step_points.count(i) for i in range(n_points)]
+        return prof if min(counts) == max(counts) else None
+    if any(len(prof[k]) != n_points for k in keys):
+        return None
+    out = {k: v for k, v in prof.items() if k not in keys}
+    for k in keys:
+        out[k.replace("_by_point", "_per_launch")] = float(
+            np.mean([prof[k][i] for i in step_points]))
     return out
 
 
 def headline_profile(args):
-    """The counter profile when this run times what it was taken on: the headline workload,
-    all of its points, at the profile's error budget; else None (the tier model prices the
+    """The counter profile when this run times what it was taken on: the headline workload
+    (timed_profile then picks the points) at the profile's error budget; else None (the tier model prices the
     run instead)."""
     if args.workload != "large" or args.points:
         return None
@@ -408,7 +428,9 @@ def roofline(prof, evals_per_launch, kernel_ms, flops_model):
     r = {"bound": "alu", "unit": "TFLOP/s", "peak": PEAK_FP32_PACKED_TFLOPS,
          "kernel": "xs_point_kernel, xs_far_kernel + xs_tile_kernel (by (P, T) point)",
          "kernel_ms_per_launch": kernel_ms,
-         "evals_per_launch": evals_per_launch}
+         "evals_per_launch": evals_per_launch,
+         "evals_basis": "(line, grid point) pairs within the cut; lines far from a point enter by "
+                        "moments of line groups, which stand for most of these pairs"}
     if prof and prof.get("evals_per_launch"):
         fpe = prof["valu_flops_per_launch"] / prof["evals_per_launch"]
         ipe = prof["valu_lane_instr_per_launch"] / prof["evals_per_launch"]
@@ -702,7 +724,7 @@ def main():
 
     H = bench_large(args, torch, xsec, synth)
     W, grid, pts = H["W"], H["grid"], H["pts"]
-    prof = headline_profile(args)
+    prof = timed_profile(headline_profile(args), H["step_points"], len(pts))
     roof = roofline(prof, H["evals_per_launch"], H["kernel_ms"], H.get("flops_model"))
 
     cpu, parity = None, None

@@ -62,3 +62,24 @@ def test_code_hash_ignores_comments():
     c = "int f(int x) {\n  return x + 2;\n}\n"
     assert bench._code_only(a) == bench._code_only(b)
     assert bench._code_only(a) != bench._code_only(c)
+
+
+def test_profile_of_the_timed_points(monkeypatch, tmp_path):
+    prof = tmp_path / "counters.md"
+    body = ("evals_per_launch: 2e12\nvalu_flops_per_launch: 3e13\n"
+            f"kernel_source_sha256: {bench.kernel_source_hash()}\n")
+    monkeypatch.setattr(bench, "COUNTER_PROFILE", str(prof))
+    prof.write_text(body + "valu_flops_by_point: 1e13 2e13 6e13\n")
+    c = bench.counter_profile()
+    assert c["valu_flops_by_point"] == [1e13, 2e13, 6e13]
+    # the mean over the steps, whichever points they took
+    t = bench.timed_profile(c, [0, 1, 1, 0], 3)
+    assert t["valu_flops_per_launch"] == 1.5e13 and t["evals_per_launch"] == 2e12
+    assert "valu_flops_by_point" not in t
+    assert bench.timed_profile(c, [0, 1], 4) is None   # a profile of another table
+    # one mean for all points: only where all were timed equally often
+    prof.write_text(body)
+    c = bench.counter_profile()
+    assert bench.timed_profile(c, [0, 1, 2, 2, 0, 1], 3) is c
+    assert bench.timed_profile(c, [0, 1, 2, 0], 3) is None
+    assert bench.timed_profile(None, [0], 1) is None
