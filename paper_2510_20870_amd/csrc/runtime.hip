@@ -305,7 +305,8 @@ static double near_distance(const GridRes& G, const xs_opts& o, const PtBounds& 
 static bool is_wide(const LinesRes& L, const GridRes& G, const xs_opts& o, const PtBounds& pb) {
   // (one point has no step: by what the point kernel would sum one by one)
   const double d = near_distance(G, o, pb);
-  return G.n > 1 ? d > kWideSteps * usual_step(G) : lines_within(L, G.first, std::min(d, o.cut_cm1)) > kWideLines;
+  if (G.n > 1) return d > kWideSteps * usual_step(G);
+  return lines_within(L, G.first, std::min(d, o.cut_cm1)) > kWideLines;
 }
 
 // Whether every line's cut at (P, T) is the fixed cut or the cap.
@@ -367,7 +368,8 @@ static bool use_moments(const LinesRes& L, const GridRes& G, const xs_pt* pts, s
 }
 
 Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, size_t npts,
-               const xs_opts& o, size_t cap_bytes, int64_t max_item_lines, int items_per_slot, bool far_moments) {
+               const xs_opts& o, size_t cap_bytes, int64_t max_item_lines, int items_per_slot,
+               bool far_moments) {
   Plan p;
   p.n_grid = (int64_t)G.n;
   // lines within the cut of a point
@@ -429,7 +431,9 @@ Plan make_plan(Ctx& c, const LinesRes& L, const GridRes& G, const xs_pt* pts, si
   std::vector<int64_t>& cost = p.tile_cost;
   cost.assign(p.n_units, 0);
   int64_t max_cost = 0;
-  for (int64_t t = 0; t < p.n_units; ++t) {
+  // (by moments only the server reads them: 9.5e5 points 0.4 ms)
+  const int64_t counted = p.moments && max_item_lines == 0 ? 0 : p.n_units;
+  for (int64_t t = 0; t < counted; ++t) {
     const int64_t j0 = t * unit, j1 = std::min<int64_t>(j0 + unit, (int64_t)G.n) - 1;
     const double lo = G.host[j0] - o.cut_cm1, hi = G.host[j1] + o.cut_cm1;
     cost[t] = (int64_t)(std::upper_bound(sm.begin(), sm.end(), hi) -

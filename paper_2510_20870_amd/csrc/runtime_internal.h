@@ -41,10 +41,10 @@ constexpr int64_t kServeItemLines = 4096;
 
 // Far field by moments: from kMomentLines lines with a fixed cut (those within the cut where the
 // list is densest, and those that a tile of 64 points spans besides: tile_lines); with fewer, for
-// a fixed cut and no wide point (kWideSteps), from kMomentList lines in the list. There a call that does not fill the device wins by its shorter
-// chains, a larger one only where a window holds so many lines that walking them costs more
-// than the point kernel's searches and sums (some 0.5 ns per point): beyond kMomentGroups1 groups
-// of points in all from kMomentLines1 lines on, beyond kMomentGroups2 from kMomentLines2.
+// a fixed cut and no wide point (kWideSteps), from kMomentList lines in the list. There a call
+// that does not fill the device wins by its shorter chains, a larger one only where a window
+// holds so many lines that walking them costs more than the point kernel's searches and sums
+// (some 0.5 ns per point): beyond kMomentGroups1 groups of points in all from kMomentLines1 lines on, beyond kMomentGroups2 from kMomentLines2.
 // Measured with a fixed cut (us, tile kernel alone / by moments; one (P, T) point of 3e4, 2e5, 1e6
 // grid points): 100 lines in the window 68 / 41, 151 / 140, 251 / 550; 500 lines 82 / 46,
 // 181 / 173, 377 / 687; 2000 lines 147 / 51, 255 / 201, 748 / 810; 5000 lines 217 / 64, 401 / 225,
@@ -62,11 +62,11 @@ constexpr int64_t kMomentLines2 = 6144, kMomentGroups2 = 125000;
 // that only some points reach are far too few per block). The orders by cut make the chain of
 // launches longer, and what tiles cost follows from the lines within their own cuts: so by moments
 // from kFwhmOwn1 lines within the widest of these on (and in a tile's span) up to kFwhmGroups1
-// groups of points in all (FP64: kFwhmOwn64 up to
-// kFwhmGroups64, then kFwhmOwn3), from kFwhmOwn2 on more, where every line's
-// cut is the cap at some point (53000 lines at 100 bar, 64 points 230 / 105), and where the cap
-// holds so many that the parameters of all of them are what counts. Measured (us, tiles / moments; one (P, T)
-// point at 1000 K of 0.001, 0.3, 1, 3 bar, for which the widest of the lines' own cuts hold 0.012,
+// groups of points in all (FP64: kFwhmOwn64 up to kFwhmGroups64, then kFwhmOwn3), from
+// kFwhmOwn2 on more, where every line's cut is the cap at some point (53000 lines at 100 bar, 64
+// points 230 / 105), and where the cap holds so many that the parameters of all of them are what
+// counts. With a given split from kFwhmLines1 within the cap, whatever the points. Measured (us,
+// tiles / moments; one (P, T) point at 1000 K of 0.001, 0.3, 1, 3 bar, for which the widest of the lines' own cuts hold 0.012,
 // 0.15, 0.5 and 1 times the lines within the cap): FP32, 17000 lines, 1349 points 45 / 107, 59 / 113,
 // 102 / 127, 158 / 116; 40000 points 101 / 91, 124 / 134, 140 / 210, 187 / 257; 400000 points
 // 242 / 288, 307 / 644, 509 / 1117, 825 / 1096; 50000 lines, 1349 points 58 / 115, 112 / 126,
