@@ -270,7 +270,8 @@ XS_HD void far_coeffs(float c1, float x, float h, float y2s, float (&b)[kFarDeg 
 // complex case their imaginary part squared is at least y^2 - 3/8, which far_line_ok uses. FP32
 // rounding of the four-term recurrence (13 steps, terms up to 2.7 times the value at the
 // default kappa) keeps the polynomial within 6.6e-7 of the closed form over tile
-// half-widths of 0.1-1e4 Doppler widths and y up to 3e4.
+// half-widths of 0.1-1e4 Doppler widths and y up to 3e4, and within 7e-7 for lines that
+// qualify by their width, beside the tile or inside it.
 struct FarRecD {
   float d1, d2, d3, d4, b0, b1, b2, b3;
 };
